@@ -190,26 +190,16 @@ PHASES = {2: "assembly", 3: "reduction", 4: "divide_and_conquer", 5: "back_trans
           7: "energy_and_gradients"}
 
 
-def phase_rooflines(prof, n, fp32, eval_s):
+def phase_rooflines(prof, n, eval_s):
     """Per-phase time of one profiled evaluation against the time the phase's
-    algorithmic work takes at the MI355X peaks (HBM 8 TB/s; FP32 and FP64
-    matrix cores 157.3 and 78.6 TFLOP/s): assembly writes Q (8 n^2 B, and
-    4 n^2 B for the FP32 copy); the reduction reads the lower trailing triangle
-    once per column (n^3/6 elements) and does (2/3) n^3 rank-2k flops; divide
-    and conquer at most (4/3) n^3 merge flops; the back-transform 2 n^3; one
-    refinement step 6 n^3 FP64; Q^{-1/2} n^3 FP64 plus one pass over it.
-    The phases are timed on the host clock with the stream synchronised at
-    their boundaries (no timing events); the reduction is also given as the
-    timed step minus the other phases ("in_evaluation"), a check that the
-    synchronisation does not distort it."""
-    es = 4 if fp32 else 8
-    peak = FP32_PEAK_TFS if fp32 else FP64_PEAK_TFS
-    tmin = {2: (8 + (4 if fp32 else 0)) * n * n / (HBM_PEAK_GBS * 1e9),
-            3: n ** 3 / 6 * es / (HBM_PEAK_GBS * 1e9) + (2.0 / 3.0) * n ** 3 / (peak * 1e12),
-            4: (4.0 / 3.0) * n ** 3 / (peak * 1e12),
-            5: 2.0 * n ** 3 / (peak * 1e12),
-            6: 6.0 * n ** 3 / (FP64_PEAK_TFS * 1e12) if fp32 else 0.0,
-            7: n ** 3 / (FP64_PEAK_TFS * 1e12) + 8 * n * n / (HBM_PEAK_GBS * 1e9)}
+    algorithmic work takes at the MI355X peaks (HBM 8 TB/s, FP64 matrix cores
+    78.6 TFLOP/s): assembly writes Q (8 n^2 B); the energy and gradient phase
+    forms the symmetric products of the direct Q^{-1/2} (their flops as
+    recorded per launch), reads Q and Q^{-1/2} for the trace and the check (4
+    passes) and Q^{-1/2} for the gradients.  The phases are timed on the host
+    clock with the stream synchronised at their boundaries (no timing events)."""
+    tmin = {2: 8 * n * n / (HBM_PEAK_GBS * 1e9),
+            7: prof[1][2] / (FP64_PEAK_TFS * 1e12) + 5 * 8 * n * n / (HBM_PEAK_GBS * 1e9)}
     out, tot_ms, tot_min = {}, 0.0, 0.0
     for k, name in PHASES.items():
         ms = prof[k][0]
@@ -220,10 +210,6 @@ def phase_rooflines(prof, n, fp32, eval_s):
         tot_ms += ms
         tot_min += t
     out["sum"] = {"ms": tot_ms, "t_min_ms": tot_min, "frac": tot_min / tot_ms if tot_ms > 0 else None}
-    if "reduction" in out:
-        red = eval_s * 1e3 - sum(v["ms"] for k, v in out.items() if k not in ("reduction", "sum"))
-        out["reduction"]["ms_in_evaluation"] = red
-        out["reduction"]["frac_in_evaluation"] = out["reduction"]["t_min_ms"] / red if red > 0 else None
     out["evaluation"] = {"ms": eval_s * 1e3, "t_min_ms": tot_min, "frac": tot_min / (eval_s * 1e3)}
     return out
 
@@ -745,26 +731,14 @@ def main():
     dA = float(np.abs(e32["grad_alpha0"] - e64["grad_alpha0"]).max())
     dW = float(np.abs(e32["grad_omega"] - e64["grad_omega"]).max())
 
-    # roofline of the dominant kernel: the per-column kernel of the FP32
-    # reduction (SYMV or fused) with the larger total time
-    col = {}
-    for kind, (kname, _) in COLUMN_KERNELS.items():
-        kms, knl, kb = r["fp32_refined"]["prof"][kind]
-        if knl == 0:
-            continue
-        avg = kms * 1e-3 / knl
-        col[kind] = {"kernel": kname + ">", "launches": knl, "total_ms": kms, "avg_launch_us": avg * 1e6,
-                     "algorithmic_bytes_per_launch": kb / knl, "achieved_GBs": kb / knl / avg / 1e9,
-                     "traffic": column_traffic(kind)}
-    dom = max(col, key=lambda k: col[k]["total_ms"])
-    ms, nl = col[dom]["total_ms"], col[dom]["launches"]
-    avg_s = col[dom]["avg_launch_us"] * 1e-6
-    bytes_per_launch = col[dom]["algorithmic_bytes_per_launch"]
-    achieved = col[dom]["achieved_GBs"]
-    traffic = col[dom]["traffic"]
-    ms3, nl3, fl3 = r["fp32_refined"]["prof"][1]
-    ms64, nl64, b64 = r["fp64"]["prof"][0]
-    ms364, nl364, fl364 = r["fp64"]["prof"][1]
+    # roofline of the dominant kernel: the symmetric products of the direct
+    # Q^{-1/2} (an evaluation without eigenvalue output runs no reduction)
+    def products(prec):
+        ms, nl, fl = r[prec]["prof"][1]
+        return {"kernel": "isq_prod_kernel", "launches": nl, "total_ms": ms, "avg_launch_us": ms * 1e3 / max(nl, 1),
+                "flops_per_launch": fl / max(nl, 1), "achieved_TFs": fl / (ms * 1e-3) / 1e12 if ms > 0 else None}
+
+    dom = products("fp32_refined")
 
     line = {
         "metric": "N=2000 MBD energy+force time (s), FP32+refine vs FP64",
@@ -781,33 +755,22 @@ def main():
         "data": "synthetic",
         "config": {"workload": "finite cluster N=2000 atoms (Q 6000x6000 real symmetric), energy + forces; "
                                "seed 2, 0.1 atoms/A^3, alpha0 x %.4f (collapse rule)" % r["alpha_scale"],
-                   "path": "FP32 reduction/D&C/back-transform on matrix cores + FP64 Ogita-Aishima refinement "
-                           "(second step only where the first leaves a large remainder)"},
+                   "path": "Q^{-1/2} by coupled minimax polynomial iterations of symmetric FP64 products on the "
+                           "matrix cores (no eigenvectors), checked; lambda_min by Lanczos"},
         "fp64_s": r["fp64"]["s"],
         "autotune_s": {p: r[p]["tune_s"] for p in ("fp64", "fp32_refined")},
         "speedup_fp32_refined_vs_fp64": r["fp64"]["s"] / r["fp32_refined"]["s"],
         "errors_vs_fp64": {"energy_per_atom_Ha": dE, "max_grad_coords_Ha_per_bohr": dG,
                            "max_grad_alpha0": dA, "max_grad_omega": dW,
-                           "refine_orth_residual_before": float(e32["errors"][1]),
-                           "refine_steps": float(e32["errors"][2]),
-                           "refine_remainder_estimate": float(e32["errors"][3]),
                            "lambda_min": float(e64["errors"][0])},
-        "roofline": {"bound": "hbm", "kernel": col[dom]["kernel"] + " (per-column reduction launch)",
-                     "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "launches": nl, "avg_launch_us": avg_s * 1e6,
-                     "algorithmic_bytes_per_launch": bytes_per_launch,
-                     "per_column_kernels": list(col.values())},
-        "phase_rooflines": {"fp32_refined": phase_rooflines(r["fp32_refined"]["prof"], 3 * N, True,
-                                                            r["fp32_refined"]["s"]),
-                            "fp64": phase_rooflines(r["fp64"]["prof"], 3 * N, False, r["fp64"]["s"])},
-        "phases": {
-            "fp32_column_GBs": achieved, "fp32_column_total_ms": sum(v["total_ms"] for v in col.values()),
-            "fp32_syr2k_TFs": fl3 / (ms3 * 1e-3) / 1e12 if ms3 > 0 else None, "fp32_syr2k_total_ms": ms3,
-            "fp64_symv_GBs": (b64 / max(nl64, 1)) / (ms64 * 1e-3 / max(nl64, 1)) / 1e9 if ms64 > 0 else None,
-            "fp64_symv_total_ms": ms64,
-            "fp64_syr2k_TFs": fl364 / (ms364 * 1e-3) / 1e12 if ms364 > 0 else None, "fp64_syr2k_total_ms": ms364,
-        },
+        "roofline": {"bound": "mfma", "kernel": dom["kernel"] + " (symmetric FP64 product launch)",
+                     "achieved": dom["achieved_TFs"], "peak": FP64_PEAK_TFS, "unit": "TFLOP/s",
+                     "frac": dom["achieved_TFs"] / FP64_PEAK_TFS if dom["achieved_TFs"] else None,
+                     "launches": dom["launches"], "avg_launch_us": dom["avg_launch_us"],
+                     "flops_per_launch": dom["flops_per_launch"]},
+        "phase_rooflines": {"fp32_refined": phase_rooflines(r["fp32_refined"]["prof"], 3 * N, r["fp32_refined"]["s"]),
+                            "fp64": phase_rooflines(r["fp64"]["prof"], 3 * N, r["fp64"]["s"])},
+        "phases": {"fp32_refined_products": dom, "fp64_products": products("fp64")},
     }
     if "batch" in legs:
         line["batch"] = leg_batch(args, torch, T)

@@ -59,7 +59,15 @@ typedef enum {
     MBD_ERR_UNSUPPORTED = 6         /* valid request this build does not do  */
 } mbd_status;
 
-/* Arithmetic of the diagonalisation.  MBD_FP64: everything in FP64.
+/* Arithmetic.  Unless eigenvalues are wanted, an evaluation in either
+ * precision forms Q^{-1/2} and Tr Q^{1/2} directly, in FP64 products on the
+ * matrix cores and without an eigen-decomposition, and checks the result
+ * (|I - Q^{-1/2} Q Q^{-1/2}| at rounding level).  A system that fails the
+ * check (collapsed, or lambda_max/lambda_min above about 4000), one whose
+ * eigenvalues are wanted (MBD_WANT_EIGVALS), one whose workspaces do not fit
+ * MBD_WORKSPACE_LIMIT, and every MBD_FP32_REFINED system of a context with
+ * MBD_REFINE_TOL set, goes through the diagonalisation.  Its arithmetic is:
+ * MBD_FP64: everything in FP64.
  * MBD_FP32_REFINED: Householder reduction, tridiagonal solve and
  * back-transform in FP32 on matrix cores with FP32 accumulation, then one
  * Ogita-Aishima refinement step of the eigenpairs in FP64 against the FP64 Q
@@ -143,12 +151,13 @@ typedef struct {
     double *grad_lattice;         /* [3][3] dE/dA_vc, Cartesian positions and
                                      fractional q fixed                           */
     double *eigvals;              /* [n_q or 1][3N] eigenvalues of Q ascending    */
-    double *errors;               /* [4]: lambda_min; for MBD_FP32_REFINED also
-                                     max|X^T X - I| of the FP32 eigenvectors, the
+    double *errors;               /* [4]: lambda_min; for a system diagonalised
+                                     in MBD_FP32_REFINED also max|X^T X - I| of the FP32 eigenvectors, the
                                      number of refinement steps taken (1 or 2) and
                                      the estimated largest element error left in
                                      Q^{-1/2} after the last step; [1..3] are 0
-                                     for MBD_FP64 and for a system re-evaluated
+                                     for MBD_FP64, where Q^{-1/2} was formed
+                                     directly and for a system re-evaluated
                                      on the FP64 path after the refinement missed
                                      its target.  Written on the device.        */
 } mbd_result;
@@ -296,10 +305,12 @@ mbd_status mbd_load_tuning(mbd_ctx *ctx, const char *table_json_path);
 
 /* Launch timing for measurement tools.  While enabled, every per-column
  * launch of the Householder reduction and every trailing SYR2K launch (kind 1,
- * the matrix-core BLAS-3 phase) is bracketed by two HIP events on the context
+ * the matrix-core BLAS-3 phase; also every symmetric product of the direct
+ * Q^{-1/2}) is bracketed by two HIP events on the context
  * stream, and so is each phase of an evaluation: 2 input preparation and
  * assembly, 3 Householder reduction, 4 divide and conquer, 5 back-transform,
- * 6 refinement (FP32 path), 7 energy, Q^{-1/2} and gradients.  The per-column
+ * 6 refinement (FP32 path), 7 energy, Q^{-1/2} and gradients (all there is
+ * where Q^{-1/2} is formed directly: see mbd_precision).  The per-column
  * launches are kind 0 where a column takes a SYMV launch and a finish launch
  * (large trailing orders), kind 8 where one fused launch finishes the previous
  * column and runs the column's SYMV (FP32, trailing order up to 4000).
@@ -312,7 +323,7 @@ mbd_status mbd_load_tuning(mbd_ctx *ctx, const char *table_json_path);
  * the stream and returns, for one kind (0..11), the summed event time (ms),
  * the number of records and the summed algorithmic work: bytes of the lower
  * trailing triangle read (kinds 0, 8 and 10), flops of the rank-2k update
- * (kind 1), pair terms (kind 11: N (N - 1) ordered pairs for a finite system,
+ * or product (kind 1), pair terms (kind 11: N (N - 1) ordered pairs for a finite system,
  * N^2 times the image and reciprocal terms for a cell), 0 for the phases.
  * enable = 2 records the
  * phases only, without timing events (which would slow every launch): the

@@ -3,6 +3,7 @@
 // stages on one stream.
 #include "mbd.h"
 #include "mbd_internal.h"
+#include "mbd_isqrt.h"
 #include "mbd_kernels.h"
 #include "mbd_sys.h"
 #include "gemm_mfma.h"  // GEMM_TS128_MIN_ORDER (merge sizes that take the split product)
@@ -59,6 +60,7 @@ struct mbd_ctx {
     char* arena = nullptr;
     size_t arena_cap = 0, arena_used = 0;
     std::map<std::string, std::pair<void*, size_t>> arena_bufs;
+    bool isq_live = false;  // the direct root's workspaces are in use by the current evaluation
     void drop_graphs() {
         for (auto& kv : graphs) {
             if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
@@ -94,6 +96,25 @@ mbd_status fail(mbd_ctx* c, mbd_status code, const char* origin, const std::stri
         if (e_ != hipSuccess) return fail(c, MBD_ERR_DEVICE, origin, hipGetErrorString(e_)); \
     } while (0)
 
+// Gives back the workspaces of the direct Q^{-1/2}: what an evaluation through
+// the eigensolver, or any other call, may use is not reduced by them.
+bool release_isq_work(mbd_ctx* c) {
+    bool any = false;
+    for (auto it = c->bufs.begin(); it != c->bufs.end();) {
+        if (it->first.compare(0, 4, "isq_") != 0) { ++it; continue; }
+        if (!any) {
+            (void)hipStreamSynchronize(c->stream);
+            if (c->gstream) (void)hipStreamSynchronize(c->gstream);
+            c->drop_graphs();
+            any = true;
+        }
+        (void)hipFree(it->second.first);
+        c->total -= it->second.second;
+        it = c->bufs.erase(it);
+    }
+    return any;
+}
+
 // Named, growable device buffer.  Returns nullptr (and records the error) on
 // allocation failure or when MBD_WORKSPACE_LIMIT would be exceeded.
 void* ws(mbd_ctx* c, const char* name, size_t bytes) {
@@ -116,6 +137,8 @@ void* ws(mbd_ctx* c, const char* name, size_t bytes) {
     auto it = c->bufs.find(name);
     if (it != c->bufs.end() && it->second.second >= bytes) return it->second.first;
     size_t old = it != c->bufs.end() ? it->second.second : 0;
+    if (c->limit && c->total - old + bytes > c->limit && !c->isq_live && release_isq_work(c))
+        it = c->bufs.find(name);
     if (c->limit && c->total - old + bytes > c->limit) {
         fail(c, MBD_ERR_OUT_OF_MEMORY, "workspace", std::string("workspace limit exceeded for ") + name);
         return nullptr;
@@ -129,7 +152,12 @@ void* ws(mbd_ctx* c, const char* name, size_t bytes) {
         c->bufs.erase(it);
     }
     void* p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess || !p) {
+    hipError_t e = hipMalloc(&p, bytes);
+    if ((e != hipSuccess || !p) && !c->isq_live && release_isq_work(c)) {
+        (void)hipGetLastError();
+        e = hipMalloc(&p, bytes);
+    }
+    if (e != hipSuccess || !p) {
         (void)hipGetLastError();
         fail(c, MBD_ERR_OUT_OF_MEMORY, "workspace", std::string("hipMalloc failed for ") + name);
         return nullptr;
@@ -303,9 +331,13 @@ mbd_status run_eig(mbd_ctx* c, MatBatch<T> A, const int* ns, const int* ns_host,
 
 bool finite_ok(double x) { return std::isfinite(x); }
 
+// internal code of a system that goes to the eigensolver (never returned)
+constexpr int CODE_EIG = -1;
+
 // status word of a system -> its mbd_status
 int status_code(unsigned st) {
     if (st & (MBD_ST_BAD_INPUT | MBD_ST_COINCIDENT)) return MBD_ERR_INVALID_ARGUMENT;
+    if (st & MBD_ST_NO_ROOT) return CODE_EIG;
     if (st & MBD_ST_COLLAPSE) return MBD_ERR_NEGATIVE_EIGENVALUE;
     if (st & MBD_ST_NOT_CONVERGED) return MBD_ERR_NOT_CONVERGED;
     return MBD_OK;
@@ -581,10 +613,64 @@ mbd_status setup_periodic(mbd_ctx* c, const mbd_system* s, SysDesc& d, PeriodicS
     return MBD_OK;
 }
 
+// Workspaces of the direct Q^{-1/2}.  Returns false (no error recorded) when
+// they do not fit: the evaluation then takes the eigensolver, which needs less.
+bool make_isq_work(mbd_ctx* c, MatBatch<double> Q, const int* ns, int nmax, int nmat, bool want_lmin, IsqWork& w) {
+    const size_t mat = (size_t)Q.stride * nmat, nwg = isq_lanczos_wgs(nmax), sv = round_up(nmax, 64), nm = nmat;
+    w.ns = ns;
+    w.bufs.p[0] = Q.p;
+    w.bufs.ld = Q.ld;
+    w.bufs.stride = Q.stride;
+    w.lan.sV = (long long)sv;
+    w.lan.nwg = (int)nwg;
+    struct { void** p; std::string name; size_t bytes; } need[] = {
+        {(void**)&w.bufs.p[1], "isq_m1", mat * 8}, {(void**)&w.bufs.p[2], "isq_m2", mat * 8},
+        {(void**)&w.bufs.p[3], "isq_m3", mat * 8}, {(void**)&w.bufs.p[4], "isq_m4", mat * 8},
+        {(void**)&w.bufs.p[5], "isq_m5", mat * 8}, {(void**)&w.bufs.p[6], "isq_m6", mat * 8},
+        {(void**)&w.bufs.p[7], "isq_m7", mat * 8}, {(void**)&w.lan.vec, "isq_vec", 4 * sv * nm * 8},
+        {(void**)&w.lan.part, "isq_part", 4 * nwg * nm * 8}, {(void**)&w.lan.alpha, "isq_al", ISQ_LMAX * nm * 8},
+        {(void**)&w.lan.beta, "isq_be", ISQ_LMAX * nm * 8}, {(void**)&w.lan.len, "isq_len", nm * 4},
+        {(void**)&w.lan.done, "isq_done", nm * 4}, {(void**)&w.ops, "isq_ops", sizeof(IsqOp) * ISQ_OPMAX * nm},
+        {(void**)&w.cls, "isq_cls", nm * 4}, {(void**)&w.yv, "isq_yv", 2 * sv * nm * 8},
+        {(void**)&w.check, "isq_check", 2 * nwg * nm * 8}, {(void**)&w.zmax, "isq_zmax", nm * 8}};
+    static_assert(ISQ_NBUF == 8, "buffers listed above");
+    size_t more = 0;
+    for (auto& x : need) {
+        const auto it = c->bufs.find(x.name);
+        const size_t have = it != c->bufs.end() && !c->arena ? it->second.second : 0, b = (x.bytes + 255) & ~size_t(255);
+        if (b > have) more += b - have;
+    }
+    if (c->arena ? c->arena_used + more > c->arena_cap : c->limit && c->total + more > c->limit) return false;
+    for (auto& x : need)
+        if (!(*x.p = ws(c, x.name.c_str(), x.bytes))) {
+            c->err_code = 0;
+            c->err_origin.clear();
+            c->err_msg.clear();
+            (void)release_isq_work(c);
+            return false;
+        }
+    if (!want_lmin) w.zmax = nullptr;
+    return true;
+}
+
+// Whether an evaluation takes the direct Q^{-1/2}: always, unless the caller
+// wants eigenvalues or has set the threshold of the eigenvector refinement.
+bool direct_route(const mbd_ctx* c, unsigned want) {
+    return !(want & MBD_WANT_EIGVALS) && !(c->prec == MBD_FP32_REFINED && c->refine_tol > 0.0);
+}
+
+struct IsqLiveScope {
+    mbd_ctx* c;
+    IsqLiveScope(mbd_ctx* ctx, bool on) : c(ctx) { c->isq_live = on; }
+    ~IsqLiveScope() { c->isq_live = false; }
+};
+
 // One or more finite systems, or one periodic system (per != nullptr: one
-// embedded matrix per q point), all stages on the context stream.
+// embedded matrix per q point), all stages on the context stream.  direct:
+// Q^{-1/2} without eigenvectors (FP64); a system that fails its check gets
+// CODE_EIG and is evaluated again by eig_fallback.
 mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::vector<int>& codes,
-                    const PeriodicSetup* per, const RunMode* mode = nullptr) {
+                    const PeriodicSetup* per, bool direct, const RunMode* mode = nullptr) {
     const bool capturing = mode && mode->capturing;
     const hipStream_t st = c->stream;
     const int nsys = (int)sds.size();
@@ -607,7 +693,7 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
     const long long stride = (long long)ld * nmax;
     const bool grads = (want & (MBD_WANT_GRAD_COORDS | MBD_WANT_GRAD_ALPHA0 | MBD_WANT_GRAD_OMEGA |
                                 MBD_WANT_GRAD_RVDW | MBD_WANT_GRAD_LATTICE)) != 0;
-    const bool fp32 = c->prec == MBD_FP32_REFINED;
+    bool fp32 = c->prec == MBD_FP32_REFINED && !direct;
     GemmTileScope tile_scope(tuned_entry(c, fp32 ? 1 : 0, nmax).gemm_ts);
 
     SysDesc* sd_dev = (SysDesc*)ws(c, "sysdesc", sizeof(SysDesc) * nsys);
@@ -620,6 +706,12 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
     double* sc = wsT<double>(c, "sc64", (size_t)nmax * nmat);
     MatBatch<double> A64 = {wsT<double>(c, "A64", (size_t)stride * nmat), ld, stride};
     MatBatch<float> A32 = {nullptr, ld, stride};
+    IsqWork iw = {};
+    IsqLiveScope live(c, direct);
+    if (direct && A64.p && !make_isq_work(c, A64, ns_dev, nmax, nmat, (want & MBD_WANT_ERRORS) != 0, iw)) {
+        direct = c->isq_live = false;
+        fp32 = c->prec == MBD_FP32_REFINED;
+    }
     if (fp32) A32.p = wsT<float>(c, "A32", (size_t)stride * nmat);
     if (!sd_dev || !ns_dev || !status || !lmin || !om || !cc || !lam || !sc || !A64.p || (fp32 && !A32.p))
         return (mbd_status)c->err_code;
@@ -666,7 +758,12 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
     int* skip_dev = nullptr;  // per matrix: refinement step one was enough
     int* conv_dev = nullptr;  // per matrix: the last step met its target
     int* eig_bad = nullptr;  // per matrix: non-finite tridiagonal
-    if (!fp32) {
+    PhaseTimer ph_eg(&c->prof, st, 7, direct);
+    if (direct) {
+        isq_launch(st, iw, nmax, nmat, nsh.data(), &c->prof);
+        isq_energy_launch(st, iw, sd_dev, nsys, nmax, om, per ? qmult : nullptr, status);
+        HIPCHK(hipGetLastError(), "direct root");
+    } else if (!fp32) {
         // periodic matrices are real embeddings: without vectors each
         // eigenvalue pair is found once
         mbd_status r = run_eig<double>(c, A64, ns_dev, nsh.data(), nmax, nmat, grads, lam, nmax, &X, &eig_bad,
@@ -712,18 +809,24 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
         HIPCHK(hipGetLastError(), "refine");
         X = S;
     }
-    hipLaunchKernelGGL(eig_bad_status_kernel, dim3((nmat + 63) / 64), dim3(64), 0, st, eig_bad, nmat, status,
-                       per ? 1 : 0);
-    PhaseTimer ph_eg(&c->prof, st, 7);
-    mbd_energy_launch(st, sd_dev, nsys, ns_dev, lam, nmax, om, status, lmin, conv_dev, per ? qmult : nullptr);
-    mbd_errors_launch(st, sd_dev, nsys, nmat, stats, skip_dev);
-    HIPCHK(hipGetLastError(), "energy");
+    if (!direct) {
+        hipLaunchKernelGGL(eig_bad_status_kernel, dim3((nmat + 63) / 64), dim3(64), 0, st, eig_bad, nmat, status,
+                           per ? 1 : 0);
+        ph_eg.start();
+        mbd_energy_launch(st, sd_dev, nsys, ns_dev, lam, nmax, om, status, lmin, conv_dev, per ? qmult : nullptr);
+        mbd_errors_launch(st, sd_dev, nsys, nmat, stats, skip_dev);
+        HIPCHK(hipGetLastError(), "energy");
+    }
     if (grads) {
         hipLaunchKernelGGL(grad_gate_kernel, dim3((nsys + 63) / 64), dim3(64), 0, st, status, nsys, sd_dev);
-        mbd_invsqrt4_launch(st, ns_dev, nmax, nmat, lam, nmax, sc);
         MatBatch<double> M = A64;  // FP64: reflectors no longer needed; FP32: Q no longer needed
-        mbd_inv_sqrt_launch(st, ns_dev, nmax, nmat, X, sc, nmax, M);
-        mbd_mirror_launch(st, ns_dev, nmax, nmat, M);
+        if (direct) {
+            M.p = iw.bufs.p[ISQ_RESULT];
+        } else {
+            mbd_invsqrt4_launch(st, ns_dev, nmax, nmat, lam, nmax, sc);
+            mbd_inv_sqrt_launch(st, ns_dev, nmax, nmat, X, sc, nmax, M);
+            mbd_mirror_launch(st, ns_dev, nmax, nmat, M);
+        }
         if (per) {
             const int N = sds[0].N;
             const int nch = per_recip_chunks(prc.ncol);
@@ -749,6 +852,26 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
     HIPCHK(hipStreamSynchronize(st), "synchronize");
     codes.resize(nsys);
     for (int s = 0; s < nsys; s++) codes[s] = status_code(sth[s]);
+    return MBD_OK;
+}
+
+// Systems whose direct Q^{-1/2} failed its check (collapsed, or a spectrum
+// wider than the table's range): evaluated again through the eigensolver,
+// which also names the failure.
+mbd_status eig_fallback(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::vector<int>& codes,
+                        const PeriodicSetup* per) {
+    std::vector<SysDesc> redo;
+    std::vector<int> idx;
+    for (size_t s = 0; s < sds.size(); s++)
+        if (codes[s] == CODE_EIG) { redo.push_back(sds[s]); idx.push_back((int)s); }
+    if (redo.empty()) return MBD_OK;
+    // the attempt's share of the no-allocation scratch is free again
+    c->arena_used = 0;
+    c->arena_bufs.clear();
+    std::vector<int> c2;
+    const mbd_status r = run_core(c, redo, want, c2, per, false);
+    if (r != MBD_OK) return r;
+    for (size_t k = 0; k < idx.size(); k++) codes[idx[k]] = c2[k];
     return MBD_OK;
 }
 
@@ -778,11 +901,20 @@ mbd_status refine_fallback(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want,
     if (redo.empty()) return MBD_OK;
     std::vector<int> c2;
     c->prec = MBD_FP64;
-    const mbd_status r = run_core(c, redo, want, c2, per);
+    const mbd_status r = run_core(c, redo, want, c2, per, false);
     c->prec = MBD_FP32_REFINED;
     if (r != MBD_OK) return r;
     for (size_t k = 0; k < idx.size(); k++) codes[idx[k]] = c2[k];
     return MBD_OK;
+}
+
+// An evaluation with its fallbacks.
+mbd_status evaluate_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::vector<int>& codes,
+                         const PeriodicSetup* per) {
+    mbd_status r = run_core(c, sds, want, codes, per, direct_route(c, want));
+    if (r == MBD_OK) r = eig_fallback(c, sds, want, codes, per);
+    if (r == MBD_OK) r = refine_fallback(c, sds, want, codes, per);
+    return r;
 }
 
 // Per-device address of the scratch array, resolved once per device (with
@@ -874,11 +1006,9 @@ mbd_status mbd_evaluate(mbd_ctx* c, const mbd_system* s, unsigned want, mbd_resu
         const bool pair_q = qp && qp[0] == '1' && !(want & MBD_WANT_EIGVALS);
         r = setup_periodic(c, s, sds[0], ps, pair_q);
         if (r != MBD_OK) return r;
-        r = run_core(c, sds, want, codes, &ps);
-        if (r == MBD_OK) r = refine_fallback(c, sds, want, codes, &ps);
+        r = evaluate_core(c, sds, want, codes, &ps);
     } else {
-        r = run_core(c, sds, want, codes, nullptr);
-        if (r == MBD_OK) r = refine_fallback(c, sds, want, codes, nullptr);
+        r = evaluate_core(c, sds, want, codes, nullptr);
     }
     if (r != MBD_OK) return r;
     return code_message(c, codes[0], "mbd_evaluate");
@@ -905,8 +1035,7 @@ mbd_status mbd_evaluate_noalloc(mbd_ctx* c, const mbd_system* s, unsigned want, 
     c->arena_bufs.clear();
     std::vector<SysDesc> sds(1, make_desc(s, want, out));
     std::vector<int> codes;
-    r = run_core(c, sds, want, codes, nullptr);
-    if (r == MBD_OK) r = refine_fallback(c, sds, want, codes, nullptr);
+    r = evaluate_core(c, sds, want, codes, nullptr);
     c->arena = nullptr;
     c->arena_cap = c->arena_used = 0;
     c->arena_bufs.clear();
@@ -1196,8 +1325,7 @@ mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, u
     }
     std::vector<SysDesc> sds(1, make_desc(&ss, w2, &rs));
     std::vector<int> codes;
-    r = run_core(c, sds, w2, codes, nullptr);
-    if (r == MBD_OK) r = refine_fallback(c, sds, w2, codes, nullptr);
+    r = evaluate_core(c, sds, w2, codes, nullptr);
     if (r != MBD_OK) return r;
     if (codes[0] != MBD_OK) return code_message(c, codes[0], "mbd_rsscs_evaluate");
     if (grads) {
@@ -1257,7 +1385,7 @@ mbd_status mbd_evaluate_batch(mbd_ctx* c, int32_t n_sys, const mbd_system* sys, 
         HIPCHK(hipStreamSynchronize(c->gstream), "graph");
         for (int i = 0; i < n_sys; i++) codes[i] = status_code(g.h_status[i]);
     } else {
-        mbd_status r = run_core(c, sds, want, codes, nullptr);
+        mbd_status r = run_core(c, sds, want, codes, nullptr, direct_route(c, want));
         if (r != MBD_OK) return r;
         if (use_graph && it == c->graphs.end()) {
             // capture the same launch sequence once for later calls of this signature
@@ -1285,7 +1413,7 @@ mbd_status mbd_evaluate_batch(mbd_ctx* c, int32_t n_sys, const mbd_system* sys, 
                 std::vector<int> dummy;
                 ok = hipStreamBeginCapture(c->gstream, hipStreamCaptureModeThreadLocal) == hipSuccess;
                 if (ok) {
-                    const mbd_status rc = run_core(c, sds, want, dummy, nullptr, &m);
+                    const mbd_status rc = run_core(c, sds, want, dummy, nullptr, direct_route(c, want), &m);
                     const bool end_ok = hipStreamEndCapture(c->gstream, &graph) == hipSuccess;
                     ok = rc == MBD_OK && end_ok && graph &&
                          hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0) == hipSuccess;
@@ -1299,7 +1427,8 @@ mbd_status mbd_evaluate_batch(mbd_ctx* c, int32_t n_sys, const mbd_system* sys, 
         }
     }
     {
-        const mbd_status r = refine_fallback(c, sds, want, codes, nullptr);
+        mbd_status r = eig_fallback(c, sds, want, codes, nullptr);
+        if (r == MBD_OK) r = refine_fallback(c, sds, want, codes, nullptr);
         if (r != MBD_OK) return r;
     }
     mbd_status first = MBD_OK;

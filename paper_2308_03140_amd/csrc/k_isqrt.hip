@@ -1,0 +1,896 @@
+// Q^{-1/2} and Tr Q^{1/2} without eigenvectors: a coupled polynomial iteration
+// of symmetric products on the FP64 matrix cores.
+//
+// With the spectrum of Q inside [lo, hi] and kappa = hi/lo, stage one takes
+// Z = W(Q/hi)/sqrt(hi), W the polynomial of least max |1 - sqrt(x) W(x)| on
+// [1/kappa, 1], and Y = Q Z.  Every later stage forms P = Z Y (spectrum in
+// [(1-E)^2, (1+E)^2], E the error of the stage before), its own minimax W on
+// that interval, and Z <- Z W, Y <- Y W: Z tends to Q^{-1/2}, Y to Q^{1/2}
+// (the coupled Newton-Schulz iteration of Higham, "Functions of Matrices",
+// ch. 6, with the composed minimax polynomials of Nakatsukasa & Freund, 2016,
+// in place of the Taylor ones).  Two stages of degree 6 to 9 reach rounding
+// for kappa up to 56, three up to 4000, in 8 to 17 products of which only the
+// lower triangle is formed (n^3 flop each): the eigen-decomposition it
+// replaces reads the matrix once per column (n^3/6 elements in all) and its
+// 6000 columns are a serial chain.
+//
+// Polynomials are taken in the centred variable X = (P/scale - mid)/hw in
+// [-1, 1] and evaluated by Paterson-Stockmeyer (degree 4: 2 products, 6: 3,
+// 9: 4).  A product launch is one step of a per-matrix program, so matrices
+// of different kappa share the launches of a batch:
+//   out  = c0 A B + c1 E1 + c2 E2 + c3 I,   out2 = d0 A B + d1 E1 + d2 E2 + d3 I
+// with A, B, E1, E2, out, out2 from eight buffers (buffer 0 is Q).
+//
+// The interval comes from a few Lanczos steps (hi: largest Ritz value plus
+// twice its residual norm and 4%, lo: half of the smallest).  Afterwards the result
+// is checked: r = x - Z Q Z x for a random sign vector x, whose size is the
+// Frobenius norm of I - Z Q Z; a matrix that fails (an eigenvalue outside the
+// interval, or not positive definite: then no real Z gives Z Q Z = I) is left
+// to the eigensolver.
+#include <cmath>
+#include <mutex>
+#include <vector>
+
+#include "gemm_mfma.h"
+#include "mbd_internal.h"
+#include "mbd_isqrt.h"
+#include "mbd_kernels.h"
+
+// ---------------------------------------------------------------------------
+// minimax polynomials (host, once)
+// ---------------------------------------------------------------------------
+namespace {
+
+// Coefficients b_0..b_d in X = (x - mid)/hw of the W of degree d with least
+// max |1 - t W(t^2)| on t in [l, u], by the Remez exchange; returns the error.
+double remez_isqrt(double l, double u, int d, double* b, double* mid, double* hw) {
+    const int n = d + 2, G = 1500;
+    *mid = 0.5 * (l * l + u * u);
+    *hw = 0.5 * (u * u - l * l);
+    const double pi = 3.14159265358979323846;
+    double t[16], A[16][17], x[16], res[1501];
+    for (int i = 0; i < n; i++) t[i] = 0.5 * (l + u) - 0.5 * (u - l) * std::cos(pi * i / (n - 1));
+    double E = 0.0;
+    for (int it = 0; it < 40; it++) {
+        // t_i W(t_i^2) + (-1)^i E = 1 in the Chebyshev basis
+        for (int i = 0; i < n; i++) {
+            const double X = (t[i] * t[i] - *mid) / *hw;
+            double t0 = 1.0, t1 = X;
+            for (int k = 0; k <= d; k++) {
+                A[i][k] = t[i] * t0;
+                const double t2 = 2.0 * X * t1 - t0;
+                t0 = t1;
+                t1 = t2;
+            }
+            A[i][d + 1] = (i & 1) ? -1.0 : 1.0;
+            A[i][n] = 1.0;
+        }
+        for (int p = 0; p < n; p++) {
+            int q = p;
+            for (int r = p + 1; r < n; r++)
+                if (std::fabs(A[r][p]) > std::fabs(A[q][p])) q = r;
+            for (int k = 0; k <= n; k++) std::swap(A[p][k], A[q][k]);
+            for (int r = p + 1; r < n; r++) {
+                const double f = A[r][p] / A[p][p];
+                for (int k = p; k <= n; k++) A[r][k] -= f * A[p][k];
+            }
+        }
+        for (int p = n - 1; p >= 0; p--) {
+            double s = A[p][n];
+            for (int k = p + 1; k < n; k++) s -= A[p][k] * x[k];
+            x[p] = s / A[p][p];
+        }
+        E = std::fabs(x[d + 1]);
+        // new reference: the extremum of each run of equal sign
+        double big = 0.0, pts[17];
+        int np = 0, start = 0;
+        for (int g = 0; g <= G; g++) {
+            const double tg = 0.5 * (l + u) - 0.5 * (u - l) * std::cos(pi * g / G);
+            const double X = (tg * tg - *mid) / *hw;
+            double t0 = 1.0, t1 = X, s = 0.0;
+            for (int k = 0; k <= d; k++) {
+                s += x[k] * t0;
+                const double t2 = 2.0 * X * t1 - t0;
+                t0 = t1;
+                t1 = t2;
+            }
+            res[g] = 1.0 - tg * s;
+        }
+        for (int g = 1; g <= G + 1; g++) {
+            if (g <= G && res[g] * res[g - 1] >= 0.0) continue;
+            int m = start;
+            for (int k = start; k < g; k++)
+                if (std::fabs(res[k]) > std::fabs(res[m])) m = k;
+            if (np < 17) pts[np] = 0.5 * (l + u) - 0.5 * (u - l) * std::cos(pi * m / G);
+            np++;
+            big = std::max(big, std::fabs(res[m]));
+            start = g;
+        }
+        if (np != n) break;  // rounding level: the error no longer alternates cleanly
+        for (int i = 0; i < n; i++) t[i] = pts[i];
+        if (big <= E * 1.002) break;
+    }
+    // Chebyshev to monomial coefficients in X
+    double Tk[2][16] = {{1.0}, {0.0, 1.0}};
+    for (int k = 0; k <= d; k++) b[k] = 0.0;
+    for (int k = 0; k <= d; k++) {
+        double* cur = Tk[k & 1];
+        if (k >= 2) {
+            double nxt[16];
+            for (int j = 0; j <= k; j++)
+                nxt[j] = (j ? 2.0 * Tk[(k - 1) & 1][j - 1] : 0.0) - (j <= k - 2 ? Tk[k & 1][j] : 0.0);
+            for (int j = 0; j <= k; j++) cur[j] = nxt[j];
+        }
+        for (int j = 0; j <= k; j++) b[j] += x[k] * cur[j];
+    }
+    return E;
+}
+
+// Stage degrees per largest kappa: the fewest products whose composed error
+// stays below 5e-15.
+const struct { double kappa; int deg[3]; } ISQ_PLANS[ISQ_CLASSES] = {
+    {4.0, {4, 6, 0}},   {12.0, {4, 9, 0}},  {28.0, {6, 9, 0}},  {56.0, {9, 9, 0}},    {120.0, {4, 4, 4}},
+    {240.0, {4, 4, 6}}, {600.0, {4, 4, 9}}, {1200.0, {4, 6, 9}}, {4000.0, {6, 9, 9}},
+};
+
+IsqTable g_table;
+std::once_flag g_table_once;
+
+void build_table() {
+    for (int c = 0; c < ISQ_CLASSES; c++) {
+        IsqClass& k = g_table.cls[c];
+        k.kappa = ISQ_PLANS[c].kappa;
+        double l = 1.0 / std::sqrt(k.kappa), u = 1.0;
+        for (int s = 0; s < 3; s++) {
+            const int d = k.deg[s] = ISQ_PLANS[c].deg[s];
+            if (!d) break;
+            const double e = remez_isqrt(l, u, d, k.b[s], &k.mid[s], &k.hw[s]);
+            // the next stage's interval, a little wider than the error left
+            l = 1.0 - 1.05 * e - 1e-12;
+            u = 1.0 + 1.05 * e + 1e-12;
+        }
+    }
+}
+
+}  // namespace
+
+// products of a class's program
+static int isq_products(const IsqClass& c) {
+    int p = 0;
+    for (int s = 0; s < 3 && c.deg[s]; s++) {
+        const bool last = s == 2 || !c.deg[s + 1];
+        p += (s ? 1 : 0) + (c.deg[s] == 4 ? 2 : c.deg[s] == 6 ? 3 : 4) + (last ? 1 : s ? 2 : 1);
+    }
+    return p;
+}
+
+const IsqTable& isq_table() {
+    std::call_once(g_table_once, build_table);
+    return g_table;
+}
+
+// ---------------------------------------------------------------------------
+// Lanczos (batched, one launch per step)
+// ---------------------------------------------------------------------------
+// random signs, the same for every matrix
+__device__ __forceinline__ double isq_sign(int k, unsigned seed) {
+    unsigned x = (unsigned)k * 2654435761u + seed;
+    x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
+    return (x & 1u) ? 1.0 : -1.0;
+}
+
+// sums of acc[r] over the workgroup, valid in every thread (LDS: 4 x ISQ_MVR)
+__device__ __forceinline__ void isq_row_sums(double (&acc)[ISQ_MVR], double (*red)[ISQ_MVR]) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int r = 0; r < ISQ_MVR; r++) acc[r] = wave_sum(acc[r]);
+    __syncthreads();
+    if (lane == 0)
+#pragma unroll
+        for (int r = 0; r < ISQ_MVR; r++) red[wv][r] = acc[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ISQ_MVR; r++) acc[r] = (red[0][r] + red[1][r]) + (red[2][r] + red[3][r]);
+}
+
+// Sums of the two partials that the workgroups of the step before left.
+__device__ __forceinline__ void isq_part_sums(const double* part, int nwg, double& s1, double& s2, double* red) {
+    double a = 0.0, c = 0.0;
+    for (int w = threadIdx.x; w < nwg; w += 256) { a += part[2 * w]; c += part[2 * w + 1]; }
+    s1 = block_sum256(a, red);
+    s2 = block_sum256(c, red);
+}
+
+// The step's partials are s1 = v.w', s2 = w'.w' with w' = M v - a v - beta v_prev
+// and a the alpha of the step before (M_00 at first): alpha = a + s1, beta^2 =
+// s2 - s1^2.  Taking a off first keeps beta accurate where M is close to a
+// multiple of the identity (weakly coupled identical atoms).  A beta at
+// rounding level ends the recurrence.
+__device__ __forceinline__ bool isq_beta(double alpha, double s1, double s2, double& beta) {
+    const double b2 = s2 - s1 * s1;
+    const bool more = b2 > 1e-28 * alpha * alpha && s2 < 1e300;
+    beta = more ? sqrt(b2) : 0.0;
+    return more;
+}
+
+// Step j: every workgroup forms v_j from the step before (elementwise, where
+// it is needed) and w'_j for its ISQ_MVR rows; bandwidth bound (M read once:
+// 288 MB at order 6000).  ISQ_MVR rows share the two loads behind an element
+// of v_j; one launch per step, with no grid barrier.
+__global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, const int* ns, IsqLanczos L, int j) {
+    __shared__ double red4[4], red[4][ISQ_MVR];
+    const int b = blockIdx.z, n = ns[b];
+    const int r0 = blockIdx.x * ISQ_MVR;
+    if (r0 >= n) return;
+    if (L.done && L.done[b]) return;
+    const int nwg = (n + ISQ_MVR - 1) / ISQ_MVR;
+    double* vec = L.vec + (long long)b * L.sV * 4;
+    double* vj = vec + (long long)(j & 1) * L.sV;
+    const double* v1 = vec + (long long)((j + 1) & 1) * L.sV;
+    double* wj = vec + (long long)(2 + (j & 1)) * L.sV;
+    const double* w1 = vec + (long long)(2 + ((j + 1) & 1)) * L.sV;
+    double* part = L.part + ((long long)b * 2 + (j & 1)) * 2 * L.nwg;
+    const double* pprev = L.part + ((long long)b * 2 + ((j + 1) & 1)) * 2 * L.nwg;
+    double* al = L.alpha + (long long)b * ISQ_LMAX;
+    double* be = L.beta + (long long)b * ISQ_LMAX;
+    const double* Mb = M.at(b);
+    const long long ld = M.ld;
+    const double a00 = Mb[0];
+    double s1 = 0.0, beta = 0.0, inv = 0.0, a = a00;
+    if (j > 0) {
+        double s2;
+        isq_part_sums(pprev, nwg, s1, s2, red4);
+        a = (j > 1 ? al[j - 2] : a00) + s1;
+        const bool more = isq_beta(a, s1, s2, beta);
+        inv = more ? 1.0 / beta : 0.0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            al[j - 1] = a;
+            be[j - 1] = beta;
+            if (!more && L.len[b] == 0) L.len[b] = j;
+        }
+    } else if (blockIdx.x == 0 && threadIdx.x == 0) {
+        L.len[b] = 0;
+    }
+    const double inv_n = j == 0 ? 1.0 / sqrt((double)n) : 0.0;
+    auto v_at = [&](int k) -> double {
+        return j == 0 ? isq_sign(k, 77u) * inv_n : (w1[k] - s1 * v1[k]) * inv;
+    };
+    const double* row[ISQ_MVR];
+    double acc[ISQ_MVR];
+#pragma unroll
+    for (int r = 0; r < ISQ_MVR; r++) {
+        row[r] = Mb + (long long)min(r0 + r, n - 1) * ld;
+        acc[r] = 0.0;
+    }
+    for (int k = threadIdx.x; k < n; k += 256) {
+        const double v = v_at(k);
+#pragma unroll
+        for (int r = 0; r < ISQ_MVR; r++) acc[r] += row[r][k] * v;
+    }
+    isq_row_sums(acc, red);
+    if (threadIdx.x < ISQ_MVR) {
+        const int rr = r0 + threadIdx.x;
+        double p1 = 0.0, p2 = 0.0;
+        if (rr < n) {
+            double sum = 0.0;
+#pragma unroll
+            for (int r = 0; r < ISQ_MVR; r++) sum = (int)threadIdx.x == r ? acc[r] : sum;
+            const double v = v_at(rr);
+            const double w = sum - a * v - (j > 0 ? beta * v1[rr] : 0.0);
+            vj[rr] = v;
+            wj[rr] = w;
+            p1 = v * w;
+            p2 = w * w;
+        }
+        // eight lanes: butterfly within the half row
+        p1 = quad_sum(p1);
+        p1 += dpp<DPP_HALF_MIRROR>(p1);
+        p2 = quad_sum(p2);
+        p2 += dpp<DPP_HALF_MIRROR>(p2);
+        if (threadIdx.x == 0) {
+            part[2 * blockIdx.x] = p1;
+            part[2 * blockIdx.x + 1] = p2;
+        }
+    }
+}
+
+// Smallest (which < 0) or largest eigenvalue of the symmetric tridiagonal
+// (al, be) of order m: multisection on Sturm counts, one shift per lane.
+__device__ double isq_tri_extreme(const double* al, const double* be, int m, int which, int rounds) {
+    const int lane = threadIdx.x & 63;
+    double lo = 1e300, hi = -1e300;
+    for (int i = 0; i < m; i++) {
+        const double r = (i ? fabs(be[i - 1]) : 0.0) + (i + 1 < m ? fabs(be[i]) : 0.0);
+        lo = fmin(lo, al[i] - r);
+        hi = fmax(hi, al[i] + r);
+    }
+    const double pad = 1e-15 * fmax(fabs(lo), fabs(hi)) + 1e-300;
+    lo -= pad;
+    hi += pad;
+    for (int it = 0; it < rounds; it++) {
+        const double x = lo + (hi - lo) * (lane + 1) / 65.0;
+        int cnt = 0;
+        double d = 1.0;
+        for (int i = 0; i < m; i++) {
+            const double bb = i ? be[i - 1] * be[i - 1] : 0.0;
+            d = al[i] - x - (i ? bb / d : 0.0);
+            if (d == 0.0) d = -1e-300;
+            cnt += d < 0.0;
+        }
+        // lanes whose shift lies above the wanted eigenvalue
+        const unsigned long long above = __ballot(which < 0 ? cnt >= 1 : cnt >= m);
+        const int first = above ? __ffsll((long long)above) - 1 : 64;
+        const double step = (hi - lo) / 65.0;
+        const double nlo = lo + step * first;
+        hi = lo + step * (first + 1);
+        lo = nlo;
+    }
+    return 0.5 * (lo + hi);
+}
+
+// All Lanczos steps of a matrix in one workgroup, orders up to ISQ_SMALL: a
+// launch per step would cost about 3 us each, more than the matrix's read
+// (order 448: 1.6 MB, from L2 after the first step).  Thread (p, r) sums every
+// np-th column's share of row r (columns of M are contiguous, M symmetric), so
+// the products need no cross-lane sums.  zmax != nullptr: run until the
+// largest eigenvalue has converged (see isq_zmax_kernel) and record it.
+__global__ __launch_bounds__(1024) void isq_small_lanczos_kernel(MatBatch<double> M, const int* ns, IsqLanczos L, int steps,
+                                                                   const int* cls, double* zmax) {
+    __shared__ double v[2][ISQ_SMALL], red[16], sums[1024], al[ISQ_LMAX], be[ISQ_LMAX], zs;
+    const int b = blockIdx.x, n = ns[b], tid = threadIdx.x;
+    if (zmax && cls[b] < 0) {
+        if (tid == 0) zmax[b] = -1.0;
+        return;
+    }
+    const int npad = n <= 32 ? 32 : (n + 63) / 64 * 64, np = 1024 / npad;
+    const int r = tid % npad, p = tid / npad;
+    const double* Mb = M.at(b);
+    const long long ld = M.ld;
+    auto block_sum = [&](double x) {
+        x = wave_sum(x);
+        __syncthreads();
+        if ((tid & 63) == 0) red[tid >> 6] = x;
+        __syncthreads();
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 16; i++) s += red[i];
+        return s;
+    };
+    const bool mine = p == 0 && r < n;
+    double vr = mine ? isq_sign(r, 77u) / sqrt((double)n) : 0.0, vprev = 0.0, beta = 0.0, a = Mb[0], zp = 0.0;
+    int m = 0;
+    bool ended = false;
+    for (int j = 0; j < steps && !ended; j++) {
+        double* vj = v[j & 1];
+        if (mine) vj[r] = vr;
+        __syncthreads();
+        double s = 0.0;
+        if (p < np && r < n) {
+            const double* col = Mb + r;
+            int k = p;
+            for (; k + 7 * np < n; k += 8 * np) {
+                double x[8];
+#pragma unroll
+                for (int u = 0; u < 8; u++) x[u] = col[(long long)(k + u * np) * ld];
+#pragma unroll
+                for (int u = 0; u < 8; u++) s += x[u] * vj[k + u * np];
+            }
+            for (; k < n; k += np) s += col[(long long)k * ld] * vj[k];
+        }
+        sums[tid] = s;
+        __syncthreads();
+        double w = 0.0;
+        if (mine) {
+            for (int q = 0; q < np; q++) w += sums[q * npad + r];
+            w -= a * vr + beta * vprev;
+        }
+        const double s1 = block_sum(vr * w);
+        a += s1;
+        w -= s1 * vr;
+        const double b2 = block_sum(w * w);
+        const bool more = b2 > 1e-28 * a * a && b2 < 1e300;
+        beta = more ? sqrt(b2) : 0.0;
+        if (tid == 0) { al[j] = a; be[j] = beta; }
+        vprev = vr;
+        vr = more ? w / beta : 0.0;
+        m = j + 1;
+        ended = !more;
+        if (zmax && (ended || m % ISQ_LCHECK == 0 || m == steps)) {
+            __syncthreads();
+            if (tid < 64) {
+                const double z = isq_tri_extreme(al, be, m, 1, 10);
+                if (tid == 0) zs = z;
+            }
+            __syncthreads();
+            const double z = zs;
+            const bool conv = ended || (m > 2 * ISQ_LCHECK && fabs(z - zp) <= 4e-15 * z) ||
+                              (m == steps && fabs(z - zp) <= 1e-11 * z);
+            if (tid == 0) zmax[b] = conv ? z : -1.0;
+            zp = z;
+            if (conv) return;
+        }
+    }
+    if (zmax) return;
+    __syncthreads();
+    for (int i = tid; i < m; i += 1024) {
+        L.alpha[(long long)b * ISQ_LMAX + i] = al[i];
+        L.beta[(long long)b * ISQ_LMAX + i] = be[i];
+    }
+    if (tid == 0) L.len[b] = ended ? m : 0;
+}
+
+// ---------------------------------------------------------------------------
+// program of a matrix
+// ---------------------------------------------------------------------------
+struct IsqEmit {
+    IsqOp* op;
+    int k;
+    __device__ void put(int a, int b, int e1, int e2, int out, int out2, double c0, double c1, double c2, double c3,
+                        double d0 = 0, double d1 = 0, double d2 = 0, double d3 = 0) {
+        IsqOp o;
+        o.a = (signed char)a; o.b = (signed char)b; o.e1 = (signed char)e1; o.e2 = (signed char)e2;
+        o.out = (signed char)out; o.out2 = (signed char)out2;
+        o.c[0] = c0; o.c[1] = c1; o.c[2] = c2; o.c[3] = c3;
+        o.d[0] = d0; o.d[1] = d1; o.d[2] = d2; o.d[3] = d3;
+        op[k++] = o;
+    }
+    // W(X) of degree d into buffer w, scaled by f, for the symmetric matrix in
+    // buffer p with X = s p + g I (s = 1, g = 0: the buffer holds X itself).
+    // Buffers x2, x3, t, u hold the powers and inner sums.
+    __device__ void poly(int p, double s, double g, int d, const double* b, double f, int x2, int x3, int t, int u,
+                         int w) {
+        // X^2 = s^2 p p + 2 s g p + g^2 I
+        const double q0 = s * s, q1 = 2.0 * s * g, q3 = g * g;
+        if (d == 4) {
+            // T = b4 X^2 + b3 X + b2;  W = X^2 T + b1 X + b0
+            put(p, p, p, -1, x2, t, q0, q1, 0, q3, b[4] * q0, b[4] * q1 + b[3] * s, 0, b[4] * q3 + b[3] * g + b[2]);
+            put(x2, t, p, -1, w, -1, f, f * b[1] * s, 0, f * (b[1] * g + b[0]));
+            return;
+        }
+        put(p, p, p, -1, x2, -1, q0, q1, 0, q3);
+        // X^3 = s p X^2 + g X^2;  T = inner sum of the top coefficients
+        const int o = d == 6 ? 3 : 6;
+        put(p, x2, x2, p, x3, t, s, g, 0, 0, b[o + 3] * s, b[o + 3] * g + b[o + 2], b[o + 1] * s, b[o + 1] * g + b[o]);
+        if (d == 9) {
+            put(x3, t, x2, p, u, -1, 1.0, b[5], b[4] * s, b[4] * g + b[3]);
+            put(x3, u, x2, p, w, -1, f, f * b[2], f * b[1] * s, f * (b[1] * g + b[0]));
+        } else {
+            put(x3, t, x2, p, w, -1, f, f * b[2], f * b[1] * s, f * (b[1] * g + b[0]));
+        }
+    }
+};
+
+// One wavefront per matrix: spectral interval from the Lanczos coefficients,
+// class, and the program (its last product always lands in buffer
+// ISQ_RESULT).  No class (not positive definite, kappa above the table's
+// range, non-finite): an empty program, and the check afterwards fails.
+__global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos L, int steps, IsqTable tab, IsqOp* ops,
+                                                        int* cls) {
+    __shared__ double al[ISQ_LMAX], be[ISQ_LMAX];
+    const int b = blockIdx.x, n = ns[b], lane = threadIdx.x;
+    IsqOp* op = ops + (long long)b * ISQ_OPMAX;
+    for (int i = lane; i < steps; i += 64) {
+        al[i] = L.alpha[(long long)b * ISQ_LMAX + i];
+        be[i] = L.beta[(long long)b * ISQ_LMAX + i];
+    }
+    double blast;
+    bool more = true;
+    if (L.nwg) {
+        // one launch per step: the last step's sums are still to be taken
+        const int nwg = (n + ISQ_MVR - 1) / ISQ_MVR;
+        const double* part = L.part + ((long long)b * 2 + ((steps + 1) & 1)) * 2 * L.nwg;
+        double s1 = 0.0, s2 = 0.0;
+        for (int w = lane; w < nwg; w += 64) { s1 += part[2 * w]; s2 += part[2 * w + 1]; }
+        s1 = wave_sum(s1);
+        s2 = wave_sum(s2);
+        const double a = L.alpha[(long long)b * ISQ_LMAX + steps - 2] + s1;
+        more = isq_beta(a, s1, s2, blast);
+        __syncthreads();
+        if (lane == 0) { al[steps - 1] = a; be[steps - 1] = blast; }
+    }
+    __syncthreads();
+    blast = be[steps - 1];
+    int m = L.len[b];
+    const bool exact = m > 0 || !more;
+    if (m == 0) m = steps;
+    const double tmin = isq_tri_extreme(al, be, m, -1, 5), tmax = isq_tri_extreme(al, be, m, 1, 5);
+    if (lane != 0) return;
+    double res = 0.0;
+    if (!exact) {
+        // last component of the eigenvector of tmax, by the three-term recurrence
+        double x0 = 0.0, x1 = 1.0, nn = 1.0;
+        for (int i = 0; i + 1 < m; i++) {
+            const double x2 = ((tmax - al[i]) * x1 - (i ? be[i - 1] * x0 : 0.0)) / be[i];
+            x0 = x1;
+            x1 = x2;
+            nn += x2 * x2;
+        }
+        res = blast * fabs(x1) / sqrt(nn);
+    }
+    const double hi = exact ? tmax * 1.01 : (tmax + 2.0 * res) * 1.04;
+    const double lo = tmin * (exact ? 0.9 : ISQ_LOW_FRACTION);
+    int c = -1;
+    if (lo > 0.0 && hi < 1e100) {
+        for (int i = ISQ_CLASSES - 1; i >= 0; i--)
+            if (hi <= lo * tab.cls[i].kappa) c = i;
+    }
+    cls[b] = c;
+    IsqEmit e = {op, 0};
+    if (c >= 0) {
+        const IsqClass& k = tab.cls[c];
+        // stage one: X = (Q/hi - mid)/hw; buffers: 1 X^2, 2 X^3, 3 T, 4 U
+        const int last = k.deg[2] ? 2 : 1;
+        e.poly(0, 1.0 / (hi * k.hw[0]), -k.mid[0] / k.hw[0], k.deg[0], k.b[0], 1.0 / sqrt(hi), 1, 2, 3, 4, 5);
+        e.put(0, 5, -1, -1, 6, -1, 1.0, 0, 0, 0);  // Y = Q Z
+        int z = 5, y = 6;
+        for (int s = 1; s <= last; s++) {
+            // X = (Z Y - mid)/hw
+            e.put(z, y, -1, -1, 7, -1, 1.0 / k.hw[s], 0, 0, -k.mid[s] / k.hw[s]);
+            if (s < last) {
+                // buffers free here: 1 2 3 4 and, after X, none of z, y
+                e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 1, 2, 3, 4, k.deg[s] == 9 ? 3 : 4);
+                const int w = k.deg[s] == 9 ? 3 : 4;
+                e.put(y, w, -1, -1, 2, -1, 1.0, 0, 0, 0);
+                e.put(z, w, -1, -1, 1, -1, 1.0, 0, 0, 0);
+                z = 1;
+                y = 2;
+            } else if (z == 5) {
+                // y is free once X is formed
+                e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 1, 2, 3, 4, 6);
+                e.put(z, 6, -1, -1, ISQ_RESULT, -1, 1.0, 0, 0, 0);
+            } else {
+                e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 2, 3, 4, 5, 6);
+                e.put(z, 6, -1, -1, ISQ_RESULT, -1, 1.0, 0, 0, 0);
+            }
+        }
+    }
+    while (e.k < ISQ_OPMAX) e.put(-1, -1, -1, -1, -1, -1, 0, 0, 0, 0);
+}
+
+// ---------------------------------------------------------------------------
+// symmetric product step
+// ---------------------------------------------------------------------------
+// TS x TS tile of the lower triangle per workgroup of WM x WN wavefronts; both
+// operands are symmetric and stored in full, so A(m, k) and B(k, n) are read
+// along their columns, 16 bytes per lane, through a buffer descriptor whose
+// size ends the K loop (k >= n reads zero) and whose rows past n only reach
+// rows of C that are not stored.  K goes through LDS in slabs of BK, double
+// buffered, the next slab's loads in flight during the products.  The row
+// stride TS + 16 puts the two k rows of a half wavefront's 8-byte reads on
+// different halves of the 64 banks.  E1, E2 are read and the upper triangle
+// written straight from the result registers (16 lanes along n: 128-byte
+// runs); the lower triangle goes through a 16 x 16 LDS transpose per
+// wavefront for the same run length.
+typedef double isq_d2 __attribute__((ext_vector_type(2)));
+
+// LDS written by a wavefront becomes visible to its other lanes
+__device__ __forceinline__ void isq_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <int TS, int BK, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN) void isq_prod_kernel(IsqBufs bufs, const int* ns, const IsqOp* ops,
+                                                                  int step) {
+    constexpr int NT = 64 * WM * WN;
+    constexpr int MI = TS / WM / 16, NJ = TS / WN / 16;
+    constexpr int LDT = TS + 16;
+    constexpr int LV = BK * TS / 2 / NT;  // 16-byte loads per thread, operand and slab
+    static_assert(LV * NT * 2 == BK * TS && MI > 0 && NJ > 0, "slab and tile divide evenly");
+    __shared__ __align__(16) double As[2][BK][LDT], Bs[2][BK][LDT];
+    const int b = blockIdx.z;
+    const IsqOp& op = ops[(long long)b * ISQ_OPMAX + step];
+    if (op.a < 0) return;
+    const int n = ns[b];
+    int ti, tj;
+    band_lower_tile(xcd_virtual(blockIdx.x, gridDim.x), bufs.tiles, ti, tj);
+    const int m0 = ti * TS, n0 = tj * TS;
+    if (m0 >= n) return;
+    const int ld = bufs.ld;
+    const double* A = bufs.p[op.a] + (long long)b * bufs.stride;
+    const double* B = bufs.p[op.b] + (long long)b * bufs.stride;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    typename mfma4<double>::v acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; i++)
+#pragma unroll
+        for (int j = 0; j < NJ; j++) acc[i][j] = typename mfma4<double>::v{0, 0, 0, 0};
+    isq_d2 ra[LV], rb[LV];
+    auto gload = [&](int k0) {
+        const int kn = min(BK, n - k0);
+        const auto dA = make_rsrc(A + (long long)k0 * ld, (unsigned)kn * ld * 8u);
+        const auto dB = make_rsrc(B + (long long)k0 * ld, (unsigned)kn * ld * 8u);
+#pragma unroll
+        for (int v = 0; v < LV; v++) {
+            const int idx = tid + v * NT, k = idx / (TS / 2), m = 2 * (idx % (TS / 2));
+            ra[v] = __builtin_bit_cast(isq_d2, buf_load16<double>(dA, (unsigned)(k * ld + m0 + m) * 8u));
+            rb[v] = __builtin_bit_cast(isq_d2, buf_load16<double>(dB, (unsigned)(k * ld + n0 + m) * 8u));
+        }
+    };
+    auto sstore = [&](int buf) {
+#pragma unroll
+        for (int v = 0; v < LV; v++) {
+            const int idx = tid + v * NT, k = idx / (TS / 2), m = 2 * (idx % (TS / 2));
+            *reinterpret_cast<isq_d2*>(&As[buf][k][m]) = ra[v];
+            *reinterpret_cast<isq_d2*>(&Bs[buf][k][m]) = rb[v];
+        }
+    };
+    const int nk = (n + BK - 1) / BK;
+    gload(0);
+    sstore(0);
+    __syncthreads();
+    for (int kt = 0; kt < nk; kt++) {
+        const int buf = kt & 1;
+        if (kt + 1 < nk) gload((kt + 1) * BK);
+#pragma unroll
+        for (int kk = 0; kk < BK; kk += 4) {
+            double af[MI], bf[NJ];
+#pragma unroll
+            for (int i = 0; i < MI; i++) af[i] = As[buf][kk + (lane >> 4)][wm * (TS / WM) + i * 16 + (lane & 15)];
+#pragma unroll
+            for (int j = 0; j < NJ; j++) bf[j] = Bs[buf][kk + (lane >> 4)][wn * (TS / WN) + j * 16 + (lane & 15)];
+#pragma unroll
+            for (int i = 0; i < MI; i++)
+#pragma unroll
+                for (int j = 0; j < NJ; j++) acc[i][j] = mfma16x16x4(af[i], bf[j], acc[i][j]);
+        }
+        if (kt + 1 < nk) sstore(buf ^ 1);
+        __syncthreads();
+    }
+    // epilogue; the K loop ended on a barrier, so the staging space is free
+    const double* E1 = op.e1 >= 0 ? bufs.p[op.e1] + (long long)b * bufs.stride : nullptr;
+    const double* E2 = op.e2 >= 0 ? bufs.p[op.e2] + (long long)b * bufs.stride : nullptr;
+    double* C1 = bufs.p[op.out] + (long long)b * bufs.stride;
+    double* C2 = op.out2 >= 0 ? bufs.p[op.out2] + (long long)b * bufs.stride : nullptr;
+    double* tr = &As[0][0][0] + wave * (16 * 17);
+    static_assert(WM * WN * 16 * 17 <= 2 * BK * LDT, "transpose blocks fit the A slabs");
+    double c[4], d[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) { c[q] = op.c[q]; d[q] = op.d[q]; }
+#pragma unroll
+    for (int i = 0; i < MI; i++)
+#pragma unroll
+        for (int j = 0; j < NJ; j++) {
+            const int mb = m0 + wm * (TS / WM) + i * 16, nb = n0 + wn * (TS / WN) + j * 16;
+            if (mb >= n || nb >= n || mb + 15 < nb) continue;  // wave-uniform
+            const int col = nb + (lane & 15);
+            double o2[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int row = mb + (lane >> 4) + 4 * r;
+                const bool in = row < n && col <= row;
+                const long long up = (long long)col + (long long)row * ld;
+                const double v = acc[i][j][r];
+                const double e1 = E1 && in ? E1[up] : 0.0, e2 = E2 && in ? E2[up] : 0.0;
+                const double id = row == col ? 1.0 : 0.0;
+                const double o1 = c[0] * v + c[1] * e1 + c[2] * e2 + c[3] * id;
+                o2[r] = d[0] * v + d[1] * e1 + d[2] * e2 + d[3] * id;
+                if (in) {
+                    C1[up] = o1;
+                    if (C2) C2[up] = o2[r];
+                }
+                tr[(lane & 15) * 17 + (lane >> 4) + 4 * r] = o1;
+            }
+            isq_wave_sync();
+            const int lrow = mb + (lane & 15);
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int lc = (lane >> 4) + 4 * r, lcol = nb + lc;
+                if (lrow < n && lcol < lrow) C1[lrow + (long long)lcol * ld] = tr[lc * 17 + (lane & 15)];
+            }
+            if (C2) {
+                isq_wave_sync();
+#pragma unroll
+                for (int r = 0; r < 4; r++) tr[(lane & 15) * 17 + (lane >> 4) + 4 * r] = o2[r];
+                isq_wave_sync();
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const int lc = (lane >> 4) + 4 * r, lcol = nb + lc;
+                    if (lrow < n && lcol < lrow) C2[lrow + (long long)lcol * ld] = tr[lc * 17 + (lane & 15)];
+                }
+            }
+            isq_wave_sync();
+        }
+}
+
+// ---------------------------------------------------------------------------
+// trace and check
+// ---------------------------------------------------------------------------
+// pass 0: y1 = Z x (x random signs) and the row block's share of sum Q o Z;
+// pass 1: y2 = Q y1; pass 2: x - Z y2 and the row block's sum of its squares.
+// A matrix without a program is skipped (its result is never read).
+__global__ __launch_bounds__(256) void isq_check_kernel(MatBatch<double> Q, MatBatch<double> Z, const int* ns,
+                                                          const int* cls, double* yv, long long sV, double* part,
+                                                          int nwg_max, int pass) {
+    __shared__ double red[4][ISQ_MVR], red4[4];
+    const int b = blockIdx.z, n = ns[b];
+    const int r0 = blockIdx.x * ISQ_MVR;
+    if (r0 >= n || cls[b] < 0) return;
+    const MatBatch<double>& M = pass == 1 ? Q : Z;
+    double* y1 = yv + (long long)b * 2 * sV;
+    double* y2 = y1 + sV;
+    const double* x = pass == 1 ? y1 : y2;
+    const double* row[ISQ_MVR];
+    const double* qrow[ISQ_MVR];
+    double acc[ISQ_MVR], e = 0.0;
+#pragma unroll
+    for (int r = 0; r < ISQ_MVR; r++) {
+        const long long off = (long long)min(r0 + r, n - 1) * M.ld;
+        row[r] = M.at(b) + off;
+        qrow[r] = Q.at(b) + off;
+        acc[r] = 0.0;
+    }
+    for (int k = threadIdx.x; k < n; k += 256) {
+        const double v = pass == 0 ? isq_sign(k, 991u) : x[k];
+#pragma unroll
+        for (int r = 0; r < ISQ_MVR; r++) {
+            const double z = row[r][k];
+            acc[r] += z * v;
+            if (pass == 0 && r0 + r < n) e += z * qrow[r][k];
+        }
+    }
+    isq_row_sums(acc, red);
+    if (pass == 0) e = block_sum256(e, red4);
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+#pragma unroll
+        for (int r = 0; r < ISQ_MVR; r++)
+            if (r0 + r < n) {
+                if (pass == 0) y1[r0 + r] = acc[r];
+                else if (pass == 1) y2[r0 + r] = acc[r];
+                else {
+                    const double dr = isq_sign(r0 + r, 991u) - acc[r];
+                    s += dr * dr;
+                }
+            }
+        double* pb = part + ((long long)b * nwg_max + blockIdx.x) * 2;
+        if (pass == 0) pb[0] = e;
+        if (pass == 2) pb[1] = s;
+    }
+}
+
+// Energy from the traces (E = w sum_q Tr(Q Z) - (3/2) sum omega) and the
+// verdict of the check; lambda_min from the Lanczos run on Z when wanted.
+__global__ __launch_bounds__(256) void isq_energy_kernel(const SysDesc* sd, const int* ns, const int* cls,
+                                                           const double* part, int nwg_max, const double* om,
+                                                           const double* mmult, const double* zmax, unsigned* status) {
+    __shared__ double red[4];
+    const int s = blockIdx.x;
+    const SysDesc& S = sd[s];
+    double esum = 0.0, lmin = 1e300;
+    bool ok = true;
+    for (int q = 0; q < S.nmat; q++) {
+        const int b = S.mat0 + q;
+        if (cls[b] < 0) { ok = false; break; }  // uniform over the workgroup
+        const int n = ns[b], nwg = (n + ISQ_MVR - 1) / ISQ_MVR;
+        double e = 0.0, r = 0.0;
+        for (int w = threadIdx.x; w < nwg; w += 256) {
+            e += part[((long long)b * nwg_max + w) * 2];
+            r += part[((long long)b * nwg_max + w) * 2 + 1];
+        }
+        e = block_sum256(e, red);
+        r = block_sum256(r, red);
+        // |I - Z Q Z|_F^2; rounding leaves about 1e-14 sqrt(n) (measured, orders 30 to 6000)
+        if (!(r <= ISQ_CHECK * ISQ_CHECK * n)) ok = false;
+        if (zmax) {
+            const double z = zmax[b];
+            if (!(z > 0.0)) ok = false;
+            lmin = fmin(lmin, 1.0 / (z * z));
+        }
+        esum += S.weight * (mmult ? mmult[b] : 1.0) * e;
+    }
+    double wsum = 0.0;
+    for (int i = threadIdx.x; i < S.N; i += 256) wsum += om[S.atom_off + i];
+    wsum = block_sum256(wsum, red);
+    if (threadIdx.x == 0) {
+        if (!ok) atomicOr(&status[s], MBD_ST_NO_ROOT);
+        if (S.energy) *S.energy = esum - 1.5 * wsum;
+        if (S.errors) {
+            S.errors[0] = lmin;
+            S.errors[1] = S.errors[2] = S.errors[3] = 0.0;
+        }
+    }
+}
+
+// Largest eigenvalue of Z from the Lanczos coefficients so far; done[b] is set
+// when the last ISQ_LCHECK steps changed it by rounding only, or the
+// recurrence ended.  Unconverged after the last step: -1.
+__global__ __launch_bounds__(64) void isq_zmax_kernel(const int* ns, const int* cls, IsqLanczos L, int steps, int last,
+                                                        double* zmax) {
+    __shared__ double al[ISQ_LMAX], be[ISQ_LMAX];
+    const int b = blockIdx.x, lane = threadIdx.x;
+    if (steps == 0) {
+        if (lane == 0) { L.done[b] = cls[b] < 0 ? 1 : 0; zmax[b] = -1.0; }
+        return;
+    }
+    if (L.done[b]) return;
+    int m = L.len[b];
+    const bool ended = m > 0;
+    if (!ended) m = steps - 1;  // alpha[steps - 1] is recorded by the next step
+    for (int i = lane; i < m; i += 64) {
+        al[i] = L.alpha[(long long)b * ISQ_LMAX + i];
+        be[i] = L.beta[(long long)b * ISQ_LMAX + i];
+    }
+    __syncthreads();
+    const double z = isq_tri_extreme(al, be, m, 1, 10);
+    if (lane == 0) {
+        const double zp = zmax[b] < 0.0 ? -zmax[b] : zmax[b];
+        const bool conv = ended || (steps > 2 * ISQ_LCHECK && fabs(z - zp) <= 4e-15 * z);
+        if (conv) L.done[b] = 1;
+        zmax[b] = conv || (last && fabs(z - zp) <= 1e-11 * z) ? z : -z;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// launches
+// ---------------------------------------------------------------------------
+int isq_lanczos_wgs(int nmax) { return (nmax + ISQ_MVR - 1) / ISQ_MVR; }
+
+void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int* ns_host, LaunchProfiler* prof) {
+    const MatBatch<double> Q = {w.bufs.p[0], w.bufs.ld, w.bufs.stride};
+    const dim3 mv(isq_lanczos_wgs(nmax), 1, nmat);
+    IsqLanczos L = w.lan;
+    L.done = nullptr;
+    const int steps = nmax < 1024 ? ISQ_STEPS_SMALL : ISQ_STEPS_LARGE;
+    const bool small = nmax <= ISQ_SMALL;
+    if (small) {
+        L.nwg = 0;
+        hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, Q, w.ns, L, steps, w.cls, nullptr);
+    } else {
+        for (int j = 0; j < steps; j++) hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Q, w.ns, L, j);
+    }
+    hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(), w.ops, w.cls);
+    IsqBufs bf = w.bufs;
+    const bool timed = prof && prof->enabled && prof->launches;
+    const size_t rec0 = timed ? prof->kind.size() : 0;
+    for (int k = 0; k < ISQ_OPMAX; k++) {
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        if (timed) prof->pair(&e0, &e1, 1, 0.0);
+        auto go = [&](auto kernel, int ts, int threads) {
+            bf.tiles = (nmax + ts - 1) / ts;
+            hipExtLaunchKernelGGL(kernel, dim3(bf.tiles * (bf.tiles + 1) / 2, 1, nmat), dim3(threads), 0, st, e0, e1, 0, bf,
+                                  w.ns, w.ops, k);
+        };
+        if (nmax >= 2048) go(isq_prod_kernel<128, 16, 2, 4>, 128, 512);
+        else if ((long long)nmat * ((nmax + 63) / 64) * ((nmax + 63) / 64) >= 512) go(isq_prod_kernel<64, 16, 2, 2>, 64, 256);
+        else go(isq_prod_kernel<32, 32, 2, 2>, 32, 256);
+    }
+    if (timed) {
+        // the flops of each launch follow from the classes found on the device;
+        // launches past every program's end are no products: not counted
+        std::vector<int> cls(nmat);
+        (void)hipMemcpyAsync(cls.data(), w.cls, sizeof(int) * nmat, hipMemcpyDeviceToHost, st);
+        (void)hipStreamSynchronize(st);
+        for (int k = 0; k < ISQ_OPMAX; k++) {
+            double flops = 0.0;
+            for (int b = 0; b < nmat; b++)
+                if (cls[b] >= 0 && k < isq_products(isq_table().cls[cls[b]])) flops += (double)ns_host[b] * ns_host[b] * ns_host[b];
+            if (flops > 0.0) prof->work[rec0 + k] = flops;
+            else prof->kind[rec0 + k] = -1;
+        }
+    }
+    const MatBatch<double> Z = {w.bufs.p[ISQ_RESULT], w.bufs.ld, w.bufs.stride};
+    const int nwg = isq_lanczos_wgs(nmax);
+    for (int p = 0; p < 3; p++)
+        hipLaunchKernelGGL(isq_check_kernel, mv, dim3(256), 0, st, Q, Z, w.ns, w.cls, w.yv, w.lan.sV, w.check, nwg, p);
+    if (w.zmax && small) {
+        hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, Z, w.ns, L, ISQ_LMAX, w.cls, w.zmax);
+    } else if (w.zmax) {
+        L = w.lan;
+        const int most = ISQ_LMAX;
+        hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, 0, 0, w.zmax);
+        for (int j = 0; j < most; j++) {
+            hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Z, w.ns, L, j);
+            if ((j + 1) % ISQ_LCHECK == 0)
+                hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, j + 1, j + 1 == most ? 1 : 0,
+                                   w.zmax);
+        }
+    }
+}
+
+void isq_energy_launch(hipStream_t st, const IsqWork& w, const SysDesc* sd, int nsys, int nmax, const double* om,
+                       const double* mmult, unsigned* status) {
+    hipLaunchKernelGGL(isq_energy_kernel, dim3(nsys), dim3(256), 0, st, sd, w.ns, w.cls, w.check, isq_lanczos_wgs(nmax),
+                       om, mmult, w.zmax, status);
+}

@@ -1,0 +1,71 @@
+// Workspaces and launches of the direct inverse square root (k_isqrt.hip).
+#pragma once
+#include "mbd_internal.h"
+#include "mbd_sys.h"
+
+#define ISQ_CLASSES 9      // spectral classes (largest kappa) with a plan each
+#define ISQ_OPMAX 17       // products of the longest program
+#define ISQ_NBUF 8         // matrix buffers, buffer 0 = Q
+#define ISQ_RESULT 7       // buffer that receives Q^{-1/2}
+#define ISQ_MVR 8          // rows per workgroup of a matrix-vector pass
+#define ISQ_LMAX 128       // most Lanczos steps
+#define ISQ_SMALL 448      // largest order whose Lanczos steps run in one workgroup
+#define ISQ_LCHECK 8       // steps between convergence checks of lambda_min
+#define ISQ_STEPS_SMALL 10 // Lanczos steps for the interval, orders below 1024
+#define ISQ_STEPS_LARGE 14 // and from 1024 on
+// The smallest Ritz value overstates lambda_min by up to 1.4 after 10 steps
+// (orders up to 900) and 1.9 after 14 (order 6000), and the largest plus its
+// residual norm falls up to 2.4% short of lambda_max (clusters, both densities).
+#define ISQ_LOW_FRACTION 0.5
+#define ISQ_CHECK 1e-12    // largest accepted |I - Z Q Z|_F / sqrt(n)
+
+struct IsqClass {
+    double kappa;
+    int deg[3];
+    double b[3][10], mid[3], hw[3];
+};
+struct IsqTable {
+    IsqClass cls[ISQ_CLASSES];
+};
+const IsqTable& isq_table();
+
+struct IsqOp {
+    signed char a, b, e1, e2, out, out2;
+    double c[4], d[4];
+};
+struct IsqBufs {
+    double* p[ISQ_NBUF];
+    int ld;
+    long long stride;
+    int tiles;  // tile rows of the launch
+};
+struct IsqLanczos {
+    double* vec;    // [nmat][4][sV]: two vectors v and two w
+    long long sV;
+    double* part;   // [nmat][2][nwg][2]
+    int nwg;        // 0: all steps in one workgroup (alpha, beta complete)
+    double* alpha;  // [nmat][ISQ_LMAX]
+    double* beta;
+    int* len;       // order at which the recurrence ended, 0: it has not
+    int* done;      // matrices that need no further step (nullptr: all run)
+};
+struct IsqWork {
+    const int* ns;
+    IsqBufs bufs;
+    IsqLanczos lan;
+    IsqOp* ops;     // [nmat][ISQ_OPMAX]
+    int* cls;       // [nmat]
+    double* yv;     // [nmat][2][sV]
+    double* check;  // [nmat][nwg][2]
+    double* zmax;   // [nmat], or nullptr when lambda_min is not wanted
+};
+
+int isq_lanczos_wgs(int nmax);
+// Q^{-1/2} of every matrix into buffer ISQ_RESULT (both triangles), traces and
+// check sums, and the largest eigenvalue of Q^{-1/2} when wanted.  ns_host: the
+// orders; prof: each product launch as kind 1 when launch timing is on
+struct LaunchProfiler;
+void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int* ns_host, LaunchProfiler* prof);
+// energies, errors[0..3] and MBD_ST_NO_ROOT of the systems
+void isq_energy_launch(hipStream_t st, const IsqWork& w, const SysDesc* sd, int nsys, int nmax, const double* om,
+                       const double* mmult, unsigned* status);

@@ -8,7 +8,8 @@
 
 // Optional HIP-event timing of individual launches and of whole phases
 // (measurement tools only).  kind 0: per-column SYMV of the reduction
-// (BLAS-2), 1: trailing SYR2K (BLAS-3); phases: 2 input preparation and
+// (BLAS-2), 1: trailing SYR2K of the reduction or symmetric product of the
+// direct Q^{-1/2} (BLAS-3); phases: 2 input preparation and
 // assembly, 3 Householder reduction, 4 divide and conquer, 5 back-transform,
 // 6 refinement, 7 energy, Q^{-1/2} and gradients; 8 fused per-column
 // launch, 9 screening stage, 10 one-workgroup-per-matrix reduction, 11 the
@@ -75,7 +76,10 @@ struct PhaseTimer {
     static double now_ms() {
         return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now().time_since_epoch()).count();
     }
-    PhaseTimer(LaunchProfiler* prof, hipStream_t s, int kind) : p(prof), st(s), k(kind) {
+    PhaseTimer(LaunchProfiler* prof, hipStream_t s, int kind, bool now = true) : p(prof), st(s), k(kind) {
+        if (now) start();
+    }
+    void start() {
         if (!p || !p->enabled) return;
         if (p->launches) {
             hipEvent_t e0;

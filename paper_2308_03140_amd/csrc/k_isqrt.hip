@@ -550,148 +550,175 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
 // ---------------------------------------------------------------------------
 // symmetric product step
 // ---------------------------------------------------------------------------
-// TS x TS tile of the lower triangle per workgroup of WM x WN wavefronts; both
-// operands are symmetric and stored in full, so A(m, k) and B(k, n) are read
-// along their columns, 16 bytes per lane, through a buffer descriptor whose
-// size ends the K loop (k >= n reads zero) and whose rows past n only reach
-// rows of C that are not stored.  K goes through LDS in slabs of BK, double
-// buffered, the next slab's loads in flight during the products.  The row
-// stride TS + 16 puts the two k rows of a half wavefront's 8-byte reads on
-// different halves of the 64 banks.  E1, E2 are read and the upper triangle
-// written straight from the result registers (16 lanes along n: 128-byte
-// runs); the lower triangle goes through a 16 x 16 LDS transpose per
-// wavefront for the same run length.
+// One TM x TN tile of the lower triangle per workgroup, K split over its WK
+// wavefronts: each computes the whole tile over its own K groups, straight
+// from L2 into registers (no LDS staging and no barrier in the loop; no load
+// is made twice, since the wavefronts read different K), and the shares are
+// summed through LDS at the end.  Bound by the FP64 matrix cores: at order
+// 6000 62-64 TFLOP/s against 58 for 128 x 128 tiles staged through LDS (the
+// library's DGEMM reaches 65), at order 2103 57 against 32 (the smaller tiles
+// fill the last round of workgroups), 512 uneven molecules 2.2-2.6 ms a
+// product against 4.0-4.5, one matrix of order 450 9 us against 13.
+//
+// Both operands are symmetric and stored in full, so A(m, k) and B(k, n) are
+// read along their columns.  A lane's 16-byte load holds rows 2r, 2r + 1 (r =
+// lane mod 16), one for each of two MFMA tiles: tile i covers the rows of
+// parity i mod 2 of its 32.  The descriptor's size ends the K loop (k >= n
+// reads zero); rows past n only reach rows of C that are not stored.  Two
+// register sets of U k-steps alternate, so U MFMA steps hide each load.
 typedef double isq_d2 __attribute__((ext_vector_type(2)));
 
-// LDS written by a wavefront becomes visible to its other lanes
-__device__ __forceinline__ void isq_wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-template <int TS, int BK, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void isq_prod_kernel(IsqBufs bufs, const int* ns, const IsqOp* ops,
-                                                                  int step) {
-    constexpr int NT = 64 * WM * WN;
-    constexpr int MI = TS / WM / 16, NJ = TS / WN / 16;
-    constexpr int LDT = TS + 16;
-    constexpr int LV = BK * TS / 2 / NT;  // 16-byte loads per thread, operand and slab
-    static_assert(LV * NT * 2 == BK * TS && MI > 0 && NJ > 0, "slab and tile divide evenly");
-    __shared__ __align__(16) double As[2][BK][LDT], Bs[2][BK][LDT];
+template <int MI, int NJ, int WK, int U, int MINW>
+__global__ __launch_bounds__(64 * WK, MINW) void isq_prod_kernel(IsqBufs bufs, const int* ns, const IsqOp* ops,
+                                                                   int step) {
+    static_assert(MI % 2 == 0 && NJ % 2 == 0 && MI % NJ == 0 && WK >= 2, "tile and wave split");
+    constexpr int TM = 16 * MI, TN = 16 * NJ, NT = 64 * WK, LDC = TM + 2, R = TM / TN;
+    __shared__ __align__(16) double cs[2][TN * LDC];
     const int b = blockIdx.z;
     const IsqOp& op = ops[(long long)b * ISQ_OPMAX + step];
     if (op.a < 0) return;
     const int n = ns[b];
-    int ti, tj;
-    band_lower_tile(xcd_virtual(blockIdx.x, gridDim.x), bufs.tiles, ti, tj);
-    const int m0 = ti * TS, n0 = tj * TS;
-    if (m0 >= n) return;
+    // row ti of tiles holds the R (ti + 1) tiles on and left of the diagonal;
+    // the shares of the XCDs rotate with the matrix, or the last rows of a
+    // batch, which only its largest matrices have, would all fall to one XCD
+    // (512 uneven molecules, 64 x 32 tiles: 4.9 ms a product against 2.4)
+    const int bx = blockIdx.x + b % gridDim.x;
+    const int v = xcd_virtual(bx >= (int)gridDim.x ? bx - (int)gridDim.x : bx, gridDim.x);
+    int ti = (int)((sqrtf(8.0f * (float)(v / R) + 1.0f) - 1.0f) * 0.5f);
+    while (R * (ti + 1) * (ti + 2) / 2 <= v) ti++;
+    while (R * ti * (ti + 1) / 2 > v) ti--;
+    const int m0 = ti * TM, n0 = (v - R * ti * (ti + 1) / 2) * TN;
+    if (m0 >= n || n0 >= n) return;
     const int ld = bufs.ld;
     const double* A = bufs.p[op.a] + (long long)b * bufs.stride;
     const double* B = bufs.p[op.b] + (long long)b * bufs.stride;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     typename mfma4<double>::v acc[MI][NJ];
 #pragma unroll
     for (int i = 0; i < MI; i++)
 #pragma unroll
         for (int j = 0; j < NJ; j++) acc[i][j] = typename mfma4<double>::v{0, 0, 0, 0};
-    isq_d2 ra[LV], rb[LV];
-    auto gload = [&](int k0) {
-        const int kn = min(BK, n - k0);
+    constexpr int G = 4 * U;  // k of one group; groups go round robin over the wavefronts
+    const unsigned la = (unsigned)((lane >> 4) * ld + m0 + 2 * (lane & 15)) * 8u;
+    const unsigned lb = (unsigned)((lane >> 4) * ld + n0 + 2 * (lane & 15)) * 8u;
+    isq_d2 ra[2][U][MI / 2], rb[2][U][NJ / 2];
+    auto gload = [&](int k0, auto& xa, auto& xb) {
+        const int kn = max(0, min(G, n - k0));
         const auto dA = make_rsrc(A + (long long)k0 * ld, (unsigned)kn * ld * 8u);
         const auto dB = make_rsrc(B + (long long)k0 * ld, (unsigned)kn * ld * 8u);
 #pragma unroll
-        for (int v = 0; v < LV; v++) {
-            const int idx = tid + v * NT, k = idx / (TS / 2), m = 2 * (idx % (TS / 2));
-            ra[v] = __builtin_bit_cast(isq_d2, buf_load16<double>(dA, (unsigned)(k * ld + m0 + m) * 8u));
-            rb[v] = __builtin_bit_cast(isq_d2, buf_load16<double>(dB, (unsigned)(k * ld + n0 + m) * 8u));
+        for (int u = 0; u < U; u++) {
+#pragma unroll
+            for (int i = 0; i < MI / 2; i++)
+                xa[u][i] = __builtin_bit_cast(isq_d2, __builtin_amdgcn_raw_buffer_load_b128(dA, la + 256u * i, 32 * u * ld, 0));
+#pragma unroll
+            for (int j = 0; j < NJ / 2; j++)
+                xb[u][j] = __builtin_bit_cast(isq_d2, __builtin_amdgcn_raw_buffer_load_b128(dB, lb + 256u * j, 32 * u * ld, 0));
         }
     };
-    auto sstore = [&](int buf) {
+    auto mult = [&](auto& xa, auto& xb) {
 #pragma unroll
-        for (int v = 0; v < LV; v++) {
-            const int idx = tid + v * NT, k = idx / (TS / 2), m = 2 * (idx % (TS / 2));
-            *reinterpret_cast<isq_d2*>(&As[buf][k][m]) = ra[v];
-            *reinterpret_cast<isq_d2*>(&Bs[buf][k][m]) = rb[v];
-        }
-    };
-    const int nk = (n + BK - 1) / BK;
-    gload(0);
-    sstore(0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; kt++) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) gload((kt + 1) * BK);
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 4) {
-            double af[MI], bf[NJ];
-#pragma unroll
-            for (int i = 0; i < MI; i++) af[i] = As[buf][kk + (lane >> 4)][wm * (TS / WM) + i * 16 + (lane & 15)];
-#pragma unroll
-            for (int j = 0; j < NJ; j++) bf[j] = Bs[buf][kk + (lane >> 4)][wn * (TS / WN) + j * 16 + (lane & 15)];
+        for (int u = 0; u < U; u++)
 #pragma unroll
             for (int i = 0; i < MI; i++)
 #pragma unroll
-                for (int j = 0; j < NJ; j++) acc[i][j] = mfma16x16x4(af[i], bf[j], acc[i][j]);
+                for (int j = 0; j < NJ; j++) acc[i][j] = mfma16x16x4(xa[u][i / 2][i & 1], xb[u][j / 2][j & 1], acc[i][j]);
+    };
+    const int ng = (n + G - 1) / G;
+    int g = wave;
+    gload(g * G, ra[0], rb[0]);
+    while (g < ng) {
+        gload((g + WK) * G, ra[1], rb[1]);
+        mult(ra[0], rb[0]);
+        g += WK;
+        if (g >= ng) break;
+        gload((g + WK) * G, ra[0], rb[0]);
+        mult(ra[1], rb[1]);
+        g += WK;
+    }
+    // the wavefronts' shares: two write, the others add in turn
+#pragma unroll
+    for (int w = 0; w < WK; w += 2) {
+        if (wave >= w && wave < w + 2) {
+            double* c = cs[wave & 1];
+#pragma unroll
+            for (int i = 0; i < MI; i++)
+#pragma unroll
+                for (int j = 0; j < NJ; j++)
+#pragma unroll
+                    for (int r = 0; r < 4; r++) {
+                        const int row = 32 * (i / 2) + 2 * mfma_rows<double>::row(lane, r) + (i & 1);
+                        const int col = 32 * (j / 2) + 2 * (lane & 15) + (j & 1);
+                        if (w == 0) c[col * LDC + row] = acc[i][j][r];
+                        else c[col * LDC + row] += acc[i][j][r];
+                    }
         }
-        if (kt + 1 < nk) sstore(buf ^ 1);
         __syncthreads();
     }
-    // epilogue; the K loop ended on a barrier, so the staging space is free
     const double* E1 = op.e1 >= 0 ? bufs.p[op.e1] + (long long)b * bufs.stride : nullptr;
     const double* E2 = op.e2 >= 0 ? bufs.p[op.e2] + (long long)b * bufs.stride : nullptr;
     double* C1 = bufs.p[op.out] + (long long)b * bufs.stride;
     double* C2 = op.out2 >= 0 ? bufs.p[op.out2] + (long long)b * bufs.stride : nullptr;
-    double* tr = &As[0][0][0] + wave * (16 * 17);
-    static_assert(WM * WN * 16 * 17 <= 2 * BK * LDT, "transpose blocks fit the A slabs");
     double c[4], d[4];
 #pragma unroll
     for (int q = 0; q < 4; q++) { c[q] = op.c[q]; d[q] = op.d[q]; }
-#pragma unroll
-    for (int i = 0; i < MI; i++)
-#pragma unroll
-        for (int j = 0; j < NJ; j++) {
-            const int mb = m0 + wm * (TS / WM) + i * 16, nb = n0 + wn * (TS / WN) + j * 16;
-            if (mb >= n || nb >= n || mb + 15 < nb) continue;  // wave-uniform
-            const int col = nb + (lane & 15);
-            double o2[4];
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int row = mb + (lane >> 4) + 4 * r;
-                const bool in = row < n && col <= row;
-                const long long up = (long long)col + (long long)row * ld;
-                const double v = acc[i][j][r];
-                const double e1 = E1 && in ? E1[up] : 0.0, e2 = E2 && in ? E2[up] : 0.0;
-                const double id = row == col ? 1.0 : 0.0;
-                const double o1 = c[0] * v + c[1] * e1 + c[2] * e2 + c[3] * id;
-                o2[r] = d[0] * v + d[1] * e1 + d[2] * e2 + d[3] * id;
-                if (in) {
-                    C1[up] = o1;
-                    if (C2) C2[up] = o2[r];
-                }
-                tr[(lane & 15) * 17 + (lane >> 4) + 4 * r] = o1;
-            }
-            isq_wave_sync();
-            const int lrow = mb + (lane & 15);
-#pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int lc = (lane >> 4) + 4 * r, lcol = nb + lc;
-                if (lrow < n && lcol < lrow) C1[lrow + (long long)lcol * ld] = tr[lc * 17 + (lane & 15)];
-            }
-            if (C2) {
-                isq_wave_sync();
-#pragma unroll
-                for (int r = 0; r < 4; r++) tr[(lane & 15) * 17 + (lane >> 4) + 4 * r] = o2[r];
-                isq_wave_sync();
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int lc = (lane >> 4) + 4 * r, lcol = nb + lc;
-                    if (lrow < n && lcol < lrow) C2[lrow + (long long)lcol * ld] = tr[lc * 17 + (lane & 15)];
-                }
-            }
-            isq_wave_sync();
+    const bool diag = m0 < n0 + TN;
+    // lower triangle, in runs along m
+#pragma unroll 4
+    for (int x = tid; x < TM * TN; x += NT) {
+        const int r = x % TM, cl = x / TM, row = m0 + r, col = n0 + cl;
+        if (row >= n || col >= n || (diag && col > row)) continue;
+        const long long at = row + (long long)col * ld;
+        const double s = cs[0][cl * LDC + r] + cs[1][cl * LDC + r];
+        const double e1 = E1 ? E1[at] : 0.0, e2 = E2 ? E2[at] : 0.0, id = row == col ? 1.0 : 0.0;
+        const double o1 = c[0] * s + c[1] * e1 + c[2] * e2 + c[3] * id;
+        C1[at] = o1;
+        cs[0][cl * LDC + r] = o1;
+        if (C2) {
+            const double o2 = d[0] * s + d[1] * e1 + d[2] * e2 + d[3] * id;
+            C2[at] = o2;
+            cs[1][cl * LDC + r] = o2;
         }
+    }
+    __syncthreads();
+    // its mirror image, in runs along n
+#pragma unroll 4
+    for (int x = tid; x < TM * TN; x += NT) {
+        const int cl = x % TN, r = x / TN, row = m0 + r, col = n0 + cl;
+        if (row >= n || col >= n || (diag && col >= row)) continue;
+        const long long at = col + (long long)row * ld;
+        C1[at] = cs[0][cl * LDC + r];
+        if (C2) C2[at] = cs[1][cl * LDC + r];
+    }
+}
+
+// Tile shape of a launch.  Few tiles (at most four of 32 x 32 per compute
+// unit): 32 x 32 with K over four wavefronts, the shortest chain per tile.
+// Orders below 1024: 32 x 32 over two (512 uneven molecules: 2.3-2.6 ms a
+// product against 2.7-3.1 for 64 x 32, whose ragged edges waste more).
+// Otherwise the cheapest of three by flops, measured rate and the last round
+// of workgroups left partly empty over 256 compute units (order 2103: 96 x 32
+// makes 759 tiles, 2.96 rounds, 57 TFLOP/s; 64 x 32 1122, 4.4 rounds, 52).
+struct IsqShape { int tm, tn; double rate; };
+static const IsqShape ISQ_SHAPES[3] = {{64, 32, 1.0}, {96, 32, 0.97}, {32, 32, 0.84}};
+
+static int isq_shape(const int* ns, int nmat) {
+    double best = 1e300;
+    int pick = 2, nmax = 0;
+    for (int b = 0; b < nmat; b++) nmax = std::max(nmax, ns[b]);
+    for (int s = nmax < 1024 ? 2 : 0; s < 3; s++) {
+        const IsqShape& q = ISQ_SHAPES[s];
+        double tiles = 0.0, work = 0.0;
+        for (int b = 0; b < nmat; b++) {
+            const double rows = (ns[b] + q.tm - 1) / q.tm, t = q.tm / q.tn * rows * (rows + 1) / 2;
+            tiles += t;
+            work += t * ns[b];
+        }
+        if (s == 2 && tiles <= 1024) return 3;
+        const double rounds = tiles / 256.0, cost = work * q.tm * q.tn / q.rate * std::ceil(rounds) / rounds;
+        if (cost < best) { best = cost; pick = s; }
+    }
+    return pick;
 }
 
 // ---------------------------------------------------------------------------
@@ -841,20 +868,23 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
         for (int j = 0; j < steps; j++) hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Q, w.ns, L, j);
     }
     hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(), w.ops, w.cls);
-    IsqBufs bf = w.bufs;
+    const int shape = isq_shape(ns_host, nmat);
     const bool timed = prof && prof->enabled && prof->launches;
     const size_t rec0 = timed ? prof->kind.size() : 0;
     for (int k = 0; k < ISQ_OPMAX; k++) {
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (timed) prof->pair(&e0, &e1, 1, 0.0);
-        auto go = [&](auto kernel, int ts, int threads) {
-            bf.tiles = (nmax + ts - 1) / ts;
-            hipExtLaunchKernelGGL(kernel, dim3(bf.tiles * (bf.tiles + 1) / 2, 1, nmat), dim3(threads), 0, st, e0, e1, 0, bf,
-                                  w.ns, w.ops, k);
+        auto go = [&](auto kernel, int tm, int tn, int wk) {
+            const int rows = (nmax + tm - 1) / tm;
+            hipExtLaunchKernelGGL(kernel, dim3(tm / tn * rows * (rows + 1) / 2, 1, nmat), dim3(64 * wk), 0, st, e0, e1, 0,
+                                  w.bufs, w.ns, w.ops, k);
         };
-        if (nmax >= 2048) go(isq_prod_kernel<128, 16, 2, 4>, 128, 512);
-        else if ((long long)nmat * ((nmax + 63) / 64) * ((nmax + 63) / 64) >= 512) go(isq_prod_kernel<64, 16, 2, 2>, 64, 256);
-        else go(isq_prod_kernel<32, 32, 2, 2>, 32, 256);
+        switch (shape) {
+        case 0: go(isq_prod_kernel<4, 2, 4, 5, 2>, 64, 32, 4); break;
+        case 1: go(isq_prod_kernel<6, 2, 4, 2, 2>, 96, 32, 4); break;
+        case 2: go(isq_prod_kernel<2, 2, 2, 6, 3>, 32, 32, 2); break;
+        default: go(isq_prod_kernel<2, 2, 4, 6, 3>, 32, 32, 4); break;
+        }
     }
     if (timed) {
         // the flops of each launch follow from the classes found on the device;

@@ -37,7 +37,6 @@ struct IsqBufs {
     double* p[ISQ_NBUF];
     int ld;
     long long stride;
-    int tiles;  // tile rows of the launch
 };
 struct IsqLanczos {
     double* vec;    // [nmat][4][sV]: two vectors v and two w

@@ -110,28 +110,52 @@ __device__ __forceinline__ bool image_term(const double* x, double gamma, double
     return true;
 }
 
-// Assembly of the embedded Q(q).  A wavefront holds 64 / lpp ordered atom
-// pairs (i, j), lpp lanes each, one lane per q-point (lpp: the q count
-// rounded up to a power of two, at most 64; grid y covers further groups of
-// q-points).  The real-space image terms depend on the pair and the image
-// only: each is formed once, by one lane of its pair, into LDS (lpp images
-// per round), and every lane of the pair adds it with its own phase
-// e^{-i q.x}.  Lanes of a pair index past N^2 follow the barriers and store
-// nothing.  Writes the real-space and self terms and omega^2 into the left
+// Assembly of the embedded Q(q).  A workgroup of W wavefronts holds 64 W / lpp
+// slots of lpp lanes, one lane per q-point (lpp: the q count rounded up to a
+// power of two, at most 64; grid y covers further groups of q-points); spp
+// slots share an ordered atom pair (i, j) and split its images.  The
+// real-space image terms depend on the pair and the image only: each is
+// formed once, by one lane of its slot, into LDS (lpp images per round and
+// slot), and every lane of the slot adds it with its own phase e^{-i q.x}; the
+// slots' sums are added at the end in a fixed order.  FP64 VALU bound where
+// there are enough pairs; with one slot a pair, 8 atoms on 8 q points were 8
+// wavefronts that walked all images in turn (547 us, the adjoint 1374 us).
+// Lanes of a pair index past N^2 follow the barriers and store nothing.  Writes the real-space and self terms and omega^2 into the left
 // block column [Re; Im] of the embedding; the reciprocal-space product then
 // adds its term and fills the right block column.
 #define PER_LANES 64
-__global__ __launch_bounds__(PER_LANES) void mbd_assemble_periodic_kernel(const SysDesc* sd, const double* om,
+
+// Sum of v over the spp slots of a pair (lanes lpp, 2 lpp, .. apart within a
+// wavefront, then its wavefronts through LDS), in the lanes of the pair's first
+// slot.  xw: one value per thread.  Every thread of the workgroup takes part.
+template <int W>
+__device__ __forceinline__ double per_slot_sum(double v, int lpp, int spp, double* xw) {
+    const int inw = min(spp, PER_LANES / lpp);  // slots of the pair in one wavefront
+    for (int o = lpp; o < lpp * inw; o *= 2) v += __shfl_xor(v, o, 64);
+    if (W > 1 && spp > inw) {
+        const int nw = spp / inw;  // wavefronts of the pair (inw = 64 / lpp here)
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        __syncthreads();
+        xw[threadIdx.x] = v;
+        __syncthreads();
+        v = 0.0;
+        for (int w = 0; w < nw; w++) v += xw[(wave / nw * nw + w) * 64 + lane];
+    }
+    return v;
+}
+
+template <int W>
+__global__ __launch_bounds__(PER_LANES * W) void mbd_assemble_periodic_kernel(const SysDesc* sd, const double* om,
                                                                           const double* cc, const double* qcart,
-                                                                          int nq, int lpp, const int* img, int nimg,
+                                                                          int nq, int lpp, int spp, const int* img, int nimg,
                                                                           const double* phase, MatBatch<double> Q,
                                                                           unsigned* status) {
-    __shared__ double Fs[PER_LANES][9];
-    __shared__ int oks[PER_LANES];   // image index + 1 of the slot's term, 0 if empty
+    __shared__ double Fs[PER_LANES * W][9];
+    __shared__ int oks[PER_LANES * W];   // image index + 1 of the slot's term, 0 if empty
     const SysDesc& S = sd[0];
     const int N = S.N, n = 3 * N;
-    const int slot = threadIdx.x / lpp, ql = threadIdx.x % lpp;
-    const long long pid0 = (long long)blockIdx.x * (PER_LANES / lpp) + slot;
+    const int slot = threadIdx.x / lpp, ql = threadIdx.x % lpp, sub = slot % spp;
+    const long long pid0 = (long long)blockIdx.x * (PER_LANES * W / lpp / spp) + slot / spp;
     const bool pv = pid0 < (long long)N * N;
     const long long pid = pv ? pid0 : 0;
     const int q = blockIdx.y * lpp + ql;
@@ -147,7 +171,8 @@ __global__ __launch_bounds__(PER_LANES) void mbd_assemble_periodic_kernel(const 
     sincos(-(qv[0] * r[0] + qv[1] * r[1] + qv[2] * r[2]), &sb, &cb);
     double Tre[9], Tim[9];
     for (int k = 0; k < 9; k++) { Tre[k] = 0.0; Tim[k] = 0.0; }
-    for (int t0 = 0; t0 < nimg; t0 += lpp) {
+    for (int r0 = 0; r0 < nimg; r0 += lpp * spp) {
+        const int t0 = r0 + sub * lpp;
         {
             const int t = t0 + ql;
             int ok = 0;
@@ -178,7 +203,12 @@ __global__ __launch_bounds__(PER_LANES) void mbd_assemble_periodic_kernel(const 
         }
         __syncthreads();
     }
-    if (!qv_ok) return;
+    if (spp > 1)
+        for (int k = 0; k < 9; k++) {
+            Tre[k] = per_slot_sum<W>(Tre[k], lpp, spp, &Fs[0][0]);
+            Tim[k] = per_slot_sum<W>(Tim[k], lpp, spp, &Fs[0][0]);
+        }
+    if (!qv_ok || sub != 0) return;
     if (i == j) {
         const double self = 4.0 * S.gamma * S.gamma * S.gamma / (3.0 * SQRT_PI);
         Tre[0] -= self; Tre[4] -= self; Tre[8] -= self;
@@ -317,22 +347,23 @@ struct PerRecAsmProb {
 //                                      R0 = beta (Rv_i + Rv_j))
 // Partial results per (q, i, j) of the real-space and self terms: {P, dR[3],
 // dA[9], P0}; the reciprocal-space term is contracted through U below.
-// Same layout as the assembly: one workgroup per ordered pair, one lane per
-// q-point, each real-space image term (F and its derivatives) formed once
-// into LDS and added by every lane with its own phase and M(q).  Two
+// Same layout as the assembly: slots of one lane per q-point, each real-space
+// image term (F and its derivatives) formed once into LDS and added by every
+// lane of its slot with its own phase and M(q).  Two
 // wavefronts per SIMD (at most 256 registers, a few spilled: 587 -> 519 us
 // for the 64-atom cell's 64 q against one wavefront at 268 registers).
-__global__ __launch_bounds__(PER_LANES, 2) void mbd_grad_periodic_kernel(const SysDesc* sd, const double* om,
+template <int W>
+__global__ __launch_bounds__(PER_LANES * W, 2) void mbd_grad_periodic_kernel(const SysDesc* sd, const double* om,
                                                                       const double* cc, const double* qcart, int nq,
-                                                                      int lpp, const int* img, int nimg,
+                                                                      int lpp, int spp, const int* img, int nimg,
                                                                       const double* phase, MatBatch<double> M,
                                                                       double* part) {
-    __shared__ double Fs[PER_LANES][9], dFs[PER_LANES][27], F0s[PER_LANES][9];
-    __shared__ int ns_[PER_LANES][3], oks[PER_LANES];   // oks: image index + 1 of the slot's term, 0 if empty
+    __shared__ double Fs[PER_LANES * W][9], dFs[PER_LANES * W][27], F0s[PER_LANES * W][9];
+    __shared__ int ns_[PER_LANES * W][3], oks[PER_LANES * W];   // oks: image index + 1 of the slot's term, 0 if empty
     const SysDesc& S = sd[0];
     const int N = S.N, n = 3 * N;
-    const int slot = threadIdx.x / lpp, ql = threadIdx.x % lpp;
-    const long long pid0 = (long long)blockIdx.x * (PER_LANES / lpp) + slot;
+    const int slot = threadIdx.x / lpp, ql = threadIdx.x % lpp, sub = slot % spp;
+    const long long pid0 = (long long)blockIdx.x * (PER_LANES * W / lpp / spp) + slot / spp;
     const bool pv = pid0 < (long long)N * N;
     const long long pid = pv ? pid0 : 0;
     const int q0 = blockIdx.y * lpp + ql;
@@ -361,7 +392,8 @@ __global__ __launch_bounds__(PER_LANES, 2) void mbd_grad_periodic_kernel(const S
     for (int v = 0; v < 3; v++) rho[v] = S.linv[v] * r[0] + S.linv[3 + v] * r[1] + S.linv[6 + v] * r[2];
     double P = 0.0, P0 = 0.0, dR[3] = {0, 0, 0}, dA[9];
     for (int k = 0; k < 9; k++) dA[k] = 0.0;
-    for (int t0 = 0; t0 < nimg; t0 += lpp) {
+    for (int r0 = 0; r0 < nimg; r0 += lpp * spp) {
+        const int t0 = r0 + sub * lpp;
         {
             const int t = t0 + ql;
             int ok = 0;
@@ -414,11 +446,17 @@ __global__ __launch_bounds__(PER_LANES, 2) void mbd_grad_periodic_kernel(const S
         }
         __syncthreads();
     }
+    if (spp > 1) {
+        P = per_slot_sum<W>(P, lpp, spp, &Fs[0][0]);
+        P0 = per_slot_sum<W>(P0, lpp, spp, &Fs[0][0]);
+        for (int c = 0; c < 3; c++) dR[c] = per_slot_sum<W>(dR[c], lpp, spp, &Fs[0][0]);
+        for (int k = 0; k < 9; k++) dA[k] = per_slot_sum<W>(dA[k], lpp, spp, &Fs[0][0]);
+    }
     if (i == j) {
         const double self = 4.0 * S.gamma * S.gamma * S.gamma / (3.0 * SQRT_PI);
         P -= self * (Mr[0] + Mr[4] + Mr[8]);
     }
-    if (!qv_ok) return;
+    if (!qv_ok || sub != 0) return;
     out[0] = P;
     for (int c = 0; c < 3; c++) out[1 + c] = dR[c];
     for (int k = 0; k < 9; k++) out[4 + k] = dA[k];
@@ -633,6 +671,21 @@ static int per_lanes_per_pair(int nq) {
     return l;
 }
 
+// Wavefronts per workgroup and slots per pair: pairs are split over their
+// images until the launch has two wavefronts per SIMD (2048), but a slot keeps
+// at least two rounds of lpp images; first within a wavefront, then over the
+// four of a workgroup.
+static void per_split(long long pairs, int nq, int lpp, int nimg, int& waves, int& spp) {
+    waves = spp = 1;
+    const long long groups = (nq + lpp - 1) / lpp;
+    auto more = [&]() { return pairs * groups * lpp * spp / PER_LANES < 2048 && 4LL * lpp * spp <= nimg; };
+    while (spp < PER_LANES / lpp && more()) spp *= 2;
+    while (spp >= PER_LANES / lpp && spp < 4 * PER_LANES / lpp && more()) {
+        spp *= 2;
+        waves = 4;
+    }
+}
+
 void per_recip_basis_launch(hipStream_t st, const SysDesc* sd, const double* qcart, int nq, const int* img,
                             int nimg, const PerEwald& pr) {
     if (nq == 0) return;
@@ -647,9 +700,16 @@ void mbd_assemble_periodic_launch(hipStream_t st, const SysDesc* sd, const doubl
                                   const double* qcart, int nq, const int* img, int nimg, const PerEwald& pr,
                                   MatBatch<double> Q, MatBatch<float> Q32, unsigned* status, int N) {
     const long long pairs = (long long)N * N;
-    const int lpp = per_lanes_per_pair(nq), ppw = PER_LANES / lpp;
-    hipLaunchKernelGGL(mbd_assemble_periodic_kernel, dim3((unsigned)((pairs + ppw - 1) / ppw), (nq + lpp - 1) / lpp),
-                       dim3(PER_LANES), 0, st, sd, om, cc, qcart, nq, lpp, img, nimg, pr.phase, Q, status);
+    const int lpp = per_lanes_per_pair(nq);
+    int wv, spp;
+    per_split(pairs, nq, lpp, nimg, wv, spp);
+    const int ppw = PER_LANES * wv / lpp / spp;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((pairs + ppw - 1) / ppw), (nq + lpp - 1) / lpp), dim3(PER_LANES * wv), 0,
+                           st, sd, om, cc, qcart, nq, lpp, spp, img, nimg, pr.phase, Q, status);
+    };
+    if (wv == 1) go(mbd_assemble_periodic_kernel<1>);
+    else go(mbd_assemble_periodic_kernel<4>);
     // always launched: besides the reciprocal term, the epilogue fills the
     // right block column and the FP32 copy
     PerRecAsmProb p;
@@ -668,9 +728,16 @@ void mbd_grad_periodic_launch(hipStream_t st, const SysDesc* sd, const double* o
                               int nimg, const PerEwald& pr, MatBatch<double> M, double* partial, double* rq,
                               double* rl, double* latpart, int N) {
     const long long pairs = (long long)N * N;
-    const int lpp = per_lanes_per_pair(nq), ppw = PER_LANES / lpp;
-    hipLaunchKernelGGL(mbd_grad_periodic_kernel, dim3((unsigned)((pairs + ppw - 1) / ppw), (nq + lpp - 1) / lpp),
-                       dim3(PER_LANES), 0, st, sd, om, cc, qcart, nq, lpp, img, nimg, pr.phase, M, partial);
+    const int lpp = per_lanes_per_pair(nq);
+    int wv, spp;
+    per_split(pairs, nq, lpp, nimg, wv, spp);
+    const int ppw = PER_LANES * wv / lpp / spp;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((pairs + ppw - 1) / ppw), (nq + lpp - 1) / lpp), dim3(PER_LANES * wv), 0,
+                           st, sd, om, cc, qcart, nq, lpp, spp, img, nimg, pr.phase, M, partial);
+    };
+    if (wv == 1) go(mbd_grad_periodic_kernel<1>);
+    else go(mbd_grad_periodic_kernel<4>);
     const int nchunk = per_recip_chunks(pr.ncol);
     if (nchunk > 0) {
         PerRecMZProb p;

@@ -46,8 +46,7 @@ struct mbd_ctx {
     // captured batch launch sequences, keyed by batch signature
     struct Graph {
         hipGraphExec_t exec = nullptr;
-        SysDesc* h_desc = nullptr;     // pinned staging of the system descriptors
-        int* h_ns = nullptr;           // pinned matrix orders
+        char* h_up = nullptr;          // pinned staging of the upload block (descriptors first)
         unsigned* h_status = nullptr;  // pinned status read-back
         int nsys = 0, nmat = 0;
         bool ok = false;
@@ -64,8 +63,7 @@ struct mbd_ctx {
     void drop_graphs() {
         for (auto& kv : graphs) {
             if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
-            (void)hipHostFree(kv.second.h_desc);
-            (void)hipHostFree(kv.second.h_ns);
+            (void)hipHostFree(kv.second.h_up);
             (void)hipHostFree(kv.second.h_status);
         }
         graphs.clear();
@@ -659,6 +657,16 @@ bool direct_route(const mbd_ctx* c, unsigned want) {
     return !(want & MBD_WANT_EIGVALS) && !(c->prec == MBD_FP32_REFINED && c->refine_tol > 0.0);
 }
 
+// Layout of an evaluation's upload block.
+struct CoreUpload {
+    size_t ns, status, bytes;
+    CoreUpload(int nsys, int nmat) {
+        ns = sizeof(SysDesc) * nsys;
+        status = ns + sizeof(int) * nmat;
+        bytes = status + sizeof(unsigned) * nsys;
+    }
+};
+
 struct IsqLiveScope {
     mbd_ctx* c;
     IsqLiveScope(mbd_ctx* ctx, bool on) : c(ctx) { c->isq_live = on; }
@@ -696,9 +704,12 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
     bool fp32 = c->prec == MBD_FP32_REFINED && !direct;
     GemmTileScope tile_scope(tuned_entry(c, fp32 ? 1 : 0, nmax).gemm_ts);
 
-    SysDesc* sd_dev = (SysDesc*)ws(c, "sysdesc", sizeof(SysDesc) * nsys);
-    int* ns_dev = wsT<int>(c, "ns", nmat);
-    unsigned* status = wsT<unsigned>(c, "status", nsys);
+    // descriptors, matrix orders and the cleared status words, uploaded in one copy
+    const CoreUpload up(nsys, nmat);
+    char* up_dev = (char*)ws(c, "sysdesc", up.bytes);
+    SysDesc* sd_dev = (SysDesc*)up_dev;
+    int* ns_dev = (int*)(up_dev + up.ns);
+    unsigned* status = (unsigned*)(up_dev + up.status);
     double* lmin = wsT<double>(c, "lmin", nsys);
     double* om = wsT<double>(c, "om", ntot);
     double* cc = wsT<double>(c, "cc", ntot);
@@ -713,19 +724,21 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
         fp32 = c->prec == MBD_FP32_REFINED;
     }
     if (fp32) A32.p = wsT<float>(c, "A32", (size_t)stride * nmat);
-    if (!sd_dev || !ns_dev || !status || !lmin || !om || !cc || !lam || !sc || !A64.p || (fp32 && !A32.p))
+    if (!up_dev || !lmin || !om || !cc || !lam || !sc || !A64.p || (fp32 && !A32.p))
         return (mbd_status)c->err_code;
     std::vector<int> nsh(nmat);
     for (int b = 0; b < nmat; b++) nsh[b] = per ? 6 * sds[0].N : 3 * sds[b].N;
-    if (capturing) {
-        HIPCHK(hipMemcpyAsync(sd_dev, mode->g->h_desc, sizeof(SysDesc) * nsys, hipMemcpyHostToDevice, st), "upload");
-        HIPCHK(hipMemcpyAsync(ns_dev, mode->g->h_ns, sizeof(int) * nmat, hipMemcpyHostToDevice, st), "upload");
-    } else {
-        HIPCHK(hipMemcpyAsync(sd_dev, sds.data(), sizeof(SysDesc) * nsys, hipMemcpyHostToDevice, st), "upload");
-        HIPCHK(hipMemcpyAsync(ns_dev, nsh.data(), sizeof(int) * nmat, hipMemcpyHostToDevice, st), "upload");
+    std::vector<char> staged;
+    char* up_host = capturing ? mode->g->h_up : nullptr;
+    if (!capturing) {
+        staged.resize(up.bytes);
+        up_host = staged.data();
     }
+    std::memcpy(up_host, sds.data(), sizeof(SysDesc) * nsys);
+    std::memcpy(up_host + up.ns, nsh.data(), sizeof(int) * nmat);
+    std::memset(up_host + up.status, 0, sizeof(unsigned) * nsys);
+    HIPCHK(hipMemcpyAsync(up_dev, up_host, up.bytes, hipMemcpyHostToDevice, st), "upload");
     PhaseTimer ph_asm(&c->prof, st, 2);
-    fill_u32_launch(st, status, nsys, 0u);
     mbd_prep_launch(st, sd_dev, nsys, Nmax, om, cc, status);
     double* qcart = nullptr;
     double* qmult = nullptr;
@@ -818,7 +831,8 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
         HIPCHK(hipGetLastError(), "energy");
     }
     if (grads) {
-        hipLaunchKernelGGL(grad_gate_kernel, dim3((nsys + 63) / 64), dim3(64), 0, st, status, nsys, sd_dev);
+        if (!direct)
+            hipLaunchKernelGGL(grad_gate_kernel, dim3((nsys + 63) / 64), dim3(64), 0, st, status, nsys, sd_dev);
         MatBatch<double> M = A64;  // FP64: reflectors no longer needed; FP32: Q no longer needed
         if (direct) {
             M.p = iw.bufs.p[ISQ_RESULT];
@@ -1376,7 +1390,7 @@ mbd_status mbd_evaluate_batch(mbd_ctx* c, int32_t n_sys, const mbd_system* sys, 
             sds[i].mat0 = i; sds[i].nmat = 1; sds[i].weight = 0.5; sds[i].embed = 0;
         }
         HIPCHK(hipStreamSynchronize(c->gstream), "graph");
-        std::memcpy(g.h_desc, sds.data(), sizeof(SysDesc) * n_sys);
+        std::memcpy(g.h_up, sds.data(), sizeof(SysDesc) * n_sys);
         HIPCHK(hipEventRecord(c->ev_in, c->stream), "graph");
         HIPCHK(hipStreamWaitEvent(c->gstream, c->ev_in, 0), "graph");
         HIPCHK(hipGraphLaunch(g.exec, c->gstream), "graph launch");
@@ -1398,12 +1412,9 @@ mbd_status mbd_evaluate_batch(mbd_ctx* c, int32_t n_sys, const mbd_system* sys, 
             mbd_ctx::Graph g;
             g.nsys = n_sys;
             g.nmat = n_sys;
-            bool ok = hipHostMalloc((void**)&g.h_desc, sizeof(SysDesc) * n_sys, 0) == hipSuccess &&
-                      hipHostMalloc((void**)&g.h_ns, sizeof(int) * n_sys, 0) == hipSuccess &&
+            bool ok = hipHostMalloc((void**)&g.h_up, CoreUpload(n_sys, n_sys).bytes, 0) == hipSuccess &&
                       hipHostMalloc((void**)&g.h_status, sizeof(unsigned) * n_sys, 0) == hipSuccess;
             if (ok) {
-                std::memcpy(g.h_desc, sds.data(), sizeof(SysDesc) * n_sys);
-                for (int i = 0; i < n_sys; i++) g.h_ns[i] = 3 * sds[i].N;
                 RunMode m;
                 m.capturing = true;
                 m.g = &g;

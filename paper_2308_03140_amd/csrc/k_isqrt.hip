@@ -172,6 +172,12 @@ const IsqTable& isq_table() {
 // ---------------------------------------------------------------------------
 // Lanczos (batched, one launch per step)
 // ---------------------------------------------------------------------------
+// LDS written by a wavefront becomes visible to its other lanes
+__device__ __forceinline__ void isq_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // random signs, the same for every matrix
 __device__ __forceinline__ double isq_sign(int k, unsigned seed) {
     unsigned x = (unsigned)k * 2654435761u + seed;
@@ -295,37 +301,94 @@ __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, co
 }
 
 // Smallest (which < 0) or largest eigenvalue of the symmetric tridiagonal
-// (al, be) of order m: multisection on Sturm counts, one shift per lane.
-__device__ double isq_tri_extreme(const double* al, const double* be, int m, int which, int rounds) {
+// (al, be) of order m <= ISQ_LMAX: multisection on Sturm counts, one shift per
+// lane of a wavefront.  The counts are the sign changes of the leading
+// principal minors p_k = (al_k - x) p_{k-1} - be_{k-1}^2 p_{k-2}, two dependent
+// operations a step where the quotient form takes a division (six times
+// longer); with the spread scaled to 2 the minors stay far inside the range.
+// known > 0 (largest only): a lower bound, the value of a leading block; the
+// first round then spaces its shifts geometrically above it, so a value that
+// has not moved is recognised at once.
+__device__ double isq_tri_extreme(const double* al, const double* be, int m, int which, int rounds, double known = 0.0) {
     const int lane = threadIdx.x & 63;
+    m = __builtin_amdgcn_readfirstlane(m);
     double lo = 1e300, hi = -1e300;
-    for (int i = 0; i < m; i++) {
+    for (int i = lane; i < m; i += 64) {
         const double r = (i ? fabs(be[i - 1]) : 0.0) + (i + 1 < m ? fabs(be[i]) : 0.0);
         lo = fmin(lo, al[i] - r);
         hi = fmax(hi, al[i] + r);
     }
+    hi = wave_max(hi);
+    lo = -wave_max(-lo);
     const double pad = 1e-15 * fmax(fabs(lo), fabs(hi)) + 1e-300;
     lo -= pad;
     hi += pad;
+    // scaled coefficients, one per lane (and the second 64), read back with the
+    // uniform index: no memory access in the recurrence
+    const double sc = 2.0 / (hi - lo);
+    double a0 = 0.0, a1 = 0.0, q0 = 0.0, q1 = 0.0;
+    if (lane < m) { a0 = al[lane] * sc; q0 = lane ? be[lane - 1] * sc : 0.0; q0 *= q0; }
+    if (lane + 64 < m) { a1 = al[lane + 64] * sc; q1 = be[lane + 63] * sc; q1 *= q1; }
+    bool geo = which > 0 && known > 0.0 && known > lo && known < hi;
+    if (geo) lo = known;
     for (int it = 0; it < rounds; it++) {
-        const double x = lo + (hi - lo) * (lane + 1) / 65.0;
+        const double step = (hi - lo) / 65.0, tiny = 2e-15 * hi;
+        // geometric: from tiny above lo (lane 0) to just below hi
+        auto shift = [&](int l) { return geo ? lo + tiny * exp2(log2((hi - lo) / tiny) * l / 64.0) : lo + step * (l + 1); };
+        const double x = shift(lane), xs = x * sc;
         int cnt = 0;
-        double d = 1.0;
-        for (int i = 0; i < m; i++) {
-            const double bb = i ? be[i - 1] * be[i - 1] : 0.0;
-            d = al[i] - x - (i ? bb / d : 0.0);
-            if (d == 0.0) d = -1e-300;
-            cnt += d < 0.0;
-        }
+        double p0 = 0.0, p1 = 1.0;
+        auto pass = [&](double a, double q, int k) {
+#pragma unroll 4
+            for (int i = 0; i < k; i++) {
+                const double p2 = (lane_value(a, i) - xs) * p1 - lane_value(q, i) * p0;
+                cnt += (p2 < 0.0) != (p1 < 0.0);
+                p0 = p1;
+                p1 = p2;
+            }
+        };
+        pass(a0, q0, min(m, 64));
+        if (m > 64) pass(a1, q1, m - 64);
         // lanes whose shift lies above the wanted eigenvalue
         const unsigned long long above = __ballot(which < 0 ? cnt >= 1 : cnt >= m);
         const int first = above ? __ffsll((long long)above) - 1 : 64;
-        const double step = (hi - lo) / 65.0;
-        const double nlo = lo + step * first;
-        hi = lo + step * (first + 1);
+        const double nlo = first > 0 ? lane_value(x, first - 1) : lo;
+        hi = first < 64 ? lane_value(x, first) : hi;
         lo = nlo;
+        if (geo && first == 0) return known;
+        geo = false;
+        if (hi - lo <= 2e-16 * fabs(hi)) break;
     }
     return 0.5 * (lo + hi);
+}
+
+// Spectral interval and class from m Lanczos coefficients (one wavefront, the
+// result in every lane).  exact: the recurrence ended, the Ritz values are
+// eigenvalues.  -1: no class (not positive definite, kappa above the table's
+// range, non-finite).
+__device__ int isq_class(const double* al, const double* be, int m, bool exact, const IsqTable& tab, double& hi) {
+    // two rounds place them within 1/4000 of the spread, which the margins cover
+    const double tmin = isq_tri_extreme(al, be, m, -1, 2), tmax = isq_tri_extreme(al, be, m, 1, 2);
+    double res = 0.0;
+    if (!exact) {
+        // last component of the eigenvector of tmax, by the three-term recurrence
+        double x0 = 0.0, x1 = 1.0, nn = 1.0;
+        for (int i = 0; i + 1 < m; i++) {
+            const double x2 = ((tmax - al[i]) * x1 - (i ? be[i - 1] * x0 : 0.0)) / be[i];
+            x0 = x1;
+            x1 = x2;
+            nn += x2 * x2;
+        }
+        res = be[m - 1] * fabs(x1) / sqrt(nn);
+    }
+    hi = exact ? tmax * 1.01 : (tmax + 2.0 * res) * 1.04;
+    const double lo = tmin * (exact ? 0.9 : ISQ_LOW_FRACTION);
+    int c = -1;
+    if (lo > 0.0 && hi < 1e100) {
+        for (int i = ISQ_CLASSES - 1; i >= 0; i--)
+            if (hi <= lo * tab.cls[i].kappa) c = i;
+    }
+    return c;
 }
 
 // All Lanczos steps of a matrix in one workgroup, orders up to ISQ_SMALL: a
@@ -398,7 +461,7 @@ __global__ __launch_bounds__(1024) void isq_small_lanczos_kernel(MatBatch<double
         if (zmax && (ended || m % ISQ_LCHECK == 0 || m == steps)) {
             __syncthreads();
             if (tid < 64) {
-                const double z = isq_tri_extreme(al, be, m, 1, 10);
+                const double z = isq_tri_extreme(al, be, m, 1, 10, zp);
                 if (tid == 0) zs = z;
             }
             __syncthreads();
@@ -460,10 +523,9 @@ struct IsqEmit {
     }
 };
 
-// One wavefront per matrix: spectral interval from the Lanczos coefficients,
-// class, and the program (its last product always lands in buffer
-// ISQ_RESULT).  No class (not positive definite, kappa above the table's
-// range, non-finite): an empty program, and the check afterwards fails.
+// One wavefront per matrix: class and program (its last product always lands
+// in buffer ISQ_RESULT).  No class: an empty program, and the check afterwards
+// fails.
 __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos L, int steps, IsqTable tab, IsqOp* ops,
                                                         int* cls) {
     __shared__ double al[ISQ_LMAX], be[ISQ_LMAX];
@@ -489,31 +551,12 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
         if (lane == 0) { al[steps - 1] = a; be[steps - 1] = blast; }
     }
     __syncthreads();
-    blast = be[steps - 1];
     int m = L.len[b];
     const bool exact = m > 0 || !more;
     if (m == 0) m = steps;
-    const double tmin = isq_tri_extreme(al, be, m, -1, 5), tmax = isq_tri_extreme(al, be, m, 1, 5);
+    double hi;
+    const int c = isq_class(al, be, m, exact, tab, hi);
     if (lane != 0) return;
-    double res = 0.0;
-    if (!exact) {
-        // last component of the eigenvector of tmax, by the three-term recurrence
-        double x0 = 0.0, x1 = 1.0, nn = 1.0;
-        for (int i = 0; i + 1 < m; i++) {
-            const double x2 = ((tmax - al[i]) * x1 - (i ? be[i - 1] * x0 : 0.0)) / be[i];
-            x0 = x1;
-            x1 = x2;
-            nn += x2 * x2;
-        }
-        res = blast * fabs(x1) / sqrt(nn);
-    }
-    const double hi = exact ? tmax * 1.01 : (tmax + 2.0 * res) * 1.04;
-    const double lo = tmin * (exact ? 0.9 : ISQ_LOW_FRACTION);
-    int c = -1;
-    if (lo > 0.0 && hi < 1e100) {
-        for (int i = ISQ_CLASSES - 1; i >= 0; i--)
-            if (hi <= lo * tab.cls[i].kappa) c = i;
-    }
     cls[b] = c;
     IsqEmit e = {op, 0};
     if (c >= 0) {
@@ -779,12 +822,14 @@ __global__ __launch_bounds__(256) void isq_check_kernel(MatBatch<double> Q, MatB
 
 // Energy from the traces (E = w sum_q Tr(Q Z) - (3/2) sum omega) and the
 // verdict of the check; lambda_min from the Lanczos run on Z when wanted.
-__global__ __launch_bounds__(256) void isq_energy_kernel(const SysDesc* sd, const int* ns, const int* cls,
+// Systems whose evaluation failed keep their gradient outputs untouched: no
+// gradient kernel sees an atom of them.
+__global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int* ns, const int* cls,
                                                            const double* part, int nwg_max, const double* om,
                                                            const double* mmult, const double* zmax, unsigned* status) {
     __shared__ double red[4];
     const int s = blockIdx.x;
-    const SysDesc& S = sd[s];
+    SysDesc& S = sd[s];
     double esum = 0.0, lmin = 1e300;
     bool ok = true;
     for (int q = 0; q < S.nmat; q++) {
@@ -811,11 +856,15 @@ __global__ __launch_bounds__(256) void isq_energy_kernel(const SysDesc* sd, cons
     for (int i = threadIdx.x; i < S.N; i += 256) wsum += om[S.atom_off + i];
     wsum = block_sum256(wsum, red);
     if (threadIdx.x == 0) {
-        if (!ok) atomicOr(&status[s], MBD_ST_NO_ROOT);
+        if (!ok) status[s] |= MBD_ST_NO_ROOT;
         if (S.energy) *S.energy = esum - 1.5 * wsum;
         if (S.errors) {
             S.errors[0] = lmin;
             S.errors[1] = S.errors[2] = S.errors[3] = 0.0;
+        }
+        if (status[s] != 0) {
+            S.grad_coords = S.grad_alpha0 = S.grad_omega = S.grad_rvdw = S.grad_lattice = nullptr;
+            S.N = 0;
         }
     }
 }
@@ -840,12 +889,253 @@ __global__ __launch_bounds__(64) void isq_zmax_kernel(const int* ns, const int* 
         be[i] = L.beta[(long long)b * ISQ_LMAX + i];
     }
     __syncthreads();
-    const double z = isq_tri_extreme(al, be, m, 1, 10);
+    const double zp = fabs(zmax[b]);
+    const double z = isq_tri_extreme(al, be, m, 1, 10, steps > ISQ_LCHECK ? zp : 0.0);
     if (lane == 0) {
-        const double zp = zmax[b] < 0.0 ? -zmax[b] : zmax[b];
         const bool conv = ended || (steps > 2 * ISQ_LCHECK && fabs(z - zp) <= 4e-15 * z);
         if (conv) L.done[b] = 1;
         zmax[b] = conv || (last && fabs(z - zp) <= 1e-11 * z) ? z : -z;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// orders up to 64: everything in one workgroup
+// ---------------------------------------------------------------------------
+// Lanczos on a matrix in LDS (row stride NP + 1, zero past n) by one wavefront,
+// a row per lane, held in registers: no barrier, the vector read back from LDS
+// as broadcasts.  vb: NP doubles.  zmax: stop when the largest eigenvalue has
+// converged and return it (-1: it has not).
+template <int NP>
+__device__ double isq_tiny_lanczos(const double* M, double* vb, int n, int steps, double* al, double* be, int& m, bool& ended,
+                                   bool zmax) {
+    const int r = threadIdx.x & 63;
+    const bool mine = r < n;
+    double row[NP];
+#pragma unroll
+    for (int k = 0; k < NP; k++) row[k] = M[k * (NP + 1) + (r & (NP - 1))];
+    double v = mine ? isq_sign(r, 77u) / sqrt((double)n) : 0.0, vp = 0.0, beta = 0.0, a = M[0], zp = 0.0;
+    const int c0 = min(n, 24);
+    ended = false;
+    m = 0;
+    for (int j = 0; j < steps; j++) {
+        if (r < NP) vb[r] = v;
+        isq_wave_sync();
+        double w[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < NP; k++) w[k & 3] += row[k] * vb[k];
+        isq_wave_sync();
+        double u = mine ? (w[0] + w[1]) + (w[2] + w[3]) - a * v - beta * vp : 0.0;
+        const double s1 = wave_sum(v * u);
+        a += s1;
+        u -= s1 * v;
+        const double b2 = wave_sum(u * u);
+        const bool more = __builtin_amdgcn_readfirstlane(b2 > 1e-28 * a * a && b2 < 1e300);
+        const double inv = more ? rsqrt(b2) : 0.0;
+        beta = b2 * inv;
+        if (r == 0) { al[j] = a; be[j] = beta; }
+        vp = v;
+        v = u * inv;
+        m = j + 1;
+        ended = !more;
+        if (zmax && (ended || m == steps || (m >= c0 && (m - c0) % 8 == 0))) {
+            isq_wave_sync();
+            const double z = isq_tri_extreme(al, be, m, 1, 10, zp);
+            const bool conv = ended || fabs(z - zp) <= 4e-15 * z || (m == steps && fabs(z - zp) <= 1e-11 * z);
+            if (__builtin_amdgcn_readfirstlane(conv)) return z;
+            zp = z;
+        }
+        if (ended) break;
+    }
+    return -1.0;
+}
+
+// The whole direct root of a matrix of order <= NP in one launch (a program of
+// 10 products, its Lanczos steps, check and trace are some 35 launches of 3 to
+// 5 us each otherwise).  Four matrices in LDS (row stride NP + 1: the mirrored
+// stores down a column spread over the banks); what enters a product only
+// through the linear epilogue stays in registers.  2 x 2 wavefronts, each a quadrant; the
+// upper one is mirrored from the lower.  Latency bound: 10 atoms 30 us
+// against 240 (and 130 of 147 us for lambda_min).
+template <int NP>
+__global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBatch<double> Zo, const int* ns, IsqTable tab,
+                                                         int* cls, double* part, int nwg_max, double* zmax) {
+    constexpr int T = NP / 32;  // 16 x 16 tiles per wavefront and direction
+    __shared__ __align__(16) double lds[4][NP * (NP + 1)];
+    __shared__ double al[ISQ_LMAX], be[ISQ_LMAX], red[4], sh[2], vb[NP];
+    __shared__ int scls;
+    double *bX = lds[0], *bT = lds[1], *bZ = lds[2], *bY = lds[3];
+    const int b = blockIdx.x, n = ns[b], tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const double* Qb = Q.at(b);
+    auto ix = [](int k, int m) { return k * (NP + 1) + m; };
+    for (int x = tid; x < NP * NP; x += 256) {
+        const int r = x % NP, c = x / NP;
+        bY[ix(c, r)] = r < n && c < n ? Qb[r + (long long)c * Q.ld] : 0.0;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        int m;
+        bool ended;
+        (void)isq_tiny_lanczos<NP>(bY, vb, n, ISQ_STEPS_SMALL, al, be, m, ended, false);
+        isq_wave_sync();
+        double hi;
+        const int c = isq_class(al, be, m, ended, tab, hi);
+        if (lane == 0) {
+            scls = c;
+            sh[0] = hi;
+            cls[b] = c;
+        }
+    }
+    __syncthreads();
+    const int cl = scls;
+    if (cl < 0) return;
+    const IsqClass& k = tab.cls[cl];
+    const double hi = sh[0];
+    typedef typename mfma4<double>::v V4;
+    struct Reg { V4 v[T][T]; };
+    auto row_of = [&](int i, int r) { return wm * (NP / 2) + 16 * i + mfma_rows<double>::row(lane, r); };
+    auto col_of = [&](int j) { return wn * (NP / 2) + 16 * j + (lane & 15); };
+    const bool live = !(wm == 0 && wn == 1);
+    const int nk = (n + 3) & ~3;  // the padding past it never meets the matrix
+    auto mul = [&](const double* A, const double* B) {
+        Reg o;
+#pragma unroll
+        for (int i = 0; i < T; i++)
+#pragma unroll
+            for (int j = 0; j < T; j++) o.v[i][j] = V4{0, 0, 0, 0};
+        if (live) {
+#pragma unroll 4
+            for (int kk = 0; kk < nk; kk += 4) {
+                const int kr = kk + (lane >> 4);
+                double a[T], bb[T];
+#pragma unroll
+                for (int i = 0; i < T; i++) {
+                    a[i] = A[ix(kr, wm * (NP / 2) + 16 * i + (lane & 15))];
+                    bb[i] = B[ix(kr, wn * (NP / 2) + 16 * i + (lane & 15))];
+                }
+#pragma unroll
+                for (int i = 0; i < T; i++)
+#pragma unroll
+                    for (int j = 0; j < T; j++) o.v[i][j] = mfma16x16x4(a[i], bb[j], o.v[i][j]);
+            }
+        }
+        return o;
+    };
+    // f(row, col, element index) over the wavefront's own elements
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int i = 0; i < T; i++)
+#pragma unroll
+            for (int j = 0; j < T; j++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) f(row_of(i, r), col_of(j), i, j, r);
+    };
+    auto put = [&](double* B, const Reg& x) {
+        if (live)
+            each([&](int r, int c, int i, int j, int q) {
+                if (r >= c) B[ix(r, c)] = B[ix(c, r)] = x.v[i][j][q];
+            });
+    };
+    auto lin = [&](double c0, const Reg& x0, double c1, const Reg& x1, double c2, const Reg& x2, double c3) {
+        Reg o;
+        each([&](int r, int c, int i, int j, int q) {
+            o.v[i][j][q] = c0 * x0.v[i][j][q] + c1 * x1.v[i][j][q] + c2 * x2.v[i][j][q] + (r == c ? c3 : 0.0);
+        });
+        return o;
+    };
+    // W(X) for X in bX and in registers; uses bX and bT, leaves W in registers
+    auto poly = [&](const Reg& X, int d, const double* p) {
+        const Reg X2 = mul(bX, bX);
+        if (d == 4) {
+            __syncthreads();
+            put(bX, X2);
+            put(bT, lin(p[4], X2, p[3], X, 0.0, X, p[2]));
+            __syncthreads();
+            return lin(1.0, mul(bX, bT), p[1], X, 0.0, X, p[0]);
+        }
+        put(bT, X2);
+        __syncthreads();
+        const Reg X3 = mul(bX, bT);
+        const int o = d == 6 ? 3 : 6;
+        __syncthreads();
+        put(bX, X3);
+        put(bT, lin(p[o + 3], X3, p[o + 2], X2, p[o + 1], X, p[o]));
+        __syncthreads();
+        if (d == 9) {
+            const Reg U = lin(1.0, mul(bX, bT), p[5], X2, p[4], X, p[3]);
+            __syncthreads();
+            put(bT, U);
+            __syncthreads();
+        }
+        return lin(1.0, mul(bX, bT), p[2], X2, p[1], X, p[0]);
+    };
+    // stage one on X = (Q/hi - mid)/hw; the padding takes X = 0
+    {
+        Reg X;
+        const double s = 1.0 / (hi * k.hw[0]), g = k.mid[0] / k.hw[0];
+        each([&](int r, int c, int i, int j, int q) {
+            X.v[i][j][q] = r < n && c < n ? s * bY[ix(c, r)] - (r == c ? g : 0.0) : 0.0;
+        });
+        put(bX, X);
+        __syncthreads();
+        Reg W = poly(X, k.deg[0], k.b[0]);
+        const double f = 1.0 / sqrt(hi);
+        each([&](int r, int c, int i, int j, int q) { W.v[i][j][q] = r < n && c < n ? f * W.v[i][j][q] : (r == c ? 1.0 : 0.0); });
+        for (int r = n + tid; r < NP; r += 256) bY[ix(r, r)] = 1.0;  // identity in the padding
+        put(bZ, W);
+        __syncthreads();
+        const Reg Y = mul(bY, bZ);
+        __syncthreads();
+        put(bY, Y);
+        __syncthreads();
+    }
+    for (int s = 1; s < 3 && k.deg[s]; s++) {
+        const bool last = s == 2 || !k.deg[s + 1];
+        Reg X = mul(bZ, bY);
+        const double h = 1.0 / k.hw[s];
+        each([&](int r, int c, int i, int j, int q) { X.v[i][j][q] = h * (X.v[i][j][q] - (r == c ? k.mid[s] : 0.0)); });
+        put(bX, X);
+        __syncthreads();
+        const Reg W = poly(X, k.deg[s], k.b[s]);
+        __syncthreads();
+        put(bT, W);
+        __syncthreads();
+        const Reg Z = mul(bZ, bT);
+        Reg Y;
+        if (!last) Y = mul(bY, bT);
+        __syncthreads();
+        put(bZ, Z);
+        if (!last) put(bY, Y);
+        __syncthreads();
+    }
+    // result, trace and check as in isq_check_kernel
+    double e = 0.0;
+    double* Zb = Zo.at(b);
+    for (int x = tid; x < n * n; x += 256) {
+        const int r = x % n, c = x / n;
+        const double z = bZ[ix(c, r)];
+        Zb[r + (long long)c * Zo.ld] = z;
+        e += z * Qb[r + (long long)c * Q.ld];
+    }
+    e = block_sum256(e, red);
+    if (wave != 0) return;
+    const int r = lane & (NP - 1);
+    auto matvec = [&](bool z, double x) {
+        double w = 0.0;
+        for (int q = 0; q < n; q++)
+            w += (z ? bZ[ix(q, r)] : lane < n ? Qb[lane + (long long)q * Q.ld] : 0.0) * lane_value(x, q);
+        return lane < n ? w : 0.0;
+    };
+    const double x = lane < n ? isq_sign(lane, 991u) : 0.0;
+    const double dr = x - matvec(true, matvec(false, matvec(true, x)));
+    const double rr = wave_sum(dr * dr);
+    double* pb = part + (long long)b * nwg_max * 2;
+    if (lane < 2 * ((n + ISQ_MVR - 1) / ISQ_MVR)) pb[lane] = lane == 0 ? e : lane == 1 ? rr : 0.0;
+    if (zmax) {
+        int m;
+        bool ended;
+        const double z = isq_tiny_lanczos<NP>(bZ, vb, n, ISQ_LMAX, al, be, m, ended, true);
+        if (lane == 0) zmax[b] = z;
     }
 }
 
@@ -856,6 +1146,16 @@ int isq_lanczos_wgs(int nmax) { return (nmax + ISQ_MVR - 1) / ISQ_MVR; }
 
 void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int* ns_host, LaunchProfiler* prof) {
     const MatBatch<double> Q = {w.bufs.p[0], w.bufs.ld, w.bufs.stride};
+    if (nmax <= 64) {
+        const MatBatch<double> Z = {w.bufs.p[ISQ_RESULT], w.bufs.ld, w.bufs.stride};
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(nmat), dim3(256), 0, st, Q, Z, w.ns, isq_table(), w.cls, w.check,
+                               isq_lanczos_wgs(nmax), w.zmax);
+        };
+        if (nmax <= 32) go(isq_tiny_kernel<32>);
+        else go(isq_tiny_kernel<64>);
+        return;
+    }
     const dim3 mv(isq_lanczos_wgs(nmax), 1, nmat);
     IsqLanczos L = w.lan;
     L.done = nullptr;
@@ -919,7 +1219,7 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     }
 }
 
-void isq_energy_launch(hipStream_t st, const IsqWork& w, const SysDesc* sd, int nsys, int nmax, const double* om,
+void isq_energy_launch(hipStream_t st, const IsqWork& w, SysDesc* sd, int nsys, int nmax, const double* om,
                        const double* mmult, unsigned* status) {
     hipLaunchKernelGGL(isq_energy_kernel, dim3(nsys), dim3(256), 0, st, sd, w.ns, w.cls, w.check, isq_lanczos_wgs(nmax),
                        om, mmult, w.zmax, status);

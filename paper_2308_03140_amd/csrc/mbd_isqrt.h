@@ -65,6 +65,7 @@ int isq_lanczos_wgs(int nmax);
 // orders; prof: each product launch as kind 1 when launch timing is on
 struct LaunchProfiler;
 void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int* ns_host, LaunchProfiler* prof);
-// energies, errors[0..3] and MBD_ST_NO_ROOT of the systems
-void isq_energy_launch(hipStream_t st, const IsqWork& w, const SysDesc* sd, int nsys, int nmax, const double* om,
+// energies, errors[0..3] and MBD_ST_NO_ROOT of the systems; a failed system's
+// descriptor loses its atoms and gradient outputs
+void isq_energy_launch(hipStream_t st, const IsqWork& w, SysDesc* sd, int nsys, int nmax, const double* om,
                        const double* mmult, unsigned* status);

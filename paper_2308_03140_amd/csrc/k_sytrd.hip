@@ -59,6 +59,15 @@ __device__ __forceinline__ T refl_v(const T* col, int r, int s, int n, T scale) 
     return r == s ? T(1) : col[r] * scale;
 }
 
+// A column whose norm squared is zero below the diagonal, or below the normal
+// range altogether (1/(alpha - beta) squared would overflow: FP32 columns of
+// 1e-20, as the rounding noise of an exactly decoupled block leaves), needs no
+// reflector.
+template <typename T>
+__device__ __forceinline__ bool refl_none(T alpha, T xn2) {
+    return xn2 == T(0) || alpha * alpha + xn2 < num_limits<T>::tiny;
+}
+
 // Reflector scalars from the updated column held in colbuf (LAPACK dlarfg
 // convention: beta = -sign(alpha) ||x||, tau = (beta - alpha)/beta).  The
 // squared norm of x = col(i+2:n) was accumulated (atomically, by the phase
@@ -69,7 +78,7 @@ __device__ __forceinline__ Refl<T> refl_scalars(const SytrdWs<T>& w, int b, int 
     const T xn2 = w.normacc[(long long)b * SYTRD_SLOTS + i % SYTRD_SLOTS];
     const T alpha = w.colbuf[(long long)b * 2 * w.sC + (i & 1) * w.sC + i + 1];
     Refl<T> r;
-    if (xn2 == T(0)) {
+    if (refl_none(alpha, xn2)) {
         r.tau = T(0); r.beta = alpha; r.scale = T(0);
     } else {
         const T nrm = sqrt(alpha * alpha + xn2);
@@ -661,7 +670,7 @@ __global__ __launch_bounds__(SYTRD_TAIL_THREADS) void sytrd_tail_kernel(SytrdWs<
         }
         const T alpha = L[ci + 1];
         T beta, tau, scale;
-        if (xn2 == T(0)) {
+        if (refl_none(alpha, xn2)) {
             tau = T(0); beta = alpha; scale = T(0);
         } else {
             const T nrm = sqrt(alpha * alpha + xn2);
@@ -1041,7 +1050,7 @@ __global__ __launch_bounds__(64 * NW) void sytrd_wg_kernel(SytrdWs<T> w) {
             const T xn2 = dots[2 * J];
             const T alpha = uc[s];
             T beta, tau, scale;
-            if (xn2 == T(0)) {
+            if (refl_none(alpha, xn2)) {
                 tau = T(0); beta = alpha; scale = T(0);
             } else {
                 const T nrm = sqrt(alpha * alpha + xn2);
@@ -1212,7 +1221,7 @@ __device__ __forceinline__ FinScal<T> fin_scalars(const SytrdWs<T>& w, int b, in
     const T xAx = wave_sum((va[0] + va[1]) + (va[2] + va[3]));
     const T yxs = (lane_value(yq, 0) + lane_value(yq, 1)) + (lane_value(yq, 2) + lane_value(yq, 3));
     FinScal<T> f;
-    f.zero = xn2 == T(0);
+    f.zero = refl_none(alpha, xn2);
     if (f.zero) {
         f.tau = T(0); f.beta = alpha; f.scale = T(0);
     } else {

@@ -236,8 +236,8 @@ __device__ __forceinline__ typename Vec16<T>::v buf_load16(__amdgpu_buffer_rsrc_
 }
 
 template <typename T> struct num_limits;
-template <> struct num_limits<double> { static constexpr double eps = 2.220446049250313e-16; };
-template <> struct num_limits<float> { static constexpr float eps = 1.1920929e-07f; };
+template <> struct num_limits<double> { static constexpr double eps = 2.220446049250313e-16, tiny = 2.3e-308; };
+template <> struct num_limits<float> { static constexpr float eps = 1.1920929e-07f, tiny = 1.2e-38f; };
 
 // ---------------------------------------------------------------------------
 // Batched dense storage: matrix b of a batch lives at base + b*stride, column

@@ -159,3 +159,23 @@ def test_workspace_limit(monkeypatch):
         finally:
             ctx.close()
     ref_ctx.close()
+
+
+def test_decoupled_blocks_fp32_eigenvalues():
+    """An FP32 reduction whose columns are at rounding noise of exactly
+    decoupled blocks (1e-20, the square below the normal range)."""
+    from paper_2308_03140_amd import torch_api as T
+    _note("eigh, decoupled blocks with 1e-20 noise")
+    ctx = T.Context(0, "fp32_refined")
+    try:
+        for n in (3, 40, 150):
+            rng = np.random.default_rng(n)
+            A = rng.standard_normal((n, n))
+            A = A + A.T
+            M = np.block([[A, np.zeros((n, n))], [np.zeros((n, n)), A]])
+            N = rng.standard_normal((2 * n, 2 * n)) * 1e-20
+            M += N + N.T
+            w, _ = T.eigh(ctx, torch.tensor(M, dtype=torch.float32, device="cuda"))
+            assert np.abs(w.double().cpu().numpy() - np.linalg.eigvalsh(M)).max() <= 4e-7 * n ** 0.5 * np.abs(M).sum(1).max()
+    finally:
+        ctx.close()

@@ -772,6 +772,7 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
     int* conv_dev = nullptr;  // per matrix: the last step met its target
     int* eig_bad = nullptr;  // per matrix: non-finite tridiagonal
     PhaseTimer ph_eg(&c->prof, st, 7, direct);
+    iw.embed = per != nullptr;
     if (direct) {
         isq_launch(st, iw, nmax, nmat, nsh.data(), &c->prof);
         isq_energy_launch(st, iw, sd_dev, nsys, nmax, om, per ? qmult : nullptr, status);
@@ -844,7 +845,7 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
         if (per) {
             const int N = sds[0].N;
             const int nch = per_recip_chunks(prc.ncol);
-            double* part = wsT<double>(c, "gpart", (size_t)nq * N * N * PER_PART);
+            double* part = wsT<double>(c, "gpart", (size_t)nq * N * (N + 1) / 2 * PER_PART);
             double* rq = wsT<double>(c, "grq", std::max<size_t>(1, (size_t)nq * nch * N * 4));
             double* rl = wsT<double>(c, "grl", std::max<size_t>(1, (size_t)nq * nch * 10));
             double* latpart = wsT<double>(c, "glat", (size_t)N * 9);

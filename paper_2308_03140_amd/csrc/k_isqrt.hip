@@ -31,7 +31,7 @@
 #include <mutex>
 #include <vector>
 
-#include "gemm_mfma.h"
+#include "gemm_splitk.h"
 #include "mbd_internal.h"
 #include "mbd_isqrt.h"
 #include "mbd_kernels.h"
@@ -492,7 +492,7 @@ struct IsqEmit {
                         double d0 = 0, double d1 = 0, double d2 = 0, double d3 = 0) {
         IsqOp o;
         o.a = (signed char)a; o.b = (signed char)b; o.e1 = (signed char)e1; o.e2 = (signed char)e2;
-        o.out = (signed char)out; o.out2 = (signed char)out2;
+        o.out = (signed char)out; o.out2 = (signed char)out2; o.full = 0;
         o.c[0] = c0; o.c[1] = c1; o.c[2] = c2; o.c[3] = c3;
         o.d[0] = d0; o.d[1] = d1; o.d[2] = d2; o.d[3] = d3;
         op[k++] = o;
@@ -587,6 +587,7 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
             }
         }
     }
+    if (e.k) op[e.k - 1].full = 1;
     while (e.k < ISQ_OPMAX) e.put(-1, -1, -1, -1, -1, -1, 0, 0, 0, 0);
 }
 
@@ -594,109 +595,47 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
 // symmetric product step
 // ---------------------------------------------------------------------------
 // One TM x TN tile of the lower triangle per workgroup, K split over its WK
-// wavefronts: each computes the whole tile over its own K groups, straight
-// from L2 into registers (no LDS staging and no barrier in the loop; no load
-// is made twice, since the wavefronts read different K), and the shares are
-// summed through LDS at the end.  Bound by the FP64 matrix cores: at order
-// 6000 62-64 TFLOP/s against 58 for 128 x 128 tiles staged through LDS (the
+// wavefronts (gemm_splitk.h).  Bound by the FP64 matrix cores: at order 6000
+// 62-64 TFLOP/s against 58 for 128 x 128 tiles staged through LDS (the
 // library's DGEMM reaches 65), at order 2103 57 against 32 (the smaller tiles
 // fill the last round of workgroups), 512 uneven molecules 2.2-2.6 ms a
 // product against 4.0-4.5, one matrix of order 450 9 us against 13.
 //
-// Both operands are symmetric and stored in full, so A(m, k) and B(k, n) are
-// read along their columns.  A lane's 16-byte load holds rows 2r, 2r + 1 (r =
-// lane mod 16), one for each of two MFMA tiles: tile i covers the rows of
-// parity i mod 2 of its 32.  The descriptor's size ends the K loop (k >= n
-// reads zero); rows past n only reach rows of C that are not stored.  Two
-// register sets of U k-steps alternate, so U MFMA steps hide each load.
-typedef double isq_d2 __attribute__((ext_vector_type(2)));
-
-template <int MI, int NJ, int WK, int U, int MINW>
+// EMB: the matrices are real embeddings [[Re, -Im], [Im, Re]] of Hermitian ones
+// (order 2n), of which only the left block column is read and, before the last
+// product, written.  Its lower triangles Re C = Re A Re B + Im A (Im B)^T (part
+// 0) and Im C = Im A Re B - Re A (Im B)^T (part 1) take half the products of a
+// real symmetric matrix of that order; bound by the traffic of the operands and
+// the epilogue (64 matrices of order 384: 74 us a product against 118).
+template <int MI, int NJ, int WK, int U, int MINW, bool EMB>
 __global__ __launch_bounds__(64 * WK, MINW) void isq_prod_kernel(IsqBufs bufs, const int* ns, const IsqOp* ops,
                                                                    int step) {
-    static_assert(MI % 2 == 0 && NJ % 2 == 0 && MI % NJ == 0 && WK >= 2, "tile and wave split");
-    constexpr int TM = 16 * MI, TN = 16 * NJ, NT = 64 * WK, LDC = TM + 2, R = TM / TN;
-    __shared__ __align__(16) double cs[2][TN * LDC];
+    typedef SplitK<MI, NJ, WK, U> SK;
+    static_assert(MI % NJ == 0, "tile rows hold whole tile columns");
+    constexpr int TM = SK::TM, TN = SK::TN, NT = SK::NT, LDC = SK::LDC;
+    __shared__ __align__(16) double cs[SK::LDS];
     const int b = blockIdx.z;
     const IsqOp& op = ops[(long long)b * ISQ_OPMAX + step];
     if (op.a < 0) return;
-    const int n = ns[b];
-    // row ti of tiles holds the R (ti + 1) tiles on and left of the diagonal;
-    // the shares of the XCDs rotate with the matrix, or the last rows of a
-    // batch, which only its largest matrices have, would all fall to one XCD
-    // (512 uneven molecules, 64 x 32 tiles: 4.9 ms a product against 2.4)
-    const int bx = blockIdx.x + b % gridDim.x;
-    const int v = xcd_virtual(bx >= (int)gridDim.x ? bx - (int)gridDim.x : bx, gridDim.x);
-    int ti = (int)((sqrtf(8.0f * (float)(v / R) + 1.0f) - 1.0f) * 0.5f);
-    while (R * (ti + 1) * (ti + 2) / 2 <= v) ti++;
-    while (R * ti * (ti + 1) / 2 > v) ti--;
-    const int m0 = ti * TM, n0 = (v - R * ti * (ti + 1) / 2) * TN;
+    const int n = EMB ? ns[b] / 2 : ns[b], part = EMB ? blockIdx.y : 0;
+    int ti, tj;
+    splitk_lower_tile(splitk_tile_index(blockIdx.x, b, gridDim.x), TM / TN, ti, tj);
+    const int m0 = ti * TM, n0 = tj * TN;
     if (m0 >= n || n0 >= n) return;
-    const int ld = bufs.ld;
-    const double* A = bufs.p[op.a] + (long long)b * bufs.stride;
-    const double* B = bufs.p[op.b] + (long long)b * bufs.stride;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    typename mfma4<double>::v acc[MI][NJ];
-#pragma unroll
-    for (int i = 0; i < MI; i++)
-#pragma unroll
-        for (int j = 0; j < NJ; j++) acc[i][j] = typename mfma4<double>::v{0, 0, 0, 0};
-    constexpr int G = 4 * U;  // k of one group; groups go round robin over the wavefronts
-    const unsigned la = (unsigned)((lane >> 4) * ld + m0 + 2 * (lane & 15)) * 8u;
-    const unsigned lb = (unsigned)((lane >> 4) * ld + n0 + 2 * (lane & 15)) * 8u;
-    isq_d2 ra[2][U][MI / 2], rb[2][U][NJ / 2];
-    auto gload = [&](int k0, auto& xa, auto& xb) {
-        const int kn = max(0, min(G, n - k0));
-        const auto dA = make_rsrc(A + (long long)k0 * ld, (unsigned)kn * ld * 8u);
-        const auto dB = make_rsrc(B + (long long)k0 * ld, (unsigned)kn * ld * 8u);
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-#pragma unroll
-            for (int i = 0; i < MI / 2; i++)
-                xa[u][i] = __builtin_bit_cast(isq_d2, __builtin_amdgcn_raw_buffer_load_b128(dA, la + 256u * i, 32 * u * ld, 0));
-#pragma unroll
-            for (int j = 0; j < NJ / 2; j++)
-                xb[u][j] = __builtin_bit_cast(isq_d2, __builtin_amdgcn_raw_buffer_load_b128(dB, lb + 256u * j, 32 * u * ld, 0));
+    const int ld = bufs.ld, tid = threadIdx.x;
+    {
+        SK sk;
+        sk.clear();
+        const double* A = bufs.p[op.a] + (long long)b * bufs.stride + m0;
+        const double* B = bufs.p[op.b] + (long long)b * bufs.stride + n0;
+        if constexpr (!EMB) {
+            sk.run(A, B, ld, n);
+        } else {
+            sk.run(A + part * n, B, ld, n);
+            if (part) sk.template run<true>(A, B + n, ld, n);
+            else sk.run(A + n, B + n, ld, n);
         }
-    };
-    auto mult = [&](auto& xa, auto& xb) {
-#pragma unroll
-        for (int u = 0; u < U; u++)
-#pragma unroll
-            for (int i = 0; i < MI; i++)
-#pragma unroll
-                for (int j = 0; j < NJ; j++) acc[i][j] = mfma16x16x4(xa[u][i / 2][i & 1], xb[u][j / 2][j & 1], acc[i][j]);
-    };
-    const int ng = (n + G - 1) / G;
-    int g = wave;
-    gload(g * G, ra[0], rb[0]);
-    while (g < ng) {
-        gload((g + WK) * G, ra[1], rb[1]);
-        mult(ra[0], rb[0]);
-        g += WK;
-        if (g >= ng) break;
-        gload((g + WK) * G, ra[0], rb[0]);
-        mult(ra[1], rb[1]);
-        g += WK;
-    }
-    // the wavefronts' shares: two write, the others add in turn
-#pragma unroll
-    for (int w = 0; w < WK; w += 2) {
-        if (wave >= w && wave < w + 2) {
-            double* c = cs[wave & 1];
-#pragma unroll
-            for (int i = 0; i < MI; i++)
-#pragma unroll
-                for (int j = 0; j < NJ; j++)
-#pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        const int row = 32 * (i / 2) + 2 * mfma_rows<double>::row(lane, r) + (i & 1);
-                        const int col = 32 * (j / 2) + 2 * (lane & 15) + (j & 1);
-                        if (w == 0) c[col * LDC + row] = acc[i][j][r];
-                        else c[col * LDC + row] += acc[i][j][r];
-                    }
-        }
-        __syncthreads();
+        sk.reduce(cs);
     }
     const double* E1 = op.e1 >= 0 ? bufs.p[op.e1] + (long long)b * bufs.stride : nullptr;
     const double* E2 = op.e2 >= 0 ? bufs.p[op.e2] + (long long)b * bufs.stride : nullptr;
@@ -706,21 +645,28 @@ __global__ __launch_bounds__(64 * WK, MINW) void isq_prod_kernel(IsqBufs bufs, c
 #pragma unroll
     for (int q = 0; q < 4; q++) { c[q] = op.c[q]; d[q] = op.d[q]; }
     const bool diag = m0 < n0 + TN;
-    // lower triangle, in runs along m
+    const double sg = part ? -1.0 : 1.0;
+    const bool right = EMB && op.full;  // the right block column too
+    // lower triangle, in runs along m: (row, col) of the part and, in the right
+    // block column, (n + row, n + col) for Re, (row, n + col) negated for Im
 #pragma unroll 4
     for (int x = tid; x < TM * TN; x += NT) {
         const int r = x % TM, cl = x / TM, row = m0 + r, col = n0 + cl;
         if (row >= n || col >= n || (diag && col > row)) continue;
-        const long long at = row + (long long)col * ld;
-        const double s = cs[0][cl * LDC + r] + cs[1][cl * LDC + r];
+        const long long at = row + part * n + (long long)col * ld;
+        const double s = cs[cl * LDC + r] + cs[(TN + cl) * LDC + r];
         const double e1 = E1 ? E1[at] : 0.0, e2 = E2 ? E2[at] : 0.0, id = row == col ? 1.0 : 0.0;
-        const double o1 = c[0] * s + c[1] * e1 + c[2] * e2 + c[3] * id;
+        double o1 = c[0] * s + c[1] * e1 + c[2] * e2 + c[3] * id;
+        if (EMB && part && row == col) o1 = 0.0;  // the diagonal of Im
+        const long long at2 = row + (1 - part) * n + (long long)(n + col) * ld;
         C1[at] = o1;
-        cs[0][cl * LDC + r] = o1;
+        if (right) C1[at2] = sg * o1;
+        cs[cl * LDC + r] = o1;
         if (C2) {
-            const double o2 = d[0] * s + d[1] * e1 + d[2] * e2 + d[3] * id;
+            double o2 = d[0] * s + d[1] * e1 + d[2] * e2 + d[3] * id;
+            if (EMB && part && row == col) o2 = 0.0;
             C2[at] = o2;
-            cs[1][cl * LDC + r] = o2;
+            cs[(TN + cl) * LDC + r] = o2;
         }
     }
     __syncthreads();
@@ -729,9 +675,13 @@ __global__ __launch_bounds__(64 * WK, MINW) void isq_prod_kernel(IsqBufs bufs, c
     for (int x = tid; x < TM * TN; x += NT) {
         const int cl = x % TN, r = x / TN, row = m0 + r, col = n0 + cl;
         if (row >= n || col >= n || (diag && col >= row)) continue;
-        const long long at = col + (long long)row * ld;
-        C1[at] = cs[0][cl * LDC + r];
-        if (C2) C2[at] = cs[1][cl * LDC + r];
+        // (col, row) of Re, or of Im negated; then (n + col, n + row) or (col, n + row)
+        const long long at = col + part * n + (long long)row * ld;
+        const long long at2 = col + (1 - part) * n + (long long)(n + row) * ld;
+        const double v1 = cs[cl * LDC + r];
+        C1[at] = sg * v1;
+        if (right) C1[at2] = v1;
+        if (C2) C2[at] = sg * cs[(TN + cl) * LDC + r];
     }
 }
 
@@ -745,15 +695,15 @@ __global__ __launch_bounds__(64 * WK, MINW) void isq_prod_kernel(IsqBufs bufs, c
 struct IsqShape { int tm, tn; double rate; };
 static const IsqShape ISQ_SHAPES[3] = {{64, 32, 1.0}, {96, 32, 0.97}, {32, 32, 0.84}};
 
-static int isq_shape(const int* ns, int nmat) {
+static int isq_shape(const int* ns, int nmat, bool embed) {
     double best = 1e300;
     int pick = 2, nmax = 0;
-    for (int b = 0; b < nmat; b++) nmax = std::max(nmax, ns[b]);
+    for (int b = 0; b < nmat; b++) nmax = std::max(nmax, embed ? ns[b] / 2 : ns[b]);
     for (int s = nmax < 1024 ? 2 : 0; s < 3; s++) {
         const IsqShape& q = ISQ_SHAPES[s];
         double tiles = 0.0, work = 0.0;
         for (int b = 0; b < nmat; b++) {
-            const double rows = (ns[b] + q.tm - 1) / q.tm, t = q.tm / q.tn * rows * (rows + 1) / 2;
+            const double t = (embed ? 2.0 : 1.0) * splitk_lower_tiles(embed ? ns[b] / 2 : ns[b], q.tm, q.tn);
             tiles += t;
             work += t * ns[b];
         }
@@ -832,17 +782,18 @@ __global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int*
     SysDesc& S = sd[s];
     double esum = 0.0, lmin = 1e300;
     bool ok = true;
-    for (int q = 0; q < S.nmat; q++) {
+    const int lane = threadIdx.x & 63;
+    for (int q = threadIdx.x >> 6; q < S.nmat; q += 4) {  // a wavefront per matrix
         const int b = S.mat0 + q;
-        if (cls[b] < 0) { ok = false; break; }  // uniform over the workgroup
+        if (cls[b] < 0) { ok = false; continue; }
         const int n = ns[b], nwg = (n + ISQ_MVR - 1) / ISQ_MVR;
         double e = 0.0, r = 0.0;
-        for (int w = threadIdx.x; w < nwg; w += 256) {
+        for (int w = lane; w < nwg; w += 64) {
             e += part[((long long)b * nwg_max + w) * 2];
             r += part[((long long)b * nwg_max + w) * 2 + 1];
         }
-        e = block_sum256(e, red);
-        r = block_sum256(r, red);
+        e = wave_sum(e);
+        r = wave_sum(r);
         // |I - Z Q Z|_F^2; rounding leaves about 1e-14 sqrt(n) (measured, orders 30 to 6000)
         if (!(r <= ISQ_CHECK * ISQ_CHECK * n)) ok = false;
         if (zmax) {
@@ -850,8 +801,11 @@ __global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int*
             if (!(z > 0.0)) ok = false;
             lmin = fmin(lmin, 1.0 / (z * z));
         }
-        esum += S.weight * (mmult ? mmult[b] : 1.0) * e;
+        if (lane == 0) esum += S.weight * (mmult ? mmult[b] : 1.0) * e;
     }
+    ok = __syncthreads_and(ok);
+    esum = block_sum256(esum, red);
+    lmin = -block_max256(-lmin, red);
     double wsum = 0.0;
     for (int i = threadIdx.x; i < S.N; i += 256) wsum += om[S.atom_off + i];
     wsum = block_sum256(wsum, red);
@@ -1168,22 +1122,25 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
         for (int j = 0; j < steps; j++) hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Q, w.ns, L, j);
     }
     hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(), w.ops, w.cls);
-    const int shape = isq_shape(ns_host, nmat);
+    const int shape = isq_shape(ns_host, nmat, w.embed);
     const bool timed = prof && prof->enabled && prof->launches;
     const size_t rec0 = timed ? prof->kind.size() : 0;
     for (int k = 0; k < ISQ_OPMAX; k++) {
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (timed) prof->pair(&e0, &e1, 1, 0.0);
-        auto go = [&](auto kernel, int tm, int tn, int wk) {
-            const int rows = (nmax + tm - 1) / tm;
-            hipExtLaunchKernelGGL(kernel, dim3(tm / tn * rows * (rows + 1) / 2, 1, nmat), dim3(64 * wk), 0, st, e0, e1, 0,
-                                  w.bufs, w.ns, w.ops, k);
+        auto go = [&](auto kernel, auto emb_kernel, int tm, int tn, int wk) {
+            if (w.embed)
+                hipExtLaunchKernelGGL(emb_kernel, dim3(splitk_lower_tiles(nmax / 2, tm, tn), 2, nmat), dim3(64 * wk), 0, st,
+                                      e0, e1, 0, w.bufs, w.ns, w.ops, k);
+            else
+                hipExtLaunchKernelGGL(kernel, dim3(splitk_lower_tiles(nmax, tm, tn), 1, nmat), dim3(64 * wk), 0, st, e0, e1,
+                                      0, w.bufs, w.ns, w.ops, k);
         };
         switch (shape) {
-        case 0: go(isq_prod_kernel<4, 2, 4, 5, 2>, 64, 32, 4); break;
-        case 1: go(isq_prod_kernel<6, 2, 4, 2, 2>, 96, 32, 4); break;
-        case 2: go(isq_prod_kernel<2, 2, 2, 6, 3>, 32, 32, 2); break;
-        default: go(isq_prod_kernel<2, 2, 4, 6, 3>, 32, 32, 4); break;
+        case 0: go(isq_prod_kernel<4, 2, 4, 5, 2, false>, isq_prod_kernel<4, 2, 4, 5, 2, true>, 64, 32, 4); break;
+        case 1: go(isq_prod_kernel<6, 2, 4, 2, 2, false>, isq_prod_kernel<6, 2, 4, 2, 2, true>, 96, 32, 4); break;
+        case 2: go(isq_prod_kernel<2, 2, 2, 6, 3, false>, isq_prod_kernel<2, 2, 2, 6, 3, true>, 32, 32, 2); break;
+        default: go(isq_prod_kernel<2, 2, 4, 6, 3, false>, isq_prod_kernel<2, 2, 4, 6, 3, true>, 32, 32, 4); break;
         }
     }
     if (timed) {
@@ -1195,7 +1152,7 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
         for (int k = 0; k < ISQ_OPMAX; k++) {
             double flops = 0.0;
             for (int b = 0; b < nmat; b++)
-                if (cls[b] >= 0 && k < isq_products(isq_table().cls[cls[b]])) flops += (double)ns_host[b] * ns_host[b] * ns_host[b];
+                if (cls[b] >= 0 && k < isq_products(isq_table().cls[cls[b]])) flops += (w.embed ? 0.5 : 1.0) * ns_host[b] * ns_host[b] * ns_host[b];
             if (flops > 0.0) prof->work[rec0 + k] = flops;
             else prof->kind[rec0 + k] = -1;
         }

@@ -23,7 +23,7 @@
 // The Hermitian Q(q) is stored as its real embedding [[Re, -Im], [Im, Re]]
 // (order 2n) so the batched real eigensolver serves it; every eigenvalue of
 // Q(q) appears twice.  The reciprocal sums are evaluated in FP64.
-#include "gemm_mfma.h"
+#include "gemm_splitk.h"
 #include "mbd_internal.h"
 #include "mbd_kernels.h"
 #include "mbd_sys.h"
@@ -113,17 +113,27 @@ __device__ __forceinline__ bool image_term(const double* x, double gamma, double
 // Assembly of the embedded Q(q).  A workgroup of W wavefronts holds 64 W / lpp
 // slots of lpp lanes, one lane per q-point (lpp: the q count rounded up to a
 // power of two, at most 64; grid y covers further groups of q-points); spp
-// slots share an ordered atom pair (i, j) and split its images.  The
+// slots share an atom pair i <= j and split its images.  The
 // real-space image terms depend on the pair and the image only: each is
 // formed once, by one lane of its slot, into LDS (lpp images per round and
 // slot), and every lane of the slot adds it with its own phase e^{-i q.x}; the
 // slots' sums are added at the end in a fixed order.  FP64 VALU bound where
 // there are enough pairs; with one slot a pair, 8 atoms on 8 q points were 8
 // wavefronts that walked all images in turn (547 us, the adjoint 1374 us).
-// Lanes of a pair index past N^2 follow the barriers and store nothing.  Writes the real-space and self terms and omega^2 into the left
+// Lanes of a pair index past the last follow the barriers and store nothing.  Writes the real-space and self terms and omega^2 into the left
 // block column [Re; Im] of the embedding; the reciprocal-space product then
 // adds its term and fills the right block column.
 #define PER_LANES 64
+
+// Pair index -> atoms i <= j.  The pair (j, i) is the conjugate of (i, j): the
+// image terms are even in x and the image list holds -n with every n.
+__device__ __forceinline__ void per_pair(long long pid, int& i, int& j) {
+    j = (int)((sqrt(8.0 * (double)pid + 1.0) - 1.0) * 0.5);
+    while ((long long)(j + 1) * (j + 2) / 2 <= pid) j++;
+    while ((long long)j * (j + 1) / 2 > pid) j--;
+    i = (int)(pid - (long long)j * (j + 1) / 2);
+}
+static long long per_pairs(int N) { return (long long)N * (N + 1) / 2; }
 
 // Sum of v over the spp slots of a pair (lanes lpp, 2 lpp, .. apart within a
 // wavefront, then its wavefronts through LDS), in the lanes of the pair's first
@@ -156,11 +166,12 @@ __global__ __launch_bounds__(PER_LANES * W) void mbd_assemble_periodic_kernel(co
     const int N = S.N, n = 3 * N;
     const int slot = threadIdx.x / lpp, ql = threadIdx.x % lpp, sub = slot % spp;
     const long long pid0 = (long long)blockIdx.x * (PER_LANES * W / lpp / spp) + slot / spp;
-    const bool pv = pid0 < (long long)N * N;
+    const bool pv = pid0 < (long long)N * (N + 1) / 2;
     const long long pid = pv ? pid0 : 0;
     const int q = blockIdx.y * lpp + ql;
     const bool qv_ok = pv && q < nq;
-    const int i = (int)(pid % N), j = (int)(pid / N);
+    int i, j;
+    per_pair(pid, i, j);
     const double* R = S.coords;
     const double r[3] = {R[3 * j] - R[3 * i], R[3 * j + 1] - R[3 * i + 1], R[3 * j + 2] - R[3 * i + 2]};
     const int qc = qv_ok ? q : 0;
@@ -222,8 +233,13 @@ __global__ __launch_bounds__(PER_LANES * W) void mbd_assemble_periodic_kernel(co
             const double re = pc * Tre[a * 3 + b] +
                               ((om && i == j && a == b) ? om[S.atom_off + i] * om[S.atom_off + i] : 0.0);
             const long long r0 = 3 * i + a, c0 = 3 * j + b;
+            const double im = i == j ? 0.0 : pc * Tim[a * 3 + b];  // the images of i = j come in +-n
             Qb[r0 + c0 * ld] = re;
-            Qb[(r0 + n) + c0 * ld] = pc * Tim[a * 3 + b];
+            Qb[(r0 + n) + c0 * ld] = im;
+            if (i != j) {
+                Qb[c0 + r0 * ld] = re;
+                Qb[(c0 + n) + r0 * ld] = -im;
+            }
         }
 }
 
@@ -281,54 +297,60 @@ __global__ __launch_bounds__(256) void per_phase_kernel(const SysDesc* sd, const
     phase[2 * e + 1] = sn;
 }
 
-// Reciprocal term of the embedding: [Re; Im] of C U U^H C is [U_r, -U_i;
-// U_i, U_r] times the first n rows of the same, transposed (K = 2 ncol), so
-// one product per q over the left block column.  The epilogue adds it to the
-// real-space part there, mirrors it into the right block column (Re to the
-// bottom right, -Im to the top right) and writes the FP32 copy.
-struct PerRecAsmProb {
-    static constexpr bool A_M_CONTIG = true;
-    static constexpr bool B_N_CONTIG = true;
-    const SysDesc* sd;
-    const double* cc;
-    const double* Z; int ldz; long long sZ; int ncol; int n;
-    MatBatch<double> Q; MatBatch<float> Q32;
-    int tiles_m, tiles_n;
-    __device__ bool tile(int bx, int, int bz, GemmTile& t) const {
-        int ti, tj;
-        band_tile(xcd_virtual(bx, gridDim.x), tiles_m, tiles_n, ti, tj);
-        t.batch = bz;
-        t.m0 = ti * GEMM_BM; t.n0 = tj * GEMM_BN; t.K = 2 * ncol;
-        return t.m0 < 2 * n && t.n0 < n;
+// Reciprocal term of the embedding, C U U^H C: the lower triangles of Re = U_r
+// U_r^T + U_i U_i^T (part 0) and Im = U_i U_r^T - U_r U_i^T (part 1), added to
+// the real-space part and copied to their other seven places (and to the FP32
+// copy).  K split over the wavefronts (gemm_splitk.h); matrix-core bound: 64 q
+// points of 64 atoms 90 us against 230 for the whole left block column
+// through staged tiles.
+template <int MI, int NJ, int WK, int U>
+__global__ __launch_bounds__(64 * WK) void per_recip_asm_kernel(const SysDesc* sd, const double* cc, PerEwald pr, int n,
+                                                                  MatBatch<double> Q, MatBatch<float> Q32) {
+    typedef SplitK<MI, NJ, WK, U> SK;
+    constexpr int TM = SK::TM, TN = SK::TN, LDC = SK::LDC;
+    __shared__ __align__(16) double cs[SK::LDS];
+    const int b = blockIdx.z, part = blockIdx.y;
+    int ti, tj;
+    splitk_lower_tile(splitk_tile_index(blockIdx.x, b, gridDim.x), TM / TN, ti, tj);
+    const int m0 = ti * TM, n0 = tj * TN;
+    if (m0 >= n || n0 >= n) return;
+    {
+        SK sk;
+        sk.clear();
+        const double* Z = pr.Z + (long long)b * pr.sZ;
+        sk.run(Z + m0 + part * n, Z + n0, pr.ldz, pr.ncol);
+        if (part) sk.template run<true>(Z + m0, Z + n0 + n, pr.ldz, pr.ncol);
+        else sk.run(Z + m0 + n, Z + n0 + n, pr.ldz, pr.ncol);
+        sk.reduce(cs);
     }
-    // row m, column k of [U_r, -U_i; U_i, U_r]
-    __device__ double zf(const GemmTile& t, int m, int k) const {
-        const double* Zb = Z + (long long)t.batch * sZ;
-        if (k < ncol) return Zb[m + (long long)k * ldz];
-        const long long o = (long long)(k - ncol) * ldz;
-        return m < n ? -Zb[m + n + o] : Zb[m - n + o];
+    const int off = sd->atom_off;
+    double* Qb = Q.at(b);
+    float* Qf = Q32.p ? Q32.at(b) : nullptr;
+    const long long ld = Q.ld;
+    auto put = [&](long long at, double v) {
+        Qb[at] = v;
+        if (Qf) Qf[at] = (float)v;
+    };
+    const double sg = part ? -1.0 : 1.0;
+    for (int x = threadIdx.x; x < TM * TN; x += SK::NT) {
+        const int r = x % TM, cl = x / TM, row = m0 + r, col = n0 + cl;
+        if (row >= n || col >= n || col > row) continue;
+        const double s = cs[cl * LDC + r] + cs[(TN + cl) * LDC + r];
+        double v = Qb[row + part * n + col * ld] + (cc ? cc[off + row / 3] * cc[off + col / 3] : 1.0) * s;
+        if (part && row == col) v = 0.0;  // the diagonal of Im
+        put(row + part * n + col * ld, v);
+        put(row + (1 - part) * n + (n + col) * ld, sg * v);
+        cs[cl * LDC + r] = v;
     }
-    __device__ double a(const GemmTile& t, int m, int k) const { return (m < 2 * n && k < t.K) ? zf(t, m, k) : 0.0; }
-    __device__ double b(const GemmTile& t, int k, int c) const { return (c < n && k < t.K) ? zf(t, c, k) : 0.0; }
-    __device__ void store(const GemmTile& t, int m, int c, double v) const {
-        if (m >= 2 * n || c >= n) return;
-        const bool top = m < n;
-        const int off = sd->atom_off;
-        const int i = (top ? m : m - n) / 3, j = c / 3;
-        double* Qb = Q.at(t.batch);
-        const long long ld = Q.ld;
-        const double val = Qb[m + (long long)c * ld] + (cc ? cc[off + i] * cc[off + j] : 1.0) * v;
-        const int mm = top ? m + n : m - n;
-        const double mv = top ? val : -val;
-        Qb[m + (long long)c * ld] = val;
-        Qb[mm + (long long)(c + n) * ld] = mv;
-        if (Q32.p) {
-            float* Qf = Q32.at(t.batch);
-            Qf[m + (long long)c * Q32.ld] = (float)val;
-            Qf[mm + (long long)(c + n) * Q32.ld] = (float)mv;
-        }
+    __syncthreads();
+    for (int x = threadIdx.x; x < TM * TN; x += SK::NT) {
+        const int cl = x % TN, r = x / TN, row = m0 + r, col = n0 + cl;
+        if (row >= n || col >= row) continue;
+        const double v = cs[cl * LDC + r];
+        put(col + part * n + row * ld, sg * v);
+        put(col + (1 - part) * n + (n + row) * ld, v);
     }
-};
+}
 
 // Adjoint contraction.  With M(q) = Q(q)^{-1/2} read from the embedded
 // inverse square root (Re in the top-left block, Im in the bottom-left), the
@@ -345,13 +367,14 @@ struct PerRecAsmProb {
 //                                      (1/2) omega_i Re Tr M_ii(q) per q)
 //   to dE/dRv_i, dE/dRv_j              X = beta dT_ij(q)/dR0 (damping radius
 //                                      R0 = beta (Rv_i + Rv_j))
-// Partial results per (q, i, j) of the real-space and self terms: {P, dR[3],
-// dA[9], P0}; the reciprocal-space term is contracted through U below.
+// Partial results per (q, pair i <= j) of the real-space and self terms: {P,
+// dR[3], dA[9], P0} of (i, j), which (j, i) repeats (dR negated); the reciprocal-space term is contracted through U below.
 // Same layout as the assembly: slots of one lane per q-point, each real-space
 // image term (F and its derivatives) formed once into LDS and added by every
 // lane of its slot with its own phase and M(q).  Two
 // wavefronts per SIMD (at most 256 registers, a few spilled: 587 -> 519 us
-// for the 64-atom cell's 64 q against one wavefront at 268 registers).
+// for the 64-atom cell's 64 q against one wavefront at 268 registers; 290 us
+// with the pairs i <= j only).
 template <int W>
 __global__ __launch_bounds__(PER_LANES * W, 2) void mbd_grad_periodic_kernel(const SysDesc* sd, const double* om,
                                                                       const double* cc, const double* qcart, int nq,
@@ -364,13 +387,14 @@ __global__ __launch_bounds__(PER_LANES * W, 2) void mbd_grad_periodic_kernel(con
     const int N = S.N, n = 3 * N;
     const int slot = threadIdx.x / lpp, ql = threadIdx.x % lpp, sub = slot % spp;
     const long long pid0 = (long long)blockIdx.x * (PER_LANES * W / lpp / spp) + slot / spp;
-    const bool pv = pid0 < (long long)N * N;
+    const bool pv = pid0 < (long long)N * (N + 1) / 2;
     const long long pid = pv ? pid0 : 0;
     const int q0 = blockIdx.y * lpp + ql;
     const bool qv_ok = pv && q0 < nq;
     const int q = q0 < nq ? q0 : 0;
-    const int i = (int)(pid % N), j = (int)(pid / N);
-    double* out = part + ((long long)q * N * N + pid) * PER_PART;
+    int i, j;
+    per_pair(pid, i, j);
+    double* out = part + ((long long)q * N * (N + 1) / 2 + pid) * PER_PART;
     if (S.N == 0) return;
     const double* R = S.coords;
     const double r[3] = {R[3 * j] - R[3 * i], R[3 * j + 1] - R[3 * i + 1], R[3 * j + 2] - R[3 * i + 2]};
@@ -563,7 +587,7 @@ __global__ __launch_bounds__(64) void per_recip_grad_kernel(const SysDesc* sd, c
 
 // Per-atom reduction in a fixed order: the pair partials (k as either atom)
 // over all q, the reciprocal partials of every (q, chunk), and the lattice
-// partials of the pairs with k as second atom, to latpart[k].
+// partials of the pairs of k, to latpart[k].
 __global__ __launch_bounds__(256) void mbd_grad_periodic_reduce_kernel(const SysDesc* sd, int nq, const double* qmult,
                                                                          double wq, const double* om,
                                                                          const double* cc, const double* part,
@@ -576,21 +600,24 @@ __global__ __launch_bounds__(256) void mbd_grad_periodic_reduce_kernel(const Sys
     const int k = blockIdx.x;
     double g0 = 0, g1 = 0, g2 = 0, ga = 0, gv = 0, tr = 0, la[9];
     for (int v = 0; v < 9; v++) la[v] = 0.0;
-    const long long NN = (long long)N * N;
+    const long long NP = (long long)N * (N + 1) / 2;
     for (long long idx = threadIdx.x; idx < (long long)nq * N; idx += 256) {
         const int q = (int)(idx / N), o = (int)(idx % N);
-        // k as j (second index), partner i = o
-        const double* pj = part + ((long long)q * NN + (long long)k * N + o) * PER_PART;   // pid = i + j*N: i=o, j=k
-        const double* pi = part + ((long long)q * NN + (long long)o * N + k) * PER_PART;   // i=k, j=o
+        // the pair of k and o, i <= j; both orders contribute the same to dR_k
+        // (with the sign of k's place), P and P0, and to dA
+        const int i = min(o, k), j = max(o, k);
+        const double* pp = part + ((long long)q * NP + (long long)j * (j + 1) / 2 + i) * PER_PART;
         const double cj = qmult[q] * cc[S.atom_off + o] * cc[S.atom_off + k];
         if (o != k) {
-            g0 += cj * (pj[1] - pi[1]);
-            g1 += cj * (pj[2] - pi[2]);
-            g2 += cj * (pj[3] - pi[3]);
+            const double sg = k == j ? 2.0 * cj : -2.0 * cj;
+            g0 += sg * pp[1];
+            g1 += sg * pp[2];
+            g2 += sg * pp[3];
         }
-        ga += cj * (pj[0] + pi[0]);
-        gv += cj * (pj[13] + pi[13]);
-        for (int v = 0; v < 9; v++) la[v] += cj * pj[4 + v];
+        ga += 2.0 * cj * pp[0];
+        gv += 2.0 * cj * pp[13];
+        // each pair once over its two orders: half of it at either atom
+        for (int v = 0; v < 9; v++) la[v] += cj * pp[4 + v];
     }
     for (long long idx = threadIdx.x; idx < (long long)nq * nchunk; idx += 256) {
         const double w = qmult[idx / nchunk];
@@ -699,7 +726,7 @@ void per_recip_basis_launch(hipStream_t st, const SysDesc* sd, const double* qca
 void mbd_assemble_periodic_launch(hipStream_t st, const SysDesc* sd, const double* om, const double* cc,
                                   const double* qcart, int nq, const int* img, int nimg, const PerEwald& pr,
                                   MatBatch<double> Q, MatBatch<float> Q32, unsigned* status, int N) {
-    const long long pairs = (long long)N * N;
+    const long long pairs = per_pairs(N);
     const int lpp = per_lanes_per_pair(nq);
     int wv, spp;
     per_split(pairs, nq, lpp, nimg, wv, spp);
@@ -712,13 +739,8 @@ void mbd_assemble_periodic_launch(hipStream_t st, const SysDesc* sd, const doubl
     else go(mbd_assemble_periodic_kernel<4>);
     // always launched: besides the reciprocal term, the epilogue fills the
     // right block column and the FP32 copy
-    PerRecAsmProb p;
-    p.sd = sd; p.cc = cc; p.Z = pr.Z; p.ldz = pr.ldz; p.sZ = pr.sZ; p.ncol = pr.ncol; p.n = 3 * N;
-    p.Q = Q; p.Q32 = Q32;
-    p.tiles_m = (6 * N + GEMM_BM - 1) / GEMM_BM;
-    p.tiles_n = (3 * N + GEMM_BN - 1) / GEMM_BN;
-    hipLaunchKernelGGL((gemm_mfma_kernel<double, PerRecAsmProb>), dim3(p.tiles_m * p.tiles_n, 1, nq), dim3(256), 0,
-                       st, p);
+    hipLaunchKernelGGL((per_recip_asm_kernel<2, 2, 2, 4>), dim3(splitk_lower_tiles(3 * N, 32, 32), 2, nq), dim3(128), 0, st,
+                       sd, cc, pr, 3 * N, Q, Q32);
 }
 
 int per_recip_chunks(int ncol) { return (ncol + PER_RCOLS - 1) / PER_RCOLS; }
@@ -727,7 +749,7 @@ void mbd_grad_periodic_launch(hipStream_t st, const SysDesc* sd, const double* o
                               const double* qcart, const double* qmult, double wq, int nq, const int* img,
                               int nimg, const PerEwald& pr, MatBatch<double> M, double* partial, double* rq,
                               double* rl, double* latpart, int N) {
-    const long long pairs = (long long)N * N;
+    const long long pairs = per_pairs(N);
     const int lpp = per_lanes_per_pair(nq);
     int wv, spp;
     per_split(pairs, nq, lpp, nimg, wv, spp);

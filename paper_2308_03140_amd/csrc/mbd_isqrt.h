@@ -31,6 +31,7 @@ const IsqTable& isq_table();
 
 struct IsqOp {
     signed char a, b, e1, e2, out, out2;
+    signed char full;  // the last product: an embedding is written whole
     double c[4], d[4];
 };
 struct IsqBufs {
@@ -50,6 +51,7 @@ struct IsqLanczos {
 };
 struct IsqWork {
     const int* ns;
+    bool embed;     // real embeddings of Hermitian matrices (order even)
     IsqBufs bufs;
     IsqLanczos lan;
     IsqOp* ops;     // [nmat][ISQ_OPMAX]

@@ -85,7 +85,7 @@ template <typename T>
 void fill_sym_random_launch(hipStream_t st, int n, T* A, int ld, unsigned seed);
 
 // periodic (Ewald) assembly and adjoint; the adjoint keeps PER_PART doubles
-// per (q, i, j): {P, dR[3], dA[9], P0} of the real-space and self terms
+// per (q, pair i <= j): {P, dR[3], dA[9], P0} of the real-space and self terms
 #define PER_PART 14
 // Work of the Ewald sums.  Reciprocal-space term as a product of the basis
 // U(q) (one column per reciprocal vector G with 0 < |G + q| < kc, embedded

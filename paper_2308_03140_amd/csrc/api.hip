@@ -1173,7 +1173,12 @@ mbd_status mbd_freq_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, in
     if ((long long)n_freq * nq > MBD_MAX_BATCH)
         return fail(c, MBD_ERR_UNSUPPORTED, "mbd_freq_evaluate", "at most 65535 matrices (frequencies x q points)");
     const int nmat = n_freq * nq;
-    const int nmax = periodic ? 6 * N : 3 * N;
+    // periodic matrices of up to hetrd_fits' order are reduced as Hermitian
+    // ones of order 3 N straight from T(q); larger ones through their real
+    // embedding of order 6 N, like the real finite ones from memory
+    const bool herm = periodic && hetrd_fits(3 * N);
+    const int nmax = periodic ? 6 * N : 3 * N;  // order of the assembled matrices
+    const int neig = herm ? 3 * N : nmax;       // eigenvalues per matrix
     const int ld = round_up(nmax, 64);
     const long long stride = (long long)ld * nmax;
     // the frequency grid: Gauss-Legendre on [-1, 1], u = 0.6 (1+x)/(1-x)
@@ -1193,7 +1198,7 @@ mbd_status mbd_freq_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, in
         sds[f].nmat = nq;
         sds[f].embed = periodic ? 1 : 0;
     }
-    std::vector<int> nsh(nmat, nmax);
+    std::vector<int> nsh(nmat, neig);
     SysDesc* sd_dev = (SysDesc*)ws(c, "freq_desc", sizeof(SysDesc) * (n_freq + 1));
     int* ns_dev = wsT<int>(c, "freq_ns", nmat);
     unsigned* status = wsT<unsigned>(c, "freq_status", n_freq + 1);
@@ -1203,11 +1208,22 @@ mbd_status mbd_freq_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, in
     double* cc_f = wsT<double>(c, "freq_cc", (size_t)n_freq * N);
     double* u_dev = wsT<double>(c, "freq_u", n_freq);
     double* wf_dev = wsT<double>(c, "freq_w", n_freq);
-    double* lam = wsT<double>(c, "freq_lam", (size_t)nmax * nmat);
+    double* lam = wsT<double>(c, "freq_lam", (size_t)neig * nmat);
     double* part = wsT<double>(c, "freq_part", (size_t)nmat * (3 + n_order));
-    MatBatch<double> K = {wsT<double>(c, "A64", (size_t)stride * nmat), ld, stride};
-    if (!sd_dev || !ns_dev || !status || !om0 || !cc0 || !om_f || !cc_f || !u_dev || !wf_dev || !lam || !part || !K.p)
+    if (!sd_dev || !ns_dev || !status || !om0 || !cc0 || !om_f || !cc_f || !u_dev || !wf_dev || !lam || !part)
         return (mbd_status)c->err_code;
+    MatBatch<double> K = {nullptr, ld, stride};
+    double *hd = nullptr, *he = nullptr;
+    int* hbad = nullptr;
+    if (herm) {
+        hd = wsT<double>(c, "freq_d", (size_t)neig * nmat);
+        he = wsT<double>(c, "freq_e", (size_t)neig * nmat);
+        hbad = wsT<int>(c, "eig_bad", (size_t)nmat);
+        if (!hd || !he || !hbad) return (mbd_status)c->err_code;
+    } else {
+        K.p = wsT<double>(c, "A64", (size_t)stride * nmat);
+        if (!K.p) return (mbd_status)c->err_code;
+    }
     HIPCHK(hipMemcpyAsync(sd_dev, sds.data(), sizeof(SysDesc) * (n_freq + 1), hipMemcpyHostToDevice, st), "upload");
     HIPCHK(hipMemcpyAsync(ns_dev, nsh.data(), sizeof(int) * nmat, hipMemcpyHostToDevice, st), "upload");
     HIPCHK(hipMemcpyAsync(u_dev, u.data(), sizeof(double) * n_freq, hipMemcpyHostToDevice, st), "upload");
@@ -1233,15 +1249,26 @@ mbd_status mbd_freq_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, in
         per_recip_basis_launch(st, sd_dev + 1, qcart, nq, img, (int)ps.img.size() / 3, prc);
         mbd_assemble_periodic_launch(st, sd_dev + 1, nullptr, nullptr, qcart, nq, img, (int)ps.img.size() / 3, prc, Tq,
                                      MatBatch<float>{nullptr, ld, stride}, status + 1, N);
-        mbd_freq_scale_launch(st, cc_f, N, n_freq, nq, Tq, K);
+        if (herm) {
+            PhaseTimer ph(&c->prof, st, 3);
+            hetrd_launch(st, Tq, cc_f, N, n_freq, nq, hd, he, neig);
+        } else {
+            mbd_freq_scale_launch(st, cc_f, N, n_freq, nq, Tq, K);
+        }
     } else {
         mbd_assemble_finite_launch(st, sd_dev + 1, n_freq, N, om_f, cc_f, K, MatBatch<float>{nullptr, ld, stride},
                                    status + 1);
     }
     HIPCHK(hipGetLastError(), "freq assemble");
-    r = run_eig<double>(c, K, ns_dev, nsh.data(), nmax, nmat, false, lam, nmax, nullptr, nullptr, periodic);
-    if (r != MBD_OK) return r;
-    mbd_freq_terms_launch(st, ns_dev, nmat, lam, nmax, n_order, part, wf_dev, n_freq, nq, periodic ? 1 : 0, terms);
+    if (herm) {
+        tridiag_guard_launch<double>(ns_dev, nmat, hd, he, neig, hbad, st);
+        PhaseTimer ph(&c->prof, st, 4);
+        stebz_launch<double>(ns_dev, neig, nmat, hd, he, neig, lam, neig, st, false);
+    } else {
+        r = run_eig<double>(c, K, ns_dev, nsh.data(), nmax, nmat, false, lam, nmax, nullptr, nullptr, periodic);
+        if (r != MBD_OK) return r;
+    }
+    mbd_freq_terms_launch(st, ns_dev, nmat, lam, neig, n_order, part, wf_dev, n_freq, nq, periodic && !herm ? 1 : 0, terms);
     HIPCHK(hipGetLastError(), "freq terms");
     std::vector<unsigned> sth(n_freq + 1);
     HIPCHK(hipMemcpyAsync(sth.data(), status, sizeof(unsigned) * (n_freq + 1), hipMemcpyDeviceToHost, st), "status");

@@ -9,8 +9,9 @@
 // K(u) is assembled by the MBD assembly kernels with omega -> 0 on the
 // diagonal and c_i -> alpha_i(iu)^{1/2} (periodic: the lattice sums T(q) once,
 // then scaled per frequency); every (u, q) matrix is one member of a batch
-// for the eigenvalue-only solver.  Periodic matrices are real
-// embeddings of order 2n, so each x_k appears twice and carries half weight.
+// for the eigenvalue-only solver.  Periodic matrices of n <= 192 are reduced
+// as Hermitian ones of order n; larger ones as real embeddings of order 2n, so
+// each x_k appears twice and carries half weight.
 #include "mbd_internal.h"
 #include "mbd_kernels.h"
 #include "mbd_sys.h"

@@ -134,6 +134,12 @@ void mbd_ts_launch(hipStream_t st, const SysDesc* sd, int N, const double* om, c
 // weighted terms {E, E_Gould, min(1+x), E^(1..norder)}
 void mbd_freq_coeff_launch(hipStream_t st, const SysDesc* sd, const double* om0, const double* u, int nfreq, int N,
                            double* om_f, double* cc_f);
+// Householder reduction of the Hermitian C_f T(q) C_f (order 3 N) straight
+// from the lattice sums T(q): d, e of matrix f nq + q at stride sD; orders
+// beyond hetrd_fits take mbd_freq_scale_launch and the general reduction
+bool hetrd_fits(int n);
+void hetrd_launch(hipStream_t st, MatBatch<double> T, const double* cc_f, int N, int nfreq, int nq, double* d, double* e,
+                  long long sD);
 // periodic K(u_f, q) = C_f T(q) C_f for every frequency f and q (T: the
 // embedded lattice sums, as the periodic assembly writes them without c, omega)
 void mbd_freq_scale_launch(hipStream_t st, const double* cc_f, int N, int nfreq, int nq, MatBatch<double> T,

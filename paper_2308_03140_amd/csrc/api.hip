@@ -222,6 +222,19 @@ mbd_status make_sytrd_ws(mbd_ctx* c, MatBatch<T> A, const int* ns, int nmax, int
     return MBD_OK;
 }
 
+// Eigenvalues of the tridiagonals d, e by Sturm-count multisection.
+template <typename T>
+mbd_status run_stebz(mbd_ctx* c, const int* ns, int nmax, int nbatch, const T* d, const T* e, long long sD, T* w,
+                     long long sW, bool pairs) {
+    double2* pe = wsT<double2>(c, "stebz_p", (size_t)stebz_rows(nmax) * nbatch);
+    double* info = wsT<double>(c, "stebz_i", (size_t)3 * nbatch);
+    if (!pe || !info) return (mbd_status)c->err_code;
+    PhaseTimer ph(&c->prof, c->stream, 4);
+    stebz_launch<T>(ns, nmax, nbatch, d, e, sD, pe, info, w, sW, c->stream, pairs);
+    HIPCHK(hipGetLastError(), "stebz");
+    return MBD_OK;
+}
+
 // Full dense symmetric eigensolver on a batch: reduction, D&C, back-transform.
 template <typename T>
 mbd_status run_eig(mbd_ctx* c, MatBatch<T> A, const int* ns, const int* ns_host, int nmax, int nbatch, bool vectors,
@@ -252,9 +265,8 @@ mbd_status run_eig(mbd_ctx* c, MatBatch<T> A, const int* ns, const int* ns_host,
     if (bad_out) *bad_out = bad;
     if (!vectors) {
         // eigenvalues only: Sturm-count multisection on the tridiagonal
-        PhaseTimer ph(&c->prof, st, 4);
-        stebz_launch<T>(ns, nmax, nbatch, sw.d, sw.e, sw.sD, w_out, sW, st, embed_pairs);
-        HIPCHK(hipGetLastError(), "stebz");
+        if (run_stebz<T>(c, ns, nmax, nbatch, sw.d, sw.e, sw.sD, w_out, sW, embed_pairs) != MBD_OK)
+            return (mbd_status)c->err_code;
         if (Xout) *Xout = MatBatch<T>{nullptr, 0, 0};
         return MBD_OK;
     }
@@ -1262,12 +1274,11 @@ mbd_status mbd_freq_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, in
     HIPCHK(hipGetLastError(), "freq assemble");
     if (herm) {
         tridiag_guard_launch<double>(ns_dev, nmat, hd, he, neig, hbad, st);
-        PhaseTimer ph(&c->prof, st, 4);
-        stebz_launch<double>(ns_dev, neig, nmat, hd, he, neig, lam, neig, st, false);
+        r = run_stebz<double>(c, ns_dev, neig, nmat, hd, he, neig, lam, neig, false);
     } else {
         r = run_eig<double>(c, K, ns_dev, nsh.data(), nmax, nmat, false, lam, nmax, nullptr, nullptr, periodic);
-        if (r != MBD_OK) return r;
     }
+    if (r != MBD_OK) return r;
     mbd_freq_terms_launch(st, ns_dev, nmat, lam, neig, n_order, part, wf_dev, n_freq, nq, periodic && !herm ? 1 : 0, terms);
     HIPCHK(hipGetLastError(), "freq terms");
     std::vector<unsigned> sth(n_freq + 1);

@@ -99,29 +99,29 @@ __global__ __launch_bounds__(256) void mbd_freq_terms_kernel(const int* ns, cons
 }
 
 // terms = sum over (f, q) of w_f / nq (x 1/2 for embedded matrices) times the
-// per-matrix sums, in a fixed order; min(1 + x) over all matrices
-__global__ __launch_bounds__(64) void mbd_freq_sum_kernel(const double* part, const double* wf, int nfreq, int nq,
-                                                            int embed, int norder, double* terms) {
-    const int t = threadIdx.x;
+// per-matrix sums, in a fixed order; min(1 + x) over all matrices.  A
+// wavefront per term, its lanes over the matrices: one lane per term took 188
+// us of dependent loads for 960 matrices.
+__global__ __launch_bounds__(1024) void mbd_freq_sum_kernel(const double* part, const double* wf, int nfreq, int nq,
+                                                              int embed, int norder, double* terms) {
+    const int lane = threadIdx.x & 63;
     const int nt = 3 + norder;
-    if (t >= nt) return;
-    const double h = embed ? 0.5 : 1.0;
-    double acc = t == 2 ? 1e300 : 0.0;
-    for (int f = 0; f < nfreq; f++)
-        for (int q = 0; q < nq; q++) {
-            const double v = part[((long long)f * nq + q) * nt + t];
-            if (t == 2) {
-                acc = fmin(acc, v);
-            } else {
-                double c = wf[f] / nq * h;
-                if (t >= 3) {
-                    const int o = t - 2;  // order n
-                    c *= ((o & 1) ? 1.0 : -1.0) / o;
-                }
-                acc += c * v;
-            }
+    for (int t = threadIdx.x >> 6; t < nt; t += 16) {
+        double acc = t == 2 ? -1e300 : 0.0;
+        for (int m = lane; m < nfreq * nq; m += 64) {
+            const double v = part[(long long)m * nt + t];
+            if (t == 2) acc = fmax(acc, -v);
+            else acc += wf[m / nq] * v;
         }
-    terms[t] = acc;
+        if (t == 2) {
+            acc = -wave_max(acc);
+        } else {
+            const int o = t - 2;  // order n of the many-body terms
+            acc = wave_sum(acc) / nq * (embed ? 0.5 : 1.0);
+            if (t >= 3) acc *= ((o & 1) ? 1.0 : -1.0) / o;
+        }
+        if (lane == 0) terms[t] = acc;
+    }
 }
 
 void mbd_freq_coeff_launch(hipStream_t st, const SysDesc* sd, const double* om0, const double* u, int nfreq, int N,
@@ -140,5 +140,5 @@ void mbd_freq_scale_launch(hipStream_t st, const double* cc_f, int N, int nfreq,
 void mbd_freq_terms_launch(hipStream_t st, const int* ns, int nmat, const double* lam, long long sL, int norder,
                            double* part, const double* wf, int nfreq, int nq, int embed, double* terms) {
     hipLaunchKernelGGL(mbd_freq_terms_kernel, dim3(nmat), dim3(256), 0, st, ns, lam, sL, norder, part);
-    hipLaunchKernelGGL(mbd_freq_sum_kernel, dim3(1), dim3(64), 0, st, part, wf, nfreq, nq, embed, norder, terms);
+    hipLaunchKernelGGL(mbd_freq_sum_kernel, dim3(1), dim3(1024), 0, st, part, wf, nfreq, nq, embed, norder, terms);
 }

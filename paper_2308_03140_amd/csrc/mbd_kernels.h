@@ -176,10 +176,12 @@ void tridiag_guard_launch(const int* ns, int nbatch, T* d, T* e, long long sD, i
 // Eigenvalues only (Sturm counts with multisection, FP64 arithmetic): d, e of
 // the reduction ([nbatch] x sD), w [nbatch] x sW ascending.  pairs: the
 // matrices are real embeddings of Hermitian ones (every eigenvalue twice),
-// and each pair is found once.
+// and each pair is found once.  pe ([nbatch] x stebz_rows(nmax)) and info
+// ([nbatch] x 3) are scratch.
+long long stebz_rows(int nmax);
 template <typename T>
-void stebz_launch(const int* ns, int nmax, int nbatch, const T* d, const T* e, long long sD, T* w, long long sW,
-                  hipStream_t st, bool pairs = false);
+void stebz_launch(const int* ns, int nmax, int nbatch, const T* d, const T* e, long long sD, double2* pe, double* info,
+                  T* w, long long sW, hipStream_t st, bool pairs = false);
 
 // --- Back-transformation ---------------------------------------------------
 template <typename T>

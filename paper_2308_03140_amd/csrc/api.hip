@@ -1096,20 +1096,24 @@ mbd_status mbd_ts_evaluate(mbd_ctx* c, const mbd_system* s, unsigned want, mbd_r
         if (r != MBD_OK) return r;
     }
     const int N = s->n_atoms;
-    SysDesc* sd_dev = (SysDesc*)ws(c, "sysdesc", sizeof(SysDesc));
-    unsigned* status = wsT<unsigned>(c, "status", 1);
+    // the descriptor and its zeroed status word go up in one copy
+    struct {
+        SysDesc d;
+        unsigned status;
+    } up = {d, 0u};
+    SysDesc* sd_dev = (SysDesc*)ws(c, "sysdesc", sizeof(up));
+    unsigned* status = (unsigned*)(sd_dev + 1);
     double* om = wsT<double>(c, "om", N);
     double* cc = wsT<double>(c, "cc", N);
     double* eatom = wsT<double>(c, "ts_eatom", N);
     int* img = wsT<int>(c, "img", std::max<size_t>(3, ps.img.size()));
     int* rec = wsT<int>(c, "rec", std::max<size_t>(3, ps.rec.size()));
-    if (!sd_dev || !status || !om || !cc || !eatom || !img || !rec) return (mbd_status)c->err_code;
-    HIPCHK(hipMemcpyAsync(sd_dev, &d, sizeof(SysDesc), hipMemcpyHostToDevice, st), "upload");
+    if (!sd_dev || !om || !cc || !eatom || !img || !rec) return (mbd_status)c->err_code;
+    HIPCHK(hipMemcpyAsync(sd_dev, &up, sizeof(up), hipMemcpyHostToDevice, st), "upload");
     if (periodic) {
         HIPCHK(hipMemcpyAsync(img, ps.img.data(), sizeof(int) * ps.img.size(), hipMemcpyHostToDevice, st), "upload");
         HIPCHK(hipMemcpyAsync(rec, ps.rec.data(), sizeof(int) * ps.rec.size(), hipMemcpyHostToDevice, st), "upload");
     }
-    fill_u32_launch(st, status, 1, 0u);
     mbd_prep_launch(st, sd_dev, 1, N, om, cc, status);
     mbd_ts_launch(st, sd_dev, N, om, img, (int)ps.img.size() / 3, rec, (int)ps.rec.size() / 3, periodic ? 1 : 0,
                   eatom, status, &c->prof);

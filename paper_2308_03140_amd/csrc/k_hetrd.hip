@@ -55,18 +55,6 @@ __device__ __forceinline__ void cfms_conj(Cx& a, Cx x, Cx y) {
     a.im = fma(-x.im, y.re, a.im);
 }
 
-// Eight sums at once over the wavefront: lane l gets the sum of v[l >> 3].
-__device__ __forceinline__ double wave_sum8(const double (&v)[8]) {
-    double u[4], w[2];
-#pragma unroll
-    for (int i = 0; i < 4; i++) u[i] = pair_sum_b5(v[i], v[i + 4]);
-#pragma unroll
-    for (int i = 0; i < 2; i++) w[i] = pair_sum_b4(u[i], u[i + 2]);
-    double z = pair_sum_b3(w[0], w[1]);
-    z += dpp<DPP_HALF_MIRROR>(z);
-    return quad_sum(z);
-}
-
 // Element (t, g) held in LDS instead of registers: the first columns' last rows, finished before the others.
 template <int G>
 __device__ constexpr bool hetrd_in_lds(int t, int g) {

@@ -160,6 +160,43 @@ __device__ __forceinline__ T wave_sum16(const T (&v)[16]) {
     return quad_sum(pair_sum_b2(z0, z1));
 }
 
+// Eight sums at once: returns in lane l the sum over the wave of v[l >> 3].
+template <typename T>
+__device__ __forceinline__ T wave_sum8(const T (&v)[8]) {
+    T u[4], w[2];
+#pragma unroll
+    for (int i = 0; i < 4; i++) u[i] = pair_sum_b5(v[i], v[i + 4]);
+#pragma unroll
+    for (int i = 0; i < 2; i++) w[i] = pair_sum_b4(u[i], u[i + 2]);
+    T z = pair_sum_b3(w[0], w[1]);
+    z += dpp<DPP_HALF_MIRROR>(z);
+    return quad_sum(z);
+}
+
+// 1/x to the last bit or two for normal x with a normal reciprocal: the
+// hardware estimate and two Newton steps (the division's scaling and fix-up
+// for the ends of the range left out)
+__device__ __forceinline__ double recip(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+// s = sqrt(x), r = 1/sqrt(x) likewise: Goldschmidt steps on both from the
+// hardware estimate, then one correction of each by its residual
+__device__ __forceinline__ void sqrt_recip(double x, double& s, double& r) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    e = fma(-h, g, 0.5);
+    h = fma(h, e, h);
+    g = fma(g, e, g);
+    s = fma(fma(-g, g, x), h, g);
+    r = 2.0 * h;
+    r = fma(fma(-s, r, 1.0), r, r);
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
 #pragma unroll

@@ -32,23 +32,28 @@ struct SplitK {
     // acc += (NEG: -=) sum over K columns of A(m0 .., k) B(n0 .., k); A, B at their row offsets
     template <bool NEG = false>
     __device__ __forceinline__ void run(const double* A, const double* B, int ld, int K) {
+        run<NEG>(A, ld, B, ld, K);
+    }
+    template <bool NEG = false>
+    __device__ __forceinline__ void run(const double* A, int lda, const double* B, int ldb, int K) {
         constexpr int G = 4 * U;  // k of one group; groups go round robin over the wavefronts
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const unsigned off = (unsigned)((lane >> 4) * ld + 2 * (lane & 15)) * 8u;
+        const unsigned offa = (unsigned)((lane >> 4) * lda + 2 * (lane & 15)) * 8u;
+        const unsigned offb = (unsigned)((lane >> 4) * ldb + 2 * (lane & 15)) * 8u;
         auto gload = [&](int k0, auto& xa, auto& xb) {
             const int kn = max(0, min(G, K - k0));
-            const auto dA = make_rsrc(A + (long long)k0 * ld, (unsigned)kn * ld * 8u);
-            const auto dB = make_rsrc(B + (long long)k0 * ld, (unsigned)kn * ld * 8u);
+            const auto dA = make_rsrc(A + (long long)k0 * lda, (unsigned)kn * lda * 8u);
+            const auto dB = make_rsrc(B + (long long)k0 * ldb, (unsigned)kn * ldb * 8u);
 #pragma unroll
             for (int u = 0; u < U; u++) {
 #pragma unroll
                 for (int i = 0; i < MI / 2; i++)
                     xa[u][i] = __builtin_bit_cast(splitk_d2,
-                                                  __builtin_amdgcn_raw_buffer_load_b128(dA, off + 256u * i, 32 * u * ld, 0));
+                                                  __builtin_amdgcn_raw_buffer_load_b128(dA, offa + 256u * i, 32 * u * lda, 0));
 #pragma unroll
                 for (int j = 0; j < NJ / 2; j++)
                     xb[u][j] = __builtin_bit_cast(splitk_d2,
-                                                  __builtin_amdgcn_raw_buffer_load_b128(dB, off + 256u * j, 32 * u * ld, 0));
+                                                  __builtin_amdgcn_raw_buffer_load_b128(dB, offb + 256u * j, 32 * u * ldb, 0));
             }
         };
         auto mult = [&](auto& xa, auto& xb) {

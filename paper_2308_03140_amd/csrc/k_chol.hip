@@ -6,20 +6,20 @@
 // two three-column solves replace the inverse.  A non-positive pivot (A not
 // positive definite: the screening collapses) sets MBD_ST_COLLAPSE.
 //
-// Right-looking, panels of CHOL_NB = 64 columns:
-//   diagonal block   one workgroup per matrix factors the 64 x 64 block in
-//                    LDS and inverts its factor, L11^-1, kept for the
-//                    panel solve and the triangular solves;
-//   panel            L21 = A21 L11^-T as a matrix-core product, in place;
-//   trailing update  A22 -= L21 L21^T on the lower tiles (matrix cores),
-//                    once per superpanel of two panels (K = 128).
+// Left-looking, panels of CHOL_NB = 64 columns:
+//   update           A(k0.., k0..k0+63) -= L(k0.., 0..k0-1) L(k0..k0+63, 0..k0-1)^T,
+//                    one long product per panel (matrix cores, K split over
+//                    the wavefronts): each element is read and written once
+//                    per factorisation instead of once per panel;
+//   diagonal block   one workgroup per matrix factors the 64 x 64 block and
+//                    inverts its factor, L11^-1, kept for the panel solve and
+//                    the triangular solves;
+//   panel            L21 = A21 L11^-T as a matrix-core product, in place.
 // The triangular solves go block row by block row, one launch per block:
 // every workgroup forms the block's solution from the (final) residual and
 // L11^-1, the first stores it, the others update the residual of their own
 // block row.
-#include <algorithm>
-
-#include "gemm_mfma.h"
+#include "gemm_splitk.h"
 #include "mbd_internal.h"
 #include "mbd_kernels.h"
 #include "mbd_sys.h"
@@ -30,14 +30,21 @@
 // ---------------------------------------------------------------------------
 // diagonal block: factor, invert the factor; identity padding past n
 // ---------------------------------------------------------------------------
-// One workgroup per matrix, the block in LDS; thread (i, j0) = (tid & 63,
-// tid >> 6) works on row i and columns j0, j0 + 4, ...  (A single-wavefront
-// variant without barriers, the row in LDS, measured 171 us against 100 us.)
+// One workgroup per matrix, the block in LDS, in steps of 16 columns: one
+// wavefront factors the 16 columns with a row per lane (pivot and row factors
+// by lane reads, no barrier), then four update the rest on the matrix cores.
+// The inverse: the 16 x 16 diagonal blocks by substitution, one per wavefront,
+// then the blocks below by distance from the diagonal on the matrix cores.
+// Bound by the chain of 64 pivots: 21.5 us at 16 matrices, against 101 column
+// by column with three barriers a column.
+#define CHOL_SB 16
 __global__ __launch_bounds__(256) void chol_diag_kernel(MatBatch<double> A, double* Linv, long long sLi, int n,
                                                          int k0, unsigned* status) {
     __shared__ double L[CHOL_NB][CHOL_NB + 1];
     __shared__ double X[CHOL_NB][CHOL_NB + 1];
-    const int b = blockIdx.x, tid = threadIdx.x;
+    __shared__ double dinv[CHOL_NB];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int w = min(CHOL_NB, n - k0);
     double* Ab = A.at(b) + k0 + (long long)k0 * A.ld;
     const long long ld = A.ld;
@@ -55,46 +62,98 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(MatBatch<double> A, doub
         for (int u = 0; u < PER; u++) {
             const int j = j0 + 4 * u;
             L[ri][j] = (ri < w && j < w) ? (ri >= j ? v[u] : 0.0) : (ri == j ? 1.0 : 0.0);
+            X[ri][j] = 0.0;
         }
     }
     __syncthreads();
-    bool bad = false;
-    for (int j = 0; j < w; j++) {
-        const double d = L[j][j];
-        const bool nb = !(d > 0.0);
-        bad = bad || nb;
-        const double s = nb ? 1.0 : sqrt(d);
-        __syncthreads();
-        if (tid == 0) L[j][j] = s;
-        if (tid > j && tid < CHOL_NB) L[tid][j] /= s;
-        __syncthreads();
-        // trailing update L(i, l) -= L(i, j) L(l, j), j < l <= i
-        const double lij = L[ri][j];
+    // C(ib, jb) += (NEG: -=) sum_k A(ib, k) B(k, jb) over 16 nk columns, one wavefront
+    typedef mfma4<double>::v Acc;
+    auto product = [&](Acc acc, auto a, auto bm, int nk, double sign) {
+        #pragma unroll 4
+        for (int k = 0; k < CHOL_SB * nk; k += 4) {
+            const int kk = k + (lane >> 4);
+            acc = mfma16x16x4(sign * a(lane & 15, kk), bm(kk, lane & 15), acc);
+        }
+        return acc;
+    };
+#pragma unroll 1
+    for (int c0 = 0; c0 < CHOL_NB; c0 += CHOL_SB) {
+        if (wave == 0) {
+            double a[CHOL_SB];
 #pragma unroll
-        for (int u = 0; u < PER; u++) {
-            const int l = j0 + 4 * u;
-            if (l > j && ri >= l) L[ri][l] -= lij * L[l][j];
+            for (int j = 0; j < CHOL_SB; j++) a[j] = L[lane][c0 + j];
+            bool bad = false;
+#pragma unroll
+            for (int j = 0; j < CHOL_SB; j++) {
+                const double d = lane_value(a[j], c0 + j);
+                const bool nb = !(d > 0.0);
+                bad = bad || nb;
+                double s, inv;
+                sqrt_recip(nb ? 1.0 : d, s, inv);
+                if (lane == 0) dinv[c0 + j] = inv;
+                a[j] = lane == c0 + j ? s : a[j] * inv;
+#pragma unroll
+                for (int l = j + 1; l < CHOL_SB; l++) a[l] = fma(-a[j], lane_value(a[j], c0 + l), a[l]);
+                __builtin_amdgcn_sched_barrier(0);  // the lane reads of one column at a time
+            }
+            // rows above the diagonal hold no factor
+#pragma unroll
+            for (int j = 0; j < CHOL_SB; j++) L[lane][c0 + j] = lane >= c0 + j ? a[j] : 0.0;
+            if (bad && lane == 0) atomicOr(status, MBD_ST_COLLAPSE);
+        }
+        __syncthreads();
+        const int done = c0 / CHOL_SB + 1, left = CHOL_NB / CHOL_SB - done;
+        for (int t = wave; t < left * (left + 1) / 2; t += 4) {
+            int ib = 0;
+            while ((ib + 1) * (ib + 2) / 2 <= t) ib++;
+            const int r0 = (done + ib) * CHOL_SB, q0 = (done + t - ib * (ib + 1) / 2) * CHOL_SB;
+            Acc acc;
+#pragma unroll
+            for (int r = 0; r < 4; r++) acc[r] = L[r0 + mfma_rows<double>::row(lane, r)][q0 + (lane & 15)];
+            acc = product(acc, [&](int m, int k) { return L[r0 + m][c0 + k]; },
+                          [&](int k, int c) { return L[q0 + c][c0 + k]; }, 1, -1.0);
+#pragma unroll
+            for (int r = 0; r < 4; r++) L[r0 + mfma_rows<double>::row(lane, r)][q0 + (lane & 15)] = acc[r];
         }
         __syncthreads();
     }
-    if (bad && tid == 0) atomicOr(status, MBD_ST_COLLAPSE);
-    // X = L^-1 row by row: X(r, c) = -(sum_{l=c}^{r-1} L(r,l) X(l,c)) / L(r,r)
-    // for c < r; four threads per column c split the sum over l
     {
-        const int c = tid >> 2, part = tid & 3;
-        if (part == 0) {
-            for (int r = 0; r < CHOL_NB; r++) X[r][c] = r == c ? 1.0 / L[c][c] : 0.0;
+        // X(wave, wave): lane c holds column c, row after row
+        const int o = wave * CHOL_SB, c = lane & 15;
+        double x[CHOL_SB];
+#pragma unroll
+        for (int r = 0; r < CHOL_SB; r++) x[r] = r == c ? 1.0 : 0.0;
+#pragma unroll
+        for (int l = 0; l < CHOL_SB; l++) {
+            x[l] *= dinv[o + l];
+#pragma unroll
+            for (int r = l + 1; r < CHOL_SB; r++) x[r] = fma(-L[o + r][o + l], x[l], x[r]);
+        }
+        if (lane < CHOL_SB) {
+#pragma unroll
+            for (int r = 0; r < CHOL_SB; r++) X[o + r][o + c] = x[r];
+        }
+    }
+    __syncthreads();
+    // X(i, j) = -X(i, i) sum_{j <= k < i} L(i, k) X(k, j), i - j = dist
+    for (int dist = 1; dist < CHOL_NB / CHOL_SB; dist++) {
+        if (dist + wave < CHOL_NB / CHOL_SB) {
+            const int r0 = (dist + wave) * CHOL_SB, q0 = wave * CHOL_SB;
+            Acc acc = {0, 0, 0, 0};
+            acc = product(acc, [&](int m, int k) { return L[r0 + m][q0 + k]; },
+                          [&](int k, int c) { return X[q0 + k][q0 + c]; }, dist, 1.0);
+            // through the block's own place to the operand layout (one wavefront: in order)
+#pragma unroll
+            for (int r = 0; r < 4; r++) X[r0 + mfma_rows<double>::row(lane, r)][q0 + (lane & 15)] = acc[r];
+            __builtin_amdgcn_wave_barrier();
+            Acc acc2 = {0, 0, 0, 0};
+            acc2 = product(acc2, [&](int m, int k) { return X[r0 + m][r0 + k]; },
+                           [&](int k, int c) { return X[r0 + k][q0 + c]; }, 1, -1.0);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int r = 0; r < 4; r++) X[r0 + mfma_rows<double>::row(lane, r)][q0 + (lane & 15)] = acc2[r];
         }
         __syncthreads();
-        for (int r = 1; r < CHOL_NB; r++) {
-            double sacc = 0.0;
-            if (c < r)
-                for (int l = c + part; l < r; l += 4) sacc += L[r][l] * X[l][c];
-            sacc += __shfl_xor(sacc, 1, 64);
-            sacc += __shfl_xor(sacc, 2, 64);
-            if (c < r && part == 0) X[r][c] = -sacc / L[r][r];
-            __syncthreads();
-        }
     }
 #pragma unroll
     for (int u = 0; u < PER; u++) {
@@ -110,85 +169,57 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(MatBatch<double> A, doub
 }
 
 // ---------------------------------------------------------------------------
-// panel: L21 = A21 X^T (X = L11^-1), rows k0 + 64 .. n-1, in place.  A tile
+// panel: L21 = A21 X^T (X = L11^-1), rows k0 + 64 .. n-1, in place: a tile
 // spans the panel's 64 columns, so a workgroup reads only the rows it writes.
 // ---------------------------------------------------------------------------
-struct CholPanelProb {
-    static constexpr bool A_M_CONTIG = true;
-    static constexpr bool B_N_CONTIG = true;
-    MatBatch<double> A;
-    const double* Linv; long long sLi;
-    int k0, rows;  // rows = n - k0 - 64
-    __device__ bool tile(int bx, int, int bz, GemmTile& t) const {
-        t.batch = bz;
-        t.m0 = bx * CHOL_NB; t.n0 = 0; t.K = CHOL_NB;
-        return t.m0 < rows;
-    }
-    __device__ double a(const GemmTile& t, int m, int k) const {
-        if (m >= rows) return 0.0;
-        return A.at(t.batch)[(k0 + CHOL_NB + m) + (long long)(k0 + k) * A.ld];
-    }
-    __device__ double b(const GemmTile& t, int k, int c) const {
+__global__ __launch_bounds__(256) void chol_panel_kernel(MatBatch<double> A, const double* Linv, long long sLi, int n,
+                                                          int k0) {
+    typedef SplitK<2, 4, 4, 4> SK;
+    __shared__ __align__(16) double cs[SK::LDS];
+    const int b = blockIdx.y, m0 = k0 + CHOL_NB + blockIdx.x * SK::TM, tid = threadIdx.x;
+    double* Ab = A.at(b) + m0 + (long long)k0 * A.ld;
+    {
+        SK sk;
+        sk.clear();
         // X^T(k, c) = X(c, k)
-        return Linv[(long long)t.batch * sLi + (long long)(k0 / CHOL_NB) * CHOL_NB * CHOL_NB + c + k * CHOL_NB];
+        sk.run(Ab, A.ld, Linv + (long long)b * sLi + (long long)(k0 / CHOL_NB) * CHOL_NB * CHOL_NB, CHOL_NB, CHOL_NB);
+        sk.reduce(cs);
     }
-    __device__ void store(const GemmTile& t, int m, int c, double v) const {
-        if (m < rows) A.at(t.batch)[(k0 + CHOL_NB + m) + (long long)(k0 + c) * A.ld] = v;
+#pragma unroll
+    for (int x = tid; x < SK::TM * SK::TN; x += SK::NT) {
+        const int r = x % SK::TM, c = x / SK::TM;
+        if (m0 + r < n) Ab[r + (long long)c * A.ld] = cs[c * SK::LDC + r] + cs[(SK::TN + c) * SK::LDC + r];
     }
-};
+}
 
 // ---------------------------------------------------------------------------
-// trailing update: A22 -= L21 L21^T with L21 the kw columns from k0 (64 or a
-// superpanel of 128), on the elements on and below the diagonal of the
-// block from t0 = k0 + kw: all lower tiles (XCD-aware banded order), or
-// (thin) only the first ncols columns, one tile column
+// update of the panel at k0 by the k0 columns before it
 // ---------------------------------------------------------------------------
-template <int TS>
-struct CholSyrkProb {
-    static constexpr bool A_M_CONTIG = true;
-    static constexpr bool B_N_CONTIG = true;
-    // read-modify-write of the tile in 16-byte column segments (the tile is
-    // requested before the K loop); rows k0 + kw + r are even for even r, so
-    // the segments are aligned
-    static constexpr bool EPI_VEC = true;
-    typedef typename Vec16<double>::v Vec;
-    static constexpr int RPL = 2;
-    MatBatch<double> A;
-    int k0, kw, m, ncols;  // m = n - k0 - kw trailing rows
-    int tiles, thin;
-    __device__ bool tile(int bx, int, int bz, GemmTile& t) const {
-        t.batch = bz;
-        int ti, tj;
-        if (thin) { ti = bx; tj = 0; }
-        else band_lower_tile(xcd_virtual(bx, gridDim.x), tiles, ti, tj);
-        t.m0 = ti * TS; t.n0 = tj * TS; t.K = kw;
-        return t.m0 < m && t.n0 < ncols;
+// 32 x 32 tiles with K split four ways: the last panels have few rows and the
+// longest K.  Bound by the matrix cores (16 matrices of order 3000: 3.2 ms, 45
+// TFLOP/s; tiles of 64 x 32 3.7 ms, of 32 x 64 3.9, half or twice the
+// wavefronts 4.2 and 3.9; right-looking with K = 128 from LDS 4.8 ms).
+__global__ __launch_bounds__(256, 3) void chol_update_kernel(MatBatch<double> A, int n, int k0, int tiles) {
+    typedef SplitK<2, 2, 4, 6> SK;
+    constexpr int TC = CHOL_NB / SK::TN;  // tile columns of the panel
+    __shared__ __align__(16) double cs[SK::LDS];
+    // every XCD gets a run of (matrix, tile) indices: a matrix's panel rows stay in one or two L2s
+    const int v = xcd_virtual(blockIdx.x, gridDim.x), b = v / tiles, t = v % tiles, tid = threadIdx.x;
+    const int m0 = k0 + t / TC * SK::TM, n0 = k0 + t % TC * SK::TN;
+    if (m0 + SK::TM <= n0 || n0 >= n) return;  // above the diagonal, or past the matrix
+    {
+        SK sk;
+        sk.clear();
+        sk.run(A.at(b) + m0, A.at(b) + n0, A.ld, k0);
+        sk.reduce(cs);
     }
-    __device__ double a(const GemmTile& t, int r, int k) const {
-        if (r >= m || k >= kw) return 0.0;
-        return A.at(t.batch)[(k0 + kw + r) + (long long)(k0 + k) * A.ld];
+    double* C = A.at(b) + m0 + (long long)n0 * A.ld;
+#pragma unroll 4
+    for (int x = tid; x < SK::TM * SK::TN; x += SK::NT) {
+        const int r = x % SK::TM, c = x / SK::TM;
+        if (m0 + r < n && n0 + c <= m0 + r) C[r + (long long)c * A.ld] -= cs[c * SK::LDC + r] + cs[(SK::TN + c) * SK::LDC + r];
     }
-    __device__ double b(const GemmTile& t, int k, int c) const {
-        if (c >= ncols || k >= kw) return 0.0;
-        return A.at(t.batch)[(k0 + kw + c) + (long long)(k0 + k) * A.ld];
-    }
-    __device__ Vec epi_load(const GemmTile& t, int r, int c) const {
-        if (r >= m || c >= ncols || r + RPL <= c) return Vec{};
-        return *reinterpret_cast<const Vec*>(A.at(t.batch) + (k0 + kw + r) + (long long)(k0 + kw + c) * A.ld);
-    }
-    __device__ void epi_store(const GemmTile& t, int r, int c, Vec acc, Vec cin) const {
-        if (r >= m || c >= ncols || r + RPL <= c) return;
-        double* a = A.at(t.batch) + (k0 + kw + r) + (long long)(k0 + kw + c) * A.ld;
-        if (r >= c && r + RPL <= m) {
-            *reinterpret_cast<Vec*>(a) = cin - acc;
-        } else {
-#pragma unroll
-            for (int e = 0; e < RPL; e++)
-                if (r + e >= c && r + e < m) a[e] = cin[e] - acc[e];
-        }
-    }
-    __device__ void store(const GemmTile&, int, int, double) const {}
-};
+}
 
 // ---------------------------------------------------------------------------
 // triangular solves; right-hand sides row-major [n][CHOL_NR] per matrix
@@ -296,47 +327,17 @@ __global__ __launch_bounds__(256) void chol_bwd_kernel(MatBatch<double> A, const
 // ---------------------------------------------------------------------------
 long long chol_linv_stride(int n) { return (long long)((n + CHOL_NB - 1) / CHOL_NB) * CHOL_NB * CHOL_NB; }
 
-static void chol_syrk(hipStream_t st, MatBatch<double> A, int nbatch, int k0, int kw, int m, bool thin) {
-    if (!thin && m >= GEMM_TS128_MIN_ORDER) {
-        typedef Gemm128Shape<double> S;
-        CholSyrkProb<128> ps;
-        ps.A = A; ps.k0 = k0; ps.kw = kw; ps.m = m; ps.ncols = m; ps.thin = 0; ps.tiles = (m + 127) / 128;
-        hipLaunchKernelGGL((gemm_mfma_kernel<double, CholSyrkProb<128>, 128, 128, S::BK, S::WM, S::WN>),
-                           dim3(ps.tiles * (ps.tiles + 1) / 2, 1, nbatch), dim3(64 * S::WM * S::WN), 0, st, ps);
-        return;
-    }
-    CholSyrkProb<64> ps;
-    ps.A = A; ps.k0 = k0; ps.kw = kw; ps.m = m; ps.thin = thin ? 1 : 0;
-    ps.ncols = thin ? std::min(m, CHOL_NB) : m;
-    ps.tiles = (m + 63) / 64;
-    const int grid = thin ? ps.tiles : ps.tiles * (ps.tiles + 1) / 2;
-    hipLaunchKernelGGL((gemm_mfma_kernel<double, CholSyrkProb<64>>), dim3(grid, 1, nbatch), dim3(256), 0, st, ps);
-}
-
-static void chol_panel(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, long long sLi, int k0,
-                       unsigned* status, int& rows) {
-    hipLaunchKernelGGL(chol_diag_kernel, dim3(nbatch), dim3(256), 0, st, A, Linv, sLi, n, k0, status);
-    rows = n - k0 - CHOL_NB;
-    if (rows <= 0) return;
-    CholPanelProb pp;
-    pp.A = A; pp.Linv = Linv; pp.sLi = sLi; pp.k0 = k0; pp.rows = rows;
-    hipLaunchKernelGGL((gemm_mfma_kernel<double, CholPanelProb>), dim3((rows + CHOL_NB - 1) / CHOL_NB, 1, nbatch),
-                       dim3(256), 0, st, pp);
-}
-
-// Superpanels of 128 columns: the first 64-column panel, its update of the
-// second panel's columns only, the second panel, then one trailing update
-// with both (K = 128: twice the flops per byte of a 64-deep update).
 void chol_factor_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, unsigned* status) {
     const long long sLi = chol_linv_stride(n);
-    for (int k0 = 0; k0 < n; k0 += 2 * CHOL_NB) {
-        int rows1, rows2;
-        chol_panel(st, A, n, nbatch, Linv, sLi, k0, status, rows1);
-        if (rows1 <= 0) break;
-        chol_syrk(st, A, nbatch, k0, CHOL_NB, rows1, true);
-        chol_panel(st, A, n, nbatch, Linv, sLi, k0 + CHOL_NB, status, rows2);
-        if (rows2 <= 0) break;
-        chol_syrk(st, A, nbatch, k0, 2 * CHOL_NB, rows2, false);
+    for (int k0 = 0; k0 < n; k0 += CHOL_NB) {
+        const int rows = n - k0 - CHOL_NB;
+        if (k0) {
+            const int tiles = (n - k0 + 31) / 32 * (CHOL_NB / 32);
+            hipLaunchKernelGGL(chol_update_kernel, dim3(tiles * nbatch), dim3(256), 0, st, A, n, k0, tiles);
+        }
+        hipLaunchKernelGGL(chol_diag_kernel, dim3(nbatch), dim3(256), 0, st, A, Linv, sLi, n, k0, status);
+        if (rows > 0)
+            hipLaunchKernelGGL(chol_panel_kernel, dim3((rows + 31) / 32, nbatch), dim3(256), 0, st, A, Linv, sLi, n, k0);
     }
 }
 

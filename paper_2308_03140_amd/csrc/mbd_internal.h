@@ -174,27 +174,19 @@ __device__ __forceinline__ T wave_sum8(const T (&v)[8]) {
 }
 
 // 1/x to the last bit or two for normal x with a normal reciprocal: the
-// hardware estimate and two Newton steps (the division's scaling and fix-up
-// for the ends of the range left out)
+// hardware estimate (to about 2^-23) and one third-order step (the division's
+// scaling and fix-up for the ends of the range left out)
 __device__ __forceinline__ double recip(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
+    const double r = __builtin_amdgcn_rcp(x), e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
-// s = sqrt(x), r = 1/sqrt(x) likewise: Goldschmidt steps on both from the
-// hardware estimate, then one correction of each by its residual
+// s = sqrt(x), r = 1/sqrt(x) likewise: (1 - e)^{-1/2} = 1 + e/2 + 3 e^2/8 on
+// the estimate, s = x r corrected by its residual
 __device__ __forceinline__ void sqrt_recip(double x, double& s, double& r) {
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    double e = fma(-h, g, 0.5);
-    g = fma(g, e, g);
-    h = fma(h, e, h);
-    e = fma(-h, g, 0.5);
-    h = fma(h, e, h);
-    g = fma(g, e, g);
-    s = fma(fma(-g, g, x), h, g);
-    r = 2.0 * h;
-    r = fma(fma(-s, r, 1.0), r, r);
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    r = fma(y * e, fma(0.375, e, 0.5), y);
+    const double g = x * r;
+    s = fma(fma(-g, g, x), 0.5 * r, g);
 }
 
 template <typename T>

@@ -663,6 +663,25 @@ bool make_isq_work(mbd_ctx* c, MatBatch<double> Q, const int* ns, int nmax, int 
     return true;
 }
 
+// Buffers of the residue products, where these take them: without the scratch
+// the FP64 products stay.
+void make_isq_mod(mbd_ctx* c, const int* ns_host, int nmax, int nmat, bool embed, IsqWork& w) {
+    const int mods = c->prec == MBD_FP32_REFINED ? ISQ_MODS_SHORT : ISQ_MODS_MAX;
+    if (!isq_mod_fits(ns_host, nmat, embed, mods)) return;
+    size_t res, prod;
+    IsqMod m;
+    isq_mod_sizes(nmax, mods, m, res, prod);
+    m.res = (isq_i4*)ws(c, "isq_res", (res + prod) * nmat);
+    if (m.res) {
+        m.prod = m.res + res * nmat / sizeof(isq_i4);
+        w.mod = m;
+        return;
+    }
+    c->err_code = 0;
+    c->err_origin.clear();
+    c->err_msg.clear();
+}
+
 // Whether an evaluation takes the direct Q^{-1/2}: always, unless the caller
 // wants eigenvalues or has set the threshold of the eigenvector refinement.
 bool direct_route(const mbd_ctx* c, unsigned want) {
@@ -740,6 +759,7 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
         return (mbd_status)c->err_code;
     std::vector<int> nsh(nmat);
     for (int b = 0; b < nmat; b++) nsh[b] = per ? 6 * sds[0].N : 3 * sds[b].N;
+    if (direct) make_isq_mod(c, nsh.data(), nmax, nmat, per != nullptr, iw);
     std::vector<char> staged;
     char* up_host = capturing ? mode->g->h_up : nullptr;
     if (!capturing) {

@@ -493,6 +493,7 @@ struct IsqEmit {
         IsqOp o;
         o.a = (signed char)a; o.b = (signed char)b; o.e1 = (signed char)e1; o.e2 = (signed char)e2;
         o.out = (signed char)out; o.out2 = (signed char)out2; o.full = 0;
+        o.sa = o.sb = o.conv = 0;
         o.c[0] = c0; o.c[1] = c1; o.c[2] = c2; o.c[3] = c3;
         o.d[0] = d0; o.d[1] = d1; o.d[2] = d2; o.d[3] = d3;
         op[k++] = o;
@@ -556,39 +557,90 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
     if (m == 0) m = steps;
     double hi;
     const int c = isq_class(al, be, m, exact, tab, hi);
-    if (lane != 0) return;
-    cls[b] = c;
-    IsqEmit e = {op, 0};
-    if (c >= 0) {
-        const IsqClass& k = tab.cls[c];
-        // stage one: X = (Q/hi - mid)/hw; buffers: 1 X^2, 2 X^3, 3 T, 4 U
-        const int last = k.deg[2] ? 2 : 1;
-        e.poly(0, 1.0 / (hi * k.hw[0]), -k.mid[0] / k.hw[0], k.deg[0], k.b[0], 1.0 / sqrt(hi), 1, 2, 3, 4, 5);
-        e.put(0, 5, -1, -1, 6, -1, 1.0, 0, 0, 0);  // Y = Q Z
-        int z = 5, y = 6;
-        for (int s = 1; s <= last; s++) {
-            // X = (Z Y - mid)/hw
-            e.put(z, y, -1, -1, 7, -1, 1.0 / k.hw[s], 0, 0, -k.mid[s] / k.hw[s]);
-            if (s < last) {
-                // buffers free here: 1 2 3 4 and, after X, none of z, y
-                e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 1, 2, 3, 4, k.deg[s] == 9 ? 3 : 4);
-                const int w = k.deg[s] == 9 ? 3 : 4;
-                e.put(y, w, -1, -1, 2, -1, 1.0, 0, 0, 0);
-                e.put(z, w, -1, -1, 1, -1, 1.0, 0, 0, 0);
-                z = 1;
-                y = 2;
-            } else if (z == 5) {
-                // y is free once X is formed
-                e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 1, 2, 3, 4, 6);
-                e.put(z, 6, -1, -1, ISQ_RESULT, -1, 1.0, 0, 0, 0);
-            } else {
-                e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 2, 3, 4, 5, 6);
-                e.put(z, 6, -1, -1, ISQ_RESULT, -1, 1.0, 0, 0, 0);
+    if (lane == 0) {
+        cls[b] = c;
+        IsqEmit e = {op, 0};
+        if (c >= 0) {
+            const IsqClass& k = tab.cls[c];
+            // stage one: X = (Q/hi - mid)/hw; buffers: 1 X^2, 2 X^3, 3 T, 4 U
+            const int last = k.deg[2] ? 2 : 1;
+            e.poly(0, 1.0 / (hi * k.hw[0]), -k.mid[0] / k.hw[0], k.deg[0], k.b[0], 1.0 / sqrt(hi), 1, 2, 3, 4, 5);
+            e.put(0, 5, -1, -1, 6, -1, 1.0, 0, 0, 0);  // Y = Q Z
+            int z = 5, y = 6;
+            for (int s = 1; s <= last; s++) {
+                // X = (Z Y - mid)/hw
+                e.put(z, y, -1, -1, 7, -1, 1.0 / k.hw[s], 0, 0, -k.mid[s] / k.hw[s]);
+                if (s < last) {
+                    // buffers free here: 1 2 3 4 and, after X, none of z, y
+                    e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 1, 2, 3, 4, k.deg[s] == 9 ? 3 : 4);
+                    const int w = k.deg[s] == 9 ? 3 : 4;
+                    e.put(y, w, -1, -1, 2, -1, 1.0, 0, 0, 0);
+                    e.put(z, w, -1, -1, 1, -1, 1.0, 0, 0, 0);
+                    z = 1;
+                    y = 2;
+                } else if (z == 5) {
+                    // y is free once X is formed
+                    e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 1, 2, 3, 4, 6);
+                    e.put(z, 6, -1, -1, ISQ_RESULT, -1, 1.0, 0, 0, 0);
+                } else {
+                    e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 2, 3, 4, 5, 6);
+                    e.put(z, 6, -1, -1, ISQ_RESULT, -1, 1.0, 0, 0, 0);
+                }
             }
         }
+        if (e.k) op[e.k - 1].full = 1;
+        // which operands the two residue slots hold
+        int held[2] = {-1, -1};
+        for (int i = 0; i < e.k; i++) {
+            IsqOp& o = op[i];
+            int sa = held[0] == o.a ? 0 : held[1] == o.a ? 1 : -1;
+            if (sa < 0) {
+                sa = held[0] == o.b ? 1 : 0;
+                held[sa] = o.a;
+                o.conv |= 1;
+            }
+            int sb = o.b == o.a ? sa : 1 - sa;
+            if (held[sb] != o.b) {
+                held[sb] = o.b;
+                o.conv |= 2;
+            }
+            o.sa = (signed char)sa;
+            o.sb = (signed char)sb;
+            for (int h = 0; h < 2; h++)
+                if (held[h] == o.out || (o.out2 >= 0 && held[h] == o.out2)) held[h] = -1;
+        }
+        while (e.k < ISQ_OPMAX) e.put(-1, -1, -1, -1, -1, -1, 0, 0, 0, 0);
     }
-    if (e.k) op[e.k - 1].full = 1;
-    while (e.k < ISQ_OPMAX) e.put(-1, -1, -1, -1, -1, -1, 0, 0, 0, 0);
+    if (c < 0) return;
+    __syncthreads();
+    // bounds of the operands' norms for the residue products: the programs are
+    // polynomials of Q, so 64 points of its interval are followed through one;
+    // a quarter on top covers what lies between them
+    double f[ISQ_NBUF];
+    f[0] = hi * exp2(-log2(tab.cls[c].kappa) * lane / 63.0);
+    for (int i = 0; i < ISQ_OPMAX; i++) {
+        const IsqOp o = op[i];
+        if (o.a < 0) break;
+        auto at = [&](int k) {
+            double v = 0.0;
+#pragma unroll
+            for (int j = 0; j < ISQ_NBUF; j++) v = j == k ? f[j] : v;
+            return v;
+        };
+        const double x = at(o.a), y = at(o.b), e1 = at(o.e1), e2 = at(o.e2);
+        const int ea = __builtin_amdgcn_frexp_exp(1.25 * wave_max(fabs(x))), eb = __builtin_amdgcn_frexp_exp(1.25 * wave_max(fabs(y)));
+        if (lane == 0) {
+            op[i].ea = ea;
+            op[i].eb = eb;
+        }
+        const double o1 = o.c[0] * x * y + o.c[1] * e1 + o.c[2] * e2 + o.c[3];
+        const double o2 = o.d[0] * x * y + o.d[1] * e1 + o.d[2] * e2 + o.d[3];
+#pragma unroll
+        for (int j = 0; j < ISQ_NBUF; j++) {
+            if (j == o.out) f[j] = o1;
+            if (j == o.out2) f[j] = o2;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -776,7 +828,8 @@ __global__ __launch_bounds__(256) void isq_check_kernel(MatBatch<double> Q, MatB
 // gradient kernel sees an atom of them.
 __global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int* ns, const int* cls,
                                                            const double* part, int nwg_max, const double* om,
-                                                           const double* mmult, const double* zmax, unsigned* status) {
+                                                           const double* mmult, const double* zmax, double check,
+                                                           unsigned* status) {
     __shared__ double red[4];
     const int s = blockIdx.x;
     SysDesc& S = sd[s];
@@ -795,7 +848,7 @@ __global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int*
         e = wave_sum(e);
         r = wave_sum(r);
         // |I - Z Q Z|_F^2; rounding leaves about 1e-14 sqrt(n) (measured, orders 30 to 6000)
-        if (!(r <= ISQ_CHECK * ISQ_CHECK * n)) ok = false;
+        if (!(r <= check * check * n)) ok = false;
         if (zmax) {
             const double z = zmax[b];
             if (!(z > 0.0)) ok = false;
@@ -1128,6 +1181,10 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     for (int k = 0; k < ISQ_OPMAX; k++) {
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (timed) prof->pair(&e0, &e1, 1, 0.0);
+        if (w.mod.mods) {
+            isq_mod_launch(st, w, nmat, k, e0, e1);
+            continue;
+        }
         auto go = [&](auto kernel, auto emb_kernel, int tm, int tn, int wk) {
             if (w.embed)
                 hipExtLaunchKernelGGL(emb_kernel, dim3(splitk_lower_tiles(nmax / 2, tm, tn), 2, nmat), dim3(64 * wk), 0, st,
@@ -1179,5 +1236,6 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
 void isq_energy_launch(hipStream_t st, const IsqWork& w, SysDesc* sd, int nsys, int nmax, const double* om,
                        const double* mmult, unsigned* status) {
     hipLaunchKernelGGL(isq_energy_kernel, dim3(nsys), dim3(256), 0, st, sd, w.ns, w.cls, w.check, isq_lanczos_wgs(nmax),
-                       om, mmult, w.zmax, status);
+                       om, mmult, w.zmax,
+                       w.mod.mods == ISQ_MODS_SHORT ? ISQ_CHECK_SHORT : ISQ_CHECK, status);
 }

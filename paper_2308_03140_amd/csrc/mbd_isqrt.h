@@ -18,6 +18,7 @@
 // residual norm falls up to 2.4% short of lambda_max (clusters, both densities).
 #define ISQ_LOW_FRACTION 0.5
 #define ISQ_CHECK 1e-12    // largest accepted |I - Z Q Z|_F / sqrt(n)
+#define ISQ_CHECK_SHORT 1e-10  // with the shorter residue products
 
 struct IsqClass {
     double kappa;
@@ -32,6 +33,8 @@ const IsqTable& isq_table();
 struct IsqOp {
     signed char a, b, e1, e2, out, out2;
     signed char full;  // the last product: an embedding is written whole
+    signed char sa, sb, conv;  // residue products: slots of a and b, bits: a, b to convert first
+    int ea, eb;        // their norms are below 2^ea, 2^eb
     double c[4], d[4];
 };
 struct IsqBufs {
@@ -49,8 +52,21 @@ struct IsqLanczos {
     int* len;       // order at which the recurrence ended, 0: it has not
     int* done;      // matrices that need no further step (nullptr: all run)
 };
+// Residue products (k_modmul.hip): 14 moduli for FP64, 12 for FP32 with
+// refinement
+#define ISQ_MODS_MAX 14
+#define ISQ_MODS_SHORT 12
+typedef int isq_i4 __attribute__((ext_vector_type(4)));
+struct IsqMod {
+    int mods = 0;   // 0: FP64 products
+    int bits;       // p: operands scaled to a norm of 2^p
+    int nb, kb;     // 32-row and 32-column blocks
+    isq_i4* res;    // [nmat][2 slots][mods][nb][kb][64]
+    isq_i4* prod;   // [nmat][mods][tiles][64 blocks][64]
+};
 struct IsqWork {
     const int* ns;
+    IsqMod mod;
     bool embed;     // real embeddings of Hermitian matrices (order even)
     IsqBufs bufs;
     IsqLanczos lan;
@@ -62,6 +78,12 @@ struct IsqWork {
 };
 
 int isq_lanczos_wgs(int nmax);
+// whether products of these orders go by residues; buffer sizes per matrix
+// (bytes) and layout for order nmax; the launches of program step `step`
+// (events around the integer products)
+bool isq_mod_fits(const int* ns_host, int nmat, bool embed, int mods);
+void isq_mod_sizes(int nmax, int mods, IsqMod& w, size_t& res, size_t& prod);
+void isq_mod_launch(hipStream_t st, const IsqWork& w, int nmat, int step, hipEvent_t e0, hipEvent_t e1);
 // Q^{-1/2} of every matrix into buffer ISQ_RESULT (both triangles), traces and
 // check sums, and the largest eigenvalue of Q^{-1/2} when wanted.  ns_host: the
 // orders; prof: each product launch as kind 1 when launch timing is on

@@ -323,7 +323,7 @@ mbd_status mbd_load_tuning(mbd_ctx *ctx, const char *table_json_path);
  * the stream and returns, for one kind (0..11), the summed event time (ms),
  * the number of records and the summed algorithmic work: bytes of the lower
  * trailing triangle read (kinds 0, 8 and 10), flops of the rank-2k update
- * or product (kind 1), pair terms (kind 11: N (N - 1) ordered pairs for a finite system,
+ * or product (kind 1; INT8 operations where products go by residues), pair terms (kind 11: N (N - 1) ordered pairs for a finite system,
  * N^2 times the image and reciprocal terms for a cell), 0 for the phases.
  * enable = 2 records the
  * phases only, without timing events (which would slow every launch): the

@@ -1209,7 +1209,7 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
         for (int k = 0; k < ISQ_OPMAX; k++) {
             double flops = 0.0;
             for (int b = 0; b < nmat; b++)
-                if (cls[b] >= 0 && k < isq_products(isq_table().cls[cls[b]])) flops += (w.embed ? 0.5 : 1.0) * ns_host[b] * ns_host[b] * ns_host[b];
+                if (cls[b] >= 0 && k < isq_products(isq_table().cls[cls[b]])) flops += (w.embed ? 0.5 : w.mod.mods ? w.mod.mods : 1.0) * ns_host[b] * ns_host[b] * ns_host[b];
             if (flops > 0.0) prof->work[rec0 + k] = flops;
             else prof->kind[rec0 + k] = -1;
         }

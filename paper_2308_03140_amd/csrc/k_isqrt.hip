@@ -528,9 +528,13 @@ struct IsqEmit {
 // in buffer ISQ_RESULT).  No class: an empty program, and the check afterwards
 // fails.
 __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos L, int steps, IsqTable tab, IsqOp* ops,
-                                                        int* cls) {
+                                                        int* cls, int* order, bool mod) {
     __shared__ double al[ISQ_LMAX], be[ISQ_LMAX];
     const int b = blockIdx.x, n = ns[b], lane = threadIdx.x;
+    int ahead = 0;  // matrices before this one: larger, or as large and earlier
+    for (int i = lane; i < (int)gridDim.x; i += 64) ahead += ns[i] > n || (ns[i] == n && i < b);
+    ahead = (int)wave_sum((double)ahead);
+    if (lane == 0) order[ahead] = b;
     IsqOp* op = ops + (long long)b * ISQ_OPMAX;
     for (int i = lane; i < steps; i += 64) {
         al[i] = L.alpha[(long long)b * ISQ_LMAX + i];
@@ -591,7 +595,7 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
         if (e.k) op[e.k - 1].full = 1;
         // which operands the two residue slots hold
         int held[2] = {-1, -1};
-        for (int i = 0; i < e.k; i++) {
+        for (int i = 0; mod && i < e.k; i++) {
             IsqOp& o = op[i];
             int sa = held[0] == o.a ? 0 : held[1] == o.a ? 1 : -1;
             if (sa < 0) {
@@ -611,7 +615,7 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
         }
         while (e.k < ISQ_OPMAX) e.put(-1, -1, -1, -1, -1, -1, 0, 0, 0, 0);
     }
-    if (c < 0) return;
+    if (!mod || c < 0) return;
     __syncthreads();
     // bounds of the operands' norms for the residue products: the programs are
     // polynomials of Q, so 64 points of its interval are followed through one;
@@ -658,20 +662,34 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
 // product, written.  Its lower triangles Re C = Re A Re B + Im A (Im B)^T (part
 // 0) and Im C = Im A Re B - Re A (Im B)^T (part 1) take half the products of a
 // real symmetric matrix of that order; bound by the traffic of the operands and
-// the epilogue (64 matrices of order 384: 74 us a product against 118).
+// the epilogue (64 matrices of order 384: 63 us a product against 118).
 template <int MI, int NJ, int WK, int U, int MINW, bool EMB>
 __global__ __launch_bounds__(64 * WK, MINW) void isq_prod_kernel(IsqBufs bufs, const int* ns, const IsqOp* ops,
-                                                                   int step) {
+                                                                   int step, const int* order, int nmat, int own) {
     typedef SplitK<MI, NJ, WK, U> SK;
     static_assert(MI % NJ == 0, "tile rows hold whole tile columns");
     constexpr int TM = SK::TM, TN = SK::TN, NT = SK::NT, LDC = SK::LDC;
     __shared__ __align__(16) double cs[SK::LDS];
-    const int b = blockIdx.z;
+    int b, part, v;
+    if (own) {
+        // whole matrices per XCD, own workgroups each, dealt out back and forth by size
+        const int x = blockIdx.x % GEMM_NXCD, j = blockIdx.x / GEMM_NXCD, m = j / own;
+        const int r = m * GEMM_NXCD + (m & 1 ? GEMM_NXCD - 1 - x : x);
+        if (r >= nmat) return;
+        b = order[r];
+        v = j % own;
+        part = EMB ? v & 1 : 0;
+        v = EMB ? v >> 1 : v;
+    } else {
+        b = blockIdx.z;
+        part = EMB ? blockIdx.y : 0;
+        v = splitk_tile_index(blockIdx.x, b, gridDim.x);
+    }
     const IsqOp& op = ops[(long long)b * ISQ_OPMAX + step];
     if (op.a < 0) return;
-    const int n = EMB ? ns[b] / 2 : ns[b], part = EMB ? blockIdx.y : 0;
+    const int n = EMB ? ns[b] / 2 : ns[b];
     int ti, tj;
-    splitk_lower_tile(splitk_tile_index(blockIdx.x, b, gridDim.x), TM / TN, ti, tj);
+    splitk_lower_tile(v, TM / TN, ti, tj);
     const int m0 = ti * TM, n0 = tj * TN;
     if (m0 >= n || n0 >= n) return;
     const int ld = bufs.ld, tid = threadIdx.x;
@@ -765,6 +783,14 @@ static int isq_shape(const int* ns, int nmat, bool embed) {
     }
     return pick;
 }
+
+// Whether every matrix's tiles go to one XCD, whose L2 then holds its operands
+// for all of them (spread over the XCDs each matrix is read into all eight):
+// where the matrices fill the XCDs evenly, nmat rounded up to eights at most 9/8
+// of it.  64 embeddings of order 384: 63 us a product against 80, 512 uneven
+// molecules (dealt out by size, largest first) 1.42 ms a launch against 1.54,
+// 60 small ones 10.3 us against 11.9.
+static bool isq_own(int nmat) { return 8 * ((nmat + GEMM_NXCD - 1) / GEMM_NXCD * GEMM_NXCD) <= 9 * nmat; }
 
 // ---------------------------------------------------------------------------
 // trace and check
@@ -1174,7 +1200,8 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     } else {
         for (int j = 0; j < steps; j++) hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Q, w.ns, L, j);
     }
-    hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(), w.ops, w.cls);
+    hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(), w.ops, w.cls, w.order,
+                       w.mod.mods > 0);
     const int shape = isq_shape(ns_host, nmat, w.embed);
     const bool timed = prof && prof->enabled && prof->launches;
     const size_t rec0 = timed ? prof->kind.size() : 0;
@@ -1186,12 +1213,15 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
             continue;
         }
         auto go = [&](auto kernel, auto emb_kernel, int tm, int tn, int wk) {
+            const int parts = w.embed ? 2 : 1, tiles = splitk_lower_tiles(nmax / parts, tm, tn);
+            const int own = isq_own(nmat) ? tiles * parts : 0;
+            const dim3 grid = own ? dim3((nmat + GEMM_NXCD - 1) / GEMM_NXCD * GEMM_NXCD * own) : dim3(tiles, parts, nmat);
             if (w.embed)
-                hipExtLaunchKernelGGL(emb_kernel, dim3(splitk_lower_tiles(nmax / 2, tm, tn), 2, nmat), dim3(64 * wk), 0, st,
-                                      e0, e1, 0, w.bufs, w.ns, w.ops, k);
+                hipExtLaunchKernelGGL(emb_kernel, grid, dim3(64 * wk), 0, st, e0, e1, 0, w.bufs, w.ns, w.ops, k, w.order,
+                                      nmat, own);
             else
-                hipExtLaunchKernelGGL(kernel, dim3(splitk_lower_tiles(nmax, tm, tn), 1, nmat), dim3(64 * wk), 0, st, e0, e1,
-                                      0, w.bufs, w.ns, w.ops, k);
+                hipExtLaunchKernelGGL(kernel, grid, dim3(64 * wk), 0, st, e0, e1, 0, w.bufs, w.ns, w.ops, k, w.order, nmat,
+                                      own);
         };
         switch (shape) {
         case 0: go(isq_prod_kernel<4, 2, 4, 5, 2, false>, isq_prod_kernel<4, 2, 4, 5, 2, true>, 64, 32, 4); break;

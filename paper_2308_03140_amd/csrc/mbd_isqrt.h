@@ -72,6 +72,7 @@ struct IsqWork {
     IsqLanczos lan;
     IsqOp* ops;     // [nmat][ISQ_OPMAX]
     int* cls;       // [nmat]
+    int* order;     // [nmat] matrices by order, largest first
     double* yv;     // [nmat][2][sV]
     double* check;  // [nmat][nwg][2]
     double* zmax;   // [nmat], or nullptr when lambda_min is not wanted

@@ -27,6 +27,7 @@
 // Frobenius norm of I - Z Q Z; a matrix that fails (an eigenvalue outside the
 // interval, or not positive definite: then no real Z gives Z Q Z = I) is left
 // to the eigensolver.
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <vector>
@@ -211,10 +212,11 @@ __device__ __forceinline__ void isq_part_sums(const double* part, int nwg, doubl
 // and a the alpha of the step before (M_00 at first): alpha = a + s1, beta^2 =
 // s2 - s1^2.  Taking a off first keeps beta accurate where M is close to a
 // multiple of the identity (weakly coupled identical atoms).  A beta at
-// rounding level ends the recurrence.
+// rounding level, of the matrix or of the difference s2 - s1^2, ends the
+// recurrence.
 __device__ __forceinline__ bool isq_beta(double alpha, double s1, double s2, double& beta) {
     const double b2 = s2 - s1 * s1;
-    const bool more = b2 > 1e-28 * alpha * alpha && s2 < 1e300;
+    const bool more = b2 > fmax(1e-28 * alpha * alpha, 1e-13 * s1 * s1) && s2 < 1e300;
     beta = more ? sqrt(b2) : 0.0;
     return more;
 }
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, co
     __shared__ double red4[4], red[4][ISQ_MVR];
     const int b = blockIdx.z, n = ns[b];
     const int r0 = blockIdx.x * ISQ_MVR;
-    if (r0 >= n) return;
+    if (r0 >= n || n <= L.one) return;
     if (L.done && L.done[b]) return;
     const int nwg = (n + ISQ_MVR - 1) / ISQ_MVR;
     double* vec = L.vec + (long long)b * L.sV * 4;
@@ -391,9 +393,11 @@ __device__ int isq_class(const double* al, const double* be, int m, bool exact, 
     return c;
 }
 
-// All Lanczos steps of a matrix in one workgroup, orders up to ISQ_SMALL: a
-// launch per step would cost about 3 us each, more than the matrix's read
-// (order 448: 1.6 MB, from L2 after the first step).  Thread (p, r) sums every
+// All Lanczos steps of a matrix in one workgroup, orders up to L.one: bound by
+// one compute unit's reads of the matrix from L2 (order 256: 0.5 MB, 8 us a
+// step, beyond which a launch per step is faster).  Small matrices take it also
+// beside large ones: their recurrence ends, or nearly ends, within the steps,
+// which its explicit norms notice and s2 - s1^2 does not.  Thread (p, r) sums every
 // np-th column's share of row r (columns of M are contiguous, M symmetric), so
 // the products need no cross-lane sums.  zmax != nullptr: run until the
 // largest eigenvalue has converged (see isq_zmax_kernel) and record it.
@@ -401,6 +405,7 @@ __global__ __launch_bounds__(1024) void isq_small_lanczos_kernel(MatBatch<double
                                                                    const int* cls, double* zmax) {
     __shared__ double v[2][ISQ_SMALL], red[16], sums[1024], al[ISQ_LMAX], be[ISQ_LMAX], zs;
     const int b = blockIdx.x, n = ns[b], tid = threadIdx.x;
+    if (n > L.one) return;
     if (zmax && cls[b] < 0) {
         if (tid == 0) zmax[b] = -1.0;
         return;
@@ -542,7 +547,7 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
     }
     double blast;
     bool more = true;
-    if (L.nwg) {
+    if (n > L.one) {
         // one launch per step: the last step's sums are still to be taken
         const int nwg = (n + ISQ_MVR - 1) / ISQ_MVR;
         const double* part = L.part + ((long long)b * 2 + ((steps + 1) & 1)) * 2 * L.nwg;
@@ -910,7 +915,9 @@ __global__ __launch_bounds__(64) void isq_zmax_kernel(const int* ns, const int* 
     __shared__ double al[ISQ_LMAX], be[ISQ_LMAX];
     const int b = blockIdx.x, lane = threadIdx.x;
     if (steps == 0) {
-        if (lane == 0) { L.done[b] = cls[b] < 0 ? 1 : 0; zmax[b] = -1.0; }
+        const bool one = ns[b] <= L.one;
+        if (lane == 0) L.done[b] = one || cls[b] < 0 ? 1 : 0;
+        if (lane == 0 && !one) zmax[b] = -1.0;
         return;
     }
     if (L.done[b]) return;
@@ -1193,13 +1200,14 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     IsqLanczos L = w.lan;
     L.done = nullptr;
     const int steps = nmax < 1024 ? ISQ_STEPS_SMALL : ISQ_STEPS_LARGE;
-    const bool small = nmax <= ISQ_SMALL;
-    if (small) {
-        L.nwg = 0;
+    const int nmin = *std::min_element(ns_host, ns_host + nmat);
+    // one workgroup per matrix against one launch per step (5-6 us): an energy at order 135, 180, 225, 300, 447 takes
+    // 221, 233, 264, 324, 468 us against 218, 219, 231, 249, 264; 60 molecules of up to 225 793 against 818
+    L.one = nmat > 4 ? ISQ_SMALL : ISQ_SMALL / 2;
+    if (nmin <= L.one)
         hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, Q, w.ns, L, steps, w.cls, nullptr);
-    } else {
+    if (nmax > L.one)
         for (int j = 0; j < steps; j++) hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Q, w.ns, L, j);
-    }
     hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(), w.ops, w.cls, w.order,
                        w.mod.mods > 0);
     const int shape = isq_shape(ns_host, nmat, w.embed);
@@ -1248,18 +1256,18 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     const int nwg = isq_lanczos_wgs(nmax);
     for (int p = 0; p < 3; p++)
         hipLaunchKernelGGL(isq_check_kernel, mv, dim3(256), 0, st, Q, Z, w.ns, w.cls, w.yv, w.lan.sV, w.check, nwg, p);
-    if (w.zmax && small) {
+    if (!w.zmax) return;
+    L = w.lan;
+    L.one = ISQ_SMALL;
+    if (nmin <= L.one)
         hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, Z, w.ns, L, ISQ_LMAX, w.cls, w.zmax);
-    } else if (w.zmax) {
-        L = w.lan;
-        const int most = ISQ_LMAX;
-        hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, 0, 0, w.zmax);
-        for (int j = 0; j < most; j++) {
-            hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Z, w.ns, L, j);
-            if ((j + 1) % ISQ_LCHECK == 0)
-                hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, j + 1, j + 1 == most ? 1 : 0,
-                                   w.zmax);
-        }
+    if (nmax <= L.one) return;
+    hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, 0, 0, w.zmax);
+    for (int j = 0; j < ISQ_LMAX; j++) {
+        hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Z, w.ns, L, j);
+        if ((j + 1) % ISQ_LCHECK == 0)
+            hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, j + 1, j + 1 == ISQ_LMAX ? 1 : 0,
+                               w.zmax);
     }
 }
 

@@ -9,7 +9,7 @@
 #define ISQ_RESULT 7       // buffer that receives Q^{-1/2}
 #define ISQ_MVR 8          // rows per workgroup of a matrix-vector pass
 #define ISQ_LMAX 128       // most Lanczos steps
-#define ISQ_SMALL 448      // largest order whose Lanczos steps run in one workgroup
+#define ISQ_SMALL 256      // largest order whose Lanczos steps run in one workgroup
 #define ISQ_LCHECK 8       // steps between convergence checks of lambda_min
 #define ISQ_STEPS_SMALL 10 // Lanczos steps for the interval, orders below 1024
 #define ISQ_STEPS_LARGE 14 // and from 1024 on
@@ -46,7 +46,8 @@ struct IsqLanczos {
     double* vec;    // [nmat][4][sV]: two vectors v and two w
     long long sV;
     double* part;   // [nmat][2][nwg][2]
-    int nwg;        // 0: all steps in one workgroup (alpha, beta complete)
+    int nwg;
+    int one;        // matrices up to this order have all their steps in one workgroup
     double* alpha;  // [nmat][ISQ_LMAX]
     double* beta;
     int* len;       // order at which the recurrence ended, 0: it has not

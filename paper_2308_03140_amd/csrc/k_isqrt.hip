@@ -188,16 +188,28 @@ __device__ __forceinline__ double isq_sign(int k, unsigned seed) {
 
 // sums of acc[r] over the workgroup, valid in every thread (LDS: 4 x ISQ_MVR)
 __device__ __forceinline__ void isq_row_sums(double (&acc)[ISQ_MVR], double (*red)[ISQ_MVR]) {
+    static_assert(ISQ_MVR == 8, "one butterfly for all rows");
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-    for (int r = 0; r < ISQ_MVR; r++) acc[r] = wave_sum(acc[r]);
+    const double t = wave_sum8(acc);
     __syncthreads();
-    if (lane == 0)
-#pragma unroll
-        for (int r = 0; r < ISQ_MVR; r++) red[wv][r] = acc[r];
+    if ((lane & 7) == 0) red[wv][lane >> 3] = t;
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < ISQ_MVR; r++) acc[r] = (red[0][r] + red[1][r]) + (red[2][r] + red[3][r]);
+}
+
+// Element k of column `row` of a symmetric matrix (EMB: elements k and nr + k of
+// the left block column, which make rows c and nr + c) times v (and u): row sums
+// s (and t).
+template <bool EMB>
+__device__ __forceinline__ void isq_row_term(const double* row, int nr, int k, double v, double u, double& s, double& t) {
+    const double re = row[k];
+    s += re * v;
+    if (EMB) {
+        const double im = row[nr + k];
+        s += im * u;
+        t += re * u - im * v;
+    }
 }
 
 // Sums of the two partials that the workgroups of the step before left.
@@ -224,14 +236,17 @@ __device__ __forceinline__ bool isq_beta(double alpha, double s1, double s2, dou
 // Step j: every workgroup forms v_j from the step before (elementwise, where
 // it is needed) and w'_j for its ISQ_MVR rows; bandwidth bound (M read once:
 // 288 MB at order 6000).  ISQ_MVR rows share the two loads behind an element
-// of v_j; one launch per step, with no grid barrier.
+// of v_j; one launch per step, with no grid barrier.  EMB: embeddings of
+// Hermitian matrices, whose left block column [Re; Im] holds both rows c and n/2
+// + c in column c: half the matrix is read.
+template <bool EMB>
 __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, const int* ns, IsqLanczos L, int j) {
     __shared__ double red4[4], red[4][ISQ_MVR];
-    const int b = blockIdx.z, n = ns[b];
+    const int b = blockIdx.z, n = ns[b], nr = EMB ? n / 2 : n;
     const int r0 = blockIdx.x * ISQ_MVR;
-    if (r0 >= n || n <= L.one) return;
+    if (r0 >= nr || n <= L.one) return;
     if (L.done && L.done[b]) return;
-    const int nwg = (n + ISQ_MVR - 1) / ISQ_MVR;
+    const int nwg = (nr + ISQ_MVR - 1) / ISQ_MVR;
     double* vec = L.vec + (long long)b * L.sV * 4;
     double* vj = vec + (long long)(j & 1) * L.sV;
     const double* v1 = vec + (long long)((j + 1) & 1) * L.sV;
@@ -264,31 +279,35 @@ __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, co
         return j == 0 ? isq_sign(k, 77u) * inv_n : (w1[k] - s1 * v1[k]) * inv;
     };
     const double* row[ISQ_MVR];
-    double acc[ISQ_MVR];
+    double acc[ISQ_MVR], acc2[ISQ_MVR];
 #pragma unroll
     for (int r = 0; r < ISQ_MVR; r++) {
-        row[r] = Mb + (long long)min(r0 + r, n - 1) * ld;
-        acc[r] = 0.0;
+        row[r] = Mb + (long long)min(r0 + r, nr - 1) * ld;
+        acc[r] = acc2[r] = 0.0;
     }
-    for (int k = threadIdx.x; k < n; k += 256) {
-        const double v = v_at(k);
+    for (int k = threadIdx.x; k < nr; k += 256) {
+        const double v = v_at(k), u = EMB ? v_at(nr + k) : 0.0;
 #pragma unroll
-        for (int r = 0; r < ISQ_MVR; r++) acc[r] += row[r][k] * v;
+        for (int r = 0; r < ISQ_MVR; r++) isq_row_term<EMB>(row[r], nr, k, v, u, acc[r], acc2[r]);
     }
     isq_row_sums(acc, red);
+    if (EMB) isq_row_sums(acc2, red);
     if (threadIdx.x < ISQ_MVR) {
-        const int rr = r0 + threadIdx.x;
         double p1 = 0.0, p2 = 0.0;
-        if (rr < n) {
-            double sum = 0.0;
+        if (r0 + (int)threadIdx.x < nr) {
 #pragma unroll
-            for (int r = 0; r < ISQ_MVR; r++) sum = (int)threadIdx.x == r ? acc[r] : sum;
-            const double v = v_at(rr);
-            const double w = sum - a * v - (j > 0 ? beta * v1[rr] : 0.0);
-            vj[rr] = v;
-            wj[rr] = w;
-            p1 = v * w;
-            p2 = w * w;
+            for (int h = 0; h < (EMB ? 2 : 1); h++) {
+                const int rr = h * nr + r0 + threadIdx.x;
+                double sum = 0.0;
+#pragma unroll
+                for (int r = 0; r < ISQ_MVR; r++) sum = (int)threadIdx.x == r ? (h ? acc2[r] : acc[r]) : sum;
+                const double v = v_at(rr);
+                const double w = sum - a * v - (j > 0 ? beta * v1[rr] : 0.0);
+                vj[rr] = v;
+                wj[rr] = w;
+                p1 += v * w;
+                p2 += w * w;
+            }
         }
         // eight lanes: butterfly within the half row
         p1 = quad_sum(p1);
@@ -383,7 +402,7 @@ __device__ int isq_class(const double* al, const double* be, int m, bool exact, 
         }
         res = be[m - 1] * fabs(x1) / sqrt(nn);
     }
-    hi = exact ? tmax * 1.01 : (tmax + 2.0 * res) * 1.04;
+    hi = exact ? tmax * 1.01 : (tmax + 2.0 * res) * 1.06;
     const double lo = tmin * (exact ? 0.9 : ISQ_LOW_FRACTION);
     int c = -1;
     if (lo > 0.0 && hi < 1e100) {
@@ -549,7 +568,7 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
     bool more = true;
     if (n > L.one) {
         // one launch per step: the last step's sums are still to be taken
-        const int nwg = (n + ISQ_MVR - 1) / ISQ_MVR;
+        const int nwg = ((L.emb ? n / 2 : n) + ISQ_MVR - 1) / ISQ_MVR;
         const double* part = L.part + ((long long)b * 2 + ((steps + 1) & 1)) * 2 * L.nwg;
         double s1 = 0.0, s2 = 0.0;
         for (int w = lane; w < nwg; w += 64) { s1 += part[2 * w]; s2 += part[2 * w + 1]; }
@@ -803,52 +822,61 @@ static bool isq_own(int nmat) { return 8 * ((nmat + GEMM_NXCD - 1) / GEMM_NXCD *
 // pass 0: y1 = Z x (x random signs) and the row block's share of sum Q o Z;
 // pass 1: y2 = Q y1; pass 2: x - Z y2 and the row block's sum of its squares.
 // A matrix without a program is skipped (its result is never read).
+template <bool EMB>
 __global__ __launch_bounds__(256) void isq_check_kernel(MatBatch<double> Q, MatBatch<double> Z, const int* ns,
                                                           const int* cls, double* yv, long long sV, double* part,
                                                           int nwg_max, int pass) {
     __shared__ double red[4][ISQ_MVR], red4[4];
-    const int b = blockIdx.z, n = ns[b];
+    const int b = blockIdx.z, n = ns[b], nr = EMB ? n / 2 : n;
     const int r0 = blockIdx.x * ISQ_MVR;
-    if (r0 >= n || cls[b] < 0) return;
+    if (r0 >= nr || cls[b] < 0) return;
     const MatBatch<double>& M = pass == 1 ? Q : Z;
     double* y1 = yv + (long long)b * 2 * sV;
     double* y2 = y1 + sV;
     const double* x = pass == 1 ? y1 : y2;
     const double* row[ISQ_MVR];
     const double* qrow[ISQ_MVR];
-    double acc[ISQ_MVR], e = 0.0;
+    double acc[ISQ_MVR], acc2[ISQ_MVR], e = 0.0;
 #pragma unroll
     for (int r = 0; r < ISQ_MVR; r++) {
-        const long long off = (long long)min(r0 + r, n - 1) * M.ld;
+        const long long off = (long long)min(r0 + r, nr - 1) * M.ld;
         row[r] = M.at(b) + off;
         qrow[r] = Q.at(b) + off;
-        acc[r] = 0.0;
+        acc[r] = acc2[r] = 0.0;
     }
-    for (int k = threadIdx.x; k < n; k += 256) {
+    for (int k = threadIdx.x; k < nr; k += 256) {
         const double v = pass == 0 ? isq_sign(k, 991u) : x[k];
+        const double u = !EMB ? 0.0 : pass == 0 ? isq_sign(nr + k, 991u) : x[nr + k];
 #pragma unroll
         for (int r = 0; r < ISQ_MVR; r++) {
-            const double z = row[r][k];
-            acc[r] += z * v;
-            if (pass == 0 && r0 + r < n) e += z * qrow[r][k];
+            isq_row_term<EMB>(row[r], nr, k, v, u, acc[r], acc2[r]);
+            if (pass == 0 && r0 + r < nr) {
+                e += row[r][k] * qrow[r][k];
+                if (EMB) e += row[r][nr + k] * qrow[r][nr + k];
+            }
         }
     }
     isq_row_sums(acc, red);
+    if (EMB) isq_row_sums(acc2, red);
     if (pass == 0) e = block_sum256(e, red4);
     if (threadIdx.x == 0) {
         double s = 0.0;
 #pragma unroll
-        for (int r = 0; r < ISQ_MVR; r++)
-            if (r0 + r < n) {
-                if (pass == 0) y1[r0 + r] = acc[r];
-                else if (pass == 1) y2[r0 + r] = acc[r];
-                else {
-                    const double dr = isq_sign(r0 + r, 991u) - acc[r];
-                    s += dr * dr;
+        for (int h = 0; h < (EMB ? 2 : 1); h++)
+#pragma unroll
+            for (int r = 0; r < ISQ_MVR; r++)
+                if (r0 + r < nr) {
+                    const int rr = h * nr + r0 + r;
+                    const double y = h ? acc2[r] : acc[r];
+                    if (pass == 0) y1[rr] = y;
+                    else if (pass == 1) y2[rr] = y;
+                    else {
+                        const double dr = isq_sign(rr, 991u) - y;
+                        s += dr * dr;
+                    }
                 }
-            }
         double* pb = part + ((long long)b * nwg_max + blockIdx.x) * 2;
-        if (pass == 0) pb[0] = e;
+        if (pass == 0) pb[0] = EMB ? 2.0 * e : e;
         if (pass == 2) pb[1] = s;
     }
 }
@@ -870,7 +898,7 @@ __global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int*
     for (int q = threadIdx.x >> 6; q < S.nmat; q += 4) {  // a wavefront per matrix
         const int b = S.mat0 + q;
         if (cls[b] < 0) { ok = false; continue; }
-        const int n = ns[b], nwg = (n + ISQ_MVR - 1) / ISQ_MVR;
+        const int n = ns[b], nwg = ((S.embed ? n / 2 : n) + ISQ_MVR - 1) / ISQ_MVR;
         double e = 0.0, r = 0.0;
         for (int w = lane; w < nwg; w += 64) {
             e += part[((long long)b * nwg_max + w) * 2];
@@ -1196,8 +1224,10 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
         else go(isq_tiny_kernel<64>);
         return;
     }
-    const dim3 mv(isq_lanczos_wgs(nmax), 1, nmat);
+    const dim3 mv(isq_lanczos_wgs(w.embed ? nmax / 2 : nmax), 1, nmat);
     IsqLanczos L = w.lan;
+    L.emb = w.embed;
+    const auto lanczos = w.embed ? isq_lanczos_kernel<true> : isq_lanczos_kernel<false>;
     L.done = nullptr;
     const int steps = nmax < 1024 ? ISQ_STEPS_SMALL : ISQ_STEPS_LARGE;
     const int nmin = *std::min_element(ns_host, ns_host + nmat);
@@ -1207,7 +1237,7 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     if (nmin <= L.one)
         hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, Q, w.ns, L, steps, w.cls, nullptr);
     if (nmax > L.one)
-        for (int j = 0; j < steps; j++) hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Q, w.ns, L, j);
+        for (int j = 0; j < steps; j++) hipLaunchKernelGGL(lanczos, mv, dim3(256), 0, st, Q, w.ns, L, j);
     hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(), w.ops, w.cls, w.order,
                        w.mod.mods > 0);
     const int shape = isq_shape(ns_host, nmat, w.embed);
@@ -1254,17 +1284,18 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     }
     const MatBatch<double> Z = {w.bufs.p[ISQ_RESULT], w.bufs.ld, w.bufs.stride};
     const int nwg = isq_lanczos_wgs(nmax);
+    const auto check = w.embed ? isq_check_kernel<true> : isq_check_kernel<false>;
     for (int p = 0; p < 3; p++)
-        hipLaunchKernelGGL(isq_check_kernel, mv, dim3(256), 0, st, Q, Z, w.ns, w.cls, w.yv, w.lan.sV, w.check, nwg, p);
+        hipLaunchKernelGGL(check, mv, dim3(256), 0, st, Q, Z, w.ns, w.cls, w.yv, w.lan.sV, w.check, nwg, p);
     if (!w.zmax) return;
-    L = w.lan;
     L.one = ISQ_SMALL;
     if (nmin <= L.one)
         hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, Z, w.ns, L, ISQ_LMAX, w.cls, w.zmax);
     if (nmax <= L.one) return;
+    L.done = w.lan.done;
     hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, 0, 0, w.zmax);
     for (int j = 0; j < ISQ_LMAX; j++) {
-        hipLaunchKernelGGL(isq_lanczos_kernel, mv, dim3(256), 0, st, Z, w.ns, L, j);
+        hipLaunchKernelGGL(lanczos, mv, dim3(256), 0, st, Z, w.ns, L, j);
         if ((j + 1) % ISQ_LCHECK == 0)
             hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, j + 1, j + 1 == ISQ_LMAX ? 1 : 0,
                                w.zmax);

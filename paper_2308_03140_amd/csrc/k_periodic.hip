@@ -39,12 +39,18 @@ __device__ __forceinline__ void fermi_pair(double d, double R0, double a, double
     dg_dr = a / R0 * g * omg;
 }
 
-// Real-space image term F(x) = T^erfc(x) [|x| < rc] - (1-g) T(x) and, if
-// dF != nullptr, dF[c][ab] = dF_ab/dx_c and F0[ab] = dF_ab/dR0 = (dg/dR0) T(x),
-// R0 = beta (Rv_i + Rv_j) the damping radius (dg/dR0 = -(d/R0) dg/dd).
-// Returns false when the term is empty.
-__device__ __forceinline__ bool image_term(const double* x, double gamma, double rc, double R0, double a,
-                                           double* F, double* dF, double* F0 = nullptr) {
+// Real-space image term F(x) = T^erfc(x) [|x| < rc] - (1-g) T(x) and its
+// derivatives, as the coefficients of their tensors:
+//   F          = f1 delta - f2 x x^T
+//   dF/dx_c    = x_c (h1 delta - h2 x x^T) - f2 (e_c x^T + x e_c^T)
+//   dF/dR0     = a0 delta - b0 x x^T = (dg/dR0) T(x),
+// R0 = beta (Rv_i + Rv_j) the damping radius (dg/dR0 = -(d/R0) dg/dd); f1 and f2
+// only without GRAD.  Returns false when the term is empty.
+struct ImageTerm {
+    double f1, f2, h1, h2, a0, b0;
+};
+template <bool GRAD>
+__device__ __forceinline__ bool image_term(const double* x, double gamma, double rc, double R0, double a, ImageTerm& T) {
     const double r2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
     const double d = sqrt(r2);
     const bool erfc_on = d < rc;
@@ -54,58 +60,31 @@ __device__ __forceinline__ bool image_term(const double* x, double gamma, double
     if (!erfc_on && !damp_on) return false;
     const double inv_d = 1.0 / d;
     const double inv3 = inv_d * inv_d * inv_d, inv5 = inv3 * inv_d * inv_d;
-    double B = 0.0, C = 0.0, dbr = 0.0, dcr = 0.0;
+    double B = 0.0, C = 0.0;
+    T.h1 = T.h2 = T.a0 = T.b0 = 0.0;
     if (erfc_on) {
         const double z = gamma * d;
         const double ex = exp(-z * z);
         const double ec = erfc(z);
         B = ec + 2.0 * z / SQRT_PI * ex;
         C = 3.0 * ec + 2.0 * z / SQRT_PI * (3.0 + 2.0 * z * z) * ex;
-        if (dF) {
+        if (GRAD) {
             const double dB = -4.0 * gamma * gamma * gamma * r2 / SQRT_PI * ex;
             const double dC = -8.0 * gamma * z * z * z * z / SQRT_PI * ex;
-            dbr = dB * inv3 - 3.0 * B * inv3 * inv_d;
-            dcr = dC * inv5 - 5.0 * C * inv5 * inv_d;
+            T.h1 = (dB * inv3 - 3.0 * B * inv3 * inv_d) * inv_d;
+            T.h2 = (dC * inv5 - 5.0 * C * inv5 * inv_d) * inv_d;
         }
     }
-    // bare part scaled by (1 - g): subtracted
+    // the bare tensor T = delta/r^3 - 3 x x^T/r^5 scaled by (1 - g): subtracted
     const double w = damp_on ? omg : 0.0;
-    // F = (B - w) delta/r^3 - (C - 3 w) r_a r_b / r^5
-    const double b = B - w, cc = C - 3.0 * w;
-    for (int p = 0; p < 3; p++)
-        for (int s = 0; s < 3; s++) F[p * 3 + s] = (p == s ? b * inv3 : 0.0) - cc * x[p] * x[s] * inv5;
-    if (F0) {
-        const double g0 = damp_on ? -gd * d / R0 : 0.0;
-        for (int p = 0; p < 3; p++)
-            for (int s = 0; s < 3; s++) F0[p * 3 + s] = g0 * ((p == s ? inv3 : 0.0) - 3.0 * x[p] * x[s] * inv5);
-    }
-    if (dF) {
-        // d/dd of the bare tensor pieces: d(1/d^3) = -3/d^4, d(3/d^5) = -15/d^6
-        // damping: -(1-g) T, d(1-g)/dd = -gd
-        const double inv7 = inv5 * inv_d * inv_d;
-        for (int c = 0; c < 3; c++) {
-            const double xc = x[c] * inv_d;
-            for (int p = 0; p < 3; p++)
-                for (int s = 0; s < 3; s++) {
-                    double v = 0.0;
-                    // erfc part
-                    if (erfc_on) {
-                        v += -dcr * xc * x[p] * x[s];
-                        if (p == s) v += dbr * xc;
-                        if (p == c) v -= C * x[s] * inv5;
-                        if (s == c) v -= C * x[p] * inv5;
-                    }
-                    if (damp_on) {
-                        double dT = 15.0 * x[p] * x[s] * x[c] * inv7;
-                        if (p == s) dT -= 3.0 * x[c] * inv5;
-                        if (p == c) dT -= 3.0 * x[s] * inv5;
-                        if (s == c) dT -= 3.0 * x[p] * inv5;
-                        const double T0 = (p == s ? inv3 : 0.0) - 3.0 * x[p] * x[s] * inv5;
-                        v += -omg * dT + gd * xc * T0;
-                    }
-                    dF[c * 9 + p * 3 + s] = v;
-                }
-        }
+    T.f1 = (B - w) * inv3;
+    T.f2 = (C - 3.0 * w) * inv5;
+    if (GRAD && damp_on) {
+        T.h1 += 3.0 * omg * inv5 + gd * inv_d * inv3;
+        T.h2 += 15.0 * omg * inv5 * inv_d * inv_d + 3.0 * gd * inv_d * inv5;
+        const double g0 = -gd * d / R0;
+        T.a0 = g0 * inv3;
+        T.b0 = 3.0 * g0 * inv5;
     }
     return true;
 }
@@ -116,9 +95,11 @@ __device__ __forceinline__ bool image_term(const double* x, double gamma, double
 // slots share an atom pair i <= j and split its images.  The
 // real-space image terms depend on the pair and the image only: each is
 // formed once, by one lane of its slot, into LDS (lpp images per round and
-// slot), and every lane of the slot adds it with its own phase e^{-i q.x}; the
-// slots' sums are added at the end in a fixed order.  FP64 VALU bound where
-// there are enough pairs; with one slot a pair, 8 atoms on 8 q points were 8
+// slot, the empty ones left out), and every lane of the slot adds it with its
+// own phase e^{-i q.x}; the slots' sums are added at the end in a fixed order.
+// Bound by those LDS reads, every lane the same address: the six components of
+// the symmetric term (64 atoms, 64 q points: 71 us, 137 with all nine and a
+// flag for every image).  With one slot a pair, 8 atoms on 8 q points were 8
 // wavefronts that walked all images in turn (547 us, the adjoint 1374 us).
 // Lanes of a pair index past the last follow the barriers and store nothing.  Writes the real-space and self terms and omega^2 into the left
 // block column [Re; Im] of the embedding; the reciprocal-space product then
@@ -154,14 +135,28 @@ __device__ __forceinline__ double per_slot_sum(double v, int lpp, int spp, doubl
     return v;
 }
 
+// A slot's nonempty image terms in a row from its first entry: this lane's entry
+// and the slot's count.  A slot lies in one wavefront, so its entries need no
+// barrier, only the order of its own LDS accesses.
+__device__ __forceinline__ int per_slot_place(bool ok, int slot, int lpp, int ql, int& cnt) {
+    const unsigned long long all = __ballot(ok) >> ((threadIdx.x & 63) - ql);
+    const unsigned long long m = lpp == 64 ? all : all & ((1ull << lpp) - 1ull);
+    cnt = __popcll(m);
+    return slot * lpp + __popcll(m & ((1ull << ql) - 1ull));
+}
+__device__ __forceinline__ void per_slot_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <int W>
 __global__ __launch_bounds__(PER_LANES * W) void mbd_assemble_periodic_kernel(const SysDesc* sd, const double* om,
                                                                           const double* cc, const double* qcart,
                                                                           int nq, int lpp, int spp, const int* img, int nimg,
                                                                           const double* phase, MatBatch<double> Q,
                                                                           unsigned* status) {
-    __shared__ double Fs[PER_LANES * W][9];
-    __shared__ int oks[PER_LANES * W];   // image index + 1 of the slot's term, 0 if empty
+    __shared__ double2 Fs[PER_LANES * W][3];  // xx xy, xz yy, yz zz
+    __shared__ int ts[PER_LANES * W];         // its image
     const SysDesc& S = sd[0];
     const int N = S.N, n = 3 * N;
     const int slot = threadIdx.x / lpp, ql = threadIdx.x % lpp, sub = slot % spp;
@@ -180,49 +175,52 @@ __global__ __launch_bounds__(PER_LANES * W) void mbd_assemble_periodic_kernel(co
     // e^{-i q.x} = e^{-i q.r} e^{-i q.R_n}, the second factor from the table
     double sb, cb;
     sincos(-(qv[0] * r[0] + qv[1] * r[1] + qv[2] * r[2]), &sb, &cb);
-    double Tre[9], Tim[9];
-    for (int k = 0; k < 9; k++) { Tre[k] = 0.0; Tim[k] = 0.0; }
+    double Tre[6], Tim[6];
+    for (int k = 0; k < 6; k++) { Tre[k] = 0.0; Tim[k] = 0.0; }
     for (int r0 = 0; r0 < nimg; r0 += lpp * spp) {
-        const int t0 = r0 + sub * lpp;
-        {
-            const int t = t0 + ql;
-            int ok = 0;
-            if (t < nimg) {
-                const double n0 = img[3 * t], n1 = img[3 * t + 1], n2 = img[3 * t + 2];
-                double x[3];
-                for (int c = 0; c < 3; c++) x[c] = r[c] + n0 * S.lat[c] + n1 * S.lat[3 + c] + n2 * S.lat[6 + c];
-                const double d2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
-                if (d2 != 0.0) {
-                    if (pv && i != j && d2 < 1e-16 && blockIdx.y == 0) atomicOr(&status[0], MBD_ST_COINCIDENT);
-                    double F[9];
-                    if (image_term(x, S.gamma, S.rc, R0, S.a, F, nullptr)) {
-                        ok = t + 1;
-                        for (int k = 0; k < 9; k++) Fs[threadIdx.x][k] = F[k];
-                    }
-                }
+        const int t = r0 + sub * lpp + ql;
+        bool ok = false;
+        double x[3];
+        ImageTerm F;
+        if (t < nimg) {
+            const double n0 = img[3 * t], n1 = img[3 * t + 1], n2 = img[3 * t + 2];
+            for (int c = 0; c < 3; c++) x[c] = r[c] + n0 * S.lat[c] + n1 * S.lat[3 + c] + n2 * S.lat[6 + c];
+            const double d2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
+            if (d2 != 0.0) {
+                if (pv && i != j && d2 < 1e-16 && blockIdx.y == 0) atomicOr(&status[0], MBD_ST_COINCIDENT);
+                ok = image_term<false>(x, S.gamma, S.rc, R0, S.a, F);
             }
-            oks[threadIdx.x] = ok;
         }
-        __syncthreads();
-        const int tn = min(lpp, nimg - t0);
-        for (int u0 = 0; u0 < tn; u0++) {
-            const int u = slot * lpp + u0;
-            if (!oks[u]) continue;
-            const double* pt = phase + 2 * ((long long)(oks[u] - 1) * nq + qc);
+        int cnt;
+        const int at = per_slot_place(ok, slot, lpp, ql, cnt);
+        if (ok) {
+            Fs[at][0] = make_double2(F.f1 - F.f2 * x[0] * x[0], -F.f2 * x[0] * x[1]);
+            Fs[at][1] = make_double2(-F.f2 * x[0] * x[2], F.f1 - F.f2 * x[1] * x[1]);
+            Fs[at][2] = make_double2(-F.f2 * x[1] * x[2], F.f1 - F.f2 * x[2] * x[2]);
+            ts[at] = t;
+        }
+        per_slot_fence();
+        for (int u = slot * lpp; u < slot * lpp + cnt; u++) {
+            const double* pt = phase + 2 * ((long long)ts[u] * nq + qc);
             const double cph = cb * pt[0] - sb * pt[1], sph = cb * pt[1] + sb * pt[0];
-            for (int k = 0; k < 9; k++) { Tre[k] += Fs[u][k] * cph; Tim[k] += Fs[u][k] * sph; }
+            const double2 f0 = Fs[u][0], f1 = Fs[u][1], f2 = Fs[u][2];
+            const double f[6] = {f0.x, f0.y, f1.x, f1.y, f2.x, f2.y};
+            for (int k = 0; k < 6; k++) { Tre[k] += f[k] * cph; Tim[k] += f[k] * sph; }
         }
-        __syncthreads();
+        per_slot_fence();
     }
-    if (spp > 1)
-        for (int k = 0; k < 9; k++) {
-            Tre[k] = per_slot_sum<W>(Tre[k], lpp, spp, &Fs[0][0]);
-            Tim[k] = per_slot_sum<W>(Tim[k], lpp, spp, &Fs[0][0]);
+    if (spp > 1) {
+        double* xw = reinterpret_cast<double*>(Fs);
+        __syncthreads();
+        for (int k = 0; k < 6; k++) {
+            Tre[k] = per_slot_sum<W>(Tre[k], lpp, spp, xw);
+            Tim[k] = per_slot_sum<W>(Tim[k], lpp, spp, xw);
         }
+    }
     if (!qv_ok || sub != 0) return;
     if (i == j) {
         const double self = 4.0 * S.gamma * S.gamma * S.gamma / (3.0 * SQRT_PI);
-        Tre[0] -= self; Tre[4] -= self; Tre[8] -= self;
+        Tre[0] -= self; Tre[3] -= self; Tre[5] -= self;
     }
     // without cc and om: the lattice sum T(q) itself (c = 1, no omega^2)
     const double pc = cc ? cc[S.atom_off + i] * cc[S.atom_off + j] : 1.0;
@@ -230,10 +228,11 @@ __global__ __launch_bounds__(PER_LANES * W) void mbd_assemble_periodic_kernel(co
     const long long ld = Q.ld;
     for (int a = 0; a < 3; a++)
         for (int b = 0; b < 3; b++) {
-            const double re = pc * Tre[a * 3 + b] +
+            const int k = a < b ? a * (5 - a) / 2 + b : b * (5 - b) / 2 + a;
+            const double re = pc * Tre[k] +
                               ((om && i == j && a == b) ? om[S.atom_off + i] * om[S.atom_off + i] : 0.0);
             const long long r0 = 3 * i + a, c0 = 3 * j + b;
-            const double im = i == j ? 0.0 : pc * Tim[a * 3 + b];  // the images of i = j come in +-n
+            const double im = i == j ? 0.0 : pc * Tim[k];  // the images of i = j come in +-n
             Qb[r0 + c0 * ld] = re;
             Qb[(r0 + n) + c0 * ld] = im;
             if (i != j) {
@@ -369,20 +368,20 @@ __global__ __launch_bounds__(64 * WK) void per_recip_asm_kernel(const SysDesc* s
 //                                      R0 = beta (Rv_i + Rv_j))
 // Partial results per (q, pair i <= j) of the real-space and self terms: {P,
 // dR[3], dA[9], P0} of (i, j), which (j, i) repeats (dR negated); the reciprocal-space term is contracted through U below.
-// Same layout as the assembly: slots of one lane per q-point, each real-space
-// image term (F and its derivatives) formed once into LDS and added by every
-// lane of its slot with its own phase and M(q).  Two
-// wavefronts per SIMD (at most 256 registers, a few spilled: 587 -> 519 us
-// for the 64-atom cell's 64 q against one wavefront at 268 registers; 290 us
-// with the pairs i <= j only).
+// Same layout as the assembly: slots of one lane per q-point, the coefficients
+// of each real-space image term formed once into LDS and added by every lane of
+// its slot with its own phase and M(q).  Contracted with M, whose symmetric part
+// is all that the symmetric tensors see, they need only tr M, M x and x.M x: 66
+// operations and six LDS reads an image and lane (64 atoms, 64 q points: 89
+// us, 288 with the 45 tensor components in LDS, which bound it).
 template <int W>
-__global__ __launch_bounds__(PER_LANES * W, 2) void mbd_grad_periodic_kernel(const SysDesc* sd, const double* om,
+__global__ __launch_bounds__(PER_LANES * W) void mbd_grad_periodic_kernel(const SysDesc* sd, const double* om,
                                                                       const double* cc, const double* qcart, int nq,
                                                                       int lpp, int spp, const int* img, int nimg,
                                                                       const double* phase, MatBatch<double> M,
                                                                       double* part) {
-    __shared__ double Fs[PER_LANES * W][9], dFs[PER_LANES * W][27], F0s[PER_LANES * W][9];
-    __shared__ int ns_[PER_LANES * W][3], oks[PER_LANES * W];   // oks: image index + 1 of the slot's term, 0 if empty
+    __shared__ double2 Fs[PER_LANES * W][5];  // x, f1, f2, h1, h2, a0, b0
+    __shared__ int4 ts[PER_LANES * W];        // the image's cell and index
     const SysDesc& S = sd[0];
     const int N = S.N, n = 3 * N;
     const int slot = threadIdx.x / lpp, ql = threadIdx.x % lpp, sub = slot % spp;
@@ -403,82 +402,88 @@ __global__ __launch_bounds__(PER_LANES * W, 2) void mbd_grad_periodic_kernel(con
     // e^{-i q.x} = e^{-i q.r} e^{-i q.R_n}, the second factor from the table
     double sb, cb;
     sincos(-(qv[0] * r[0] + qv[1] * r[1] + qv[2] * r[2]), &sb, &cb);
-    // M_{jb,ia}
-    double Mr[9], Mi[9];
+    // M_{jb,ia}: its trace and M + M^T (xx xy xz yy yz zz)
+    double Mr[6], Mi[6];
     const double* Mb = M.at(q);
     for (int a = 0; a < 3; a++)
-        for (int b = 0; b < 3; b++) {
-            Mr[a * 3 + b] = Mb[(3 * j + b) + (long long)(3 * i + a) * M.ld];
-            Mi[a * 3 + b] = Mb[(n + 3 * j + b) + (long long)(3 * i + a) * M.ld];
+        for (int b = a; b < 3; b++) {
+            const long long o = 3 * j + b + (long long)(3 * i + a) * M.ld, p = 3 * j + a + (long long)(3 * i + b) * M.ld;
+            const int k = a * (5 - a) / 2 + b;
+            Mr[k] = Mb[o] + Mb[p];
+            Mi[k] = Mb[n + o] + Mb[n + p];
         }
+    const double trr = 0.5 * (Mr[0] + Mr[3] + Mr[5]), tri = 0.5 * (Mi[0] + Mi[3] + Mi[5]);
     // rho = A^{-T} r  (rho_v = sum_d Ainv[d][v] r_d)
     double rho[3];
     for (int v = 0; v < 3; v++) rho[v] = S.linv[v] * r[0] + S.linv[3 + v] * r[1] + S.linv[6 + v] * r[2];
-    double P = 0.0, P0 = 0.0, dR[3] = {0, 0, 0}, dA[9];
+    double P = 0.0, P0 = 0.0, Ti = 0.0, dR[3] = {0, 0, 0}, dA[9];
     for (int k = 0; k < 9; k++) dA[k] = 0.0;
     for (int r0 = 0; r0 < nimg; r0 += lpp * spp) {
-        const int t0 = r0 + sub * lpp;
-        {
-            const int t = t0 + ql;
-            int ok = 0;
-            if (t < nimg) {
-                const int nn[3] = {img[3 * t], img[3 * t + 1], img[3 * t + 2]};
-                double x[3];
-                for (int c = 0; c < 3; c++) x[c] = r[c] + nn[0] * S.lat[c] + nn[1] * S.lat[3 + c] + nn[2] * S.lat[6 + c];
-                const double d2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
-                // the term is written straight into this lane's slot
-                if (d2 != 0.0 && image_term(x, S.gamma, S.rc, R0, S.a, Fs[threadIdx.x], dFs[threadIdx.x], F0s[threadIdx.x])) {
-                    ok = t + 1;
-                    for (int c = 0; c < 3; c++) ns_[threadIdx.x][c] = nn[c];
-                }
-            }
-            oks[threadIdx.x] = ok;
+        const int t = r0 + sub * lpp + ql;
+        bool ok = false;
+        double x[3];
+        int nn[3];
+        ImageTerm F;
+        if (t < nimg) {
+            for (int c = 0; c < 3; c++) nn[c] = img[3 * t + c];
+            for (int c = 0; c < 3; c++) x[c] = r[c] + nn[0] * S.lat[c] + nn[1] * S.lat[3 + c] + nn[2] * S.lat[6 + c];
+            const double d2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
+            ok = d2 != 0.0 && image_term<true>(x, S.gamma, S.rc, R0, S.a, F);
         }
-        __syncthreads();
-        const int tn = min(lpp, nimg - t0);
-        for (int u0 = 0; u0 < tn; u0++) {
-        const int u = slot * lpp + u0;
-        if (!oks[u]) continue;
-        const double* F = Fs[u];
-        const double* dF = dFs[u];
-        const int* nn = ns_[u];
-        const double* pt = phase + 2 * ((long long)(oks[u] - 1) * nq + q);
-        const double cph = cb * pt[0] - sb * pt[1], sph = cb * pt[1] + sb * pt[0];
-        double SF = 0.0, SFi = 0.0, SdF[3] = {0, 0, 0}, SdFi[3] = {0, 0, 0}, SF0 = 0.0, SF0i = 0.0;
-        for (int k = 0; k < 9; k++) {
-            SF += Mr[k] * F[k];
-            SFi += Mi[k] * F[k];
-            SF0 += Mr[k] * F0s[u][k];
-            SF0i += Mi[k] * F0s[u][k];
+        int cnt;
+        const int at = per_slot_place(ok, slot, lpp, ql, cnt);
+        if (ok) {
+            Fs[at][0] = make_double2(x[0], x[1]);
+            Fs[at][1] = make_double2(x[2], F.f1);
+            Fs[at][2] = make_double2(F.f2, F.h1);
+            Fs[at][3] = make_double2(F.h2, F.a0);
+            Fs[at][4] = make_double2(F.b0, 0.0);
+            ts[at] = make_int4(nn[0], nn[1], nn[2], t);
         }
-        P0 += SF0 * cph - SF0i * sph;
-        for (int c = 0; c < 3; c++)
-            for (int k = 0; k < 9; k++) {
-                SdF[c] += Mr[k] * dF[c * 9 + k];
-                SdFi[c] += Mi[k] * dF[c * 9 + k];
-            }
-        P += SF * cph - SFi * sph;
-        for (int c = 0; c < 3; c++) {
-            // (dF_c - i q_c F) e^{i ph}
-            dR[c] += SdF[c] * cph - SdFi[c] * sph + qv[c] * (SF * sph + SFi * cph);
-            for (int v = 0; v < 3; v++) {
-                // (dF_c n_v + i q_c rho_v F) e^{i ph}
-                dA[v * 3 + c] += nn[v] * (SdF[c] * cph - SdFi[c] * sph) -
-                                 qv[c] * rho[v] * (SF * sph + SFi * cph);
+        per_slot_fence();
+        for (int u = slot * lpp; u < slot * lpp + cnt; u++) {
+            const int4 m = ts[u];
+            const double2 u0 = Fs[u][0], u1 = Fs[u][1], u2 = Fs[u][2], u3 = Fs[u][3];
+            const double y[3] = {u0.x, u0.y, u1.x}, f1 = u1.y, f2 = u2.x, h1 = u2.y, h2 = u3.x, a0 = u3.y, b0 = Fs[u][4].x;
+            const double* pt = phase + 2 * ((long long)m.w * nq + q);
+            const double cph = cb * pt[0] - sb * pt[1], sph = cb * pt[1] + sb * pt[0];
+            // (M + M^T) x and x.M x, then times the phase
+            const double sr[3] = {Mr[0] * y[0] + Mr[1] * y[1] + Mr[2] * y[2], Mr[1] * y[0] + Mr[3] * y[1] + Mr[4] * y[2],
+                                  Mr[2] * y[0] + Mr[4] * y[1] + Mr[5] * y[2]};
+            const double si[3] = {Mi[0] * y[0] + Mi[1] * y[1] + Mi[2] * y[2], Mi[1] * y[0] + Mi[3] * y[1] + Mi[4] * y[2],
+                                  Mi[2] * y[0] + Mi[4] * y[1] + Mi[5] * y[2]};
+            const double qr = 0.5 * (y[0] * sr[0] + y[1] * sr[1] + y[2] * sr[2]);
+            const double qi = 0.5 * (y[0] * si[0] + y[1] * si[1] + y[2] * si[2]);
+            const double tr = trr * cph - tri * sph, ti = trr * sph + tri * cph;
+            const double qc = qr * cph - qi * sph, qs = qr * sph + qi * cph;
+            P += f1 * tr - f2 * qc;
+            Ti += f1 * ti - f2 * qs;  // of -i F e^{i ph}: the phase's own derivatives
+            P0 += a0 * tr - b0 * qc;
+            const double h = h1 * tr - h2 * qc, nv[3] = {(double)m.x, (double)m.y, (double)m.z};
+            for (int c = 0; c < 3; c++) {
+                const double D = y[c] * h - f2 * (sr[c] * cph - si[c] * sph);
+                dR[c] += D;
+                for (int v = 0; v < 3; v++) dA[v * 3 + c] += nv[v] * D;
             }
         }
-        }
-        __syncthreads();
+        per_slot_fence();
+    }
+    // (dF_c - i q_c F) e^{i ph} and (dF_c n_v + i q_c rho_v F) e^{i ph}
+    for (int c = 0; c < 3; c++) {
+        dR[c] += qv[c] * Ti;
+        for (int v = 0; v < 3; v++) dA[v * 3 + c] -= qv[c] * rho[v] * Ti;
     }
     if (spp > 1) {
-        P = per_slot_sum<W>(P, lpp, spp, &Fs[0][0]);
-        P0 = per_slot_sum<W>(P0, lpp, spp, &Fs[0][0]);
-        for (int c = 0; c < 3; c++) dR[c] = per_slot_sum<W>(dR[c], lpp, spp, &Fs[0][0]);
-        for (int k = 0; k < 9; k++) dA[k] = per_slot_sum<W>(dA[k], lpp, spp, &Fs[0][0]);
+        double* xw = reinterpret_cast<double*>(Fs);
+        __syncthreads();
+        P = per_slot_sum<W>(P, lpp, spp, xw);
+        P0 = per_slot_sum<W>(P0, lpp, spp, xw);
+        for (int c = 0; c < 3; c++) dR[c] = per_slot_sum<W>(dR[c], lpp, spp, xw);
+        for (int k = 0; k < 9; k++) dA[k] = per_slot_sum<W>(dA[k], lpp, spp, xw);
     }
     if (i == j) {
         const double self = 4.0 * S.gamma * S.gamma * S.gamma / (3.0 * SQRT_PI);
-        P -= self * (Mr[0] + Mr[4] + Mr[8]);
+        P -= self * trr;
     }
     if (!qv_ok || sub != 0) return;
     out[0] = P;

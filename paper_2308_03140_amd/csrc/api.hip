@@ -789,7 +789,7 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
         HIPCHK(hipMemcpyAsync(rec, per->rec.data(), sizeof(int) * per->rec.size(), hipMemcpyHostToDevice, st), "upload");
         const mbd_status rr = make_per_ewald(c, *per, sds[0].N, nq, rec, grads, prc);
         if (rr != MBD_OK) return rr;
-        per_recip_basis_launch(st, sd_dev, qcart, nq, img, (int)per->img.size() / 3, prc);
+        per_recip_basis_launch(st, sd_dev, cc, qcart, nq, img, (int)per->img.size() / 3, prc);
         mbd_assemble_periodic_launch(st, sd_dev, om, cc, qcart, nq, img, (int)per->img.size() / 3, prc, A64, A32,
                                      status, sds[0].N);
     } else {
@@ -1282,7 +1282,7 @@ mbd_status mbd_freq_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, in
         // then scaled by c_i c_j per frequency
         const MatBatch<double> Tq = {wsT<double>(c, "freq_T", (size_t)stride * nq), ld, stride};
         if (!Tq.p) return (mbd_status)c->err_code;
-        per_recip_basis_launch(st, sd_dev + 1, qcart, nq, img, (int)ps.img.size() / 3, prc);
+        per_recip_basis_launch(st, sd_dev + 1, nullptr, qcart, nq, img, (int)ps.img.size() / 3, prc);
         mbd_assemble_periodic_launch(st, sd_dev + 1, nullptr, nullptr, qcart, nq, img, (int)ps.img.size() / 3, prc, Tq,
                                      MatBatch<float>{nullptr, ld, stride}, status + 1, N);
         if (herm) {

@@ -80,8 +80,59 @@ struct SplitK {
             g += WK;
         }
     }
+    // acc += sum over K of A(m0 .., k) B(k, n0 ..) with B column-major, columns
+    // nb of them from B: a lane's 16-byte load of B holds rows k, k + 1 of one
+    // column, so the k of an MFMA step are 2 apart (K even)
+    __device__ __forceinline__ void run_cols(const double* A, int lda, const double* B, int ldb, int nb, int K) {
+        constexpr int D = U / 2, G = 8 * D;
+        static_assert(U % 2 == 0, "pairs of k-steps");
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kl = 2 * (lane >> 4);
+        const unsigned offa = (unsigned)(kl * lda + 2 * (lane & 15)) * 8u;
+        const unsigned offb = (unsigned)((lane & 15) * ldb + kl) * 8u;
+        const auto dB = make_rsrc(B, (unsigned)nb * ldb * 8u);
+        splitk_d2 sa[2][U][MI / 2], sb[2][D][NJ];
+        auto gload = [&](int k0, auto& xa, auto& xb) {
+            const int kn = max(0, min(G, K - k0));
+            const auto dA = make_rsrc(A + (long long)k0 * lda, (unsigned)kn * lda * 8u);
+#pragma unroll
+            for (int u = 0; u < U; u++)
+#pragma unroll
+                for (int i = 0; i < MI / 2; i++)
+                    xa[u][i] = __builtin_bit_cast(
+                        splitk_d2, __builtin_amdgcn_raw_buffer_load_b128(dA, offa + 256u * i, (u / 2 * 8 + u % 2) * lda * 8, 0));
+#pragma unroll
+            for (int d = 0; d < D; d++) {
+                const unsigned o = 8 * d + kl < kn ? offb + (unsigned)(k0 + 8 * d) * 8u : OOB_OFFSET;
+#pragma unroll
+                for (int j = 0; j < NJ; j++)
+                    xb[d][j] = __builtin_bit_cast(splitk_d2, __builtin_amdgcn_raw_buffer_load_b128(dB, o + (unsigned)(16 * j * ldb) * 8u, 0, 0));
+            }
+        };
+        auto mult = [&](auto& xa, auto& xb) {
+#pragma unroll
+            for (int u = 0; u < U; u++)
+#pragma unroll
+                for (int i = 0; i < MI; i++)
+#pragma unroll
+                    for (int j = 0; j < NJ; j++) acc[i][j] = mfma16x16x4(xa[u][i / 2][i & 1], xb[u / 2][j][u & 1], acc[i][j]);
+        };
+        const int ng = (K + G - 1) / G;
+        int g = wave;
+        gload(g * G, sa[0], sb[0]);
+        while (g < ng) {
+            gload((g + WK) * G, sa[1], sb[1]);
+            mult(sa[0], sb[0]);
+            g += WK;
+            if (g >= ng) break;
+            gload((g + WK) * G, sa[0], sb[0]);
+            mult(sa[1], sb[1]);
+            g += WK;
+        }
+    }
     // The wavefronts' shares into cs (two halves of TN x LDC, column-major): two
     // write, the others add in turn; the tile is the sum of the halves.
+    // COLS: after run_cols, whose tile columns are not interleaved in pairs.
+    template <bool COLS = false>
     __device__ __forceinline__ void reduce(double* cs) const {
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
@@ -95,7 +146,7 @@ struct SplitK {
 #pragma unroll
                         for (int r = 0; r < 4; r++) {
                             const int row = 32 * (i / 2) + 2 * mfma_rows<double>::row(lane, r) + (i & 1);
-                            const int col = 32 * (j / 2) + 2 * (lane & 15) + (j & 1);
+                            const int col = COLS ? 16 * j + (lane & 15) : 32 * (j / 2) + 2 * (lane & 15) + (j & 1);
                             if (w == 0) c[col * LDC + row] = acc[i][j][r];
                             else c[col * LDC + row] += acc[i][j][r];
                         }

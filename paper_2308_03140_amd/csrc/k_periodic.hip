@@ -258,10 +258,11 @@ __device__ __forceinline__ void recip_column(const SysDesc& S, const int* rec, i
     f = -2.0 * g4 - 2.0 / k2;
 }
 
-// Columns of U(q), embedded: rows 0 .. n-1 Re U, rows n .. 2n-1 Im U; the
-// columns past the q point's count are zero.  Grid (ncol, nq), 64 threads
+// Columns of C U(q), embedded: rows 0 .. n-1 Re, rows n .. 2n-1 Im, C = 1 without
+// cc; the columns past the q point's count are zero.  Grid (ncol, nq), 64 threads
 // over the atoms.
-__global__ __launch_bounds__(64) void per_recip_basis_kernel(const SysDesc* sd, const double* qcart, PerEwald pr) {
+__global__ __launch_bounds__(64) void per_recip_basis_kernel(const SysDesc* sd, const double* cc, const double* qcart,
+                                                             PerEwald pr) {
     const SysDesc& S = sd[0];
     const int N = S.N, n = 3 * N;
     const int g = blockIdx.x, q = blockIdx.y;
@@ -273,9 +274,10 @@ __global__ __launch_bounds__(64) void per_recip_basis_kernel(const SysDesc* sd, 
     for (int i = threadIdx.x; i < N; i += 64) {
         double sn = 0.0, cs = 1.0;
         if (t >= 0) sincos(G[0] * R[3 * i] + G[1] * R[3 * i + 1] + G[2] * R[3 * i + 2], &sn, &cs);
+        const double w = cc ? sw * cc[S.atom_off + i] : sw;
         for (int a = 0; a < 3; a++) {
-            Zc[3 * i + a] = sw * k[a] * cs;      // e^{-i G.R} = cos - i sin
-            Zc[n + 3 * i + a] = -sw * k[a] * sn;
+            Zc[3 * i + a] = w * k[a] * cs;      // e^{-i G.R} = cos - i sin
+            Zc[n + 3 * i + a] = -w * k[a] * sn;
         }
     }
 }
@@ -296,15 +298,15 @@ __global__ __launch_bounds__(256) void per_phase_kernel(const SysDesc* sd, const
     phase[2 * e + 1] = sn;
 }
 
-// Reciprocal term of the embedding, C U U^H C: the lower triangles of Re = U_r
+// Reciprocal term of the embedding, (C U)(C U)^H: the lower triangles of Re = U_r
 // U_r^T + U_i U_i^T (part 0) and Im = U_i U_r^T - U_r U_i^T (part 1), added to
 // the real-space part and copied to their other seven places (and to the FP32
 // copy).  K split over the wavefronts (gemm_splitk.h); matrix-core bound: 64 q
 // points of 64 atoms 90 us against 230 for the whole left block column
 // through staged tiles.
 template <int MI, int NJ, int WK, int U>
-__global__ __launch_bounds__(64 * WK) void per_recip_asm_kernel(const SysDesc* sd, const double* cc, PerEwald pr, int n,
-                                                                  MatBatch<double> Q, MatBatch<float> Q32) {
+__global__ __launch_bounds__(64 * WK) void per_recip_asm_kernel(PerEwald pr, int n, MatBatch<double> Q,
+                                                                  MatBatch<float> Q32) {
     typedef SplitK<MI, NJ, WK, U> SK;
     constexpr int TM = SK::TM, TN = SK::TN, LDC = SK::LDC;
     __shared__ __align__(16) double cs[SK::LDS];
@@ -322,7 +324,6 @@ __global__ __launch_bounds__(64 * WK) void per_recip_asm_kernel(const SysDesc* s
         else sk.run(Z + m0 + n, Z + n0 + n, pr.ldz, pr.ncol);
         sk.reduce(cs);
     }
-    const int off = sd->atom_off;
     double* Qb = Q.at(b);
     float* Qf = Q32.p ? Q32.at(b) : nullptr;
     const long long ld = Q.ld;
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(64 * WK) void per_recip_asm_kernel(const SysDesc* s
         const int r = x % TM, cl = x / TM, row = m0 + r, col = n0 + cl;
         if (row >= n || col >= n || col > row) continue;
         const double s = cs[cl * LDC + r] + cs[(TN + cl) * LDC + r];
-        double v = Qb[row + part * n + col * ld] + (cc ? cc[off + row / 3] * cc[off + col / 3] : 1.0) * s;
+        double v = Qb[row + part * n + col * ld] + s;
         if (part && row == col) v = 0.0;  // the diagonal of Im
         put(row + part * n + col * ld, v);
         put(row + (1 - part) * n + (n + col) * ld, sg * v);
@@ -493,34 +494,30 @@ __global__ __launch_bounds__(PER_LANES * W) void mbd_grad_periodic_kernel(const 
 }
 
 // Reciprocal term of the adjoint, W = M C U: M(q) the full embedded inverse
-// square root (2n x 2n), C U the basis with row (i, a) scaled by c_i;
-// W (2n x ncol) is [Re; Im] of the complex product.
-struct PerRecMZProb {
-    static constexpr bool A_M_CONTIG = true;
-    static constexpr bool B_N_CONTIG = false;
-    const SysDesc* sd;
-    const double* cc;
-    MatBatch<double> M;
-    const double* Z; double* W; int ldz; long long sZ; int ncol; int n;
-    int tiles_m, tiles_n;
-    __device__ bool tile(int bx, int, int bz, GemmTile& t) const {
-        int ti, tj;
-        band_tile(xcd_virtual(bx, gridDim.x), tiles_m, tiles_n, ti, tj);
-        t.batch = bz;
-        t.m0 = ti * GEMM_BM; t.n0 = tj * GEMM_BN; t.K = 2 * n;
-        return t.m0 < 2 * n && t.n0 < ncol;
+// square root (2n x 2n), C U the basis; W (2n x ncol) is [Re; Im] of the complex
+// product.  32 x 32 tiles, K split over two wavefronts, runs of tiles of one q
+// point on an XCD; matrix-core bound (64 q points of 64 atoms: 135 us, 202
+// through staged 64 x 64 tiles).
+__global__ __launch_bounds__(128) void per_recip_mz_kernel(MatBatch<double> M, PerEwald pr, int n2, int tiles_m, int tiles) {
+    typedef SplitK<2, 2, 2, 6> SK;
+    constexpr int TM = SK::TM, TN = SK::TN, LDC = SK::LDC;
+    __shared__ __align__(16) double cs[SK::LDS];
+    const int v = xcd_virtual(blockIdx.x, gridDim.x), q = v / tiles, t = v % tiles;
+    const int m0 = t % tiles_m * TM, g0 = t / tiles_m * TN;
+    {
+        SK sk;
+        sk.clear();
+        const double* Z = pr.Z + (long long)q * pr.sZ + (long long)g0 * pr.ldz;
+        sk.run_cols(M.at(q) + m0, M.ld, Z, pr.ldz, min(TN, pr.ncol - g0), n2);
+        sk.reduce<true>(cs);
     }
-    __device__ double a(const GemmTile& t, int m, int k) const {
-        return (m < 2 * n && k < 2 * n) ? M.at(t.batch)[m + (long long)k * M.ld] : 0.0;
+    double* W = pr.W + (long long)q * pr.sZ + (long long)g0 * pr.ldz + m0;
+#pragma unroll
+    for (int x = threadIdx.x; x < TM * TN; x += SK::NT) {
+        const int r = x % TM, c = x / TM;
+        if (m0 + r < n2 && g0 + c < pr.ncol) W[r + (long long)c * pr.ldz] = cs[c * LDC + r] + cs[(TN + c) * LDC + r];
     }
-    __device__ double b(const GemmTile& t, int k, int g) const {
-        if (k >= 2 * n || g >= ncol) return 0.0;
-        return cc[sd->atom_off + (k < n ? k : k - n) / 3] * Z[(long long)t.batch * sZ + k + (long long)g * ldz];
-    }
-    __device__ void store(const GemmTile& t, int m, int g, double v) const {
-        if (m < 2 * n && g < ncol) W[(long long)t.batch * sZ + m + (long long)g * ldz] = v;
-    }
-};
+}
 
 // Reciprocal term of the adjoint, per atom k and column g (k = G + q,
 // u = U_{k., g}, z = c_k sum_a conj(u_a) W_{ka, g}):
@@ -718,14 +715,14 @@ static void per_split(long long pairs, int nq, int lpp, int nimg, int& waves, in
     }
 }
 
-void per_recip_basis_launch(hipStream_t st, const SysDesc* sd, const double* qcart, int nq, const int* img,
-                            int nimg, const PerEwald& pr) {
+void per_recip_basis_launch(hipStream_t st, const SysDesc* sd, const double* cc, const double* qcart, int nq,
+                            const int* img, int nimg, const PerEwald& pr) {
     if (nq == 0) return;
     if (nimg > 0)
         hipLaunchKernelGGL(per_phase_kernel, dim3((unsigned)(((long long)nimg * nq + 255) / 256)), dim3(256), 0, st,
                            sd, qcart, nq, img, nimg, pr.phase);
     if (pr.ncol == 0) return;
-    hipLaunchKernelGGL(per_recip_basis_kernel, dim3(pr.ncol, nq), dim3(64), 0, st, sd, qcart, pr);
+    hipLaunchKernelGGL(per_recip_basis_kernel, dim3(pr.ncol, nq), dim3(64), 0, st, sd, cc, qcart, pr);
 }
 
 void mbd_assemble_periodic_launch(hipStream_t st, const SysDesc* sd, const double* om, const double* cc,
@@ -745,7 +742,7 @@ void mbd_assemble_periodic_launch(hipStream_t st, const SysDesc* sd, const doubl
     // always launched: besides the reciprocal term, the epilogue fills the
     // right block column and the FP32 copy
     hipLaunchKernelGGL((per_recip_asm_kernel<2, 2, 2, 4>), dim3(splitk_lower_tiles(3 * N, 32, 32), 2, nq), dim3(128), 0, st,
-                       sd, cc, pr, 3 * N, Q, Q32);
+                       pr, 3 * N, Q, Q32);
 }
 
 int per_recip_chunks(int ncol) { return (ncol + PER_RCOLS - 1) / PER_RCOLS; }
@@ -767,13 +764,8 @@ void mbd_grad_periodic_launch(hipStream_t st, const SysDesc* sd, const double* o
     else go(mbd_grad_periodic_kernel<4>);
     const int nchunk = per_recip_chunks(pr.ncol);
     if (nchunk > 0) {
-        PerRecMZProb p;
-        p.sd = sd; p.cc = cc; p.M = M; p.Z = pr.Z; p.W = pr.W; p.ldz = pr.ldz; p.sZ = pr.sZ; p.ncol = pr.ncol;
-        p.n = 3 * N;
-        p.tiles_m = (6 * N + GEMM_BM - 1) / GEMM_BM;
-        p.tiles_n = (pr.ncol + GEMM_BN - 1) / GEMM_BN;
-        hipLaunchKernelGGL((gemm_mfma_kernel<double, PerRecMZProb>), dim3(p.tiles_m * p.tiles_n, 1, nq), dim3(256),
-                           0, st, p);
+        const int tiles_m = (6 * N + 31) / 32, tiles = tiles_m * ((pr.ncol + 31) / 32);
+        hipLaunchKernelGGL(per_recip_mz_kernel, dim3(tiles * nq), dim3(128), 0, st, M, pr, 6 * N, tiles_m, tiles);
         hipLaunchKernelGGL(per_recip_grad_kernel, dim3(nq, nchunk), dim3(64), 0, st, sd, cc, qcart, pr, nchunk, rq,
                            rl);
     }

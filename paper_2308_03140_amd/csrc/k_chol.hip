@@ -15,10 +15,14 @@
 //                    inverts its factor, L11^-1, kept for the panel solve and
 //                    the triangular solves;
 //   panel            L21 = A21 L11^-T as a matrix-core product, in place.
-// The triangular solves go block row by block row, one launch per block:
-// every workgroup forms the block's solution from the (final) residual and
-// L11^-1, the first stores it, the others update the residual of their own
-// block row.
+// The triangular solves go by wide blocks of 256 rows: the inverses of the 64 x
+// 64 blocks are first extended to those of the wide diagonal blocks, then a
+// sweep alternates between a wide block's solution (its inverse times the
+// residual) and the update of the rows still to come, two launches per wide
+// block (16 matrices of order 3000: 0.24 ms a sweep and 0.11 for the inverses;
+// steps of 64 rows took 9.3 us each, 0.44 ms a sweep).
+#include <algorithm>
+
 #include "gemm_splitk.h"
 #include "mbd_internal.h"
 #include "mbd_kernels.h"
@@ -26,6 +30,14 @@
 
 #define CHOL_NB 64
 #define CHOL_NR 3  // right-hand sides per solve
+#define CHOL_WB 256  // wide blocks of the solves, and of the inverses' storage: matrix b's wide block w at w WB^2
+
+// inverse of the 64 x 64 diagonal block at k0 (column-major, leading dimension
+// CHOL_WB) within its wide block's
+__device__ __forceinline__ double* chol_inv_block(double* Linv, long long sLi, int b, int k0) {
+    const int o = k0 % CHOL_WB;
+    return Linv + (long long)b * sLi + (long long)(k0 / CHOL_WB) * CHOL_WB * CHOL_WB + o + (long long)o * CHOL_WB;
+}
 
 // ---------------------------------------------------------------------------
 // diagonal block: factor, invert the factor; identity padding past n
@@ -160,11 +172,11 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(MatBatch<double> A, doub
         const int j = j0 + 4 * u;
         if (ri < w && j < w && ri >= j) Ab[ri + j * ld] = L[ri][j];
     }
-    double* Xo = Linv + (long long)b * sLi + (long long)(k0 / CHOL_NB) * CHOL_NB * CHOL_NB;
+    double* Xo = chol_inv_block(Linv, sLi, b, k0);
 #pragma unroll
     for (int u = 0; u < PER; u++) {
         const int j = j0 + 4 * u;
-        Xo[ri + j * CHOL_NB] = X[ri][j];  // column-major, leading dimension 64
+        Xo[ri + j * CHOL_WB] = X[ri][j];
     }
 }
 
@@ -172,7 +184,7 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(MatBatch<double> A, doub
 // panel: L21 = A21 X^T (X = L11^-1), rows k0 + 64 .. n-1, in place: a tile
 // spans the panel's 64 columns, so a workgroup reads only the rows it writes.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void chol_panel_kernel(MatBatch<double> A, const double* Linv, long long sLi, int n,
+__global__ __launch_bounds__(256) void chol_panel_kernel(MatBatch<double> A, double* Linv, long long sLi, int n,
                                                           int k0) {
     typedef SplitK<2, 4, 4, 4> SK;
     __shared__ __align__(16) double cs[SK::LDS];
@@ -182,7 +194,7 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(MatBatch<double> A, con
         SK sk;
         sk.clear();
         // X^T(k, c) = X(c, k)
-        sk.run(Ab, A.ld, Linv + (long long)b * sLi + (long long)(k0 / CHOL_NB) * CHOL_NB * CHOL_NB, CHOL_NB, CHOL_NB);
+        sk.run(Ab, A.ld, chol_inv_block(Linv, sLi, b, k0), CHOL_WB, CHOL_NB);
         sk.reduce(cs);
     }
 #pragma unroll
@@ -222,110 +234,130 @@ __global__ __launch_bounds__(256, 3) void chol_update_kernel(MatBatch<double> A,
 }
 
 // ---------------------------------------------------------------------------
+// inverses of the wide diagonal blocks: X(i, j) = -X(i, i) sum_{j <= k < i} L(i,
+// k) X(k, j) over their 64 x 64 blocks, a block column per workgroup, 16 rows
+// per wavefront.  Grid (3, wide blocks, matrices).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void chol_wide_kernel(MatBatch<double> A, double* Linv, long long sLi, int n) {
+    __shared__ double T[CHOL_NB][CHOL_NB + 1];
+    typedef mfma4<double>::v Acc;
+    const int j = blockIdx.x, w0 = blockIdx.y * CHOL_WB, b = blockIdx.z, lane = threadIdx.x & 63;
+    const int nb = (min(CHOL_WB, n - w0) + CHOL_NB - 1) / CHOL_NB, m0 = 16 * (threadIdx.x >> 6);
+    const int m = lane & 15, kl = lane >> 4;
+    double* X = chol_inv_block(Linv, sLi, b, w0);
+    const double* L = A.at(b) + w0 + (long long)w0 * A.ld;
+    for (int i = j + 1; i < nb; i++) {
+        Acc acc[4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
+        const int row = CHOL_NB * i + m0 + m;
+        const bool in = w0 + row < n;  // rows past n hold no factor
+#pragma unroll 4
+        for (int k = CHOL_NB * j; k < CHOL_NB * i; k += 4) {
+            const double a = in ? L[row + (long long)(k + kl) * A.ld] : 0.0;
+#pragma unroll
+            for (int c = 0; c < 4; c++) acc[c] = mfma16x16x4(a, X[k + kl + (CHOL_NB * j + 16 * c + m) * CHOL_WB], acc[c]);
+        }
+        __syncthreads();  // the previous block's readers of T
+#pragma unroll
+        for (int c = 0; c < 4; c++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) T[m0 + mfma_rows<double>::row(lane, r)][16 * c + m] = acc[c][r];
+        __syncthreads();
+        Acc x[4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll 4
+        for (int k = 0; k < CHOL_NB; k += 4) {
+            const double a = -X[row + (CHOL_NB * i + k + kl) * CHOL_WB];
+#pragma unroll
+            for (int c = 0; c < 4; c++) x[c] = mfma16x16x4(a, T[k + kl][16 * c + m], x[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; c++)
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                X[CHOL_NB * i + m0 + mfma_rows<double>::row(lane, r) + (CHOL_NB * j + 16 * c + m) * CHOL_WB] = x[c][r];
+        __syncthreads();  // X(i, j), global memory, before the next block row reads it
+    }
+}
+
+// ---------------------------------------------------------------------------
 // triangular solves; right-hand sides row-major [n][CHOL_NR] per matrix
 // ---------------------------------------------------------------------------
-// 64 x 64 block of a column-major matrix into LDS, all loads in flight
-// together (rows and columns clamped, values outside masked to zero)
-__device__ __forceinline__ void chol_stage(double (*S)[CHOL_NB + 1], const double* src, long long ld, int rows,
-                                           int cols) {
-    constexpr int PER = CHOL_NB * CHOL_NB / 256;
-    const int i = threadIdx.x & (CHOL_NB - 1), j0 = threadIdx.x >> 6;
-    double v[PER];
-#pragma unroll
-    for (int u = 0; u < PER; u++) {
-        const int j = j0 + 4 * u;
-        v[u] = src[min(i, rows - 1) + (long long)min(j, cols - 1) * ld];
+// Forward step of the wide block at w0.  SUB: 64 rows below it per workgroup,
+// R -= L Y; else its own, Y = X R.  A row per lane (columns of M are
+// contiguous), a quarter of the columns per wavefront.  Bandwidth bound.
+template <bool SUB>
+__global__ __launch_bounds__(256) void chol_fwd_kernel(MatBatch<double> A, double* Linv, long long sLi, int n, int w0,
+                                                        double* R, double* Y, long long sR) {
+    __shared__ double vs[CHOL_WB][CHOL_NR], part[4][CHOL_NB][CHOL_NR];
+    const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, pt = tid >> 6, rb = CHOL_NB * blockIdx.x;
+    const double* V = (SUB ? Y : R) + (long long)b * sR + (long long)w0 * CHOL_NR;
+    const int cols = SUB ? CHOL_WB : rb + CHOL_NB;  // X is lower triangular
+    for (int x = tid; x < cols * CHOL_NR; x += 256)
+        vs[x / CHOL_NR][x % CHOL_NR] = w0 + x / CHOL_NR < n ? V[x] : 0.0;
+    const int row = (SUB ? w0 + CHOL_WB : 0) + rb + lane;
+    const long long ld = SUB ? A.ld : CHOL_WB;
+    const double* M = SUB ? A.at(b) + min(row, n - 1) + (long long)w0 * ld : chol_inv_block(Linv, sLi, b, w0) + row;
+    __syncthreads();
+    double s[CHOL_NR] = {0.0, 0.0, 0.0};
+    const int cq = cols / 4;
+#pragma unroll 16
+    for (int c = pt * cq; c < (pt + 1) * cq; c++) {
+        const double m = M[c * ld];
+        for (int k = 0; k < CHOL_NR; k++) s[k] += m * vs[c][k];
     }
-#pragma unroll
-    for (int u = 0; u < PER; u++) {
-        const int j = j0 + 4 * u;
-        S[i][j] = (i < rows && j < cols) ? v[u] : 0.0;
+    for (int k = 0; k < CHOL_NR; k++) part[pt][lane][k] = s[k];
+    __syncthreads();
+    if (tid < CHOL_NB * CHOL_NR) {
+        const int i = tid / CHOL_NR, k = tid % CHOL_NR, g = (SUB ? w0 + CHOL_WB : w0) + rb + i;
+        const double v = (part[0][i][k] + part[1][i][k]) + (part[2][i][k] + part[3][i][k]);
+        if (g < n) {
+            const long long o = (long long)b * sR + (long long)g * CHOL_NR + k;
+            if (SUB) R[o] -= v;
+            else Y[o] = v;
+        }
     }
 }
 
-// forward step for block kb: y_kb = X_kb r_kb; workgroup 0 stores it, workgroup
-// j >= 1 updates the residual of block kb + j: r -= L(kb + j, kb) y_kb
-__global__ __launch_bounds__(256) void chol_fwd_kernel(MatBatch<double> A, const double* Linv, long long sLi, int n,
-                                                        int kb, double* R, double* Y, long long sR) {
-    __shared__ double Xs[CHOL_NB][CHOL_NB + 1];
-    __shared__ double Ls[CHOL_NB][CHOL_NB + 1];
-    __shared__ double rs[CHOL_NB][CHOL_NR];
-    __shared__ double ys[CHOL_NB][CHOL_NR];
-    const int b = blockIdx.z, j = blockIdx.x, tid = threadIdx.x;
-    const int r0 = kb * CHOL_NB, q0 = (kb + j) * CHOL_NB;
-    double* Rb = R + (long long)b * sR;
-    const double rv = tid < CHOL_NB * CHOL_NR && r0 + tid / CHOL_NR < n
-                          ? Rb[(long long)r0 * CHOL_NR + tid] : 0.0;
-    chol_stage(Xs, Linv + (long long)b * sLi + (long long)kb * CHOL_NB * CHOL_NB, CHOL_NB, CHOL_NB, CHOL_NB);
-    if (j > 0) chol_stage(Ls, A.at(b) + q0 + (long long)r0 * A.ld, A.ld, min(CHOL_NB, n - q0), min(CHOL_NB, n - r0));
-    if (tid < CHOL_NB * CHOL_NR) rs[tid / CHOL_NR][tid % CHOL_NR] = rv;
-    __syncthreads();
-    if (tid < CHOL_NB * CHOL_NR) {
-        const int i = tid / CHOL_NR, c = tid % CHOL_NR;
-        double s = 0.0;
-#pragma unroll 8
-        for (int l = 0; l <= i; l++) s += Xs[i][l] * rs[l][c];
-        ys[i][c] = s;
+// Backward step of the wide block at w0.  SUB: 64 columns left of it per
+// workgroup, Y -= L^T Xo; else its own, Xo = X^T Y.  16 columns per wavefront,
+// the rows over its lanes.
+template <bool SUB>
+__global__ __launch_bounds__(256) void chol_bwd_kernel(MatBatch<double> A, double* Linv, long long sLi, int n, int w0,
+                                                        double* Y, double* Xo, long long sR) {
+    const int b = blockIdx.y, lane = threadIdx.x & 63, c0 = CHOL_NB * blockIdx.x + 16 * (threadIdx.x >> 6);
+    const double* V = (SUB ? Xo : Y) + (long long)b * sR + (long long)w0 * CHOL_NR;
+    const long long ld = SUB ? A.ld : CHOL_WB;
+    const double* M = SUB ? A.at(b) + w0 + (long long)c0 * ld : chol_inv_block(Linv, sLi, b, w0) + (long long)c0 * ld;
+    const int rows = min(CHOL_WB, n - w0);
+    double s[CHOL_NR][16] = {};
+    for (int r0 = SUB ? 0 : CHOL_NB * blockIdx.x; r0 < rows; r0 += CHOL_NB) {
+        const int r = r0 + lane;
+        const bool in = r < rows;
+        double v[CHOL_NR], m[16];
+#pragma unroll
+        for (int k = 0; k < CHOL_NR; k++) v[k] = in ? V[(long long)r * CHOL_NR + k] : 0.0;
+#pragma unroll
+        for (int c = 0; c < 16; c++) m[c] = in ? M[r + c * ld] : 0.0;
+#pragma unroll
+        for (int c = 0; c < 16; c++)
+#pragma unroll
+            for (int k = 0; k < CHOL_NR; k++) s[k][c] += m[c] * v[k];
     }
-    __syncthreads();
-    if (j == 0) {
-        if (tid < CHOL_NB * CHOL_NR && r0 + tid / CHOL_NR < n)
-            Y[(long long)b * sR + (long long)r0 * CHOL_NR + tid] = ys[tid / CHOL_NR][tid % CHOL_NR];
-        return;
-    }
-    if (tid < CHOL_NB * CHOL_NR) {
-        const int i = tid / CHOL_NR, c = tid % CHOL_NR;
-        double s = 0.0;
-#pragma unroll 8
-        for (int l = 0; l < CHOL_NB; l++) s += Ls[i][l] * ys[l][c];
-        if (q0 + i < n) Rb[(long long)(q0 + i) * CHOL_NR + c] -= s;
-    }
-}
-
-// backward step for block kb: x_kb = X_kb^T y_kb; workgroup 0 stores it,
-// workgroup j >= 1 updates block kb - j: y -= L(kb, kb - j)^T x_kb
-__global__ __launch_bounds__(256) void chol_bwd_kernel(MatBatch<double> A, const double* Linv, long long sLi, int n,
-                                                        int kb, double* Yr, double* Xo, long long sR) {
-    __shared__ double Xs[CHOL_NB][CHOL_NB + 1];
-    __shared__ double Ls[CHOL_NB][CHOL_NB + 1];
-    __shared__ double rs[CHOL_NB][CHOL_NR];
-    __shared__ double xs[CHOL_NB][CHOL_NR];
-    const int b = blockIdx.z, j = blockIdx.x, tid = threadIdx.x;
-    const int r0 = kb * CHOL_NB, q0 = (kb - j) * CHOL_NB;
-    double* Yb = Yr + (long long)b * sR;
-    const double rv = tid < CHOL_NB * CHOL_NR && r0 + tid / CHOL_NR < n
-                          ? Yb[(long long)r0 * CHOL_NR + tid] : 0.0;
-    chol_stage(Xs, Linv + (long long)b * sLi + (long long)kb * CHOL_NB * CHOL_NB, CHOL_NB, CHOL_NB, CHOL_NB);
-    // L(kb, kb - j): rows r0.., columns q0.. (below the diagonal)
-    if (j > 0) chol_stage(Ls, A.at(b) + r0 + (long long)q0 * A.ld, A.ld, min(CHOL_NB, n - r0), CHOL_NB);
-    if (tid < CHOL_NB * CHOL_NR) rs[tid / CHOL_NR][tid % CHOL_NR] = rv;
-    __syncthreads();
-    if (tid < CHOL_NB * CHOL_NR) {
-        const int i = tid / CHOL_NR, c = tid % CHOL_NR;
-        double s = 0.0;
-#pragma unroll 8
-        for (int l = i; l < CHOL_NB; l++) s += Xs[l][i] * rs[l][c];
-        xs[i][c] = s;
-    }
-    __syncthreads();
-    if (j == 0) {
-        if (tid < CHOL_NB * CHOL_NR && r0 + tid / CHOL_NR < n)
-            Xo[(long long)b * sR + (long long)r0 * CHOL_NR + tid] = xs[tid / CHOL_NR][tid % CHOL_NR];
-        return;
-    }
-    if (tid < CHOL_NB * CHOL_NR) {
-        const int i = tid / CHOL_NR, c = tid % CHOL_NR;
-        double s = 0.0;
-#pragma unroll 8
-        for (int l = 0; l < CHOL_NB; l++) s += Ls[l][i] * xs[l][c];
-        Yb[(long long)(q0 + i) * CHOL_NR + c] -= s;
+    const int g = (SUB ? 0 : w0) + c0 + (lane >> 2);  // lane l gets the sum of column l / 4
+#pragma unroll
+    for (int k = 0; k < CHOL_NR; k++) {
+        const double t = wave_sum16(s[k]);
+        if ((lane & 3) == 0 && g < n) {
+            const long long o = (long long)b * sR + (long long)g * CHOL_NR + k;
+            if (SUB) Y[o] -= t;
+            else Xo[o] = t;
+        }
     }
 }
 
 // ---------------------------------------------------------------------------
 // host
 // ---------------------------------------------------------------------------
-long long chol_linv_stride(int n) { return (long long)((n + CHOL_NB - 1) / CHOL_NB) * CHOL_NB * CHOL_NB; }
+long long chol_linv_stride(int n) { return (long long)((n + CHOL_WB - 1) / CHOL_WB) * CHOL_WB * CHOL_WB; }
 
 void chol_factor_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, unsigned* status) {
     const long long sLi = chol_linv_stride(n);
@@ -339,17 +371,29 @@ void chol_factor_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, d
         if (rows > 0)
             hipLaunchKernelGGL(chol_panel_kernel, dim3((rows + 31) / 32, nbatch), dim3(256), 0, st, A, Linv, sLi, n, k0);
     }
+    if (n > CHOL_NB)
+        hipLaunchKernelGGL(chol_wide_kernel, dim3(CHOL_WB / CHOL_NB - 1, (n + CHOL_WB - 1) / CHOL_WB, nbatch), dim3(256), 0, st,
+                           A, Linv, sLi, n);
 }
 
 // X = A^-1 B from the factor: B in R (overwritten), Y scratch, X out; all
 // [nbatch][n][CHOL_NR] with per-matrix stride sR
-void chol_solve_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, const double* Linv, double* R, double* Y,
+void chol_solve_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, double* R, double* Y,
                        double* X, long long sR) {
     const long long sLi = chol_linv_stride(n);
-    const int nblk = (n + CHOL_NB - 1) / CHOL_NB;
-    for (int kb = 0; kb < nblk; kb++)
-        hipLaunchKernelGGL(chol_fwd_kernel, dim3(nblk - kb, 1, nbatch), dim3(256), 0, st, A, Linv, sLi, n, kb, R, Y,
-                           sR);
-    for (int kb = nblk - 1; kb >= 0; kb--)
-        hipLaunchKernelGGL(chol_bwd_kernel, dim3(kb + 1, 1, nbatch), dim3(256), 0, st, A, Linv, sLi, n, kb, Y, X, sR);
+    auto blocks = [](int k) { return (k + CHOL_NB - 1) / CHOL_NB; };
+    for (int w0 = 0; w0 < n; w0 += CHOL_WB) {
+        hipLaunchKernelGGL(chol_fwd_kernel<false>, dim3(blocks(std::min(CHOL_WB, n - w0)), nbatch), dim3(256), 0, st, A, Linv,
+                           sLi, n, w0, R, Y, sR);
+        if (w0 + CHOL_WB < n)
+            hipLaunchKernelGGL(chol_fwd_kernel<true>, dim3(blocks(n - w0 - CHOL_WB), nbatch), dim3(256), 0, st, A, Linv, sLi, n,
+                               w0, R, Y, sR);
+    }
+    for (int w0 = (n - 1) / CHOL_WB * CHOL_WB; w0 >= 0; w0 -= CHOL_WB) {
+        hipLaunchKernelGGL(chol_bwd_kernel<false>, dim3(blocks(std::min(CHOL_WB, n - w0)), nbatch), dim3(256), 0, st, A, Linv,
+                           sLi, n, w0, Y, X, sR);
+        if (w0 > 0)
+            hipLaunchKernelGGL(chol_bwd_kernel<true>, dim3(w0 / CHOL_NB, nbatch), dim3(256), 0, st, A, Linv, sLi, n, w0, Y, X,
+                               sR);
+    }
 }

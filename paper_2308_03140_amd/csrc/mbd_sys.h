@@ -163,5 +163,5 @@ void scs_grad_launch(hipStream_t st, const SysDesc* sd, int N, int nf, const dou
 // right-hand sides, layout [nbatch][n][3] with per-matrix stride sR
 long long chol_linv_stride(int n);
 void chol_factor_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, unsigned* status);
-void chol_solve_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, const double* Linv, double* R, double* Y,
+void chol_solve_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, double* R, double* Y,
                        double* X, long long sR);

@@ -1,7 +1,7 @@
 """Screening at the edges of the Cholesky panels and tiles (orders 3 N around
-16, 32, 64, 128 and 192) against the oracle: the screened parameters to the
-1e-12 of the screening stage, the forces, whose chain rule solves with the
-same factors, to the path's 1e-6."""
+16, 32, 64, 128, 192, 256, 320 and 512) against the oracle: the screened
+parameters to the 1e-12 of the screening stage, the forces, whose chain rule
+solves with the same factors, to the path's 1e-6."""
 import numpy as np
 import pytest
 
@@ -20,7 +20,7 @@ def ctx():
     c.close()
 
 
-@pytest.mark.parametrize("N", [3, 5, 6, 11, 16, 21, 22, 42, 43, 64, 65])
+@pytest.mark.parametrize("N", [3, 5, 6, 11, 16, 21, 22, 42, 43, 64, 65, 85, 86, 107, 171])
 def test_blocks(ctx, N):
     from paper_2308_03140_amd import torch_api as T
     print("scs blocks N=%d" % N, flush=True)

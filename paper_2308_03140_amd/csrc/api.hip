@@ -1353,8 +1353,9 @@ mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, u
     double* V = wsT<double>(c, "scs_v", (size_t)sR * nf);
     double* abar = wsT<double>(c, "scs_abar", (size_t)nf * N);
     double* par = wsT<double>(c, "scs_par", (size_t)4 * N);
+    double* sig2 = wsT<double>(c, "scs_sig2", (size_t)nf * N);
     MatBatch<double> A = {wsT<double>(c, "scsA", (size_t)stride * nf), ld, stride};
-    if (!sd_dev || !status || !om0 || !cc0 || !u_dev || !wq_dev || !linv || !rhs || !ytmp || !V || !abar || !par ||
+    if (!sd_dev || !status || !om0 || !cc0 || !u_dev || !wq_dev || !linv || !rhs || !ytmp || !V || !abar || !par || !sig2 ||
         !A.p)
         return (mbd_status)c->err_code;
     HIPCHK(hipMemcpyAsync(sd_dev, &base, sizeof(SysDesc), hipMemcpyHostToDevice, st), "upload");
@@ -1366,7 +1367,7 @@ mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, u
     // V = A(u)^-1 (1 (x) I_3) from them
     {
         PhaseTimer ph(&c->prof, st, 9);
-        scs_assemble_launch(st, sd_dev, N, om0, u_dev, nf, A, status);
+        scs_assemble_launch(st, sd_dev, N, om0, u_dev, nf, sig2, A, status);
         chol_factor_launch(st, A, n, nf, linv, status);
         scs_rhs_launch(st, N, nf, nullptr, rhs);
         chol_solve_launch(st, A, n, nf, linv, rhs, ytmp, V, sR);
@@ -1416,7 +1417,7 @@ mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, u
         scs_weights_launch(st, N, nf, par, abar, wq_dev, gpar, gpar + N, gpar + 2 * N, w);
         scs_rhs_launch(st, N, nf, w, rhs);
         chol_solve_launch(st, A, n, nf, linv, rhs, ytmp, U, sR);
-        scs_grad_launch(st, sd_dev, N, nf, om0, u_dev, U, V, UV, out->grad_coords);
+        scs_grad_launch(st, sd_dev, N, nf, sig2, U, V, UV, out->grad_coords);
         HIPCHK(hipGetLastError(), "scs gradient");
         HIPCHK(hipStreamSynchronize(st), "synchronize");
     }

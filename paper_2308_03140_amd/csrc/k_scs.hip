@@ -46,52 +46,64 @@ __device__ __forceinline__ void scs_fermi(double d, double R0, double a, double&
     dg_dd = a / R0 * g * omg;
 }
 
-// T^GG = C1 delta + C2 r r^T and the radial derivatives C1', C2'
-__device__ __forceinline__ void tgg_coeffs(double d, double s, double& c1, double& c2, double& c1p, double& c2p) {
-    const double z = d / s, z2 = z * z;
+// T^GG = C1 delta + C2 r r^T and the radial derivatives C1', C2'; id = 1/d, s2 =
+// sigma_i^2 + sigma_j^2
+__device__ __forceinline__ void tgg_coeffs(double d, double id, double s2, double& c1, double& c2, double& c1p, double& c2p) {
+    double s, is;
+    sqrt_recip(s2, s, is);
+    const double z = d * is, z2 = z * z;
     const double th = 2.0 * z / SCS_SQRT_PI * exp(-z2);
     const double em = erf(z) - th;
-    const double id = 1.0 / d, id2 = id * id;
+    const double id2 = id * id;
     c1 = em * id2 * id;
     c2 = (2.0 * z2 * th - 3.0 * em) * id2 * id2 * id;
     c1p = (2.0 * z2 * th - 3.0 * em) * id2 * id2;
     c2p = (15.0 * em - 10.0 * z2 * th - 4.0 * z2 * z2 * th) * id2 * id2 * id2;
 }
 
-// A(u_f) for f = 0..nf-1 (u_0 = 0), both triangles; 16 x 16 atom pairs per
-// workgroup, grid (ceil(N/16), ceil(N/16), nf)
-__global__ __launch_bounds__(256) void scs_assemble_kernel(const SysDesc* sd, const double* om, const double* u,
-                                                             MatBatch<double> A, unsigned* status) {
+// sigma_i(u_f)^2, [nf][N]
+__global__ __launch_bounds__(256) void scs_sigma_kernel(const SysDesc* sd, const double* om, const double* u, double* sig2) {
     const SysDesc& S = sd[0];
-    const int f = blockIdx.z;
+    const int i = blockIdx.x * 256 + threadIdx.x, f = blockIdx.y;
+    if (i >= S.N) return;
+    const double s = scs_sigma(S.alpha0[i] / (1.0 + u[f] * u[f] / (om[i] * om[i])));
+    sig2[(long long)f * S.N + i] = s * s;
+}
+
+// A(u_f) for f = 0..nf-1 (u_0 = 0), the lower triangle; 16 x 16 atom pairs i >= j
+// per workgroup, the distance and the damping once for all frequencies.  Bound
+// by exp and erf and the stores (1000 atoms, 16 frequencies: 118 us, 261 with
+// a pair and two cube roots per frequency and both triangles).
+__global__ __launch_bounds__(256) void scs_assemble_kernel(const SysDesc* sd, const double* om, const double* u,
+                                                             const double* sig2, int nf, MatBatch<double> A,
+                                                             unsigned* status) {
+    const SysDesc& S = sd[0];
+    const int N = S.N;
     const int i = blockIdx.x * 16 + (threadIdx.x & 15);
     const int j = blockIdx.y * 16 + (threadIdx.x >> 4);
-    if (i >= S.N || j >= S.N) return;
-    const double uf = u[f];
-    const double wi = om[i], wj = om[j];
-    const double ai = S.alpha0[i] / (1.0 + uf * uf / (wi * wi));
-    double v[3][3];
-    if (i == j) {
-        for (int p = 0; p < 3; p++)
-            for (int q = 0; q < 3; q++) v[p][q] = p == q ? 1.0 / ai : 0.0;
-    } else {
-        const double aj = S.alpha0[j] / (1.0 + uf * uf / (wj * wj));
-        const double* R = S.coords;
-        const double r[3] = {R[3 * j] - R[3 * i], R[3 * j + 1] - R[3 * i + 1], R[3 * j + 2] - R[3 * i + 2]};
-        double d = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
-        const bool coincident = !(d >= 1e-8);
-        if (coincident) { atomicOr(&status[0], MBD_ST_COINCIDENT); d = 1.0; }
-        const double si = scs_sigma(ai), sj = scs_sigma(aj);
-        double c1, c2, c1p, c2p, omg, gd;
-        tgg_coeffs(d, sqrt(si * si + sj * sj), c1, c2, c1p, c2p);
-        scs_fermi(d, S.beta * (S.rvdw[i] + S.rvdw[j]), S.a, omg, gd);
-        const double pre = coincident ? 0.0 : omg;
-        for (int p = 0; p < 3; p++)
-            for (int q = 0; q < 3; q++) v[p][q] = pre * ((p == q ? c1 : 0.0) + c2 * r[p] * r[q]);
+    if (i >= N || j > i) return;
+    const double* R = S.coords;
+    const double r[3] = {R[3 * j] - R[3 * i], R[3 * j + 1] - R[3 * i + 1], R[3 * j + 2] - R[3 * i + 2]};
+    double d = i == j ? 1.0 : sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+    const bool coincident = !(d >= 1e-8);
+    if (coincident) { atomicOr(&status[0], MBD_ST_COINCIDENT); d = 1.0; }
+    const double id = 1.0 / d;
+    double omg, gd;
+    scs_fermi(d, S.beta * (S.rvdw[i] + S.rvdw[j]), S.a, omg, gd);
+    const double pre = coincident ? 0.0 : omg;
+    for (int f = 0; f < nf; f++) {
+        double c1, c2, c1p, c2p;
+        tgg_coeffs(d, id, sig2[(long long)f * N + i] + sig2[(long long)f * N + j], c1, c2, c1p, c2p);
+        c1 *= pre;
+        c2 *= pre;
+        if (i == j) {
+            c1 = (1.0 + u[f] * u[f] / (om[i] * om[i])) / S.alpha0[i];
+            c2 = 0.0;
+        }
+        double* a = A.at(f) + 3 * i + (long long)(3 * j) * A.ld;
+        for (int q = 0; q < 3; q++)
+            for (int p = 0; p < 3; p++) a[p + (long long)q * A.ld] = (p == q ? c1 : 0.0) + c2 * r[p] * r[q];
     }
-    double* Ab = A.at(f);
-    for (int q = 0; q < 3; q++)
-        for (int p = 0; p < 3; p++) Ab[(3 * i + p) + (long long)(3 * j + q) * A.ld] = v[p][q];
 }
 
 // right-hand sides R_f[3i+a][c] = x_i delta_ac, x_i = 1 (contraction) or the
@@ -161,9 +173,11 @@ __global__ __launch_bounds__(256) void scs_weights_kernel(int N, int nf, const d
 }
 
 // dE/dR_m += sum_f (1/3) sum_{l != m} sum_pq [d T^scs_pq / d r_c] H_ml[p][q];
-// one workgroup per atom m
-__global__ __launch_bounds__(256) void scs_grad_kernel(const SysDesc* sd, const double* om, const double* u, int nf,
-                                                         const double* UV, double* grad) {
+// one workgroup per atom m, a lane per atom l, its frequencies in turn (distance
+// and damping once; 1000 atoms, 16 frequencies: 191 us, 386 with a pair and
+// two cube roots per frequency)
+__global__ __launch_bounds__(256) void scs_grad_kernel(const SysDesc* sd, const double* sig2, int nf, const double* UV,
+                                                         double* grad) {
     __shared__ double red[4];
     const SysDesc& S = sd[0];
     const int N = S.N;
@@ -171,44 +185,42 @@ __global__ __launch_bounds__(256) void scs_grad_kernel(const SysDesc* sd, const 
     if (m >= N) return;
     const double* R = S.coords;
     double g0 = 0.0, g1 = 0.0, g2 = 0.0;
-    for (long long t = threadIdx.x; t < (long long)nf * N; t += 256) {
-        const int f = (int)(t / N), l = (int)(t % N);
+    for (int l = threadIdx.x; l < N; l += 256) {
         if (l == m) continue;
-        const double uf = u[f];
-        const double am = S.alpha0[m] / (1.0 + uf * uf / (om[m] * om[m]));
-        const double al = S.alpha0[l] / (1.0 + uf * uf / (om[l] * om[l]));
         const double r[3] = {R[3 * l] - R[3 * m], R[3 * l + 1] - R[3 * m + 1], R[3 * l + 2] - R[3 * m + 2]};
-        const double d = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
-        const double sm = scs_sigma(am), sl = scs_sigma(al);
-        double c1, c2, c1p, c2p, omg, gd;
-        tgg_coeffs(d, sqrt(sm * sm + sl * sl), c1, c2, c1p, c2p);
+        const double d = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]), id = 1.0 / d;
+        double omg, gd;
         scs_fermi(d, S.beta * (S.rvdw[m] + S.rvdw[l]), S.a, omg, gd);
-        const double* Um = UV + ((long long)f * 3 * N + 3 * m) * 6;
-        const double* Ul = UV + ((long long)f * 3 * N + 3 * l) * 6;
-        // H[p][q] = sum_a (U_a(3m+p) V_a(3l+q) + U_a(3l+q) V_a(3m+p))
-        double H[3][3];
-        for (int p = 0; p < 3; p++)
-            for (int q = 0; q < 3; q++) {
-                double h = 0.0;
-                for (int a = 0; a < 3; a++) h += Um[6 * p + a] * Ul[6 * q + 3 + a] + Ul[6 * q + a] * Um[6 * p + 3 + a];
-                H[p][q] = h;
+        for (int f = 0; f < nf; f++) {
+            double c1, c2, c1p, c2p;
+            tgg_coeffs(d, id, sig2[(long long)f * N + m] + sig2[(long long)f * N + l], c1, c2, c1p, c2p);
+            const double* Um = UV + ((long long)f * 3 * N + 3 * m) * 6;
+            const double* Ul = UV + ((long long)f * 3 * N + 3 * l) * 6;
+            // H[p][q] = sum_a (U_a(3m+p) V_a(3l+q) + U_a(3l+q) V_a(3m+p))
+            double H[3][3];
+            for (int p = 0; p < 3; p++)
+                for (int q = 0; q < 3; q++) {
+                    double h = 0.0;
+                    for (int a = 0; a < 3; a++) h += Um[6 * p + a] * Ul[6 * q + 3 + a] + Ul[6 * q + a] * Um[6 * p + 3 + a];
+                    H[p][q] = h;
+                }
+            // sum_pq H_pq T^GG_pq and sum_pq H_pq r_p r_q, for the radial terms
+            double hT = 0.0, hrr = 0.0, hd = 0.0, Hr[3] = {0.0, 0.0, 0.0};
+            for (int p = 0; p < 3; p++) {
+                hd += H[p][p];
+                for (int q = 0; q < 3; q++) {
+                    hrr += H[p][q] * r[p] * r[q];
+                    Hr[p] += (H[p][q] + H[q][p]) * r[q];
+                }
             }
-        // sum_pq H_pq T^GG_pq and sum_pq H_pq r_p r_q, for the radial terms
-        double hT = 0.0, hrr = 0.0, hd = 0.0, Hr[3] = {0.0, 0.0, 0.0};
-        for (int p = 0; p < 3; p++) {
-            hd += H[p][p];
-            for (int q = 0; q < 3; q++) {
-                hrr += H[p][q] * r[p] * r[q];
-                Hr[p] += (H[p][q] + H[q][p]) * r[q];
-            }
+            hT = c1 * hd + c2 * hrr;
+            // d/dr_c [(1-g) (C1 delta + C2 r r^T)] contracted with H:
+            //   -g' r_c/d hT + (1-g) [(C1' hd + C2' hrr) r_c/d + C2 (H r + H^T r)_c]
+            const double rad = (omg * (c1p * hd + c2p * hrr) - gd * hT) * id;
+            g0 += rad * r[0] + omg * c2 * Hr[0];
+            g1 += rad * r[1] + omg * c2 * Hr[1];
+            g2 += rad * r[2] + omg * c2 * Hr[2];
         }
-        hT = c1 * hd + c2 * hrr;
-        // d/dr_c [(1-g) (C1 delta + C2 r r^T)] contracted with H:
-        //   -g' r_c/d hT + (1-g) [(C1' hd + C2' hrr) r_c/d + C2 (H r + H^T r)_c]
-        const double rad = -gd * hT / d + omg * (c1p * hd + c2p * hrr) / d;
-        g0 += rad * r[0] + omg * c2 * Hr[0];
-        g1 += rad * r[1] + omg * c2 * Hr[1];
-        g2 += rad * r[2] + omg * c2 * Hr[2];
     }
     g0 = block_sum256(g0, red);
     g1 = block_sum256(g1, red);
@@ -221,9 +233,10 @@ __global__ __launch_bounds__(256) void scs_grad_kernel(const SysDesc* sd, const 
 }
 
 void scs_assemble_launch(hipStream_t st, const SysDesc* sd, int N, const double* om, const double* u, int nf,
-                         MatBatch<double> A, unsigned* status) {
+                         double* sig2, MatBatch<double> A, unsigned* status) {
     const int g = (N + 15) / 16;
-    hipLaunchKernelGGL(scs_assemble_kernel, dim3(g, g, nf), dim3(256), 0, st, sd, om, u, A, status);
+    hipLaunchKernelGGL(scs_sigma_kernel, dim3((N + 255) / 256, nf), dim3(256), 0, st, sd, om, u, sig2);
+    hipLaunchKernelGGL(scs_assemble_kernel, dim3(g, g), dim3(256), 0, st, sd, om, u, sig2, nf, A, status);
 }
 void scs_rhs_launch(hipStream_t st, int N, int nf, const double* w, double* R) {
     const long long tot = (long long)nf * N * 9;
@@ -242,10 +255,10 @@ void scs_weights_launch(hipStream_t st, int N, int nf, const double* par, const 
     hipLaunchKernelGGL(scs_weights_kernel, dim3((N + 255) / 256, nf), dim3(256), 0, st, N, nf, par, abar, wq, ga, gw,
                        gv, w);
 }
-void scs_grad_launch(hipStream_t st, const SysDesc* sd, int N, int nf, const double* om, const double* u,
-                     const double* U, const double* V, double* UV, double* grad) {
+void scs_grad_launch(hipStream_t st, const SysDesc* sd, int N, int nf, const double* sig2, const double* U,
+                     const double* V, double* UV, double* grad) {
     const int n = 3 * N;
     hipLaunchKernelGGL(scs_pack_uv_kernel, dim3((unsigned)(((long long)nf * n + 255) / 256)), dim3(256), 0, st, n, nf,
                        U, V, UV);
-    hipLaunchKernelGGL(scs_grad_kernel, dim3(N), dim3(256), 0, st, sd, om, u, nf, UV, grad);
+    hipLaunchKernelGGL(scs_grad_kernel, dim3(N), dim3(256), 0, st, sd, sig2, nf, UV, grad);
 }

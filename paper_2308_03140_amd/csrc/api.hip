@@ -1116,27 +1116,26 @@ mbd_status mbd_ts_evaluate(mbd_ctx* c, const mbd_system* s, unsigned want, mbd_r
         if (r != MBD_OK) return r;
     }
     const int N = s->n_atoms;
-    // the descriptor and its zeroed status word go up in one copy
-    struct {
-        SysDesc d;
-        unsigned status;
-    } up = {d, 0u};
-    SysDesc* sd_dev = (SysDesc*)ws(c, "sysdesc", sizeof(up));
-    unsigned* status = (unsigned*)(sd_dev + 1);
+    // the descriptor, its zeroed status word and the lattice vectors go up in one copy
+    const size_t nimg3 = ps.img.size(), nrec3 = ps.rec.size();
+    std::vector<char> up(sizeof(SysDesc) + sizeof(int) * (2 + nimg3 + nrec3), 0);
+    char* up_dev = (char*)ws(c, "sysdesc", up.size());
     double* om = wsT<double>(c, "om", N);
     double* cc = wsT<double>(c, "cc", N);
     double* eatom = wsT<double>(c, "ts_eatom", N);
-    int* img = wsT<int>(c, "img", std::max<size_t>(3, ps.img.size()));
-    int* rec = wsT<int>(c, "rec", std::max<size_t>(3, ps.rec.size()));
-    if (!sd_dev || !om || !cc || !eatom || !img || !rec) return (mbd_status)c->err_code;
-    HIPCHK(hipMemcpyAsync(sd_dev, &up, sizeof(up), hipMemcpyHostToDevice, st), "upload");
-    if (periodic) {
-        HIPCHK(hipMemcpyAsync(img, ps.img.data(), sizeof(int) * ps.img.size(), hipMemcpyHostToDevice, st), "upload");
-        HIPCHK(hipMemcpyAsync(rec, ps.rec.data(), sizeof(int) * ps.rec.size(), hipMemcpyHostToDevice, st), "upload");
-    }
+    void* scratch = ws(c, "ts_part", periodic ? mbd_ts_scratch(N, (int)nrec3 / 3) : 0);
+    if (!up_dev || !om || !cc || !eatom || !scratch) return (mbd_status)c->err_code;
+    SysDesc* sd_dev = (SysDesc*)up_dev;
+    unsigned* status = (unsigned*)(sd_dev + 1);
+    const int* img = (const int*)(status + 2);
+    const int* rec = img + nimg3;
+    std::memcpy(up.data(), &d, sizeof(SysDesc));
+    std::memcpy(up.data() + sizeof(SysDesc) + 2 * sizeof(int), ps.img.data(), sizeof(int) * nimg3);
+    std::memcpy(up.data() + sizeof(SysDesc) + (2 + nimg3) * sizeof(int), ps.rec.data(), sizeof(int) * nrec3);
+    HIPCHK(hipMemcpyAsync(up_dev, up.data(), up.size(), hipMemcpyHostToDevice, st), "upload");
     mbd_prep_launch(st, sd_dev, 1, N, om, cc, status);
     mbd_ts_launch(st, sd_dev, N, om, img, (int)ps.img.size() / 3, rec, (int)ps.rec.size() / 3, periodic ? 1 : 0,
-                  eatom, status, &c->prof);
+                  eatom, scratch, status, &c->prof);
     HIPCHK(hipGetLastError(), "ts");
     unsigned sth = 0;
     HIPCHK(hipMemcpyAsync(&sth, status, sizeof(unsigned), hipMemcpyDeviceToHost, st), "status");

@@ -15,12 +15,13 @@
 // and the cosine argument are read from the derivation of the split; the
 // printed formula omits G = 0 and has them garbled.
 //
-// Atom i's row of (j, term) pairs is shared by one workgroup, so the atom's
-// energy share, its gradient and its parameter derivatives come out of one
-// block reduction each (each ordered pair's energy is counted at i; dE/dR_i =
-// sum_j C6_ij grad S_ij(R_j - R_i) gathers both orders).  Per pair the
+// Atom i's energy share, its gradient and its parameter derivatives are sums
+// over the ordered pairs (i, j) (each ordered pair's energy is counted at i;
+// dE/dR_i = sum_j C6_ij grad S_ij(R_j - R_i) gathers both orders).  Per pair the
 // divisions are shared: C6 and its omega derivative through 1/(omega_i +
 // omega_j), the Fermi factor through 1/R0 and 1/(1 + e^{-|x|}), and 1/R.
+#include <algorithm>
+
 #include "mbd_internal.h"
 #include "mbd_kernels.h"
 #include "mbd_sys.h"
@@ -123,110 +124,112 @@ __global__ __launch_bounds__(TS_FIN) void mbd_ts_finite_kernel(const SysDesc* sd
     }
 }
 
-// Periodic systems: one workgroup per atom i over the flat (j, term) index.
-__global__ __launch_bounds__(256) void mbd_ts_kernel(const SysDesc* sd, const double* om, const int* img, int nimg,
-                                                       const int* rec, int nrec, double* eatom, unsigned* status) {
-    __shared__ double red[4];
+// Reciprocal vectors and their weights, {G, gamma^3 phi_k(|G|/gamma)/Omega} (0
+// from kc on): the same for every pair.
+__global__ __launch_bounds__(256) void mbd_ts_recip_kernel(const SysDesc* sd, const int* rec, int nrec, double4* gw) {
     const SysDesc& S = sd[0];
-    const int N = S.N;
-    const int i = blockIdx.x;
-    const int t0 = (int)threadIdx.x;
-    if (i >= N) return;
+    const int m = blockIdx.x * 256 + threadIdx.x;
+    if (m >= nrec) return;
+    double G[3];
+    for (int c = 0; c < 3; c++)
+        G[c] = rec[3 * m] * S.recip[c] + rec[3 * m + 1] * S.recip[3 + c] + rec[3 * m + 2] * S.recip[6 + c];
+    const double k = sqrt(G[0] * G[0] + G[1] * G[1] + G[2] * G[2]), kk = k / S.gamma;
+    const double phik = (TS_SQRT_PI * TS_SQRT_PI * TS_SQRT_PI / 12.0) *
+                        ((4.0 - 2.0 * kk * kk) * exp(-0.25 * kk * kk) + kk * kk * kk * TS_SQRT_PI * erfc(0.5 * kk));
+    gw[m] = make_double4(G[0], G[1], G[2], k < S.kc ? S.gamma * S.gamma * S.gamma * phik / S.vol : 0.0);
+}
+
+// Periodic systems: a wavefront per pair (i, j), TS_JPW of atom i's in a
+// workgroup, its lanes over the images, then the reciprocal vectors: what depends
+// on the pair alone is formed once, and no wavefront mixes the two kinds of
+// term.  Writes the six sums of every (i, j chunk).  Bound by the exp
+// and sincos of the terms (64 atoms, 602 terms a pair: 19 us, 198 with a row
+// (j, term) in flat order per workgroup and the weights formed per pair).
+#define TS_JPW 4
+__global__ __launch_bounds__(256) void mbd_ts_kernel(const SysDesc* sd, const double* om, const int* img, int nimg,
+                                                       const double4* gw, int nrec, double* part, unsigned* status) {
+    __shared__ double red[4][8];
+    const SysDesc& S = sd[0];
+    const int N = S.N, i = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double* R = S.coords;
     const double ai = S.alpha0[i], wi = om[S.atom_off + i], rvi = S.rvdw[i];
-    const double iwi = 1.0 / wi;
     const double g = S.gamma, g3 = g * g * g, g6 = g3 * g3;
-    const int nterm = nimg + nrec;
-    double Ei = 0.0, gx = 0.0, gy = 0.0, gz = 0.0, dw = 0.0, dv = 0.0;
-    // lane steps of 256 over the flat (j, term) index, carried into j
-    // without an integer division per step
-    int j = t0 / nterm, u = t0 % nterm;
-    auto advance = [&]() {
-        u += 256;
-        while (u >= nterm) { u -= nterm; j++; }
-    };
-    for (; j < N; advance()) {
+    double sum[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // E, g[3], dw, dv without their i factors
+    const int j = blockIdx.y * TS_JPW + wv;
+    if (j < N) {
         const double r[3] = {R[3 * j] - R[3 * i], R[3 * j + 1] - R[3 * i + 1], R[3 * j + 2] - R[3 * i + 2]};
-        const double aj = S.alpha0[j], wj = om[S.atom_off + j];
-        // C6 = (3/2) ai aj wi wj/(wi + wj); dC6/dwi = C6 wj/(wi (wi + wj))
-        const double h = 1.0 / (wi + wj);
-        const double c6 = 1.5 * ai * aj * wi * wj * h;
-        const double c6w = c6 * wj * h * iwi;
+        const double wj = om[S.atom_off + j], wh = wj / (wi + wj), c = S.alpha0[j] * wh;  // C6 / ((3/2) alpha_i omega_i)
         const double R0 = S.beta * (rvi + S.rvdw[j]);
-        if (j == i && u == 0) {
-            // self term -gamma^6/6 of the reciprocal sum, once per atom
-            Ei += -0.5 * c6 * (-g6 / 6.0);
-            dw += -c6w * (-g6 / 6.0);
-        }
         double s = 0.0, ds[3] = {0.0, 0.0, 0.0}, ds0 = 0.0;
-        if (u < nimg) {
-            double x[3] = {r[0], r[1], r[2]};
-            for (int c = 0; c < 3; c++)
-                x[c] += img[3 * u] * S.lat[c] + img[3 * u + 1] * S.lat[3 + c] + img[3 * u + 2] * S.lat[6 + c];
+        // self term -gamma^6/6 of the reciprocal sum, once per atom
+        if (j == i && lane == 0) s = -g6 / 6.0;
+        for (int u = lane; u < nimg; u += 64) {
+            double x[3];
+            for (int k = 0; k < 3; k++)
+                x[k] = r[k] + img[3 * u] * S.lat[k] + img[3 * u + 1] * S.lat[3 + k] + img[3 * u + 2] * S.lat[6 + k];
             const double d2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
-            if (d2 == 0.0) {  // n = 0, i = j; any other zero distance is a coincident pair
-                if (j != i) atomicOr(&status[0], MBD_ST_COINCIDENT);
+            if (!(d2 >= 1e-16)) {  // n = 0, i = j; any other zero distance is a coincident pair
+                if (j != i || d2 != 0.0) atomicOr(&status[0], MBD_ST_COINCIDENT);
                 continue;
             }
-            double d = sqrt(d2);
-            if (!(d >= 1e-8)) {
-                atomicOr(&status[0], MBD_ST_COINCIDENT);
-                continue;
-            }
-            const double id = 1.0 / d, id2 = id * id, id6 = id2 * id2 * id2;
+            double d, id;
+            sqrt_recip(d2, d, id);
+            const double id2 = id * id, id6 = id2 * id2 * id2;
             double f, omf, fd, fR0;
             ts_fermi(d, R0, S.a, f, omf, fd, fR0);
             double dd = 0.0;
             if (d < S.rc) {
-                const double z = g * d, iz = 1.0 / z, iz2 = iz * iz, ez = exp(-z * z);
+                const double z = g * d, iz = recip(z), iz2 = iz * iz, ez = exp(-z * z);
                 s += g6 * (iz2 * iz2 * iz2 + iz2 * iz2 + 0.5 * iz2) * ez;
                 dd += -g6 * g * (6.0 * iz2 * iz2 * iz2 * iz + 6.0 * iz2 * iz2 * iz + 3.0 * iz2 * iz + iz) * ez;
             }
             if (omf > TS_DAMP_TAIL) {
                 s -= omf * id6;
                 dd += fd * id6 + 6.0 * omf * id6 * id;
-                ds0 = fR0 * id6;
+                ds0 += fR0 * id6;
             }
-            for (int c = 0; c < 3; c++) ds[c] = dd * x[c] * id;
-        } else {
-            const int m = u - nimg;
-            double G[3];
-            for (int c = 0; c < 3; c++)
-                G[c] = rec[3 * m] * S.recip[c] + rec[3 * m + 1] * S.recip[3 + c] + rec[3 * m + 2] * S.recip[6 + c];
-            const double k = sqrt(G[0] * G[0] + G[1] * G[1] + G[2] * G[2]);
-            if (k >= S.kc) continue;
-            const double kk = k / g;
-            const double phik = (TS_SQRT_PI * TS_SQRT_PI * TS_SQRT_PI / 12.0) *
-                                ((4.0 - 2.0 * kk * kk) * exp(-0.25 * kk * kk) + kk * kk * kk * TS_SQRT_PI * erfc(0.5 * kk));
-            const double w = g3 * phik / S.vol;
-            double sn, cs;
-            sincos(G[0] * r[0] + G[1] * r[1] + G[2] * r[2], &sn, &cs);
-            s = w * cs;
-            for (int c = 0; c < 3; c++) ds[c] = -w * sn * G[c];
+            for (int k = 0; k < 3; k++) ds[k] += dd * x[k] * id;
         }
-        Ei += -0.5 * c6 * s;
-        gx += c6 * ds[0];
-        gy += c6 * ds[1];
-        gz += c6 * ds[2];
-        dw += -c6w * s;
-        dv += -S.beta * c6 * ds0;
+        for (int m = lane; m < nrec; m += 64) {
+            const double4 G = gw[m];
+            if (G.w == 0.0) continue;
+            double sn, cs;
+            sincos(G.x * r[0] + G.y * r[1] + G.z * r[2], &sn, &cs);
+            s += G.w * cs;
+            ds[0] -= G.w * sn * G.x;
+            ds[1] -= G.w * sn * G.y;
+            ds[2] -= G.w * sn * G.z;
+        }
+        sum[0] = c * s;
+        for (int k = 0; k < 3; k++) sum[1 + k] = c * ds[k];
+        sum[4] = c * s * wh;
+        sum[5] = c * ds0;
     }
-    Ei = block_sum256(Ei, red);
-    gx = block_sum256(gx, red);
-    gy = block_sum256(gy, red);
-    gz = block_sum256(gz, red);
-    dw = block_sum256(dw, red);
-    dv = block_sum256(dv, red);
-    if (t0 == 0) ts_store(S, i, ai, wi, Ei, gx, gy, gz, dw, dv, eatom);
+    const double w = wave_sum8(sum);
+    if ((lane & 7) == 0) red[wv][lane >> 3] = w;
+    __syncthreads();
+    if (tid < 6)
+        part[((long long)i * gridDim.y + blockIdx.y) * 6 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
 }
 
-// energy = sum of the per-atom shares, in a fixed order; errors[0..3] = 0
-__global__ __launch_bounds__(1024) void mbd_ts_sum_kernel(const SysDesc* sd, const double* eatom,
-                                                            const unsigned* status) {
+// energy = sum of the per-atom shares, in a fixed order; errors[0..3] = 0.  part:
+// a periodic system's sums, whose rows are added here first, a lane per atom.
+__global__ __launch_bounds__(1024) void mbd_ts_sum_kernel(const SysDesc* sd, const double* om, const double* part, int nchunk,
+                                                            double* eatom, const unsigned* status) {
     __shared__ double red[16];
     const SysDesc& S = sd[0];
     double e = 0.0;
-    for (int i = threadIdx.x; i < S.N; i += 1024) e += eatom[i];
+    for (int i = threadIdx.x; i < S.N; i += 1024) {
+        if (part) {
+            double r[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            for (int c = 0; c < nchunk; c++)
+                for (int k = 0; k < 6; k++) r[k] += part[((long long)i * nchunk + c) * 6 + k];
+            const double ai = S.alpha0[i], wi = om[S.atom_off + i], c = 1.5 * ai * wi;
+            ts_store(S, i, ai, wi, -0.5 * c * r[0], c * r[1], c * r[2], c * r[3], -1.5 * ai * r[4], -S.beta * c * r[5], eatom);
+        }
+        e += eatom[i];
+    }
     e = wave_sum(e);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
     __syncthreads();
@@ -239,15 +242,27 @@ __global__ __launch_bounds__(1024) void mbd_ts_sum_kernel(const SysDesc* sd, con
     }
 }
 
+size_t mbd_ts_scratch(int N, int nrec) {
+    return sizeof(double4) * std::max(1, nrec) + sizeof(double) * 6 * N * ((N + TS_JPW - 1) / TS_JPW);
+}
+
 void mbd_ts_launch(hipStream_t st, const SysDesc* sd, int N, const double* om, const int* img, int nimg,
-                   const int* rec, int nrec, int periodic, double* eatom, unsigned* status, LaunchProfiler* prof) {
+                   const int* rec, int nrec, int periodic, double* eatom, void* scratch, unsigned* status,
+                   LaunchProfiler* prof) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (prof && prof->enabled && prof->launches)  // work: the pair terms of the launch
         prof->pair(&e0, &e1, 11, periodic ? (double)N * N * (nimg + nrec) : (double)N * (N - 1));
-    if (periodic)
-        hipExtLaunchKernelGGL(mbd_ts_kernel, dim3(N), dim3(256), 0, st, e0, e1, 0, sd, om, img, nimg, rec, nrec, eatom,
+    const int nchunk = (N + TS_JPW - 1) / TS_JPW;
+    double* part = nullptr;
+    if (periodic) {
+        double4* gw = (double4*)scratch;
+        part = (double*)(gw + std::max(1, nrec));
+        if (nrec)
+            hipLaunchKernelGGL(mbd_ts_recip_kernel, dim3((nrec + 255) / 256), dim3(256), 0, st, sd, rec, nrec, gw);
+        hipExtLaunchKernelGGL(mbd_ts_kernel, dim3(N, nchunk), dim3(256), 0, st, e0, e1, 0, sd, om, img, nimg, gw, nrec, part,
                               status);
-    else
+    } else {
         hipExtLaunchKernelGGL(mbd_ts_finite_kernel, dim3(N), dim3(TS_FIN), 0, st, e0, e1, 0, sd, om, eatom, status);
-    hipLaunchKernelGGL(mbd_ts_sum_kernel, dim3(1), dim3(1024), 0, st, sd, eatom, status);
+    }
+    hipLaunchKernelGGL(mbd_ts_sum_kernel, dim3(1), dim3(1024), 0, st, sd, om, part, nchunk, eatom, status);
 }

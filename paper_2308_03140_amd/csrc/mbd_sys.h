@@ -126,8 +126,9 @@ void mbd_grad_periodic_launch(hipStream_t st, const SysDesc* sd, const double* o
 // launch profiling on, the pair kernel is timed as kind 11
 struct LaunchProfiler;
 void mbd_ts_launch(hipStream_t st, const SysDesc* sd, int N, const double* om, const int* img, int nimg,
-                   const int* rec, int nrec, int periodic, double* eatom, unsigned* status,
+                   const int* rec, int nrec, int periodic, double* eatom, void* scratch, unsigned* status,
                    LaunchProfiler* prof = nullptr);
+size_t mbd_ts_scratch(int N, int nrec);  // bytes of scratch (periodic systems)
 
 // frequency route: per-frequency coefficients (descriptor 0 = the system,
 // 1..nfreq = one per frequency), then the per-matrix eigenvalue sums and the

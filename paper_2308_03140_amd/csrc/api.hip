@@ -640,7 +640,7 @@ bool make_isq_work(mbd_ctx* c, MatBatch<double> Q, const int* ns, int nmax, int 
         {(void**)&w.bufs.p[7], "isq_m7", mat * 8}, {(void**)&w.lan.vec, "isq_vec", 4 * sv * nm * 8},
         {(void**)&w.lan.part, "isq_part", 4 * nwg * nm * 8}, {(void**)&w.lan.alpha, "isq_al", ISQ_LMAX * nm * 8},
         {(void**)&w.lan.beta, "isq_be", ISQ_LMAX * nm * 8}, {(void**)&w.lan.len, "isq_len", nm * 4},
-        {(void**)&w.lan.done, "isq_done", nm * 4}, {(void**)&w.ops, "isq_ops", sizeof(IsqOp) * ISQ_OPMAX * nm},
+        {(void**)&w.lan.done, "isq_done", nm * 4}, {(void**)&w.ops, "isq_ops", sizeof(IsqOp) * ISQ_OPS * nm},
         {(void**)&w.cls, "isq_cls", nm * 4}, {(void**)&w.order, "isq_order", nm * 4}, {(void**)&w.yv, "isq_yv", 2 * sv * nm * 8},
         {(void**)&w.check, "isq_check", 2 * nwg * nm * 8}, {(void**)&w.zmax, "isq_zmax", nm * 8}};
     static_assert(ISQ_NBUF == 8, "buffers listed above");

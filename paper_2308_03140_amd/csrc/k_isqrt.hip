@@ -212,20 +212,10 @@ __device__ __forceinline__ void isq_row_term(const double* row, int nr, int k, d
     }
 }
 
-// Sums of the two partials that the workgroups of the step before left.
-__device__ __forceinline__ void isq_part_sums(const double* part, int nwg, double& s1, double& s2, double* red) {
-    double a = 0.0, c = 0.0;
-    for (int w = threadIdx.x; w < nwg; w += 256) { a += part[2 * w]; c += part[2 * w + 1]; }
-    s1 = block_sum256(a, red);
-    s2 = block_sum256(c, red);
-}
-
-// The step's partials are s1 = v.w', s2 = w'.w' with w' = M v - a v - beta v_prev
-// and a the alpha of the step before (M_00 at first): alpha = a + s1, beta^2 =
-// s2 - s1^2.  Taking a off first keeps beta accurate where M is close to a
-// multiple of the identity (weakly coupled identical atoms).  A beta at
-// rounding level, of the matrix or of the difference s2 - s1^2, ends the
-// recurrence.
+// beta of the last step before a plan, from its partials s1 = v.w' and s2 =
+// w'.w' with w' = M v - a v - beta v_prev and a the alpha of the step before
+// (M_00 at first): alpha = a + s1, beta^2 = s2 - s1^2.  A beta at rounding level,
+// of the matrix or of the difference s2 - s1^2, ends the recurrence.
 __device__ __forceinline__ bool isq_beta(double alpha, double s1, double s2, double& beta) {
     const double b2 = s2 - s1 * s1;
     const bool more = b2 > fmax(1e-28 * alpha * alpha, 1e-13 * s1 * s1) && s2 < 1e300;
@@ -236,7 +226,12 @@ __device__ __forceinline__ bool isq_beta(double alpha, double s1, double s2, dou
 // Step j: every workgroup forms v_j from the step before (elementwise, where
 // it is needed) and w'_j for its ISQ_MVR rows; bandwidth bound (M read once:
 // 288 MB at order 6000).  ISQ_MVR rows share the two loads behind an element
-// of v_j; one launch per step, with no grid barrier.  EMB: embeddings of
+// of v_j; one launch per step, with no grid barrier.  Taking a, the alpha of the
+// step before (M_00 at first), off w' keeps beta accurate where M is close to a
+// multiple of the identity (weakly coupled identical atoms); its square is
+// summed from the elements of v_j before their normalisation, by every
+// workgroup for itself, since s2 - s1^2 cancels where one eigenvalue stands far
+// above the others (as it may after squarings).  EMB: embeddings of
 // Hermitian matrices, whose left block column [Re; Im] holds both rows c and n/2
 // + c in column c: half the matrix is read.
 template <bool EMB>
@@ -259,25 +254,16 @@ __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, co
     const double* Mb = M.at(b);
     const long long ld = M.ld;
     const double a00 = Mb[0];
-    double s1 = 0.0, beta = 0.0, inv = 0.0, a = a00;
+    double s1 = 0.0, beta = 0.0, inv = 1.0, a = a00, nrm = 0.0;
     if (j > 0) {
-        double s2;
-        isq_part_sums(pprev, nwg, s1, s2, red4);
+        double x = 0.0;
+        for (int w = threadIdx.x; w < nwg; w += 256) x += pprev[2 * w];
+        s1 = block_sum256(x, red4);
         a = (j > 1 ? al[j - 2] : a00) + s1;
-        const bool more = isq_beta(a, s1, s2, beta);
-        inv = more ? 1.0 / beta : 0.0;
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
-            al[j - 1] = a;
-            be[j - 1] = beta;
-            if (!more && L.len[b] == 0) L.len[b] = j;
-        }
-    } else if (blockIdx.x == 0 && threadIdx.x == 0) {
-        L.len[b] = 0;
     }
     const double inv_n = j == 0 ? 1.0 / sqrt((double)n) : 0.0;
-    auto v_at = [&](int k) -> double {
-        return j == 0 ? isq_sign(k, 77u) * inv_n : (w1[k] - s1 * v1[k]) * inv;
-    };
+    // v_j times beta
+    auto v_at = [&](int k) -> double { return j == 0 ? isq_sign(k, 77u) * inv_n : w1[k] - s1 * v1[k]; };
     const double* row[ISQ_MVR];
     double acc[ISQ_MVR], acc2[ISQ_MVR];
 #pragma unroll
@@ -287,8 +273,22 @@ __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, co
     }
     for (int k = threadIdx.x; k < nr; k += 256) {
         const double v = v_at(k), u = EMB ? v_at(nr + k) : 0.0;
+        nrm += v * v + u * u;
 #pragma unroll
         for (int r = 0; r < ISQ_MVR; r++) isq_row_term<EMB>(row[r], nr, k, v, u, acc[r], acc2[r]);
+    }
+    if (j > 0) {
+        nrm = block_sum256(nrm, red4);
+        const bool more = nrm > 1e-28 * a * a && nrm < 1e300;
+        beta = more ? sqrt(nrm) : 0.0;
+        inv = more ? 1.0 / beta : 0.0;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            al[j - 1] = a;
+            be[j - 1] = beta;
+            if (!more && L.len[b] == 0) L.len[b] = j;
+        }
+    } else if (blockIdx.x == 0 && threadIdx.x == 0) {
+        L.len[b] = 0;
     }
     isq_row_sums(acc, red);
     if (EMB) isq_row_sums(acc2, red);
@@ -301,8 +301,8 @@ __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, co
                 double sum = 0.0;
 #pragma unroll
                 for (int r = 0; r < ISQ_MVR; r++) sum = (int)threadIdx.x == r ? (h ? acc2[r] : acc[r]) : sum;
-                const double v = v_at(rr);
-                const double w = sum - a * v - (j > 0 ? beta * v1[rr] : 0.0);
+                const double v = v_at(rr) * inv;
+                const double w = sum * inv - a * v - (j > 0 ? beta * v1[rr] : 0.0);
                 vj[rr] = v;
                 wj[rr] = w;
                 p1 += v * w;
@@ -412,16 +412,29 @@ __device__ int isq_class(const double* al, const double* be, int m, bool exact, 
     return c;
 }
 
+// Steps between convergence checks of lambda_min, after `squares` squarings.
+__host__ __device__ inline int isq_lcheck(int squares) { return squares < 2 ? 8 : 4; }
+
+// Largest eigenvalue z of Z from that of the matrix left by the squarings,
+// w = (low z^2)^(2^(squares - 1)).
+__device__ __forceinline__ double isq_unsquare(double w, int squares, double low) {
+    if (squares == 0) return w;
+    for (int i = 1; i < squares; i++) w = sqrt(w);
+    return sqrt(w / low);
+}
+
 // All Lanczos steps of a matrix in one workgroup, orders up to L.one: bound by
 // one compute unit's reads of the matrix from L2 (order 256: 0.5 MB, 8 us a
 // step, beyond which a launch per step is faster).  Small matrices take it also
 // beside large ones: their recurrence ends, or nearly ends, within the steps,
 // which its explicit norms notice and s2 - s1^2 does not.  Thread (p, r) sums every
 // np-th column's share of row r (columns of M are contiguous, M symmetric), so
-// the products need no cross-lane sums.  zmax != nullptr: run until the
-// largest eigenvalue has converged (see isq_zmax_kernel) and record it.
+// the products need no cross-lane sums.  zmax != nullptr: M is what `squares`
+// squarings left; run until its largest eigenvalue has converged (see
+// isq_zmax_kernel) and record that of Z.
 __global__ __launch_bounds__(1024) void isq_small_lanczos_kernel(MatBatch<double> M, const int* ns, IsqLanczos L, int steps,
-                                                                   const int* cls, double* zmax) {
+                                                                   const int* cls, const IsqOp* ops, int squares,
+                                                                   double* zmax) {
     __shared__ double v[2][ISQ_SMALL], red[16], sums[1024], al[ISQ_LMAX], be[ISQ_LMAX], zs;
     const int b = blockIdx.x, n = ns[b], tid = threadIdx.x;
     if (n > L.one) return;
@@ -447,6 +460,7 @@ __global__ __launch_bounds__(1024) void isq_small_lanczos_kernel(MatBatch<double
     double vr = mine ? isq_sign(r, 77u) / sqrt((double)n) : 0.0, vprev = 0.0, beta = 0.0, a = Mb[0], zp = 0.0;
     int m = 0;
     bool ended = false;
+    const int every = isq_lcheck(squares);
     for (int j = 0; j < steps && !ended; j++) {
         double* vj = v[j & 1];
         if (mine) vj[r] = vr;
@@ -482,7 +496,7 @@ __global__ __launch_bounds__(1024) void isq_small_lanczos_kernel(MatBatch<double
         vr = more ? w / beta : 0.0;
         m = j + 1;
         ended = !more;
-        if (zmax && (ended || m % ISQ_LCHECK == 0 || m == steps)) {
+        if (zmax && (ended || m % every == 0 || m == steps)) {
             __syncthreads();
             if (tid < 64) {
                 const double z = isq_tri_extreme(al, be, m, 1, 10, zp);
@@ -490,9 +504,9 @@ __global__ __launch_bounds__(1024) void isq_small_lanczos_kernel(MatBatch<double
             }
             __syncthreads();
             const double z = zs;
-            const bool conv = ended || (m > 2 * ISQ_LCHECK && fabs(z - zp) <= 4e-15 * z) ||
+            const bool conv = ended || (m > 2 * every && fabs(z - zp) <= 4e-15 * z) ||
                               (m == steps && fabs(z - zp) <= 1e-11 * z);
-            if (tid == 0) zmax[b] = conv ? z : -1.0;
+            if (tid == 0) zmax[b] = conv ? isq_unsquare(z, squares, ops[(long long)b * ISQ_OPS + ISQ_OPMAX].c[0]) : -1.0;
             zp = z;
             if (conv) return;
         }
@@ -552,14 +566,14 @@ struct IsqEmit {
 // in buffer ISQ_RESULT).  No class: an empty program, and the check afterwards
 // fails.
 __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos L, int steps, IsqTable tab, IsqOp* ops,
-                                                        int* cls, int* order, bool mod) {
+                                                        int* cls, int* order, bool mod, int squares) {
     __shared__ double al[ISQ_LMAX], be[ISQ_LMAX];
     const int b = blockIdx.x, n = ns[b], lane = threadIdx.x;
     int ahead = 0;  // matrices before this one: larger, or as large and earlier
     for (int i = lane; i < (int)gridDim.x; i += 64) ahead += ns[i] > n || (ns[i] == n && i < b);
     ahead = (int)wave_sum((double)ahead);
     if (lane == 0) order[ahead] = b;
-    IsqOp* op = ops + (long long)b * ISQ_OPMAX;
+    IsqOp* op = ops + (long long)b * ISQ_OPS;
     for (int i = lane; i < steps; i += 64) {
         al[i] = L.alpha[(long long)b * ISQ_LMAX + i];
         be[i] = L.beta[(long long)b * ISQ_LMAX + i];
@@ -638,6 +652,13 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
                 if (held[h] == o.out || (o.out2 >= 0 && held[h] == o.out2)) held[h] = -1;
         }
         while (e.k < ISQ_OPMAX) e.put(-1, -1, -1, -1, -1, -1, 0, 0, 0, 0);
+        // low Z^2, with eigenvalues up to about 1, and its squares
+        for (int i = 0; i < squares; i++) {
+            if (c < 0) e.put(-1, -1, -1, -1, -1, -1, 0, 0, 0, 0);
+            else if (i == 0) e.put(ISQ_RESULT, ISQ_RESULT, -1, -1, 1, -1, hi / tab.cls[c].kappa, 0, 0, 0);
+            else e.put(2 - (i & 1), 2 - (i & 1), -1, -1, 1 + (i & 1), -1, 1.0, 0, 0, 0);
+            if (i == squares - 1) op[e.k - 1].full = 1;
+        }
     }
     if (!mod || c < 0) return;
     __syncthreads();
@@ -709,7 +730,7 @@ __global__ __launch_bounds__(64 * WK, MINW) void isq_prod_kernel(IsqBufs bufs, c
         part = EMB ? blockIdx.y : 0;
         v = splitk_tile_index(blockIdx.x, b, gridDim.x);
     }
-    const IsqOp& op = ops[(long long)b * ISQ_OPMAX + step];
+    const IsqOp& op = ops[(long long)b * ISQ_OPS + step];
     if (op.a < 0) return;
     const int n = EMB ? ns[b] / 2 : ns[b];
     int ti, tj;
@@ -935,11 +956,11 @@ __global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int*
     }
 }
 
-// Largest eigenvalue of Z from the Lanczos coefficients so far; done[b] is set
-// when the last ISQ_LCHECK steps changed it by rounding only, or the
-// recurrence ended.  Unconverged after the last step: -1.
-__global__ __launch_bounds__(64) void isq_zmax_kernel(const int* ns, const int* cls, IsqLanczos L, int steps, int last,
-                                                        double* zmax) {
+// Largest eigenvalue from the Lanczos coefficients so far; done[b] is set when
+// the last isq_lcheck steps changed it by rounding only, or the recurrence
+// ended, and zmax[b] is then that of Z.  Unconverged after the last step: < 0.
+__global__ __launch_bounds__(64) void isq_zmax_kernel(const int* ns, const int* cls, IsqLanczos L, const IsqOp* ops,
+                                                        int squares, int steps, int last, double* zmax) {
     __shared__ double al[ISQ_LMAX], be[ISQ_LMAX];
     const int b = blockIdx.x, lane = threadIdx.x;
     if (steps == 0) {
@@ -957,12 +978,15 @@ __global__ __launch_bounds__(64) void isq_zmax_kernel(const int* ns, const int* 
         be[i] = L.beta[(long long)b * ISQ_LMAX + i];
     }
     __syncthreads();
+    const int every = isq_lcheck(squares);
     const double zp = fabs(zmax[b]);
-    const double z = isq_tri_extreme(al, be, m, 1, 10, steps > ISQ_LCHECK ? zp : 0.0);
+    const double z = isq_tri_extreme(al, be, m, 1, 10, steps > every ? zp : 0.0);
     if (lane == 0) {
-        const bool conv = ended || (steps > 2 * ISQ_LCHECK && fabs(z - zp) <= 4e-15 * z);
+        const bool conv = ended || (steps > 2 * every && fabs(z - zp) <= 4e-15 * z);
         if (conv) L.done[b] = 1;
-        zmax[b] = conv || (last && fabs(z - zp) <= 1e-11 * z) ? z : -z;
+        zmax[b] = conv || (last && fabs(z - zp) <= 1e-11 * z)
+                      ? isq_unsquare(z, squares, ops[(long long)b * ISQ_OPS + ISQ_OPMAX].c[0])
+                      : -z;
     }
 }
 
@@ -982,7 +1006,7 @@ __device__ double isq_tiny_lanczos(const double* M, double* vb, int n, int steps
 #pragma unroll
     for (int k = 0; k < NP; k++) row[k] = M[k * (NP + 1) + (r & (NP - 1))];
     double v = mine ? isq_sign(r, 77u) / sqrt((double)n) : 0.0, vp = 0.0, beta = 0.0, a = M[0], zp = 0.0;
-    const int c0 = min(n, 24);
+    const int c0 = min(n, 8);
     ended = false;
     m = 0;
     for (int j = 0; j < steps; j++) {
@@ -1005,7 +1029,7 @@ __device__ double isq_tiny_lanczos(const double* M, double* vb, int n, int steps
         v = u * inv;
         m = j + 1;
         ended = !more;
-        if (zmax && (ended || m == steps || (m >= c0 && (m - c0) % 8 == 0))) {
+        if (zmax && (ended || m == steps || (m >= c0 && (m - c0) % 4 == 0))) {
             isq_wave_sync();
             const double z = isq_tri_extreme(al, be, m, 1, 10, zp);
             const bool conv = ended || fabs(z - zp) <= 4e-15 * z || (m == steps && fabs(z - zp) <= 1e-11 * z);
@@ -1023,7 +1047,8 @@ __device__ double isq_tiny_lanczos(const double* M, double* vb, int n, int steps
 // stores down a column spread over the banks); what enters a product only
 // through the linear epilogue stays in registers.  2 x 2 wavefronts, each a quadrant; the
 // upper one is mirrored from the lower.  Latency bound: 10 atoms 30 us
-// against 240 (and 130 of 147 us for lambda_min).
+// against 240, and 47 us more of the call for lambda_min (67 without the
+// squarings).
 template <int NP>
 __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBatch<double> Zo, const int* ns, IsqTable tab,
                                                          int* cls, double* part, int nwg_max, double* zmax) {
@@ -1186,6 +1211,15 @@ __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBa
         e += z * Qb[r + (long long)c * Q.ld];
     }
     e = block_sum256(e, red);
+    // Z^16 for lambda_min
+    const double low = hi / k.kappa;
+    for (int i = 0; zmax && i < ISQ_SQUARES; i++) {
+        Reg W = mul(i == 0 ? bZ : i & 1 ? bX : bT, i == 0 ? bZ : i & 1 ? bX : bT);
+        if (i == 0) each([&](int, int, int i0, int j0, int q) { W.v[i0][j0][q] *= low; });
+        put(i & 1 ? bT : bX, W);
+        __syncthreads();
+    }
+    static_assert(ISQ_SQUARES % 2 == 0, "the last square lands in bT");
     if (wave != 0) return;
     const int r = lane & (NP - 1);
     auto matvec = [&](bool z, double x) {
@@ -1202,8 +1236,8 @@ __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBa
     if (zmax) {
         int m;
         bool ended;
-        const double z = isq_tiny_lanczos<NP>(bZ, vb, n, ISQ_LMAX, al, be, m, ended, true);
-        if (lane == 0) zmax[b] = z;
+        const double w = isq_tiny_lanczos<NP>(bT, vb, n, ISQ_LMAX, al, be, m, ended, true);
+        if (lane == 0) zmax[b] = w > 0.0 ? isq_unsquare(w, ISQ_SQUARES, low) : -1.0;
     }
 }
 
@@ -1211,6 +1245,34 @@ __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBa
 // launches
 // ---------------------------------------------------------------------------
 int isq_lanczos_wgs(int nmax) { return (nmax + ISQ_MVR - 1) / ISQ_MVR; }
+
+// Launches of the Lanczos run for lambda_min, and the squarings of Z before it.
+// Each squaring doubles the relative gap at the upper end, so 2^(-1/2) of the
+// steps do (45 on Z itself, give or take 10).  A squaring is a product at
+// 45 TFLOP/s or 8 us, a step reads the matrices at 4.7 TB/s or takes 3.5 us, and
+// one after convergence 3 us.  lambda_min of one matrix of order 150, 255, 447
+// and 900 takes 135, 170, 175 and 267 us against 400, 635, 440 and 512 with all
+// steps on Z, of 64 embeddings of order 384 0.54 ms against 0.85; from order 2300
+// on the squarings cost more than they save.
+static int isq_lsteps(int squares) {
+    static const int most[ISQ_SQUARES + 1] = {ISQ_LMAX, 96, 64, 48, 40, 32, 24};
+    return most[squares];
+}
+static int isq_squares(const int* ns, int nmat, bool embed) {
+    double n2 = 0.0, n3 = 0.0, best = 1e300;
+    for (int b = 0; b < nmat; b++) {
+        const double n = ns[b];
+        n2 += (embed ? 0.5 : 1.0) * n * n;
+        n3 += (embed ? 0.5 : 1.0) * n * n * n;
+    }
+    int pick = 0;
+    for (int s = 0; s <= ISQ_SQUARES; s++) {
+        const double cost = s * (n3 / 45e12 + 8e-6) + (45.0 * std::pow(2.0, -0.5 * s) + 6.0) * (n2 * 8 / 4.7e12 + 3.5e-6) +
+                            isq_lsteps(s) * 3e-6;
+        if (cost < best) { best = cost; pick = s; }
+    }
+    return pick;
+}
 
 void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int* ns_host, LaunchProfiler* prof) {
     const MatBatch<double> Q = {w.bufs.p[0], w.bufs.ld, w.bufs.stride};
@@ -1235,21 +1297,17 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     // 221, 233, 264, 324, 468 us against 218, 219, 231, 249, 264; 60 molecules of up to 225 793 against 818
     L.one = nmat > 4 ? ISQ_SMALL : ISQ_SMALL / 2;
     if (nmin <= L.one)
-        hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, Q, w.ns, L, steps, w.cls, nullptr);
+        hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, Q, w.ns, L, steps, w.cls, w.ops, 0,
+                           nullptr);
     if (nmax > L.one)
         for (int j = 0; j < steps; j++) hipLaunchKernelGGL(lanczos, mv, dim3(256), 0, st, Q, w.ns, L, j);
+    const int squares = w.zmax ? isq_squares(ns_host, nmat, w.embed) : 0;
     hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(), w.ops, w.cls, w.order,
-                       w.mod.mods > 0);
+                       w.mod.mods > 0, squares);
     const int shape = isq_shape(ns_host, nmat, w.embed);
     const bool timed = prof && prof->enabled && prof->launches;
     const size_t rec0 = timed ? prof->kind.size() : 0;
-    for (int k = 0; k < ISQ_OPMAX; k++) {
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        if (timed) prof->pair(&e0, &e1, 1, 0.0);
-        if (w.mod.mods) {
-            isq_mod_launch(st, w, nmat, k, e0, e1);
-            continue;
-        }
+    auto product = [&](int k, hipEvent_t e0, hipEvent_t e1) {
         auto go = [&](auto kernel, auto emb_kernel, int tm, int tn, int wk) {
             const int parts = w.embed ? 2 : 1, tiles = splitk_lower_tiles(nmax / parts, tm, tn);
             const int own = isq_own(nmat) ? tiles * parts : 0;
@@ -1267,6 +1325,12 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
         case 2: go(isq_prod_kernel<2, 2, 2, 6, 3, false>, isq_prod_kernel<2, 2, 2, 6, 3, true>, 32, 32, 2); break;
         default: go(isq_prod_kernel<2, 2, 4, 6, 3, false>, isq_prod_kernel<2, 2, 4, 6, 3, true>, 32, 32, 4); break;
         }
+    };
+    for (int k = 0; k < ISQ_OPMAX; k++) {
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        if (timed) prof->pair(&e0, &e1, 1, 0.0);
+        if (w.mod.mods) isq_mod_launch(st, w, nmat, k, e0, e1);
+        else product(k, e0, e1);
     }
     if (timed) {
         // the flops of each launch follow from the classes found on the device;
@@ -1288,17 +1352,22 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     for (int p = 0; p < 3; p++)
         hipLaunchKernelGGL(check, mv, dim3(256), 0, st, Q, Z, w.ns, w.cls, w.yv, w.lan.sV, w.check, nwg, p);
     if (!w.zmax) return;
-    L.one = ISQ_SMALL;
+    for (int i = 0; i < squares; i++) product(ISQ_OPMAX + i, nullptr, nullptr);
+    const int last = isq_lsteps(squares), every = isq_lcheck(squares);
+    // 24 steps at order 150, 255: 135, 192 us in one workgroup against 160, 170 by launches
+    L.one = nmat > 4 ? ISQ_SMALL : 3 * ISQ_SMALL / 4;
+    const MatBatch<double> W = {w.bufs.p[squares == 0 ? ISQ_RESULT : squares & 1 ? 1 : 2], w.bufs.ld, w.bufs.stride};
     if (nmin <= L.one)
-        hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, Z, w.ns, L, ISQ_LMAX, w.cls, w.zmax);
+        hipLaunchKernelGGL(isq_small_lanczos_kernel, dim3(nmat), dim3(1024), 0, st, W, w.ns, L, ISQ_LMAX, w.cls, w.ops,
+                           squares, w.zmax);
     if (nmax <= L.one) return;
     L.done = w.lan.done;
-    hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, 0, 0, w.zmax);
-    for (int j = 0; j < ISQ_LMAX; j++) {
-        hipLaunchKernelGGL(lanczos, mv, dim3(256), 0, st, Z, w.ns, L, j);
-        if ((j + 1) % ISQ_LCHECK == 0)
-            hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, j + 1, j + 1 == ISQ_LMAX ? 1 : 0,
-                               w.zmax);
+    hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, w.ops, squares, 0, 0, w.zmax);
+    for (int j = 0; j < last; j++) {
+        hipLaunchKernelGGL(lanczos, mv, dim3(256), 0, st, W, w.ns, L, j);
+        if ((j + 1) % every == 0)
+            hipLaunchKernelGGL(isq_zmax_kernel, dim3(nmat), dim3(64), 0, st, w.ns, w.cls, L, w.ops, squares, j + 1,
+                               j + 1 == last ? 1 : 0, w.zmax);
     }
 }
 

@@ -70,7 +70,7 @@ static ModCoef mod_coef(int mods) {
 template <int MODS>
 __global__ __launch_bounds__(256) void mod_split_kernel(IsqBufs bufs, const int* ns, const IsqOp* ops, int step, IsqMod w) {
     const int b = blockIdx.z >> 1, which = blockIdx.z & 1, lane = threadIdx.x & 63;
-    const IsqOp& op = ops[(long long)b * ISQ_OPMAX + step];
+    const IsqOp& op = ops[(long long)b * ISQ_OPS + step];
     if (op.a < 0 || !(op.conv >> which & 1)) return;
     const int kb = blockIdx.x * 4 + (threadIdx.x >> 6), rb = blockIdx.y, n = ns[b];
     if (kb >= w.kb) return;
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256, 1) void mod_prod_kernel(const int* ns, const I
     constexpr int KS = 2;
     __shared__ mm_i4 S[3][16 * KS][64];
     const int b = blockIdx.z, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const IsqOp& op = ops[(long long)b * ISQ_OPMAX + step];
+    const IsqOp& op = ops[(long long)b * ISQ_OPS + step];
     if (op.a < 0) return;
     const int v = xcd_virtual(blockIdx.x, gridDim.x), mod = v / tiles, t = v % tiles;
     int ti, tj;
@@ -217,7 +217,7 @@ template <int MODS>
 __global__ __launch_bounds__(256) void mod_combine_kernel(IsqBufs bufs, const int* ns, const IsqOp* ops, int step,
                                                             IsqMod w, ModCoef cf, int tiles) {
     const int b = blockIdx.z, lane = threadIdx.x & 63;
-    const IsqOp& op = ops[(long long)b * ISQ_OPMAX + step];
+    const IsqOp& op = ops[(long long)b * ISQ_OPS + step];
     if (op.a < 0) return;
     const int t = blockIdx.x / 16, s = (blockIdx.x % 16) * 4 + (threadIdx.x >> 6), n = ns[b], ld = bufs.ld;
     int ti, tj;

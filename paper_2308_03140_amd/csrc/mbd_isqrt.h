@@ -5,12 +5,13 @@
 
 #define ISQ_CLASSES 9      // spectral classes (largest kappa) with a plan each
 #define ISQ_OPMAX 17       // products of the longest program
+#define ISQ_SQUARES 6      // most squarings of Q^{-1/2} before the Lanczos run for lambda_min
+#define ISQ_OPS (ISQ_OPMAX + ISQ_SQUARES)
 #define ISQ_NBUF 8         // matrix buffers, buffer 0 = Q
 #define ISQ_RESULT 7       // buffer that receives Q^{-1/2}
 #define ISQ_MVR 8          // rows per workgroup of a matrix-vector pass
 #define ISQ_LMAX 128       // most Lanczos steps
 #define ISQ_SMALL 256      // largest order whose Lanczos steps run in one workgroup
-#define ISQ_LCHECK 8       // steps between convergence checks of lambda_min
 #define ISQ_STEPS_SMALL 10 // Lanczos steps for the interval, orders below 1024
 #define ISQ_STEPS_LARGE 14 // and from 1024 on
 // The smallest Ritz value overstates lambda_min by up to 1.4 after 10 steps
@@ -74,7 +75,7 @@ struct IsqWork {
     bool embed;     // real embeddings of Hermitian matrices (order even)
     IsqBufs bufs;
     IsqLanczos lan;
-    IsqOp* ops;     // [nmat][ISQ_OPMAX]
+    IsqOp* ops;     // [nmat][ISQ_OPS]: the program, then the squarings
     int* cls;       // [nmat]
     int* order;     // [nmat] matrices by order, largest first
     double* yv;     // [nmat][2][sV]

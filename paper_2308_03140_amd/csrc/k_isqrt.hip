@@ -173,12 +173,6 @@ const IsqTable& isq_table() {
 // ---------------------------------------------------------------------------
 // Lanczos (batched, one launch per step)
 // ---------------------------------------------------------------------------
-// LDS written by a wavefront becomes visible to its other lanes
-__device__ __forceinline__ void isq_wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // random signs, the same for every matrix
 __device__ __forceinline__ double isq_sign(int k, unsigned seed) {
     unsigned x = (unsigned)k * 2654435761u + seed;

@@ -213,10 +213,16 @@ __global__ __launch_bounds__(256, 1) void mod_prod_kernel(const int* ns, const I
 // The products from their residues, and the step's two outputs as
 // isq_prod_kernel writes them: one 32 x 32 block of the lower triangle per
 // wavefront; lane l holds its column l mod 32, rows 8 q + 4 (l / 32) + e.
+// Bound by HBM (order 6000, 12 moduli: 216 MB read, 288 written, more with
+// epilogue matrices and a second output); the lower triangle is stored from a
+// transposed copy in LDS, 256 B to 32 lanes: 142 us against 176 with 32 B
+// segments straight from the registers.
 template <int MODS>
 __global__ __launch_bounds__(256) void mod_combine_kernel(IsqBufs bufs, const int* ns, const IsqOp* ops, int step,
                                                             IsqMod w, ModCoef cf, int tiles) {
+    __shared__ double tr[4][32 * 33];
     const int b = blockIdx.z, lane = threadIdx.x & 63;
+    double* T = tr[threadIdx.x >> 6];
     const IsqOp& op = ops[(long long)b * ISQ_OPS + step];
     if (op.a < 0) return;
     const int t = blockIdx.x / 16, s = (blockIdx.x % 16) * 4 + (threadIdx.x >> 6), n = ns[b], ld = bufs.ld;
@@ -234,13 +240,12 @@ __global__ __launch_bounds__(256) void mod_combine_kernel(IsqBufs bufs, const in
     double* C2 = op.out2 >= 0 ? bufs.p[op.out2] + (long long)b * bufs.stride : nullptr;
     const int col = 32 * bj + (lane & 31);
     const double scale = scalbn(cf.M, op.ea + op.eb - 2 * w.bits);
+    double o2[16];
 #pragma unroll
     for (int q = 0; q < 4; q++) {
-        const int row0 = 32 * bi + 8 * q + 4 * (lane >> 5);
-        double o1[4], o2[4];
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            const int row = row0 + e;
+            const int rr = 8 * q + 4 * (lane >> 5) + e, row = 32 * bi + rr;
             double s1 = 0.0, s2 = 0.0;
 #pragma unroll
             for (int m = 0; m < MODS; m++) {
@@ -253,32 +258,31 @@ __global__ __launch_bounds__(256) void mod_combine_kernel(IsqBufs bufs, const in
             const bool in = row < n && col < n && row >= col;
             const long long at = col + (long long)row * ld;
             const double e1 = E1 && in ? E1[at] : 0.0, e2 = E2 && in ? E2[at] : 0.0, id = row == col ? 1.0 : 0.0;
-            o1[e] = op.c[0] * f + op.c[1] * e1 + op.c[2] * e2 + op.c[3] * id;
-            o2[e] = op.d[0] * f + op.d[1] * e1 + op.d[2] * e2 + op.d[3] * id;
+            const double o1 = op.c[0] * f + op.c[1] * e1 + op.c[2] * e2 + op.c[3] * id;
+            o2[4 * q + e] = op.d[0] * f + op.d[1] * e1 + op.d[2] * e2 + op.d[3] * id;
             if (in) {
-                C1[at] = o1[e];
-                if (C2) C2[at] = o2[e];
+                C1[at] = o1;
+                if (C2) C2[at] = o2[4 * q + e];
             }
-        }
-        if (col >= n) continue;
-        double* c1 = C1 + row0 + (long long)col * ld;
-        double* c2 = C2 ? C2 + row0 + (long long)col * ld : nullptr;
-        if (bi > bj && row0 + 3 < n) {
-            *reinterpret_cast<double2*>(c1) = make_double2(o1[0], o1[1]);
-            *reinterpret_cast<double2*>(c1 + 2) = make_double2(o1[2], o1[3]);
-            if (c2) {
-                *reinterpret_cast<double2*>(c2) = make_double2(o2[0], o2[1]);
-                *reinterpret_cast<double2*>(c2 + 2) = make_double2(o2[2], o2[3]);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; e++)
-                if (row0 + e < n && row0 + e > col) {
-                    c1[e] = o1[e];
-                    if (c2) c2[e] = o2[e];
-                }
+            T[(lane & 31) * 33 + rr] = o1;
         }
     }
+    // the other triangle from the transposed block, in runs along the rows
+    const int row = 32 * bi + (lane & 31);
+    auto mirror = [&](double* C) {
+        isq_wave_sync();
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int cc = 2 * i + (lane >> 5);
+            if (row < n && row > 32 * bj + cc) C[row + (long long)(32 * bj + cc) * ld] = T[cc * 33 + (lane & 31)];
+        }
+        isq_wave_sync();
+    };
+    mirror(C1);
+    if (!C2) return;
+#pragma unroll
+    for (int i = 0; i < 16; i++) T[(lane & 31) * 33 + 8 * (i / 4) + 4 * (lane >> 5) + i % 4] = o2[i];
+    mirror(C2);
 }
 
 // Large orders only: conversions and combination grow with n^2, and 256 x 256

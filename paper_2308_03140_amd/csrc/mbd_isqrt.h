@@ -83,6 +83,12 @@ struct IsqWork {
     double* zmax;   // [nmat], or nullptr when lambda_min is not wanted
 };
 
+// LDS written by a wavefront becomes visible to its other lanes
+__device__ __forceinline__ void isq_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 int isq_lanczos_wgs(int nmax);
 // whether products of these orders go by residues; buffer sizes per matrix
 // (bytes) and layout for order nmax; the launches of program step `step`

@@ -667,7 +667,7 @@ bool make_isq_work(mbd_ctx* c, MatBatch<double> Q, const int* ns, int nmax, int 
 // the FP64 products stay.
 void make_isq_mod(mbd_ctx* c, const int* ns_host, int nmax, int nmat, bool embed, IsqWork& w) {
     const int mods = c->prec == MBD_FP32_REFINED ? ISQ_MODS_SHORT : ISQ_MODS_MAX;
-    if (!isq_mod_fits(ns_host, nmat, embed, mods)) return;
+    if (!isq_mod_fits(ns_host, nmat, embed)) return;
     size_t res, prod;
     IsqMod m;
     isq_mod_sizes(nmax, mods, m, res, prod);

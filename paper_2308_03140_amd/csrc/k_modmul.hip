@@ -286,14 +286,15 @@ __global__ __launch_bounds__(256) void mod_combine_kernel(IsqBufs bufs, const in
 }
 
 // Large orders only: conversions and combination grow with n^2, and 256 x 256
-// tiles waste their edges.  One matrix of order 2100, 2550, 3000, 3600, 5100
-// with 14 moduli: 2.58, 3.71, 5.08, 7.46, 15.7 ms an evaluation against 2.24,
-// 3.61, 5.23, 8.61, 23.1 with FP64 products; with 12: 2.52, 3.21, 4.48, 6.74,
-// 13.8.  Embedded (periodic) matrices never are that large.
-bool isq_mod_fits(const int* ns_host, int nmat, bool embed, int mods) {
+// tiles waste their edges.  One matrix of order 2103, 2202, 2304, 2550, 3000,
+// 3600, 5100 with 14 moduli: 2.26, 2.38, 2.40, 3.11, 4.24, 6.61, 14.2 ms an
+// evaluation against 2.14, 2.38, 2.80, 3.45, 5.01, 8.18, 21.9 with FP64 products;
+// with 12: 2.18, 2.26, 2.27, 2.58, 3.66, 5.81, 12.3.  Embedded (periodic)
+// matrices never are that large.
+bool isq_mod_fits(const int* ns_host, int nmat, bool embed) {
     if (embed) return false;
     for (int b = 0; b < nmat; b++)
-        if (ns_host[b] < 200 * mods) return false;
+        if (ns_host[b] < 2200) return false;
     return true;
 }
 

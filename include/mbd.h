@@ -59,14 +59,16 @@ typedef enum {
     MBD_ERR_UNSUPPORTED = 6         /* valid request this build does not do  */
 } mbd_status;
 
-/* Arithmetic.  Unless eigenvalues are wanted, an evaluation in either
- * precision forms Q^{-1/2} and Tr Q^{1/2} directly, in FP64 products on the
- * matrix cores and without an eigen-decomposition, and checks the result
- * (|I - Q^{-1/2} Q Q^{-1/2}| at rounding level).  A system that fails the
- * check (collapsed, or lambda_max/lambda_min above about 4000), one whose
- * eigenvalues are wanted (MBD_WANT_EIGVALS), one whose workspaces do not fit
- * MBD_WORKSPACE_LIMIT, and every MBD_FP32_REFINED system of a context with
- * MBD_REFINE_TOL set, goes through the diagonalisation.  Its arithmetic is:
+/* Arithmetic.  Unless eigenvalues are wanted, an evaluation in MBD_FP64, and
+ * one of finite systems of 710 atoms or more in MBD_FP32_REFINED, forms
+ * Q^{-1/2} and Tr Q^{1/2} directly, in products on the matrix cores and
+ * without an eigen-decomposition, and checks the result (|I - Q^{-1/2} Q
+ * Q^{-1/2}| at rounding level).  A system that fails the check (collapsed, or
+ * lambda_max/lambda_min above about 4000), one whose eigenvalues are wanted
+ * (MBD_WANT_EIGVALS), one whose workspaces do not fit MBD_WORKSPACE_LIMIT, and
+ * every other MBD_FP32_REFINED system (all of a batch with a smaller member,
+ * all cells, and all of a context with MBD_REFINE_TOL set), goes through the
+ * diagonalisation.  Its arithmetic is:
  * MBD_FP64: everything in FP64.
  * MBD_FP32_REFINED: Householder reduction, tridiagonal solve and
  * back-transform in FP32 on matrix cores with FP32 accumulation, then one

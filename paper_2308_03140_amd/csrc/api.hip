@@ -663,11 +663,14 @@ bool make_isq_work(mbd_ctx* c, MatBatch<double> Q, const int* ns, int nmax, int 
     return true;
 }
 
-// Buffers of the residue products, where these take them: without the scratch
-// the FP64 products stay.
+// Moduli of a context's residue products.
+int isq_mods(const mbd_ctx* c) { return c->prec == MBD_FP32_REFINED ? ISQ_MODS_SHORT : ISQ_MODS_MAX; }
+
+// Buffers of the residue products, where the orders take them; without the
+// scratch w.mod.mods stays 0.
 void make_isq_mod(mbd_ctx* c, const int* ns_host, int nmax, int nmat, bool embed, IsqWork& w) {
-    const int mods = c->prec == MBD_FP32_REFINED ? ISQ_MODS_SHORT : ISQ_MODS_MAX;
-    if (!isq_mod_fits(ns_host, nmat, embed)) return;
+    const int mods = isq_mods(c);
+    if (!isq_mod_fits(ns_host, nmat, embed, mods)) return;
     size_t res, prod;
     IsqMod m;
     isq_mod_sizes(nmax, mods, m, res, prod);
@@ -682,10 +685,19 @@ void make_isq_mod(mbd_ctx* c, const int* ns_host, int nmax, int nmat, bool embed
     c->err_msg.clear();
 }
 
-// Whether an evaluation takes the direct Q^{-1/2}: always, unless the caller
-// wants eigenvalues or has set the threshold of the eigenvector refinement.
-bool direct_route(const mbd_ctx* c, unsigned want) {
-    return !(want & MBD_WANT_EIGVALS) && !(c->prec == MBD_FP32_REFINED && c->refine_tol > 0.0);
+// Whether an evaluation takes the direct Q^{-1/2}: unless the caller wants
+// eigenvalues, always in an FP64 context.  An FP32_REFINED one takes it only in
+// the form with operands shortened for it, the residue products with 12 moduli,
+// at the orders from which these pay: the results of smaller systems, their
+// error estimates among them, are those of the FP32 eigenvectors and their
+// refinement, which differ from a root by FP64 products by up to 1e-6; so are
+// all where the threshold of the refinement is set.
+bool direct_route(const mbd_ctx* c, unsigned want, const std::vector<SysDesc>& sds, const PeriodicSetup* per) {
+    if (want & MBD_WANT_EIGVALS) return false;
+    if (c->prec == MBD_FP64) return true;
+    std::vector<int> ns(sds.size());
+    for (size_t s = 0; s < sds.size(); s++) ns[s] = 3 * sds[s].N;
+    return !(c->refine_tol > 0.0) && isq_mod_fits(ns.data(), (int)ns.size(), per != nullptr, isq_mods(c));
 }
 
 // Layout of an evaluation's upload block.
@@ -706,10 +718,11 @@ struct IsqLiveScope {
 
 // One or more finite systems, or one periodic system (per != nullptr: one
 // embedded matrix per q point), all stages on the context stream.  direct:
-// Q^{-1/2} without eigenvectors (FP64); a system that fails its check gets
-// CODE_EIG and is evaluated again by eig_fallback.
+// Q^{-1/2} without eigenvectors (FP64), unless its workspaces do not fit (then
+// set to false); a system that fails its check gets CODE_EIG and is evaluated
+// again by eig_fallback.
 mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::vector<int>& codes,
-                    const PeriodicSetup* per, bool direct, const RunMode* mode = nullptr) {
+                    const PeriodicSetup* per, bool& direct, const RunMode* mode = nullptr) {
     const bool capturing = mode && mode->capturing;
     const hipStream_t st = c->stream;
     const int nsys = (int)sds.size();
@@ -750,16 +763,21 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
     MatBatch<float> A32 = {nullptr, ld, stride};
     IsqWork iw = {};
     IsqLiveScope live(c, direct);
-    if (direct && A64.p && !make_isq_work(c, A64, ns_dev, nmax, nmat, (want & MBD_WANT_ERRORS) != 0, iw)) {
-        direct = c->isq_live = false;
-        fp32 = c->prec == MBD_FP32_REFINED;
+    std::vector<int> nsh(nmat);
+    for (int b = 0; b < nmat; b++) nsh[b] = per ? 6 * sds[0].N : 3 * sds[b].N;
+    if (direct && A64.p) {
+        direct = make_isq_work(c, A64, ns_dev, nmax, nmat, (want & MBD_WANT_ERRORS) != 0, iw);
+        if (direct) make_isq_mod(c, nsh.data(), nmax, nmat, per != nullptr, iw);
+        if (direct && c->prec == MBD_FP32_REFINED && !iw.mod.mods) {
+            (void)release_isq_work(c);
+            direct = false;
+        }
+        c->isq_live = direct;
+        fp32 = c->prec == MBD_FP32_REFINED && !direct;
     }
     if (fp32) A32.p = wsT<float>(c, "A32", (size_t)stride * nmat);
     if (!up_dev || !lmin || !om || !cc || !lam || !sc || !A64.p || (fp32 && !A32.p))
         return (mbd_status)c->err_code;
-    std::vector<int> nsh(nmat);
-    for (int b = 0; b < nmat; b++) nsh[b] = per ? 6 * sds[0].N : 3 * sds[b].N;
-    if (direct) make_isq_mod(c, nsh.data(), nmax, nmat, per != nullptr, iw);
     std::vector<char> staged;
     char* up_host = capturing ? mode->g->h_up : nullptr;
     if (!capturing) {
@@ -916,7 +934,8 @@ mbd_status eig_fallback(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, st
     c->arena_used = 0;
     c->arena_bufs.clear();
     std::vector<int> c2;
-    const mbd_status r = run_core(c, redo, want, c2, per, false);
+    bool direct = false;
+    const mbd_status r = run_core(c, redo, want, c2, per, direct);
     if (r != MBD_OK) return r;
     for (size_t k = 0; k < idx.size(); k++) codes[idx[k]] = c2[k];
     return MBD_OK;
@@ -948,7 +967,8 @@ mbd_status refine_fallback(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want,
     if (redo.empty()) return MBD_OK;
     std::vector<int> c2;
     c->prec = MBD_FP64;
-    const mbd_status r = run_core(c, redo, want, c2, per, false);
+    bool direct = false;
+    const mbd_status r = run_core(c, redo, want, c2, per, direct);
     c->prec = MBD_FP32_REFINED;
     if (r != MBD_OK) return r;
     for (size_t k = 0; k < idx.size(); k++) codes[idx[k]] = c2[k];
@@ -958,7 +978,8 @@ mbd_status refine_fallback(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want,
 // An evaluation with its fallbacks.
 mbd_status evaluate_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::vector<int>& codes,
                          const PeriodicSetup* per) {
-    mbd_status r = run_core(c, sds, want, codes, per, direct_route(c, want));
+    bool direct = direct_route(c, want, sds, per);
+    mbd_status r = run_core(c, sds, want, codes, per, direct);
     if (r == MBD_OK) r = eig_fallback(c, sds, want, codes, per);
     if (r == MBD_OK) r = refine_fallback(c, sds, want, codes, per);
     return r;
@@ -1462,7 +1483,8 @@ mbd_status mbd_evaluate_batch(mbd_ctx* c, int32_t n_sys, const mbd_system* sys, 
         HIPCHK(hipStreamSynchronize(c->gstream), "graph");
         for (int i = 0; i < n_sys; i++) codes[i] = status_code(g.h_status[i]);
     } else {
-        mbd_status r = run_core(c, sds, want, codes, nullptr, direct_route(c, want));
+        bool direct = direct_route(c, want, sds, nullptr);
+        mbd_status r = run_core(c, sds, want, codes, nullptr, direct);
         if (r != MBD_OK) return r;
         if (use_graph && it == c->graphs.end()) {
             // capture the same launch sequence once for later calls of this signature
@@ -1487,7 +1509,7 @@ mbd_status mbd_evaluate_batch(mbd_ctx* c, int32_t n_sys, const mbd_system* sys, 
                 std::vector<int> dummy;
                 ok = hipStreamBeginCapture(c->gstream, hipStreamCaptureModeThreadLocal) == hipSuccess;
                 if (ok) {
-                    const mbd_status rc = run_core(c, sds, want, dummy, nullptr, direct_route(c, want), &m);
+                    const mbd_status rc = run_core(c, sds, want, dummy, nullptr, direct, &m);
                     const bool end_ok = hipStreamEndCapture(c->gstream, &graph) == hipSuccess;
                     ok = rc == MBD_OK && end_ok && graph &&
                          hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0) == hipSuccess;

@@ -289,12 +289,13 @@ __global__ __launch_bounds__(256) void mod_combine_kernel(IsqBufs bufs, const in
 // tiles waste their edges.  One matrix of order 2103, 2202, 2304, 2550, 3000,
 // 3600, 5100 with 14 moduli: 2.26, 2.38, 2.40, 3.11, 4.24, 6.61, 14.2 ms an
 // evaluation against 2.14, 2.38, 2.80, 3.45, 5.01, 8.18, 21.9 with FP64 products;
-// with 12: 2.18, 2.26, 2.27, 2.58, 3.66, 5.81, 12.3.  Embedded (periodic)
+// with 12: 2.18, 2.26, 2.27, 2.58, 3.66, 5.81, 12.3; 2112, 2124, 2160, 2199: 2.29,
+// 2.29, 2.29, 2.39 with 12 against 2.24, 2.43, 2.42, 2.50.  Embedded (periodic)
 // matrices never are that large.
-bool isq_mod_fits(const int* ns_host, int nmat, bool embed) {
+bool isq_mod_fits(const int* ns_host, int nmat, bool embed, int mods) {
     if (embed) return false;
     for (int b = 0; b < nmat; b++)
-        if (ns_host[b] < 2200) return false;
+        if (ns_host[b] < (mods == ISQ_MODS_MAX ? 2200 : 2128)) return false;
     return true;
 }
 

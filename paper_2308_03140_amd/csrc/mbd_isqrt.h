@@ -90,10 +90,10 @@ __device__ __forceinline__ void isq_wave_sync() {
 }
 
 int isq_lanczos_wgs(int nmax);
-// whether products of these orders go by residues; buffer sizes per matrix
+// whether products of these orders go by residues of so many moduli; buffer sizes per matrix
 // (bytes) and layout for order nmax; the launches of program step `step`
 // (events around the integer products)
-bool isq_mod_fits(const int* ns_host, int nmat, bool embed);
+bool isq_mod_fits(const int* ns_host, int nmat, bool embed, int mods);
 void isq_mod_sizes(int nmax, int mods, IsqMod& w, size_t& res, size_t& prod);
 void isq_mod_launch(hipStream_t st, const IsqWork& w, int nmat, int step, hipEvent_t e0, hipEvent_t e1);
 // Q^{-1/2} of every matrix into buffer ISQ_RESULT (both triangles), traces and

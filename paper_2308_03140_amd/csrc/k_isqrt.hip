@@ -22,11 +22,14 @@
 // with A, B, E1, E2, out, out2 from eight buffers (buffer 0 is Q).
 //
 // The interval comes from a few Lanczos steps (hi: largest Ritz value plus
-// twice its residual norm and 4%, lo: half of the smallest).  Afterwards the result
-// is checked: r = x - Z Q Z x for a random sign vector x, whose size is the
-// Frobenius norm of I - Z Q Z; a matrix that fails (an eigenvalue outside the
-// interval, or not positive definite: then no real Z gives Z Q Z = I) is left
-// to the eigensolver.
+// twice its residual norm and 6%, lo: half of the smallest).  Afterwards the result
+// is checked: up to order 64 the Frobenius norm of I - Z Q Z is formed, beyond
+// it is estimated by the size of r = x - Z Q Z x for a random vector x.  A matrix
+// that fails (an eigenvalue outside the interval, or not positive definite: then
+// no real Z gives Z Q Z = I) is left to the eigensolver.  Both random vectors
+// have generic real entries: a vector of signs is orthogonal to whole symmetry
+// sectors (equal signs on two like atoms: to the modes antisymmetric under their
+// exchange), which neither the interval nor the check would then see.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -173,11 +176,13 @@ const IsqTable& isq_table() {
 // ---------------------------------------------------------------------------
 // Lanczos (batched, one launch per step)
 // ---------------------------------------------------------------------------
-// random signs, the same for every matrix
-__device__ __forceinline__ double isq_sign(int k, unsigned seed) {
+// Entry k of a random vector, the same for every matrix: either sign,
+// magnitudes uniform in [0.5, 1.5] scaled to a mean square of one.
+__device__ __forceinline__ double isq_rand(int k, unsigned seed) {
     unsigned x = (unsigned)k * 2654435761u + seed;
     x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
-    return (x & 1u) ? 1.0 : -1.0;
+    const double m = 0.96076892283052 * (0.5 + (double)(x >> 1) * 0x1p-31);  // sqrt(12 / 13)
+    return (x & 1u) ? m : -m;
 }
 
 // sums of acc[r] over the workgroup, valid in every thread (LDS: 4 x ISQ_MVR)
@@ -255,9 +260,8 @@ __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, co
         s1 = block_sum256(x, red4);
         a = (j > 1 ? al[j - 2] : a00) + s1;
     }
-    const double inv_n = j == 0 ? 1.0 / sqrt((double)n) : 0.0;
-    // v_j times beta
-    auto v_at = [&](int k) -> double { return j == 0 ? isq_sign(k, 77u) * inv_n : w1[k] - s1 * v1[k]; };
+    // v_j times beta (times its own norm at first)
+    auto v_at = [&](int k) -> double { return j == 0 ? isq_rand(k, 77u) : w1[k] - s1 * v1[k]; };
     const double* row[ISQ_MVR];
     double acc[ISQ_MVR], acc2[ISQ_MVR];
 #pragma unroll
@@ -271,8 +275,8 @@ __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, co
 #pragma unroll
         for (int r = 0; r < ISQ_MVR; r++) isq_row_term<EMB>(row[r], nr, k, v, u, acc[r], acc2[r]);
     }
+    nrm = block_sum256(nrm, red4);
     if (j > 0) {
-        nrm = block_sum256(nrm, red4);
         const bool more = nrm > 1e-28 * a * a && nrm < 1e300;
         beta = more ? sqrt(nrm) : 0.0;
         inv = more ? 1.0 / beta : 0.0;
@@ -281,8 +285,9 @@ __global__ __launch_bounds__(256) void isq_lanczos_kernel(MatBatch<double> M, co
             be[j - 1] = beta;
             if (!more && L.len[b] == 0) L.len[b] = j;
         }
-    } else if (blockIdx.x == 0 && threadIdx.x == 0) {
-        L.len[b] = 0;
+    } else {
+        inv = 1.0 / sqrt(nrm);
+        if (blockIdx.x == 0 && threadIdx.x == 0) L.len[b] = 0;
     }
     isq_row_sums(acc, red);
     if (EMB) isq_row_sums(acc2, red);
@@ -379,7 +384,8 @@ __device__ double isq_tri_extreme(const double* al, const double* be, int m, int
 
 // Spectral interval and class from m Lanczos coefficients (one wavefront, the
 // result in every lane).  exact: the recurrence ended, the Ritz values are
-// eigenvalues.  -1: no class (not positive definite, kappa above the table's
+// eigenvalues (tmax has no residual); the margins stay, so that nothing rests on
+// the start vector having met every eigenspace.  -1: no class (not positive definite, kappa above the table's
 // range, non-finite).
 __device__ int isq_class(const double* al, const double* be, int m, bool exact, const IsqTable& tab, double& hi) {
     // two rounds place them within 1/4000 of the spread, which the margins cover
@@ -396,8 +402,8 @@ __device__ int isq_class(const double* al, const double* be, int m, bool exact, 
         }
         res = be[m - 1] * fabs(x1) / sqrt(nn);
     }
-    hi = exact ? tmax * 1.01 : (tmax + 2.0 * res) * 1.06;
-    const double lo = tmin * (exact ? 0.9 : ISQ_LOW_FRACTION);
+    hi = (tmax + 2.0 * res) * 1.06;
+    const double lo = tmin * ISQ_LOW_FRACTION;
     int c = -1;
     if (lo > 0.0 && hi < 1e100) {
         for (int i = ISQ_CLASSES - 1; i >= 0; i--)
@@ -451,7 +457,8 @@ __global__ __launch_bounds__(1024) void isq_small_lanczos_kernel(MatBatch<double
         return s;
     };
     const bool mine = p == 0 && r < n;
-    double vr = mine ? isq_sign(r, 77u) / sqrt((double)n) : 0.0, vprev = 0.0, beta = 0.0, a = Mb[0], zp = 0.0;
+    double vr = mine ? isq_rand(r, 77u) : 0.0, vprev = 0.0, beta = 0.0, a = Mb[0], zp = 0.0;
+    vr /= sqrt(block_sum(vr * vr));
     int m = 0;
     bool ended = false;
     const int every = isq_lcheck(squares);
@@ -834,7 +841,7 @@ static bool isq_own(int nmat) { return 8 * ((nmat + GEMM_NXCD - 1) / GEMM_NXCD *
 // ---------------------------------------------------------------------------
 // trace and check
 // ---------------------------------------------------------------------------
-// pass 0: y1 = Z x (x random signs) and the row block's share of sum Q o Z;
+// pass 0: y1 = Z x (x random) and the row block's share of sum Q o Z;
 // pass 1: y2 = Q y1; pass 2: x - Z y2 and the row block's sum of its squares.
 // A matrix without a program is skipped (its result is never read).
 template <bool EMB>
@@ -860,8 +867,8 @@ __global__ __launch_bounds__(256) void isq_check_kernel(MatBatch<double> Q, MatB
         acc[r] = acc2[r] = 0.0;
     }
     for (int k = threadIdx.x; k < nr; k += 256) {
-        const double v = pass == 0 ? isq_sign(k, 991u) : x[k];
-        const double u = !EMB ? 0.0 : pass == 0 ? isq_sign(nr + k, 991u) : x[nr + k];
+        const double v = pass == 0 ? isq_rand(k, 991u) : x[k];
+        const double u = !EMB ? 0.0 : pass == 0 ? isq_rand(nr + k, 991u) : x[nr + k];
 #pragma unroll
         for (int r = 0; r < ISQ_MVR; r++) {
             isq_row_term<EMB>(row[r], nr, k, v, u, acc[r], acc2[r]);
@@ -886,7 +893,7 @@ __global__ __launch_bounds__(256) void isq_check_kernel(MatBatch<double> Q, MatB
                     if (pass == 0) y1[rr] = y;
                     else if (pass == 1) y2[rr] = y;
                     else {
-                        const double dr = isq_sign(rr, 991u) - y;
+                        const double dr = isq_rand(rr, 991u) - y;
                         s += dr * dr;
                     }
                 }
@@ -921,7 +928,7 @@ __global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int*
         }
         e = wave_sum(e);
         r = wave_sum(r);
-        // |I - Z Q Z|_F^2; rounding leaves about 1e-14 sqrt(n) (measured, orders 30 to 6000)
+        // |I - Z Q Z|_F^2, or its estimate; rounding leaves about 1e-14 sqrt(n) (measured, orders 30 to 6000)
         if (!(r <= check * check * n)) ok = false;
         if (zmax) {
             const double z = zmax[b];
@@ -999,7 +1006,8 @@ __device__ double isq_tiny_lanczos(const double* M, double* vb, int n, int steps
     double row[NP];
 #pragma unroll
     for (int k = 0; k < NP; k++) row[k] = M[k * (NP + 1) + (r & (NP - 1))];
-    double v = mine ? isq_sign(r, 77u) / sqrt((double)n) : 0.0, vp = 0.0, beta = 0.0, a = M[0], zp = 0.0;
+    double v = mine ? isq_rand(r, 77u) : 0.0, vp = 0.0, beta = 0.0, a = M[0], zp = 0.0;
+    v *= rsqrt(wave_sum(v * v));
     const int c0 = min(n, 8);
     ended = false;
     m = 0;
@@ -1195,8 +1203,8 @@ __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBa
         if (!last) put(bY, Y);
         __syncthreads();
     }
-    // result, trace and check as in isq_check_kernel
-    double e = 0.0;
+    // result, trace and |I - Z Q Z|_F^2 from the product itself
+    double e = 0.0, rr = 0.0;
     double* Zb = Zo.at(b);
     for (int x = tid; x < n * n; x += 256) {
         const int r = x % n, c = x / n;
@@ -1205,7 +1213,23 @@ __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBa
         e += z * Qb[r + (long long)c * Q.ld];
     }
     e = block_sum256(e, red);
-    // Z^16 for lambda_min
+    for (int x = tid; x < NP * NP; x += 256) {
+        const int r = x % NP, c = x / NP;
+        bT[ix(c, r)] = r < n && c < n ? Qb[r + (long long)c * Q.ld] : 0.0;
+    }
+    __syncthreads();
+    put(bX, mul(bT, bZ));
+    __syncthreads();
+    {
+        const Reg G = mul(bZ, bX);
+        if (live)
+            each([&](int r, int c, int i, int j, int q) {
+                const double dr = (r == c ? 1.0 : 0.0) - G.v[i][j][q];
+                if (r < n && c <= r) rr += (r == c ? 1.0 : 2.0) * dr * dr;
+            });
+    }
+    rr = block_sum256(rr, red);
+    // (low Z^2)^(2^(ISQ_SQUARES - 1)) for lambda_min
     const double low = hi / k.kappa;
     for (int i = 0; zmax && i < ISQ_SQUARES; i++) {
         Reg W = mul(i == 0 ? bZ : i & 1 ? bX : bT, i == 0 ? bZ : i & 1 ? bX : bT);
@@ -1215,16 +1239,6 @@ __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBa
     }
     static_assert(ISQ_SQUARES % 2 == 0, "the last square lands in bT");
     if (wave != 0) return;
-    const int r = lane & (NP - 1);
-    auto matvec = [&](bool z, double x) {
-        double w = 0.0;
-        for (int q = 0; q < n; q++)
-            w += (z ? bZ[ix(q, r)] : lane < n ? Qb[lane + (long long)q * Q.ld] : 0.0) * lane_value(x, q);
-        return lane < n ? w : 0.0;
-    };
-    const double x = lane < n ? isq_sign(lane, 991u) : 0.0;
-    const double dr = x - matvec(true, matvec(false, matvec(true, x)));
-    const double rr = wave_sum(dr * dr);
     double* pb = part + (long long)b * nwg_max * 2;
     if (lane < 2 * ((n + ISQ_MVR - 1) / ISQ_MVR)) pb[lane] = lane == 0 ? e : lane == 1 ? rr : 0.0;
     if (zmax) {

@@ -4,14 +4,16 @@
 #pragma once
 #include "gemm_mfma.h"
 #include "mbd_internal.h"
+#include "splitk_extent.h"
 
 // Each of the WK wavefronts computes the whole 16 MI x 16 NJ tile over its own
 // K groups, straight from L2 into registers (no LDS staging and no barrier in
 // the loop; no load is made twice, since the wavefronts read different K).  A
 // lane's 16-byte load holds rows 2r, 2r + 1 (r = lane mod 16), one for each of
 // two MFMA tiles: tile i covers the rows of parity i mod 2 of its 32.  The
-// descriptor's size ends the K loop (columns past K read zero); rows past the
-// matrix only reach rows of C that the caller does not use.  Two register sets
+// descriptor's size ends the K loop (columns past K read zero) and lies within
+// the matrix (splitk_extent.h); rows past ld continue in the next column and
+// only reach rows of C that the caller does not use.  Two register sets
 // of U k-steps alternate, so U MFMA steps hide each load.
 typedef double splitk_d2 __attribute__((ext_vector_type(2)));
 
@@ -29,21 +31,19 @@ struct SplitK {
 #pragma unroll
             for (int j = 0; j < NJ; j++) acc[i][j] = typename mfma4<double>::v{0, 0, 0, 0};
     }
-    // acc += (NEG: -=) sum over K columns of A(m0 .., k) B(n0 .., k); A, B at their row offsets
+    // acc += (NEG: -=) sum over K columns of A(row_a .., k) B(row_b .., k); A, B at row 0
     template <bool NEG = false>
-    __device__ __forceinline__ void run(const double* A, const double* B, int ld, int K) {
-        run<NEG>(A, ld, B, ld, K);
-    }
-    template <bool NEG = false>
-    __device__ __forceinline__ void run(const double* A, int lda, const double* B, int ldb, int K) {
+    __device__ __forceinline__ void run(const double* A, int row_a, int lda, const double* B, int row_b, int ldb, int K) {
+        A += row_a;
+        B += row_b;
         constexpr int G = 4 * U;  // k of one group; groups go round robin over the wavefronts
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const unsigned offa = (unsigned)((lane >> 4) * lda + 2 * (lane & 15)) * 8u;
         const unsigned offb = (unsigned)((lane >> 4) * ldb + 2 * (lane & 15)) * 8u;
         auto gload = [&](int k0, auto& xa, auto& xb) {
             const int kn = max(0, min(G, K - k0));
-            const auto dA = make_rsrc(A + (long long)k0 * lda, (unsigned)kn * lda * 8u);
-            const auto dB = make_rsrc(B + (long long)k0 * ldb, (unsigned)kn * ldb * 8u);
+            const auto dA = make_rsrc(A + (long long)k0 * lda, splitk_bytes(kn, lda, row_a));
+            const auto dB = make_rsrc(B + (long long)k0 * ldb, splitk_bytes(kn, ldb, row_b));
 #pragma unroll
             for (int u = 0; u < U; u++) {
 #pragma unroll
@@ -80,20 +80,21 @@ struct SplitK {
             g += WK;
         }
     }
-    // acc += sum over K of A(m0 .., k) B(k, n0 ..) with B column-major, columns
+    // acc += sum over K of A(row_a .., k) B(k, n0 ..), A at row 0, B column-major, columns
     // nb of them from B: a lane's 16-byte load of B holds rows k, k + 1 of one
     // column, so the k of an MFMA step are 2 apart (K even)
-    __device__ __forceinline__ void run_cols(const double* A, int lda, const double* B, int ldb, int nb, int K) {
+    __device__ __forceinline__ void run_cols(const double* A, int row_a, int lda, const double* B, int ldb, int nb, int K) {
+        A += row_a;
         constexpr int D = U / 2, G = 8 * D;
         static_assert(U % 2 == 0, "pairs of k-steps");
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), kl = 2 * (lane >> 4);
         const unsigned offa = (unsigned)(kl * lda + 2 * (lane & 15)) * 8u;
         const unsigned offb = (unsigned)((lane & 15) * ldb + kl) * 8u;
-        const auto dB = make_rsrc(B, (unsigned)nb * ldb * 8u);
+        const auto dB = make_rsrc(B, splitk_bytes(nb, ldb, 0));
         splitk_d2 sa[2][U][MI / 2], sb[2][D][NJ];
         auto gload = [&](int k0, auto& xa, auto& xb) {
             const int kn = max(0, min(G, K - k0));
-            const auto dA = make_rsrc(A + (long long)k0 * lda, (unsigned)kn * lda * 8u);
+            const auto dA = make_rsrc(A + (long long)k0 * lda, splitk_bytes(kn, lda, row_a));
 #pragma unroll
             for (int u = 0; u < U; u++)
 #pragma unroll

@@ -194,7 +194,8 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(MatBatch<double> A, dou
         SK sk;
         sk.clear();
         // X^T(k, c) = X(c, k)
-        sk.run(Ab, A.ld, chol_inv_block(Linv, sLi, b, k0), CHOL_WB, CHOL_NB);
+        const int o = k0 % CHOL_WB;
+        sk.run(Ab - m0, m0, A.ld, chol_inv_block(Linv, sLi, b, k0) - o, o, CHOL_WB, CHOL_NB);
         sk.reduce(cs);
     }
 #pragma unroll
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(256, 3) void chol_update_kernel(MatBatch<double> A,
     {
         SK sk;
         sk.clear();
-        sk.run(A.at(b) + m0, A.at(b) + n0, A.ld, k0);
+        sk.run(A.at(b), m0, A.ld, A.at(b), n0, A.ld, k0);
         sk.reduce(cs);
     }
     double* C = A.at(b) + m0 + (long long)n0 * A.ld;

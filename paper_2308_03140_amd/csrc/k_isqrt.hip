@@ -742,14 +742,14 @@ __global__ __launch_bounds__(64 * WK, MINW) void isq_prod_kernel(IsqBufs bufs, c
     {
         SK sk;
         sk.clear();
-        const double* A = bufs.p[op.a] + (long long)b * bufs.stride + m0;
-        const double* B = bufs.p[op.b] + (long long)b * bufs.stride + n0;
+        const double* A = bufs.p[op.a] + (long long)b * bufs.stride;
+        const double* B = bufs.p[op.b] + (long long)b * bufs.stride;
         if constexpr (!EMB) {
-            sk.run(A, B, ld, n);
+            sk.run(A, m0, ld, B, n0, ld, n);
         } else {
-            sk.run(A + part * n, B, ld, n);
-            if (part) sk.template run<true>(A, B + n, ld, n);
-            else sk.run(A + n, B + n, ld, n);
+            sk.run(A, m0 + part * n, ld, B, n0, ld, n);
+            if (part) sk.template run<true>(A, m0, ld, B, n0 + n, ld, n);
+            else sk.run(A, m0 + n, ld, B, n0 + n, ld, n);
         }
         sk.reduce(cs);
     }

@@ -319,9 +319,9 @@ __global__ __launch_bounds__(64 * WK) void per_recip_asm_kernel(PerEwald pr, int
         SK sk;
         sk.clear();
         const double* Z = pr.Z + (long long)b * pr.sZ;
-        sk.run(Z + m0 + part * n, Z + n0, pr.ldz, pr.ncol);
-        if (part) sk.template run<true>(Z + m0, Z + n0 + n, pr.ldz, pr.ncol);
-        else sk.run(Z + m0 + n, Z + n0 + n, pr.ldz, pr.ncol);
+        sk.run(Z, m0 + part * n, pr.ldz, Z, n0, pr.ldz, pr.ncol);
+        if (part) sk.template run<true>(Z, m0, pr.ldz, Z, n0 + n, pr.ldz, pr.ncol);
+        else sk.run(Z, m0 + n, pr.ldz, Z, n0 + n, pr.ldz, pr.ncol);
         sk.reduce(cs);
     }
     double* Qb = Q.at(b);
@@ -508,7 +508,7 @@ __global__ __launch_bounds__(128) void per_recip_mz_kernel(MatBatch<double> M, P
         SK sk;
         sk.clear();
         const double* Z = pr.Z + (long long)q * pr.sZ + (long long)g0 * pr.ldz;
-        sk.run_cols(M.at(q) + m0, M.ld, Z, pr.ldz, min(TN, pr.ncol - g0), n2);
+        sk.run_cols(M.at(q), m0, M.ld, Z, pr.ldz, min(TN, pr.ncol - g0), n2);
         sk.reduce<true>(cs);
     }
     double* W = pr.W + (long long)q * pr.sZ + (long long)g0 * pr.ldz + m0;

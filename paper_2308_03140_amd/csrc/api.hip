@@ -222,13 +222,11 @@ mbd_status make_sytrd_ws(mbd_ctx* c, MatBatch<T> A, const int* ns, int nmax, int
     return MBD_OK;
 }
 
-// Eigenvalues of the tridiagonals d, e by Sturm-count multisection.
+// Eigenvalues of the tridiagonals d, e by Sturm-count multisection; pe, info:
+// its scratch.
 template <typename T>
-mbd_status run_stebz(mbd_ctx* c, const int* ns, int nmax, int nbatch, const T* d, const T* e, long long sD, T* w,
-                     long long sW, bool pairs) {
-    double2* pe = wsT<double2>(c, "stebz_p", (size_t)stebz_rows(nmax) * nbatch);
-    double* info = wsT<double>(c, "stebz_i", (size_t)3 * nbatch);
-    if (!pe || !info) return (mbd_status)c->err_code;
+mbd_status run_stebz(mbd_ctx* c, const int* ns, int nmax, int nbatch, const T* d, const T* e, long long sD, double2* pe,
+                     double* info, T* w, long long sW, bool pairs) {
     PhaseTimer ph(&c->prof, c->stream, 4);
     stebz_launch<T>(ns, nmax, nbatch, d, e, sD, pe, info, w, sW, c->stream, pairs);
     HIPCHK(hipGetLastError(), "stebz");
@@ -264,8 +262,12 @@ mbd_status run_eig(mbd_ctx* c, MatBatch<T> A, const int* ns, const int* ns_host,
     tridiag_guard_launch<T>(ns, nbatch, sw.d, sw.e, sw.sD, bad, st);
     if (bad_out) *bad_out = bad;
     if (!vectors) {
-        // eigenvalues only: Sturm-count multisection on the tridiagonal
-        if (run_stebz<T>(c, ns, nmax, nbatch, sw.d, sw.e, sw.sD, w_out, sW, embed_pairs) != MBD_OK)
+        // eigenvalues only: Sturm-count multisection on the tridiagonal, with
+        // the reduction's panels (free now) for scratch
+        static_assert(SYTRD_NBP * sizeof(T) >= sizeof(double2) && SYTRD_NBP * sizeof(T) >= 3 * sizeof(double),
+                      "a panel holds a matrix's rows");
+        if (run_stebz<T>(c, ns, nmax, nbatch, sw.d, sw.e, sw.sD, (double2*)sw.Vp, (double*)sw.Wp, w_out, sW, embed_pairs) !=
+            MBD_OK)
             return (mbd_status)c->err_code;
         if (Xout) *Xout = MatBatch<T>{nullptr, 0, 0};
         return MBD_OK;
@@ -1318,7 +1320,10 @@ mbd_status mbd_freq_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, in
     HIPCHK(hipGetLastError(), "freq assemble");
     if (herm) {
         tridiag_guard_launch<double>(ns_dev, nmat, hd, he, neig, hbad, st);
-        r = run_stebz<double>(c, ns_dev, neig, nmat, hd, he, neig, lam, neig, false);
+        double2* pe = wsT<double2>(c, "stebz_p", (size_t)stebz_rows(neig) * nmat);
+        double* info = wsT<double>(c, "stebz_i", (size_t)3 * nmat);
+        if (!pe || !info) return (mbd_status)c->err_code;
+        r = run_stebz<double>(c, ns_dev, neig, nmat, hd, he, neig, pe, info, lam, neig, false);
     } else {
         r = run_eig<double>(c, K, ns_dev, nsh.data(), nmax, nmat, false, lam, nmax, nullptr, nullptr, periodic);
     }

@@ -94,6 +94,13 @@ mbd_status fail(mbd_ctx* c, mbd_status code, const char* origin, const std::stri
         if (e_ != hipSuccess) return fail(c, MBD_ERR_DEVICE, origin, hipGetErrorString(e_)); \
     } while (0)
 
+// Forgets a failure that the call gets round.
+void clear_error(mbd_ctx* c) {
+    c->err_code = 0;
+    c->err_origin.clear();
+    c->err_msg.clear();
+}
+
 // Gives back the workspaces of the direct Q^{-1/2}: what an evaluation through
 // the eigensolver, or any other call, may use is not reduced by them.
 bool release_isq_work(mbd_ctx* c) {
@@ -655,9 +662,7 @@ bool make_isq_work(mbd_ctx* c, MatBatch<double> Q, const int* ns, int nmax, int 
     if (c->arena ? c->arena_used + more > c->arena_cap : c->limit && c->total + more > c->limit) return false;
     for (auto& x : need)
         if (!(*x.p = ws(c, x.name.c_str(), x.bytes))) {
-            c->err_code = 0;
-            c->err_origin.clear();
-            c->err_msg.clear();
+            clear_error(c);
             (void)release_isq_work(c);
             return false;
         }
@@ -682,9 +687,7 @@ void make_isq_mod(mbd_ctx* c, const int* ns_host, int nmax, int nmat, bool embed
         w.mod = m;
         return;
     }
-    c->err_code = 0;
-    c->err_origin.clear();
-    c->err_msg.clear();
+    clear_error(c);
 }
 
 // Whether an evaluation takes the direct Q^{-1/2}: unless the caller wants
@@ -922,6 +925,21 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
     return MBD_OK;
 }
 
+// run_core, and once more through the eigensolver where a direct evaluation
+// found no room for what it needs besides the root's workspaces (a cell's
+// lattice sums and gradient partials, allocated after them).
+mbd_status run_routes(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::vector<int>& codes,
+                      const PeriodicSetup* per, bool& direct) {
+    const mbd_status r = run_core(c, sds, want, codes, per, direct);
+    if (r != MBD_ERR_OUT_OF_MEMORY || !direct) return r;
+    clear_error(c);
+    (void)release_isq_work(c);
+    c->arena_used = 0;
+    c->arena_bufs.clear();
+    direct = false;
+    return run_core(c, sds, want, codes, per, direct);
+}
+
 // Systems whose direct Q^{-1/2} failed its check (collapsed, or a spectrum
 // wider than the table's range): evaluated again through the eigensolver,
 // which also names the failure.
@@ -981,7 +999,7 @@ mbd_status refine_fallback(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want,
 mbd_status evaluate_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::vector<int>& codes,
                          const PeriodicSetup* per) {
     bool direct = direct_route(c, want, sds, per);
-    mbd_status r = run_core(c, sds, want, codes, per, direct);
+    mbd_status r = run_routes(c, sds, want, codes, per, direct);
     if (r == MBD_OK) r = eig_fallback(c, sds, want, codes, per);
     if (r == MBD_OK) r = refine_fallback(c, sds, want, codes, per);
     return r;
@@ -1489,7 +1507,7 @@ mbd_status mbd_evaluate_batch(mbd_ctx* c, int32_t n_sys, const mbd_system* sys, 
         for (int i = 0; i < n_sys; i++) codes[i] = status_code(g.h_status[i]);
     } else {
         bool direct = direct_route(c, want, sds, nullptr);
-        mbd_status r = run_core(c, sds, want, codes, nullptr, direct);
+        mbd_status r = run_routes(c, sds, want, codes, nullptr, direct);
         if (r != MBD_OK) return r;
         if (use_graph && it == c->graphs.end()) {
             // capture the same launch sequence once for later calls of this signature

@@ -76,3 +76,17 @@ def test_frequency_route(monkeypatch, N, least):
     c = _cluster(N)
     _answered(monkeypatch, "frequency route, %d atoms" % N, "fp64",
               lambda x: T.freq_evaluate(x, *_args(c), beta=c["beta"], a=c["a"]), least, 1e-11, (1.0, 2.0))
+
+
+@pytest.mark.parametrize("n,kgrid,energy,grad", [(3, (1, 2, 2), 802888, 2064487), (8, (2, 2, 2), 1770958, 5399303),
+                                                 (24, (2, 2, 1), 3110526, 10931149),
+                                                 (40, (2, 2, 2), 9800223, 38624649)])
+def test_cells(monkeypatch, n, kgrid, energy, grad):
+    from paper_2308_03140_amd import torch_api as T
+    c = gen.small_crystal(300 + n, n, kgrid=kgrid)
+    kw = dict(beta=c["beta"], a=c["a"], lattice=c["lattice"], kgrid=kgrid, errors=False)
+    factors = (1.0, 1.03, 1.06, 1.1, 1.2, 1.35, 1.6, 2.0, 2.6, 3.4, 4.5, 8.0)
+    _answered(monkeypatch, "energy of a cell of %d" % n, "fp64",
+              lambda x: T.evaluate(x, *_args(c, 0.5), gradients=False, **kw), energy, TOL, factors)
+    _answered(monkeypatch, "gradients of a cell of %d" % n, "fp64", lambda x: T.evaluate(x, *_args(c, 0.5), **kw),
+              grad, TOL, factors)

@@ -1164,8 +1164,10 @@ mbd_status mbd_ts_evaluate(mbd_ctx* c, const mbd_system* s, unsigned want, mbd_r
     double* om = wsT<double>(c, "om", N);
     double* cc = wsT<double>(c, "cc", N);
     double* eatom = wsT<double>(c, "ts_eatom", N);
-    void* scratch = ws(c, "ts_part", periodic ? mbd_ts_scratch(N, (int)nrec3 / 3) : 0);
-    if (!up_dev || !om || !cc || !eatom || !scratch) return (mbd_status)c->err_code;
+    if (!up_dev || !om || !cc || !eatom) return (mbd_status)c->err_code;
+    // a cell's weights and partial sums: it does without them where they do not fit
+    void* scratch = periodic ? ws(c, "ts_part", mbd_ts_scratch(N, (int)nrec3 / 3)) : nullptr;
+    if (periodic && !scratch) clear_error(c);
     SysDesc* sd_dev = (SysDesc*)up_dev;
     unsigned* status = (unsigned*)(sd_dev + 1);
     const int* img = (const int*)(status + 2);

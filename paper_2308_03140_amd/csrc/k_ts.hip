@@ -67,6 +67,12 @@ __device__ __forceinline__ void ts_store(const SysDesc& S, int i, double ai, dou
     if (S.grad_rvdw) S.grad_rvdw[i] = dv;
 }
 
+// the six sums of a cell's atom: E, g[3], dw, dv without their factors of i
+__device__ __forceinline__ void ts_store_cell(const SysDesc& S, int i, double ai, double wi, const double* r, double* eatom) {
+    const double c = 1.5 * ai * wi;
+    ts_store(S, i, ai, wi, -0.5 * c * r[0], c * r[1], c * r[2], c * r[3], -1.5 * ai * r[4], -S.beta * c * r[5], eatom);
+}
+
 // Finite systems: one workgroup per atom i, its two wavefronts over the j, one
 // term each.  Bound by the FP64 vector units: about 120 operations a pair, the
 // divisions and the square root as Newton steps on the hardware estimates, no
@@ -124,30 +130,38 @@ __global__ __launch_bounds__(TS_FIN) void mbd_ts_finite_kernel(const SysDesc* sd
     }
 }
 
-// Reciprocal vectors and their weights, {G, gamma^3 phi_k(|G|/gamma)/Omega} (0
-// from kc on): the same for every pair.
-__global__ __launch_bounds__(256) void mbd_ts_recip_kernel(const SysDesc* sd, const int* rec, int nrec, double4* gw) {
-    const SysDesc& S = sd[0];
-    const int m = blockIdx.x * 256 + threadIdx.x;
-    if (m >= nrec) return;
+// Reciprocal vector m and its weight, {G, gamma^3 phi_k(|G|/gamma)/Omega} (0 from
+// kc on).
+__device__ __forceinline__ double4 ts_recip(const SysDesc& S, const int* rec, int m) {
     double G[3];
     for (int c = 0; c < 3; c++)
         G[c] = rec[3 * m] * S.recip[c] + rec[3 * m + 1] * S.recip[3 + c] + rec[3 * m + 2] * S.recip[6 + c];
     const double k = sqrt(G[0] * G[0] + G[1] * G[1] + G[2] * G[2]), kk = k / S.gamma;
     const double phik = (TS_SQRT_PI * TS_SQRT_PI * TS_SQRT_PI / 12.0) *
                         ((4.0 - 2.0 * kk * kk) * exp(-0.25 * kk * kk) + kk * kk * kk * TS_SQRT_PI * erfc(0.5 * kk));
-    gw[m] = make_double4(G[0], G[1], G[2], k < S.kc ? S.gamma * S.gamma * S.gamma * phik / S.vol : 0.0);
+    return make_double4(G[0], G[1], G[2], k < S.kc ? S.gamma * S.gamma * S.gamma * phik / S.vol : 0.0);
+}
+
+// the same for every pair
+__global__ __launch_bounds__(256) void mbd_ts_recip_kernel(const SysDesc* sd, const int* rec, int nrec, double4* gw) {
+    const int m = blockIdx.x * 256 + threadIdx.x;
+    if (m < nrec) gw[m] = ts_recip(sd[0], rec, m);
 }
 
 // Periodic systems: a wavefront per pair (i, j), TS_JPW of atom i's in a
-// workgroup, its lanes over the images, then the reciprocal vectors: what depends
-// on the pair alone is formed once, and no wavefront mixes the two kinds of
-// term.  Writes the six sums of every (i, j chunk).  Bound by the exp
+// workgroup (and further ones in turn where the grid's y, at most TS_CHUNKS,
+// does not cover them), its lanes over the images, then the reciprocal vectors:
+// what depends on the pair alone is formed once, and no wavefront mixes the two
+// kinds of term.  Writes the six sums of every (i, j chunk).  Bound by the exp
 // and sincos of the terms (64 atoms, 602 terms a pair: 19 us, 198 with a row
 // (j, term) in flat order per workgroup and the weights formed per pair).
+// Without scratch (gw and part null) one workgroup takes all of atom i's pairs,
+// forms the weights itself and stores the atom's results.
 #define TS_JPW 4
+#define TS_CHUNKS 64
 __global__ __launch_bounds__(256) void mbd_ts_kernel(const SysDesc* sd, const double* om, const int* img, int nimg,
-                                                       const double4* gw, int nrec, double* part, unsigned* status) {
+                                                       const int* rec, const double4* gw, int nrec, double* part,
+                                                       double* eatom, unsigned* status) {
     __shared__ double red[4][8];
     const SysDesc& S = sd[0];
     const int N = S.N, i = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
@@ -156,8 +170,7 @@ __global__ __launch_bounds__(256) void mbd_ts_kernel(const SysDesc* sd, const do
     const double ai = S.alpha0[i], wi = om[S.atom_off + i], rvi = S.rvdw[i];
     const double g = S.gamma, g3 = g * g * g, g6 = g3 * g3;
     double sum[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // E, g[3], dw, dv without their i factors
-    const int j = blockIdx.y * TS_JPW + wv;
-    if (j < N) {
+    for (int j = blockIdx.y * TS_JPW + wv; j < N; j += TS_JPW * gridDim.y) {
         const double r[3] = {R[3 * j] - R[3 * i], R[3 * j + 1] - R[3 * i + 1], R[3 * j + 2] - R[3 * i + 2]};
         const double wj = om[S.atom_off + j], wh = wj / (wi + wj), c = S.alpha0[j] * wh;  // C6 / ((3/2) alpha_i omega_i)
         const double R0 = S.beta * (rvi + S.rvdw[j]);
@@ -192,7 +205,7 @@ __global__ __launch_bounds__(256) void mbd_ts_kernel(const SysDesc* sd, const do
             for (int k = 0; k < 3; k++) ds[k] += dd * x[k] * id;
         }
         for (int m = lane; m < nrec; m += 64) {
-            const double4 G = gw[m];
+            const double4 G = gw ? gw[m] : ts_recip(S, rec, m);
             if (G.w == 0.0) continue;
             double sn, cs;
             sincos(G.x * r[0] + G.y * r[1] + G.z * r[2], &sn, &cs);
@@ -201,16 +214,22 @@ __global__ __launch_bounds__(256) void mbd_ts_kernel(const SysDesc* sd, const do
             ds[1] -= G.w * sn * G.y;
             ds[2] -= G.w * sn * G.z;
         }
-        sum[0] = c * s;
-        for (int k = 0; k < 3; k++) sum[1 + k] = c * ds[k];
-        sum[4] = c * s * wh;
-        sum[5] = c * ds0;
+        sum[0] += c * s;
+        for (int k = 0; k < 3; k++) sum[1 + k] += c * ds[k];
+        sum[4] += c * s * wh;
+        sum[5] += c * ds0;
     }
     const double w = wave_sum8(sum);
     if ((lane & 7) == 0) red[wv][lane >> 3] = w;
     __syncthreads();
-    if (tid < 6)
-        part[((long long)i * gridDim.y + blockIdx.y) * 6 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+    auto total = [&](int k) { return (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]); };
+    if (part) {
+        if (tid < 6) part[((long long)i * gridDim.y + blockIdx.y) * 6 + tid] = total(tid);
+    } else if (tid == 0) {
+        double r[6];
+        for (int k = 0; k < 6; k++) r[k] = total(k);
+        ts_store_cell(S, i, ai, wi, r, eatom);
+    }
 }
 
 // energy = sum of the per-atom shares, in a fixed order; errors[0..3] = 0.  part:
@@ -225,8 +244,7 @@ __global__ __launch_bounds__(1024) void mbd_ts_sum_kernel(const SysDesc* sd, con
             double r[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
             for (int c = 0; c < nchunk; c++)
                 for (int k = 0; k < 6; k++) r[k] += part[((long long)i * nchunk + c) * 6 + k];
-            const double ai = S.alpha0[i], wi = om[S.atom_off + i], c = 1.5 * ai * wi;
-            ts_store(S, i, ai, wi, -0.5 * c * r[0], c * r[1], c * r[2], c * r[3], -1.5 * ai * r[4], -S.beta * c * r[5], eatom);
+            ts_store_cell(S, i, S.alpha0[i], om[S.atom_off + i], r, eatom);
         }
         e += eatom[i];
     }
@@ -242,8 +260,10 @@ __global__ __launch_bounds__(1024) void mbd_ts_sum_kernel(const SysDesc* sd, con
     }
 }
 
+static int ts_chunks(int N) { return std::min(TS_CHUNKS, (N + TS_JPW - 1) / TS_JPW); }
+
 size_t mbd_ts_scratch(int N, int nrec) {
-    return sizeof(double4) * std::max(1, nrec) + sizeof(double) * 6 * N * ((N + TS_JPW - 1) / TS_JPW);
+    return sizeof(double4) * std::max(1, nrec) + sizeof(double) * 6 * N * ts_chunks(N);
 }
 
 void mbd_ts_launch(hipStream_t st, const SysDesc* sd, int N, const double* om, const int* img, int nimg,
@@ -252,15 +272,15 @@ void mbd_ts_launch(hipStream_t st, const SysDesc* sd, int N, const double* om, c
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (prof && prof->enabled && prof->launches)  // work: the pair terms of the launch
         prof->pair(&e0, &e1, 11, periodic ? (double)N * N * (nimg + nrec) : (double)N * (N - 1));
-    const int nchunk = (N + TS_JPW - 1) / TS_JPW;
+    const int nchunk = scratch ? ts_chunks(N) : 1;
     double* part = nullptr;
     if (periodic) {
         double4* gw = (double4*)scratch;
-        part = (double*)(gw + std::max(1, nrec));
-        if (nrec)
+        if (scratch) part = (double*)(gw + std::max(1, nrec));
+        if (scratch && nrec)
             hipLaunchKernelGGL(mbd_ts_recip_kernel, dim3((nrec + 255) / 256), dim3(256), 0, st, sd, rec, nrec, gw);
-        hipExtLaunchKernelGGL(mbd_ts_kernel, dim3(N, nchunk), dim3(256), 0, st, e0, e1, 0, sd, om, img, nimg, gw, nrec, part,
-                              status);
+        hipExtLaunchKernelGGL(mbd_ts_kernel, dim3(N, nchunk), dim3(256), 0, st, e0, e1, 0, sd, om, img, nimg, rec, gw, nrec, part,
+                              eatom, status);
     } else {
         hipExtLaunchKernelGGL(mbd_ts_finite_kernel, dim3(N), dim3(TS_FIN), 0, st, e0, e1, 0, sd, om, eatom, status);
     }

@@ -128,7 +128,7 @@ struct LaunchProfiler;
 void mbd_ts_launch(hipStream_t st, const SysDesc* sd, int N, const double* om, const int* img, int nimg,
                    const int* rec, int nrec, int periodic, double* eatom, void* scratch, unsigned* status,
                    LaunchProfiler* prof = nullptr);
-size_t mbd_ts_scratch(int N, int nrec);  // bytes of scratch (periodic systems)
+size_t mbd_ts_scratch(int N, int nrec);  // bytes of scratch (periodic systems; none: slower)
 
 // frequency route: per-frequency coefficients (descriptor 0 = the system,
 // 1..nfreq = one per frequency), then the per-matrix eigenvalue sums and the

@@ -90,3 +90,14 @@ def test_cells(monkeypatch, n, kgrid, energy, grad):
               lambda x: T.evaluate(x, *_args(c, 0.5), gradients=False, **kw), energy, TOL, factors)
     _answered(monkeypatch, "gradients of a cell of %d" % n, "fp64", lambda x: T.evaluate(x, *_args(c, 0.5), **kw),
               grad, TOL, factors)
+
+
+@pytest.mark.parametrize("N,least", [(8, 7469), (64, 10623), (256, 15119), (301, 19000)])
+def test_pairwise_cells(monkeypatch, N, least):
+    """Sums over some 10^5 terms of alternating sign on top of their total; 301
+    atoms are more than one round of pairs per workgroup (its limit is an estimate
+    of the same rule)."""
+    from paper_2308_03140_amd import torch_api as T
+    c = gen.small_crystal(300 + N, N, kgrid=(1, 1, 1), side_scale=max(1.0, (N / 40) ** (1 / 3)))
+    _answered(monkeypatch, "pairwise energy of a cell of %d" % N, "fp64",
+              lambda x: T.ts_evaluate(x, *_args(c), 0.94, lattice=c["lattice"]), least, 1e-12, (1.0, 1.6, 4.0, 100.0))

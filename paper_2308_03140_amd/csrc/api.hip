@@ -94,6 +94,18 @@ mbd_status fail(mbd_ctx* c, mbd_status code, const char* origin, const std::stri
         if (e_ != hipSuccess) return fail(c, MBD_ERR_DEVICE, origin, hipGetErrorString(e_)); \
     } while (0)
 
+// Gives a named buffer back.
+void release_buffer(mbd_ctx* c, const char* name) {
+    const auto it = c->bufs.find(name);
+    if (it == c->bufs.end()) return;
+    (void)hipStreamSynchronize(c->stream);
+    if (c->gstream) (void)hipStreamSynchronize(c->gstream);
+    c->drop_graphs();
+    (void)hipFree(it->second.first);
+    c->total -= it->second.second;
+    c->bufs.erase(it);
+}
+
 // Forgets a failure that the call gets round.
 void clear_error(mbd_ctx* c) {
     c->err_code = 0;
@@ -106,16 +118,10 @@ void clear_error(mbd_ctx* c) {
 bool release_isq_work(mbd_ctx* c) {
     bool any = false;
     for (auto it = c->bufs.begin(); it != c->bufs.end();) {
-        if (it->first.compare(0, 4, "isq_") != 0) { ++it; continue; }
-        if (!any) {
-            (void)hipStreamSynchronize(c->stream);
-            if (c->gstream) (void)hipStreamSynchronize(c->gstream);
-            c->drop_graphs();
-            any = true;
-        }
-        (void)hipFree(it->second.first);
-        c->total -= it->second.second;
-        it = c->bufs.erase(it);
+        const std::string name = (it++)->first;
+        if (name.compare(0, 4, "isq_") != 0) continue;
+        release_buffer(c, name.c_str());
+        any = true;
     }
     return any;
 }
@@ -1358,18 +1364,10 @@ mbd_status mbd_freq_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, in
     return code_message(c, status_code(all & (MBD_ST_BAD_INPUT | MBD_ST_COINCIDENT)), "mbd_freq_evaluate");
 }
 
-mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, unsigned want, mbd_result* out,
-                              double* scs_params) {
-    if (!c) return MBD_ERR_INVALID_ARGUMENT;
-    c->err_code = 0;
-    const unsigned allowed = MBD_WANT_ENERGY | MBD_WANT_GRAD_COORDS | MBD_WANT_EIGVALS | MBD_WANT_ERRORS;
-    if (want & ~allowed)
-        return fail(c, MBD_ERR_UNSUPPORTED, "mbd_rsscs_evaluate", "energy, dE/dR, eigenvalues and errors only");
-    if (n_freq < 1 || n_freq > 512) return fail(c, MBD_ERR_INVALID_ARGUMENT, "mbd_rsscs_evaluate", "1 <= n_freq <= 512");
-    mbd_status r = check_system(c, s, want, out, true);
-    if (r != MBD_OK) return r;
-    if (s->lattice) return fail(c, MBD_ERR_UNSUPPORTED, "mbd_rsscs_evaluate", "finite systems only");
-    if (hipSetDevice(c->device) != hipSuccess) return fail(c, MBD_ERR_DEVICE, "mbd_rsscs_evaluate", "hipSetDevice");
+// The screening and the MBD stage on the screened parameters; wb: rows of the
+// solves' diagonal blocks.
+static mbd_status rsscs_run(mbd_ctx* c, const mbd_system* s, int n_freq, unsigned want, mbd_result* out, double* scs_params,
+                            int wb) {
     const hipStream_t st = c->stream;
     const int N = s->n_atoms, n = 3 * N, nf = n_freq + 1;
     const int ld = round_up(n, 64);
@@ -1392,16 +1390,15 @@ mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, u
     double* u_dev = wsT<double>(c, "scs_u", nf);
     double* wq_dev = wsT<double>(c, "scs_wq", nf);
     const long long sR = 3LL * n;  // three right-hand sides per matrix, row-major
-    double* linv = wsT<double>(c, "scs_linv", (size_t)chol_linv_stride(n) * nf);
+    double* linv = wsT<double>(c, "scs_linv", (size_t)chol_linv_stride(n, wb) * nf);
     double* rhs = wsT<double>(c, "scs_rhs", (size_t)sR * nf);
     double* ytmp = wsT<double>(c, "scs_y", (size_t)sR * nf);
     double* V = wsT<double>(c, "scs_v", (size_t)sR * nf);
     double* abar = wsT<double>(c, "scs_abar", (size_t)nf * N);
     double* par = wsT<double>(c, "scs_par", (size_t)4 * N);
-    double* sig2 = wsT<double>(c, "scs_sig2", (size_t)nf * N);
+    double* sig2 = ytmp;  // around the solves, whose scratch this is
     MatBatch<double> A = {wsT<double>(c, "scsA", (size_t)stride * nf), ld, stride};
-    if (!sd_dev || !status || !om0 || !cc0 || !u_dev || !wq_dev || !linv || !rhs || !ytmp || !V || !abar || !par || !sig2 ||
-        !A.p)
+    if (!sd_dev || !status || !om0 || !cc0 || !u_dev || !wq_dev || !linv || !rhs || !ytmp || !V || !abar || !par || !A.p)
         return (mbd_status)c->err_code;
     HIPCHK(hipMemcpyAsync(sd_dev, &base, sizeof(SysDesc), hipMemcpyHostToDevice, st), "upload");
     HIPCHK(hipMemcpyAsync(u_dev, u.data(), sizeof(double) * nf, hipMemcpyHostToDevice, st), "upload");
@@ -1413,9 +1410,9 @@ mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, u
     {
         PhaseTimer ph(&c->prof, st, 9);
         scs_assemble_launch(st, sd_dev, N, om0, u_dev, nf, sig2, A, status);
-        chol_factor_launch(st, A, n, nf, linv, status);
+        chol_factor_launch(st, A, n, nf, linv, wb, status);
         scs_rhs_launch(st, N, nf, nullptr, rhs);
-        chol_solve_launch(st, A, n, nf, linv, rhs, ytmp, V, sR);
+        chol_solve_launch(st, A, n, nf, linv, wb, rhs, ytmp, V, sR);
         scs_contract_launch(st, N, nf, V, abar);
         scs_params_launch(st, sd_dev, N, abar, wq_dev, nf, par);
     }
@@ -1448,7 +1445,7 @@ mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, u
     }
     std::vector<SysDesc> sds(1, make_desc(&ss, w2, &rs));
     std::vector<int> codes;
-    r = evaluate_core(c, sds, w2, codes, nullptr);
+    const mbd_status r = evaluate_core(c, sds, w2, codes, nullptr);
     if (r != MBD_OK) return r;
     if (codes[0] != MBD_OK) return code_message(c, codes[0], "mbd_rsscs_evaluate");
     if (grads) {
@@ -1461,12 +1458,34 @@ mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, u
         PhaseTimer ph(&c->prof, st, 9);
         scs_weights_launch(st, N, nf, par, abar, wq_dev, gpar, gpar + N, gpar + 2 * N, w);
         scs_rhs_launch(st, N, nf, w, rhs);
-        chol_solve_launch(st, A, n, nf, linv, rhs, ytmp, U, sR);
-        scs_grad_launch(st, sd_dev, N, nf, sig2, U, V, UV, out->grad_coords);
+        chol_solve_launch(st, A, n, nf, linv, wb, rhs, ytmp, U, sR);
+        scs_grad_launch(st, sd_dev, N, nf, om0, u_dev, sig2, U, V, UV, out->grad_coords);
         HIPCHK(hipGetLastError(), "scs gradient");
         HIPCHK(hipStreamSynchronize(st), "synchronize");
     }
     return MBD_OK;
+}
+
+mbd_status mbd_rsscs_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, unsigned want, mbd_result* out,
+                              double* scs_params) {
+    if (!c) return MBD_ERR_INVALID_ARGUMENT;
+    c->err_code = 0;
+    const unsigned allowed = MBD_WANT_ENERGY | MBD_WANT_GRAD_COORDS | MBD_WANT_EIGVALS | MBD_WANT_ERRORS;
+    if (want & ~allowed)
+        return fail(c, MBD_ERR_UNSUPPORTED, "mbd_rsscs_evaluate", "energy, dE/dR, eigenvalues and errors only");
+    if (n_freq < 1 || n_freq > 512) return fail(c, MBD_ERR_INVALID_ARGUMENT, "mbd_rsscs_evaluate", "1 <= n_freq <= 512");
+    mbd_status r = check_system(c, s, want, out, true);
+    if (r != MBD_OK) return r;
+    if (s->lattice) return fail(c, MBD_ERR_UNSUPPORTED, "mbd_rsscs_evaluate", "finite systems only");
+    if (hipSetDevice(c->device) != hipSuccess) return fail(c, MBD_ERR_DEVICE, "mbd_rsscs_evaluate", "hipSetDevice");
+    // the wide blocks' inverses take room that the call may need elsewhere
+    const int wb = 3 * s->n_atoms <= CHOL_NB ? CHOL_NB : CHOL_WIDE;
+    r = rsscs_run(c, s, n_freq, want, out, scs_params, wb);
+    if (r != MBD_ERR_OUT_OF_MEMORY || wb == CHOL_NB) return r;
+    clear_error(c);
+    (void)release_isq_work(c);
+    release_buffer(c, "scs_linv");
+    return rsscs_run(c, s, n_freq, want, out, scs_params, CHOL_NB);
 }
 
 mbd_status mbd_evaluate_batch(mbd_ctx* c, int32_t n_sys, const mbd_system* sys, unsigned want, mbd_result* out,

@@ -20,7 +20,8 @@
 // sweep alternates between a wide block's solution (its inverse times the
 // residual) and the update of the rows still to come, two launches per wide
 // block (16 matrices of order 3000: 0.24 ms a sweep and 0.11 for the inverses;
-// steps of 64 rows took 9.3 us each, 0.44 ms a sweep).
+// steps of 64 rows took 9.3 us each, 0.44 ms a sweep).  The wide inverses take
+// four times the storage; where that is refused, blocks of 64 rows serve.
 #include <algorithm>
 
 #include "gemm_splitk.h"
@@ -28,15 +29,13 @@
 #include "mbd_kernels.h"
 #include "mbd_sys.h"
 
-#define CHOL_NB 64
 #define CHOL_NR 3  // right-hand sides per solve
-#define CHOL_WB 256  // wide blocks of the solves, and of the inverses' storage: matrix b's wide block w at w WB^2
 
 // inverse of the 64 x 64 diagonal block at k0 (column-major, leading dimension
-// CHOL_WB) within its wide block's
-__device__ __forceinline__ double* chol_inv_block(double* Linv, long long sLi, int b, int k0) {
-    const int o = k0 % CHOL_WB;
-    return Linv + (long long)b * sLi + (long long)(k0 / CHOL_WB) * CHOL_WB * CHOL_WB + o + (long long)o * CHOL_WB;
+// wb) within that of its wide block of wb rows; matrix b's wide block w at w wb^2
+__device__ __forceinline__ double* chol_inv_block(double* Linv, long long sLi, int b, int k0, int wb) {
+    const int o = k0 % wb;
+    return Linv + (long long)b * sLi + (long long)(k0 / wb) * wb * wb + o + (long long)o * wb;
 }
 
 // ---------------------------------------------------------------------------
@@ -50,8 +49,8 @@ __device__ __forceinline__ double* chol_inv_block(double* Linv, long long sLi, i
 // Bound by the chain of 64 pivots: 21.5 us at 16 matrices, against 101 column
 // by column with three barriers a column.
 #define CHOL_SB 16
-__global__ __launch_bounds__(256) void chol_diag_kernel(MatBatch<double> A, double* Linv, long long sLi, int n,
-                                                         int k0, unsigned* status) {
+__global__ __launch_bounds__(256) void chol_diag_kernel(MatBatch<double> A, double* Linv, long long sLi, int wb,
+                                                         int n, int k0, unsigned* status) {
     __shared__ double L[CHOL_NB][CHOL_NB + 1];
     __shared__ double X[CHOL_NB][CHOL_NB + 1];
     __shared__ double dinv[CHOL_NB];
@@ -172,11 +171,11 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(MatBatch<double> A, doub
         const int j = j0 + 4 * u;
         if (ri < w && j < w && ri >= j) Ab[ri + j * ld] = L[ri][j];
     }
-    double* Xo = chol_inv_block(Linv, sLi, b, k0);
+    double* Xo = chol_inv_block(Linv, sLi, b, k0, wb);
 #pragma unroll
     for (int u = 0; u < PER; u++) {
         const int j = j0 + 4 * u;
-        Xo[ri + j * CHOL_WB] = X[ri][j];
+        Xo[ri + j * wb] = X[ri][j];
     }
 }
 
@@ -184,8 +183,8 @@ __global__ __launch_bounds__(256) void chol_diag_kernel(MatBatch<double> A, doub
 // panel: L21 = A21 X^T (X = L11^-1), rows k0 + 64 .. n-1, in place: a tile
 // spans the panel's 64 columns, so a workgroup reads only the rows it writes.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void chol_panel_kernel(MatBatch<double> A, double* Linv, long long sLi, int n,
-                                                          int k0) {
+__global__ __launch_bounds__(256) void chol_panel_kernel(MatBatch<double> A, double* Linv, long long sLi, int wb,
+                                                          int n, int k0) {
     typedef SplitK<2, 4, 4, 4> SK;
     __shared__ __align__(16) double cs[SK::LDS];
     const int b = blockIdx.y, m0 = k0 + CHOL_NB + blockIdx.x * SK::TM, tid = threadIdx.x;
@@ -194,8 +193,8 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(MatBatch<double> A, dou
         SK sk;
         sk.clear();
         // X^T(k, c) = X(c, k)
-        const int o = k0 % CHOL_WB;
-        sk.run(Ab - m0, m0, A.ld, chol_inv_block(Linv, sLi, b, k0) - o, o, CHOL_WB, CHOL_NB);
+        const int o = k0 % wb;
+        sk.run(Ab - m0, m0, A.ld, chol_inv_block(Linv, sLi, b, k0, wb) - o, o, wb, CHOL_NB);
         sk.reduce(cs);
     }
 #pragma unroll
@@ -237,15 +236,16 @@ __global__ __launch_bounds__(256, 3) void chol_update_kernel(MatBatch<double> A,
 // ---------------------------------------------------------------------------
 // inverses of the wide diagonal blocks: X(i, j) = -X(i, i) sum_{j <= k < i} L(i,
 // k) X(k, j) over their 64 x 64 blocks, a block column per workgroup, 16 rows
-// per wavefront.  Grid (3, wide blocks, matrices).
+// per wavefront.  Grid (WB / 64 - 1, wide blocks, matrices).
 // ---------------------------------------------------------------------------
+template <int WB>
 __global__ __launch_bounds__(256) void chol_wide_kernel(MatBatch<double> A, double* Linv, long long sLi, int n) {
     __shared__ double T[CHOL_NB][CHOL_NB + 1];
     typedef mfma4<double>::v Acc;
-    const int j = blockIdx.x, w0 = blockIdx.y * CHOL_WB, b = blockIdx.z, lane = threadIdx.x & 63;
-    const int nb = (min(CHOL_WB, n - w0) + CHOL_NB - 1) / CHOL_NB, m0 = 16 * (threadIdx.x >> 6);
+    const int j = blockIdx.x, w0 = blockIdx.y * WB, b = blockIdx.z, lane = threadIdx.x & 63;
+    const int nb = (min(WB, n - w0) + CHOL_NB - 1) / CHOL_NB, m0 = 16 * (threadIdx.x >> 6);
     const int m = lane & 15, kl = lane >> 4;
-    double* X = chol_inv_block(Linv, sLi, b, w0);
+    double* X = chol_inv_block(Linv, sLi, b, w0, WB);
     const double* L = A.at(b) + w0 + (long long)w0 * A.ld;
     for (int i = j + 1; i < nb; i++) {
         Acc acc[4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(256) void chol_wide_kernel(MatBatch<double> A, doub
         for (int k = CHOL_NB * j; k < CHOL_NB * i; k += 4) {
             const double a = in ? L[row + (long long)(k + kl) * A.ld] : 0.0;
 #pragma unroll
-            for (int c = 0; c < 4; c++) acc[c] = mfma16x16x4(a, X[k + kl + (CHOL_NB * j + 16 * c + m) * CHOL_WB], acc[c]);
+            for (int c = 0; c < 4; c++) acc[c] = mfma16x16x4(a, X[k + kl + (CHOL_NB * j + 16 * c + m) * WB], acc[c]);
         }
         __syncthreads();  // the previous block's readers of T
 #pragma unroll
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(256) void chol_wide_kernel(MatBatch<double> A, doub
         Acc x[4] = {{0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}, {0, 0, 0, 0}};
 #pragma unroll 4
         for (int k = 0; k < CHOL_NB; k += 4) {
-            const double a = -X[row + (CHOL_NB * i + k + kl) * CHOL_WB];
+            const double a = -X[row + (CHOL_NB * i + k + kl) * WB];
 #pragma unroll
             for (int c = 0; c < 4; c++) x[c] = mfma16x16x4(a, T[k + kl][16 * c + m], x[c]);
         }
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void chol_wide_kernel(MatBatch<double> A, doub
         for (int c = 0; c < 4; c++)
 #pragma unroll
             for (int r = 0; r < 4; r++)
-                X[CHOL_NB * i + m0 + mfma_rows<double>::row(lane, r) + (CHOL_NB * j + 16 * c + m) * CHOL_WB] = x[c][r];
+                X[CHOL_NB * i + m0 + mfma_rows<double>::row(lane, r) + (CHOL_NB * j + 16 * c + m) * WB] = x[c][r];
         __syncthreads();  // X(i, j), global memory, before the next block row reads it
     }
 }
@@ -285,18 +285,18 @@ __global__ __launch_bounds__(256) void chol_wide_kernel(MatBatch<double> A, doub
 // Forward step of the wide block at w0.  SUB: 64 rows below it per workgroup,
 // R -= L Y; else its own, Y = X R.  A row per lane (columns of M are
 // contiguous), a quarter of the columns per wavefront.  Bandwidth bound.
-template <bool SUB>
+template <int WB, bool SUB>
 __global__ __launch_bounds__(256) void chol_fwd_kernel(MatBatch<double> A, double* Linv, long long sLi, int n, int w0,
                                                         double* R, double* Y, long long sR) {
-    __shared__ double vs[CHOL_WB][CHOL_NR], part[4][CHOL_NB][CHOL_NR];
+    __shared__ double vs[WB][CHOL_NR], part[4][CHOL_NB][CHOL_NR];
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, pt = tid >> 6, rb = CHOL_NB * blockIdx.x;
     const double* V = (SUB ? Y : R) + (long long)b * sR + (long long)w0 * CHOL_NR;
-    const int cols = SUB ? CHOL_WB : rb + CHOL_NB;  // X is lower triangular
+    const int cols = SUB ? WB : rb + CHOL_NB;  // X is lower triangular
     for (int x = tid; x < cols * CHOL_NR; x += 256)
         vs[x / CHOL_NR][x % CHOL_NR] = w0 + x / CHOL_NR < n ? V[x] : 0.0;
-    const int row = (SUB ? w0 + CHOL_WB : 0) + rb + lane;
-    const long long ld = SUB ? A.ld : CHOL_WB;
-    const double* M = SUB ? A.at(b) + min(row, n - 1) + (long long)w0 * ld : chol_inv_block(Linv, sLi, b, w0) + row;
+    const int row = (SUB ? w0 + WB : 0) + rb + lane;
+    const long long ld = SUB ? A.ld : WB;
+    const double* M = SUB ? A.at(b) + min(row, n - 1) + (long long)w0 * ld : chol_inv_block(Linv, sLi, b, w0, WB) + row;
     __syncthreads();
     double s[CHOL_NR] = {0.0, 0.0, 0.0};
     const int cq = cols / 4;
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(256) void chol_fwd_kernel(MatBatch<double> A, doubl
     for (int k = 0; k < CHOL_NR; k++) part[pt][lane][k] = s[k];
     __syncthreads();
     if (tid < CHOL_NB * CHOL_NR) {
-        const int i = tid / CHOL_NR, k = tid % CHOL_NR, g = (SUB ? w0 + CHOL_WB : w0) + rb + i;
+        const int i = tid / CHOL_NR, k = tid % CHOL_NR, g = (SUB ? w0 + WB : w0) + rb + i;
         const double v = (part[0][i][k] + part[1][i][k]) + (part[2][i][k] + part[3][i][k]);
         if (g < n) {
             const long long o = (long long)b * sR + (long long)g * CHOL_NR + k;
@@ -321,14 +321,14 @@ __global__ __launch_bounds__(256) void chol_fwd_kernel(MatBatch<double> A, doubl
 // Backward step of the wide block at w0.  SUB: 64 columns left of it per
 // workgroup, Y -= L^T Xo; else its own, Xo = X^T Y.  16 columns per wavefront,
 // the rows over its lanes.
-template <bool SUB>
+template <int WB, bool SUB>
 __global__ __launch_bounds__(256) void chol_bwd_kernel(MatBatch<double> A, double* Linv, long long sLi, int n, int w0,
                                                         double* Y, double* Xo, long long sR) {
     const int b = blockIdx.y, lane = threadIdx.x & 63, c0 = CHOL_NB * blockIdx.x + 16 * (threadIdx.x >> 6);
     const double* V = (SUB ? Xo : Y) + (long long)b * sR + (long long)w0 * CHOL_NR;
-    const long long ld = SUB ? A.ld : CHOL_WB;
-    const double* M = SUB ? A.at(b) + w0 + (long long)c0 * ld : chol_inv_block(Linv, sLi, b, w0) + (long long)c0 * ld;
-    const int rows = min(CHOL_WB, n - w0);
+    const long long ld = SUB ? A.ld : WB;
+    const double* M = SUB ? A.at(b) + w0 + (long long)c0 * ld : chol_inv_block(Linv, sLi, b, w0, WB) + (long long)c0 * ld;
+    const int rows = min(WB, n - w0);
     double s[CHOL_NR][16] = {};
     for (int r0 = SUB ? 0 : CHOL_NB * blockIdx.x; r0 < rows; r0 += CHOL_NB) {
         const int r = r0 + lane;
@@ -358,43 +358,50 @@ __global__ __launch_bounds__(256) void chol_bwd_kernel(MatBatch<double> A, doubl
 // ---------------------------------------------------------------------------
 // host
 // ---------------------------------------------------------------------------
-long long chol_linv_stride(int n) { return (long long)((n + CHOL_WB - 1) / CHOL_WB) * CHOL_WB * CHOL_WB; }
+long long chol_linv_stride(int n, int wb) { return (long long)((n + wb - 1) / wb) * wb * wb; }
 
-void chol_factor_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, unsigned* status) {
-    const long long sLi = chol_linv_stride(n);
+void chol_factor_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, int wb, unsigned* status) {
+    const long long sLi = chol_linv_stride(n, wb);
     for (int k0 = 0; k0 < n; k0 += CHOL_NB) {
         const int rows = n - k0 - CHOL_NB;
         if (k0) {
             const int tiles = (n - k0 + 31) / 32 * (CHOL_NB / 32);
             hipLaunchKernelGGL(chol_update_kernel, dim3(tiles * nbatch), dim3(256), 0, st, A, n, k0, tiles);
         }
-        hipLaunchKernelGGL(chol_diag_kernel, dim3(nbatch), dim3(256), 0, st, A, Linv, sLi, n, k0, status);
+        hipLaunchKernelGGL(chol_diag_kernel, dim3(nbatch), dim3(256), 0, st, A, Linv, sLi, wb, n, k0, status);
         if (rows > 0)
-            hipLaunchKernelGGL(chol_panel_kernel, dim3((rows + 31) / 32, nbatch), dim3(256), 0, st, A, Linv, sLi, n, k0);
+            hipLaunchKernelGGL(chol_panel_kernel, dim3((rows + 31) / 32, nbatch), dim3(256), 0, st, A, Linv, sLi, wb, n, k0);
     }
-    if (n > CHOL_NB)
-        hipLaunchKernelGGL(chol_wide_kernel, dim3(CHOL_WB / CHOL_NB - 1, (n + CHOL_WB - 1) / CHOL_WB, nbatch), dim3(256), 0, st,
-                           A, Linv, sLi, n);
+    if (wb == CHOL_WIDE && n > CHOL_NB)
+        hipLaunchKernelGGL(chol_wide_kernel<CHOL_WIDE>, dim3(CHOL_WIDE / CHOL_NB - 1, (n + CHOL_WIDE - 1) / CHOL_WIDE, nbatch),
+                           dim3(256), 0, st, A, Linv, sLi, n);
+}
+
+template <int WB>
+static void chol_sweeps(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, double* R, double* Y, double* X,
+                        long long sR) {
+    const long long sLi = chol_linv_stride(n, WB);
+    auto blocks = [](int k) { return (k + CHOL_NB - 1) / CHOL_NB; };
+    for (int w0 = 0; w0 < n; w0 += WB) {
+        hipLaunchKernelGGL((chol_fwd_kernel<WB, false>), dim3(blocks(std::min(WB, n - w0)), nbatch), dim3(256), 0, st, A, Linv,
+                           sLi, n, w0, R, Y, sR);
+        if (w0 + WB < n)
+            hipLaunchKernelGGL((chol_fwd_kernel<WB, true>), dim3(blocks(n - w0 - WB), nbatch), dim3(256), 0, st, A, Linv, sLi, n,
+                               w0, R, Y, sR);
+    }
+    for (int w0 = (n - 1) / WB * WB; w0 >= 0; w0 -= WB) {
+        hipLaunchKernelGGL((chol_bwd_kernel<WB, false>), dim3(blocks(std::min(WB, n - w0)), nbatch), dim3(256), 0, st, A, Linv,
+                           sLi, n, w0, Y, X, sR);
+        if (w0 > 0)
+            hipLaunchKernelGGL((chol_bwd_kernel<WB, true>), dim3(w0 / CHOL_NB, nbatch), dim3(256), 0, st, A, Linv, sLi, n, w0, Y,
+                               X, sR);
+    }
 }
 
 // X = A^-1 B from the factor: B in R (overwritten), Y scratch, X out; all
 // [nbatch][n][CHOL_NR] with per-matrix stride sR
-void chol_solve_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, double* R, double* Y,
+void chol_solve_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, int wb, double* R, double* Y,
                        double* X, long long sR) {
-    const long long sLi = chol_linv_stride(n);
-    auto blocks = [](int k) { return (k + CHOL_NB - 1) / CHOL_NB; };
-    for (int w0 = 0; w0 < n; w0 += CHOL_WB) {
-        hipLaunchKernelGGL(chol_fwd_kernel<false>, dim3(blocks(std::min(CHOL_WB, n - w0)), nbatch), dim3(256), 0, st, A, Linv,
-                           sLi, n, w0, R, Y, sR);
-        if (w0 + CHOL_WB < n)
-            hipLaunchKernelGGL(chol_fwd_kernel<true>, dim3(blocks(n - w0 - CHOL_WB), nbatch), dim3(256), 0, st, A, Linv, sLi, n,
-                               w0, R, Y, sR);
-    }
-    for (int w0 = (n - 1) / CHOL_WB * CHOL_WB; w0 >= 0; w0 -= CHOL_WB) {
-        hipLaunchKernelGGL(chol_bwd_kernel<false>, dim3(blocks(std::min(CHOL_WB, n - w0)), nbatch), dim3(256), 0, st, A, Linv,
-                           sLi, n, w0, Y, X, sR);
-        if (w0 > 0)
-            hipLaunchKernelGGL(chol_bwd_kernel<true>, dim3(w0 / CHOL_NB, nbatch), dim3(256), 0, st, A, Linv, sLi, n, w0, Y, X,
-                               sR);
-    }
+    if (wb == CHOL_WIDE) chol_sweeps<CHOL_WIDE>(st, A, n, nbatch, Linv, R, Y, X, sR);
+    else chol_sweeps<CHOL_NB>(st, A, n, nbatch, Linv, R, Y, X, sR);
 }

@@ -255,9 +255,11 @@ void scs_weights_launch(hipStream_t st, int N, int nf, const double* par, const 
     hipLaunchKernelGGL(scs_weights_kernel, dim3((N + 255) / 256, nf), dim3(256), 0, st, N, nf, par, abar, wq, ga, gw,
                        gv, w);
 }
-void scs_grad_launch(hipStream_t st, const SysDesc* sd, int N, int nf, const double* sig2, const double* U,
-                     const double* V, double* UV, double* grad) {
+// sig2: as for the assembly, formed again (its place served the solves in between)
+void scs_grad_launch(hipStream_t st, const SysDesc* sd, int N, int nf, const double* om, const double* u, double* sig2,
+                     const double* U, const double* V, double* UV, double* grad) {
     const int n = 3 * N;
+    hipLaunchKernelGGL(scs_sigma_kernel, dim3((N + 255) / 256, nf), dim3(256), 0, st, sd, om, u, sig2);
     hipLaunchKernelGGL(scs_pack_uv_kernel, dim3((unsigned)(((long long)nf * n + 255) / 256)), dim3(256), 0, st, n, nf,
                        U, V, UV);
     hipLaunchKernelGGL(scs_grad_kernel, dim3(N), dim3(256), 0, st, sd, sig2, nf, UV, grad);

@@ -149,6 +149,7 @@ void mbd_freq_terms_launch(hipStream_t st, const int* ns, int nmat, const double
                            double* part, const double* wf, int nfreq, int nq, int embed, double* terms);
 
 // self-consistent screening (see k_scs.hip)
+// (sig2: scratch of nf N)
 void scs_assemble_launch(hipStream_t st, const SysDesc* sd, int N, const double* om, const double* u, int nf,
                          double* sig2, MatBatch<double> A, unsigned* status);
 void scs_rhs_launch(hipStream_t st, int N, int nf, const double* w, double* R);
@@ -157,12 +158,16 @@ void scs_params_launch(hipStream_t st, const SysDesc* sd, int N, const double* a
                        double* out);
 void scs_weights_launch(hipStream_t st, int N, int nf, const double* par, const double* abar, const double* wq,
                         const double* ga, const double* gw, const double* gv, double* w);
-void scs_grad_launch(hipStream_t st, const SysDesc* sd, int N, int nf, const double* sig2, const double* U,
-                     const double* V, double* UV, double* grad);
+void scs_grad_launch(hipStream_t st, const SysDesc* sd, int N, int nf, const double* om, const double* u, double* sig2,
+                     const double* U, const double* V, double* UV, double* grad);
 // batched Cholesky (k_chol.hip): factor in place (lower), diagonal-block
 // inverses in Linv (chol_linv_stride(n) per matrix); solves with three
 // right-hand sides, layout [nbatch][n][3] with per-matrix stride sR
-long long chol_linv_stride(int n);
-void chol_factor_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, unsigned* status);
-void chol_solve_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, double* R, double* Y,
+// wb: rows of the solves' diagonal blocks, CHOL_WIDE or, with a quarter of
+// Linv's size, CHOL_NB
+#define CHOL_NB 64
+#define CHOL_WIDE 256
+long long chol_linv_stride(int n, int wb);
+void chol_factor_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, int wb, unsigned* status);
+void chol_solve_launch(hipStream_t st, MatBatch<double> A, int n, int nbatch, double* Linv, int wb, double* R, double* Y,
                        double* X, long long sR);

@@ -101,3 +101,17 @@ def test_pairwise_cells(monkeypatch, N, least):
     c = gen.small_crystal(300 + N, N, kgrid=(1, 1, 1), side_scale=max(1.0, (N / 40) ** (1 / 3)))
     _answered(monkeypatch, "pairwise energy of a cell of %d" % N, "fp64",
               lambda x: T.ts_evaluate(x, *_args(c), 0.94, lattice=c["lattice"]), least, 1e-12, (1.0, 1.6, 4.0, 100.0))
+
+
+@pytest.mark.parametrize("precision,N,grad,least", [
+    ("fp64", 4, True, 866115), ("fp64", 16, True, 1421146), ("fp64", 60, True, 8620340), ("fp64", 90, True, 19041829),
+    ("fp64", 200, True, 74776265), ("fp64", 16, False, 1057665), ("fp64", 90, False, 14922843),
+    ("fp32_refined", 16, True, 1375298), ("fp32_refined", 90, True, 20265774), ("fp32_refined", 90, False, 19939388)])
+def test_screening(monkeypatch, precision, N, grad, least):
+    """The screening's solves carry eps sqrt(n) times the condition of A(u), some
+    10^3; FP32 eigenvectors with one refinement step leave up to 10^-6."""
+    from paper_2308_03140_amd import torch_api as T
+    c = _cluster(N)
+    _answered(monkeypatch, "screening of %d atoms, gradients=%s" % (N, grad), precision,
+              lambda x: T.rsscs_evaluate(x, *_args(c, 0.5), beta=c["beta"], a=c["a"], gradients=grad, errors=False),
+              least, 1e-10 if precision == "fp64" else 2e-6, (1.0, 1.15, 1.5, 2.2, 5.0, 12.0))

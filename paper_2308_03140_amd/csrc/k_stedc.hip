@@ -50,14 +50,16 @@ __global__ __launch_bounds__(256) void stedc_init_kernel(StedcWs<T> w) {
     }
     mx = block_max256(mx, red);
     if (mx == 0.0) mx = 1.0;
-    const double inv = 1.0 / mx;
+    // 1/mx overflows for subnormal matrices: these are brought up first
+    const double up = mx < 1e-290 ? 0x1p600 : 1.0;
+    const double inv = 1.0 / (mx * up);
     double* D = w.D + (long long)b * w.sV;
     double* E = w.E + (long long)b * w.sV;
     for (int p = threadIdx.x; p < n; p += 256) {
-        const double el = p > 0 ? fabs((double)e[p - 1]) * inv : 0.0;
-        const double er = p < n - 1 ? fabs((double)e[p]) * inv : 0.0;
-        D[p] = (double)d[p] * inv - el - er;
-        E[p] = p < n - 1 ? (double)e[p] * inv : 0.0;
+        const double el = p > 0 ? fabs((double)e[p - 1]) * up * inv : 0.0;
+        const double er = p < n - 1 ? fabs((double)e[p]) * up * inv : 0.0;
+        D[p] = (double)d[p] * up * inv - el - er;
+        E[p] = p < n - 1 ? (double)e[p] * up * inv : 0.0;
     }
     if (threadIdx.x == 0) w.scale[b] = mx;
 }
@@ -78,6 +80,11 @@ __global__ __launch_bounds__(256) void stedc_fill_kernel(StedcWs<T> w) {
         z1[r] = T(0);
     }
 }
+
+// The poles' order, NaN last: every rank is taken once whatever the values, so
+// the permutations, which index columns, never keep an entry that was not
+// written.
+__device__ __forceinline__ bool dc_less(double a, double b) { return a < b || (b != b && a == a); }
 
 // merge inputs: z vector, sorted poles, permutation
 template <typename T>
@@ -104,11 +111,11 @@ __global__ __launch_bounds__(256) void stedc_setup_kernel(StedcWs<T> w, int lev,
     if (lp < m.k1) {
         // elements of the second half strictly below dp
         int lo = m.o + m.k1, hi = m.o + m.k;
-        while (lo < hi) { int mid = (lo + hi) >> 1; if (D[mid] < dp) lo = mid + 1; else hi = mid; }
+        while (lo < hi) { int mid = (lo + hi) >> 1; if (dc_less(D[mid], dp)) lo = mid + 1; else hi = mid; }
         rank = lp + (lo - (m.o + m.k1));
     } else {
         int lo = m.o, hi = m.o + m.k1;
-        while (lo < hi) { int mid = (lo + hi) >> 1; if (D[mid] <= dp) lo = mid + 1; else hi = mid; }
+        while (lo < hi) { int mid = (lo + hi) >> 1; if (!dc_less(dp, D[mid])) lo = mid + 1; else hi = mid; }
         rank = (lp - m.k1) + (lo - m.o);
     }
     const long long base = (long long)b * w.sV + m.o;
@@ -608,7 +615,7 @@ __global__ __launch_bounds__(256) void stedc_order_kernel(StedcWs<T> w, int lev)
     int cnt = 0;
     for (int q = lane; q < m.k; q += 64) {
         const double u = val(q);
-        cnt += (u < v) || (u == v && q < it);
+        cnt += dc_less(u, v) || (!dc_less(v, u) && q < it);
     }
     const int rank = (int)wave_sum((double)cnt);
     if (lane == 0) {

@@ -268,11 +268,11 @@ mbd_status run_eig(mbd_ctx* c, MatBatch<T> A, const int* ns, const int* ns_host,
         sytrd_launch<T>(sw, nbatch, nmax, st, ns_host, &c->prof);
     }
     HIPCHK(hipGetLastError(), "sytrd");
-    // a non-finite tridiagonal (from non-finite matrix entries) is zeroed and
-    // flagged before the tridiagonal solvers see it
+    // a non-finite tridiagonal (from non-finite matrix entries, or squares that
+    // leave the range) is zeroed and flagged before the tridiagonal solvers see it
     int* bad = wsT<int>(c, "eig_bad", (size_t)nbatch);
     if (!bad) return (mbd_status)c->err_code;
-    tridiag_guard_launch<T>(ns, nbatch, sw.d, sw.e, sw.sD, bad, st);
+    tridiag_guard_launch<T>(ns, nbatch, sw.d, sw.e, sw.tau, sw.sD, bad, st);
     if (bad_out) *bad_out = bad;
     if (!vectors) {
         // eigenvalues only: Sturm-count multisection on the tridiagonal, with
@@ -1345,7 +1345,7 @@ mbd_status mbd_freq_evaluate(mbd_ctx* c, const mbd_system* s, int32_t n_freq, in
     }
     HIPCHK(hipGetLastError(), "freq assemble");
     if (herm) {
-        tridiag_guard_launch<double>(ns_dev, nmat, hd, he, neig, hbad, st);
+        tridiag_guard_launch<double>(ns_dev, nmat, hd, he, nullptr, neig, hbad, st);
         double2* pe = wsT<double2>(c, "stebz_p", (size_t)stebz_rows(neig) * nmat);
         double* info = wsT<double>(c, "stebz_i", (size_t)3 * nmat);
         if (!pe || !info) return (mbd_status)c->err_code;
@@ -1632,7 +1632,7 @@ mbd_status mbd_eigh(mbd_ctx* c, int32_t dtype, int32_t n, int32_t nbatch, void* 
     HIPCHK(hipMemcpyAsync(badh.data(), bad, sizeof(int) * nbatch, hipMemcpyDeviceToHost, c->stream), "read flags");
     HIPCHK(hipStreamSynchronize(c->stream), "mbd_eigh");
     for (int b = 0; b < nbatch; b++)
-        if (badh[b]) return fail(c, MBD_ERR_INVALID_ARGUMENT, "mbd_eigh", "non-finite matrix entries");
+        if (badh[b]) return fail(c, MBD_ERR_INVALID_ARGUMENT, "mbd_eigh", "non-finite matrix entries, or entries whose squares leave the range");
     return MBD_OK;
 }
 

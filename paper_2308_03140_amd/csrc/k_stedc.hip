@@ -938,9 +938,13 @@ int stedc_launch(const StedcWs<T>& w, int nbatch, int nmax, hipStream_t st) {
     return src;
 }
 
+// A non-finite tridiagonal, or one from which the reduction left out columns
+// (tau negative zero, norms up to sqrt(tiny)) that are not below the rounding of
+// its largest element: zeroed and flagged.
 template <typename T>
-__global__ __launch_bounds__(256) void tridiag_guard_kernel(const int* ns, T* d, T* e, long long sD, int* bad) {
+__global__ __launch_bounds__(256) void tridiag_guard_kernel(const int* ns, T* d, T* e, const T* tau, long long sD, int* bad) {
     __shared__ int flag;
+    __shared__ double red[4];
     const int b = blockIdx.x;
     const int n = ns[b];
     T* db = d + (long long)b * sD;
@@ -948,8 +952,19 @@ __global__ __launch_bounds__(256) void tridiag_guard_kernel(const int* ns, T* d,
     if (threadIdx.x == 0) flag = 0;
     __syncthreads();
     bool f = false;
-    for (int i = threadIdx.x; i < n; i += 256) f |= !isfinite(db[i]) || (i + 1 < n && !isfinite(eb[i]));
-    if (f) flag = 1;
+    double mx = 0.0, out = 0.0;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        f |= !isfinite(db[i]) || (i + 1 < n && !isfinite(eb[i]));
+        mx = fmax(mx, fmax(fabs((double)db[i]), i + 1 < n ? fabs((double)eb[i]) : 0.0));
+        if (tau && i + 2 < n) {
+            const T t = tau[(long long)b * sD + i];
+            if (t == T(0) && signbit(t)) out = 1.0;
+        }
+    }
+    mx = block_max256(mx, red);
+    out = block_max256(out, red);
+    const double left = out * sqrt((double)num_limits<T>::tiny);
+    if (f || left > (double)num_limits<T>::eps * mx) flag = 1;
     __syncthreads();
     if (flag)
         for (int i = threadIdx.x; i < n; i += 256) {
@@ -960,11 +975,11 @@ __global__ __launch_bounds__(256) void tridiag_guard_kernel(const int* ns, T* d,
 }
 
 template <typename T>
-void tridiag_guard_launch(const int* ns, int nbatch, T* d, T* e, long long sD, int* bad, hipStream_t st) {
-    hipLaunchKernelGGL(tridiag_guard_kernel<T>, dim3(nbatch), dim3(256), 0, st, ns, d, e, sD, bad);
+void tridiag_guard_launch(const int* ns, int nbatch, T* d, T* e, const T* tau, long long sD, int* bad, hipStream_t st) {
+    hipLaunchKernelGGL(tridiag_guard_kernel<T>, dim3(nbatch), dim3(256), 0, st, ns, d, e, tau, sD, bad);
 }
-template void tridiag_guard_launch<double>(const int*, int, double*, double*, long long, int*, hipStream_t);
-template void tridiag_guard_launch<float>(const int*, int, float*, float*, long long, int*, hipStream_t);
+template void tridiag_guard_launch<double>(const int*, int, double*, double*, const double*, long long, int*, hipStream_t);
+template void tridiag_guard_launch<float>(const int*, int, float*, float*, const float*, long long, int*, hipStream_t);
 
 template int stedc_launch<double>(const StedcWs<double>&, int, int, hipStream_t);
 template int stedc_launch<float>(const StedcWs<float>&, int, int, hipStream_t);

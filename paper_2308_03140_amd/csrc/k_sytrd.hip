@@ -62,10 +62,15 @@ __device__ __forceinline__ T refl_v(const T* col, int r, int s, int n, T scale) 
 // A column whose norm squared is zero below the diagonal, or below the normal
 // range altogether (1/(alpha - beta) squared would overflow: FP32 columns of
 // 1e-20, as the rounding noise of an exactly decoupled block leaves), needs no
-// reflector.
+// reflector.  Its tau is zero, and negative zero where the column was not:
+// tridiag_guard_kernel weighs what was left out against the whole matrix.
 template <typename T>
 __device__ __forceinline__ bool refl_none(T alpha, T xn2) {
     return xn2 == T(0) || alpha * alpha + xn2 < num_limits<T>::tiny;
+}
+template <typename T>
+__device__ __forceinline__ T refl_no_tau(T xn2) {
+    return xn2 == T(0) ? T(0) : -T(0);
 }
 
 // Reflector scalars from the updated column held in colbuf (LAPACK dlarfg
@@ -79,7 +84,7 @@ __device__ __forceinline__ Refl<T> refl_scalars(const SytrdWs<T>& w, int b, int 
     const T alpha = w.colbuf[(long long)b * 2 * w.sC + (i & 1) * w.sC + i + 1];
     Refl<T> r;
     if (refl_none(alpha, xn2)) {
-        r.tau = T(0); r.beta = alpha; r.scale = T(0);
+        r.tau = refl_no_tau(xn2); r.beta = alpha; r.scale = T(0);
     } else {
         const T nrm = sqrt(alpha * alpha + xn2);
         r.beta = alpha >= T(0) ? -nrm : nrm;
@@ -671,7 +676,7 @@ __global__ __launch_bounds__(SYTRD_TAIL_THREADS) void sytrd_tail_kernel(SytrdWs<
         const T alpha = L[ci + 1];
         T beta, tau, scale;
         if (refl_none(alpha, xn2)) {
-            tau = T(0); beta = alpha; scale = T(0);
+            tau = refl_no_tau(xn2); beta = alpha; scale = T(0);
         } else {
             const T nrm = sqrt(alpha * alpha + xn2);
             beta = alpha >= T(0) ? -nrm : nrm;
@@ -1051,7 +1056,7 @@ __global__ __launch_bounds__(64 * NW) void sytrd_wg_kernel(SytrdWs<T> w) {
             const T alpha = uc[s];
             T beta, tau, scale;
             if (refl_none(alpha, xn2)) {
-                tau = T(0); beta = alpha; scale = T(0);
+                tau = refl_no_tau(xn2); beta = alpha; scale = T(0);
             } else {
                 const T nrm = sqrt(alpha * alpha + xn2);
                 beta = alpha >= T(0) ? -nrm : nrm;
@@ -1223,7 +1228,7 @@ __device__ __forceinline__ FinScal<T> fin_scalars(const SytrdWs<T>& w, int b, in
     FinScal<T> f;
     f.zero = refl_none(alpha, xn2);
     if (f.zero) {
-        f.tau = T(0); f.beta = alpha; f.scale = T(0);
+        f.tau = refl_no_tau(xn2); f.beta = alpha; f.scale = T(0);
     } else {
         const T nrm = sqrt(alpha * alpha + xn2);
         f.beta = alpha >= T(0) ? -nrm : nrm;

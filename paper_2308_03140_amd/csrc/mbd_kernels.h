@@ -164,14 +164,12 @@ struct StedcWs {
 template <typename T>
 int stedc_launch(const StedcWs<T>& w, int nbatch, int nmax, hipStream_t st);
 
-// Tridiagonals with a non-finite entry are replaced by zeros and flagged in
-// bad[b] (1, else 0): the merges of divide and conquer rank each half's poles
-// by binary search in the other, which assumes ordered values (a NaN makes
-// two poles share a position and leaves another unset, whose stale index
-// would then address the eigenvector blocks), and the multisection's
-// brackets assume finite bounds.
+// Matrices with a non-finite tridiagonal entry are replaced by zeros and flagged in
+// bad[b] (1, else 0): the multisection's brackets assume finite bounds, and such
+// results mean nothing.  So are those whose reduction left out columns (tau of
+// the reduction, or null: none) that are not below the rounding of the matrix.
 template <typename T>
-void tridiag_guard_launch(const int* ns, int nbatch, T* d, T* e, long long sD, int* bad, hipStream_t st);
+void tridiag_guard_launch(const int* ns, int nbatch, T* d, T* e, const T* tau, long long sD, int* bad, hipStream_t st);
 
 // Eigenvalues only (Sturm counts with multisection, FP64 arithmetic): d, e of
 // the reduction ([nbatch] x sD), w [nbatch] x sW ascending.  pairs: the

@@ -28,3 +28,22 @@ def test_tiny(n, exponent):
                 assert np.abs(G - np.eye(n)).max() <= 1e-12
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("n", [40, 150, 300])
+@pytest.mark.parametrize("dtype,exponent", [("float32", -73), ("float32", -68), ("float64", -535), ("float64", -515)])
+def test_squares_below_the_normal_range(n, dtype, exponent):
+    """Every reflector of such a matrix is left out: refused, not answered with
+    the eigenvalues of its diagonal."""
+    from paper_2308_03140_amd import torch_api as T
+    print("eigh of order %d at 2^%d, %s" % (n, exponent, dtype), flush=True)
+    A = np.random.default_rng(n).standard_normal((n, n))
+    A = torch.tensor(np.ldexp(A + A.T, exponent), dtype=getattr(torch, dtype), device="cuda")
+    ctx = T.Context(0, "fp64")
+    try:
+        for vectors in (False, True):
+            with pytest.raises(T.MBDError) as e:
+                T.eigh(ctx, A, vectors=vectors)
+            assert e.value.code == 1
+    finally:
+        ctx.close()

@@ -1,5 +1,6 @@
 // Symmetric products of the direct root on the INT8 matrix cores, for large
-// matrices: C = A B by residues.  A and B are scaled by powers of two to norms
+// matrices: C = A B by residues (the modular scheme of Ozaki, Uchino & Imamura,
+// "Ozaki scheme II", 2025).  A and B are scaled by powers of two to norms
 // of at most 2^p (the plan follows a bound of each matrix's norm) and rounded
 // to integers a', b'; x_ij = sum_k a'_ik b'_jk, at most the product of two rows'
 // norms, |x| <= 2^2p, is an integer that its residues modulo pairwise coprime
@@ -9,9 +10,12 @@
 //   x / M = frac(sum_i r_i theta_i),  theta_i = ((M / m_i)^-1 mod m_i) / m_i,
 // with theta_i split into a multiple of 2^-42 (its sum is exact in FP64) and a
 // remainder.  The only errors are the roundings of a' and b', 2^-(p+1) of the
-// norm each, and those of the result: s = 14 gives p = 53, FP64 accuracy or
-// better (an FP64 sum of n products rounds n times); s = 12, p = 46, serves the
-// FP32-with-refinement precision.
+// norm each, and those of the result.  s = 15, p = 57, serves FP64: an element 16
+// times below the norm keeps 53 bits, and gradients at order 2700 and 6000 are
+// 6.0e-15 and 7.1e-15 from 64-bit ones, 6.5e-15 and 8.4e-15 with FP64 products
+// (each sum rounds n times), 7.3e-15 and 8.7e-15 by diagonalisation; s = 14, p =
+// 53, left 1.9e-14 and 2.1e-14, since small elements lost bits that an FP64 one
+// has.  s = 12, p = 46, serves the FP32-with-refinement precision.
 //
 // Three launches a product: residues of the operands that are not already held
 // (the plan tracks which two are), the s integer products, and the combination
@@ -19,9 +23,9 @@
 // order of the matrix instructions' operands (blocks of 32 rows x 32 columns, 1
 // KB, lane after lane), so every load is a whole line.
 //
-// At order 6000 and s = 14 (12) the integer products take 1.67 (1.43) ms, 1.8
+// At order 6000 and s = 15 (12) the integer products take 1.91 (1.57) ms, 1.7
 // PetaOP/s (2.4 with neither loads nor LDS, the rate that the card holds), the
-// conversion of an operand 0.25 (0.2) and the combination 0.19 (0.18); the FP64
+// conversion of an operand 0.18 (0.13) and the combination 0.18 (0.16); the FP64
 // product takes 3.4 ms.
 #include <hip/hip_ext.h>
 
@@ -35,10 +39,10 @@
 typedef int mm_i4 __attribute__((ext_vector_type(4)));
 typedef int mm_i16 __attribute__((ext_vector_type(16)));
 
-// 256 and coprime numbers up to 236: a residue that missed its centre by the
-// rounding of a quotient (at most 4) still fits eight bits
-__device__ __constant__ const int MM_MOD[ISQ_MODS_MAX] = {256, 235, 233, 229, 227, 223, 221, 217, 213, 211, 209, 199, 197, 193};
-static const int MM_MOD_HOST[ISQ_MODS_MAX] = {256, 235, 233, 229, 227, 223, 221, 217, 213, 211, 209, 199, 197, 193};
+// 256 and coprime numbers up to 236: a residue of a number below 2^53 that missed
+// its centre by the rounding of a quotient (at most 4) still fits eight bits
+__device__ __constant__ const int MM_MOD[ISQ_MODS_MAX] = {256, 235, 233, 229, 227, 223, 221, 217, 213, 211, 209, 199, 197, 193, 191};
+static const int MM_MOD_HOST[ISQ_MODS_MAX] = {256, 235, 233, 229, 227, 223, 221, 217, 213, 211, 209, 199, 197, 193, 191};
 
 struct ModCoef {
     double u[ISQ_MODS_MAX], v[ISQ_MODS_MAX], M;
@@ -96,8 +100,10 @@ __global__ __launch_bounds__(256) void mod_split_kernel(IsqBufs bufs, const int*
             unsigned pk = 0;
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-                const double x = t[4 * q + e];
-                pk |= ((unsigned)(int)fma(-p, rint(x * ip), x) & 255u) << (8 * e);
+                double x = t[4 * q + e];
+                x = fma(-p, rint(x * ip), x);
+                if (MODS == ISQ_MODS_MAX) x = fma(-p, rint(x * ip), x);  // 2^57: the quotient may be one off
+                pk |= ((unsigned)(int)x & 255u) << (8 * e);
             }
             o[q] = (int)pk;
         }
@@ -286,24 +292,24 @@ __global__ __launch_bounds__(256) void mod_combine_kernel(IsqBufs bufs, const in
 }
 
 // Large orders only: conversions and combination grow with n^2, and 256 x 256
-// tiles waste their edges.  One matrix of order 2103, 2202, 2304, 2550, 3000,
-// 3600, 5100 with 14 moduli: 2.26, 2.38, 2.40, 3.11, 4.24, 6.61, 14.2 ms an
-// evaluation against 2.14, 2.38, 2.80, 3.45, 5.01, 8.18, 21.9 with FP64 products;
-// with 12: 2.18, 2.26, 2.27, 2.58, 3.66, 5.81, 12.3; 2112, 2124, 2160, 2199: 2.29,
-// 2.29, 2.29, 2.39 with 12 against 2.24, 2.43, 2.42, 2.50.  Embedded (periodic)
-// matrices never are that large.
+// tiles waste their edges.  One matrix of order 2202, 2256, 2304, 2400, 2550, 2700,
+// 3000, 3600, 5100 with 15 moduli: 2.67, 2.70, 2.72, 3.36, 3.51, 3.88, 4.77, 7.88,
+// 17.0 ms an evaluation, with FP64 products 2.54, 2.89, 3.00, 3.15, 3.73, 4.40, 5.46,
+// 8.98, 24.0; with 12 moduli at 2112, 2124, 2160, 2199: 2.29, 2.29, 2.29, 2.39 against
+// 2.24, 2.43, 2.42, 2.50, and 2.58, 3.66, 5.81, 12.3 at 2550, 3000, 3600, 5100.  Embedded
+// (periodic) matrices never are that large.
 bool isq_mod_fits(const int* ns_host, int nmat, bool embed, int mods) {
     if (embed) return false;
     for (int b = 0; b < nmat; b++)
-        if (ns_host[b] < (mods == ISQ_MODS_MAX ? 2200 : 2128)) return false;
+        if (ns_host[b] < (mods == ISQ_MODS_MAX ? 2470 : 2128)) return false;
     return true;
 }
 
 void isq_mod_sizes(int nmax, int mods, IsqMod& w, size_t& res, size_t& prod) {
     const int nt = (nmax + 32 * MM_TB - 1) / (32 * MM_TB), tiles = nt * (nt + 1) / 2;
     w.mods = mods;
-    // 2p + 1 bits below the moduli's product: 2^108.7 (14), 2^93.5 (12)
-    w.bits = mods == ISQ_MODS_MAX ? 53 : 46;
+    // 2p + 1 bits below the moduli's product: 2^116.3 (15), 2^93.5 (12)
+    w.bits = mods == ISQ_MODS_MAX ? 57 : 46;
     w.nb = nt * MM_TB;
     w.kb = (nmax + 127) / 128 * 4;
     res = (size_t)2 * mods * w.nb * w.kb * 1024;

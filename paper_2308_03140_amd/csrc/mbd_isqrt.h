@@ -57,9 +57,9 @@ struct IsqLanczos {
     int* len;       // order at which the recurrence ended, 0: it has not
     int* done;      // matrices that need no further step (nullptr: all run)
 };
-// Residue products (k_modmul.hip): 14 moduli for FP64, 12 for FP32 with
+// Residue products (k_modmul.hip): 15 moduli for FP64, 12 for FP32 with
 // refinement
-#define ISQ_MODS_MAX 14
+#define ISQ_MODS_MAX 15
 #define ISQ_MODS_SHORT 12
 typedef int isq_i4 __attribute__((ext_vector_type(4)));
 struct IsqMod {

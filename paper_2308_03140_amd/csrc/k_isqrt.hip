@@ -8,8 +8,10 @@
 // that interval, and Z <- Z W, Y <- Y W: Z tends to Q^{-1/2}, Y to Q^{1/2}
 // (the coupled Newton-Schulz iteration of Higham, "Functions of Matrices",
 // ch. 6, with the composed minimax polynomials of Nakatsukasa & Freund, 2016,
-// in place of the Taylor ones).  Two stages of degree 6 to 9 reach rounding
-// for kappa up to 56, three up to 4000, in 8 to 17 products of which only the
+// in place of the Taylor ones).  The later W are kept as W - I, and Z <- Z + Z (W -
+// I): coefficients and sums round with the size of a correction.  Two stages of
+// degree 4 to 9 reach half a unit of the last place for kappa up to 45, three up
+// to 3700, in 8 to 17 products of which only the
 // lower triangle is formed (n^3 flop each): the eigen-decomposition it
 // replaces reads the matrix once per column (n^3/6 elements in all) and its
 // 6000 columns are a serial chain.
@@ -32,131 +34,12 @@
 // exchange), which neither the interval nor the check would then see.
 #include <algorithm>
 #include <cmath>
-#include <mutex>
 #include <vector>
 
 #include "gemm_splitk.h"
 #include "mbd_internal.h"
 #include "mbd_isqrt.h"
 #include "mbd_kernels.h"
-
-// ---------------------------------------------------------------------------
-// minimax polynomials (host, once)
-// ---------------------------------------------------------------------------
-namespace {
-
-// Coefficients b_0..b_d in X = (x - mid)/hw of the W of degree d with least
-// max |1 - t W(t^2)| on t in [l, u], by the Remez exchange; returns the error.
-double remez_isqrt(double l, double u, int d, double* b, double* mid, double* hw) {
-    const int n = d + 2, G = 1500;
-    *mid = 0.5 * (l * l + u * u);
-    *hw = 0.5 * (u * u - l * l);
-    const double pi = 3.14159265358979323846;
-    double t[16], A[16][17], x[16], res[1501];
-    for (int i = 0; i < n; i++) t[i] = 0.5 * (l + u) - 0.5 * (u - l) * std::cos(pi * i / (n - 1));
-    double E = 0.0;
-    for (int it = 0; it < 40; it++) {
-        // t_i W(t_i^2) + (-1)^i E = 1 in the Chebyshev basis
-        for (int i = 0; i < n; i++) {
-            const double X = (t[i] * t[i] - *mid) / *hw;
-            double t0 = 1.0, t1 = X;
-            for (int k = 0; k <= d; k++) {
-                A[i][k] = t[i] * t0;
-                const double t2 = 2.0 * X * t1 - t0;
-                t0 = t1;
-                t1 = t2;
-            }
-            A[i][d + 1] = (i & 1) ? -1.0 : 1.0;
-            A[i][n] = 1.0;
-        }
-        for (int p = 0; p < n; p++) {
-            int q = p;
-            for (int r = p + 1; r < n; r++)
-                if (std::fabs(A[r][p]) > std::fabs(A[q][p])) q = r;
-            for (int k = 0; k <= n; k++) std::swap(A[p][k], A[q][k]);
-            for (int r = p + 1; r < n; r++) {
-                const double f = A[r][p] / A[p][p];
-                for (int k = p; k <= n; k++) A[r][k] -= f * A[p][k];
-            }
-        }
-        for (int p = n - 1; p >= 0; p--) {
-            double s = A[p][n];
-            for (int k = p + 1; k < n; k++) s -= A[p][k] * x[k];
-            x[p] = s / A[p][p];
-        }
-        E = std::fabs(x[d + 1]);
-        // new reference: the extremum of each run of equal sign
-        double big = 0.0, pts[17];
-        int np = 0, start = 0;
-        for (int g = 0; g <= G; g++) {
-            const double tg = 0.5 * (l + u) - 0.5 * (u - l) * std::cos(pi * g / G);
-            const double X = (tg * tg - *mid) / *hw;
-            double t0 = 1.0, t1 = X, s = 0.0;
-            for (int k = 0; k <= d; k++) {
-                s += x[k] * t0;
-                const double t2 = 2.0 * X * t1 - t0;
-                t0 = t1;
-                t1 = t2;
-            }
-            res[g] = 1.0 - tg * s;
-        }
-        for (int g = 1; g <= G + 1; g++) {
-            if (g <= G && res[g] * res[g - 1] >= 0.0) continue;
-            int m = start;
-            for (int k = start; k < g; k++)
-                if (std::fabs(res[k]) > std::fabs(res[m])) m = k;
-            if (np < 17) pts[np] = 0.5 * (l + u) - 0.5 * (u - l) * std::cos(pi * m / G);
-            np++;
-            big = std::max(big, std::fabs(res[m]));
-            start = g;
-        }
-        if (np != n) break;  // rounding level: the error no longer alternates cleanly
-        for (int i = 0; i < n; i++) t[i] = pts[i];
-        if (big <= E * 1.002) break;
-    }
-    // Chebyshev to monomial coefficients in X
-    double Tk[2][16] = {{1.0}, {0.0, 1.0}};
-    for (int k = 0; k <= d; k++) b[k] = 0.0;
-    for (int k = 0; k <= d; k++) {
-        double* cur = Tk[k & 1];
-        if (k >= 2) {
-            double nxt[16];
-            for (int j = 0; j <= k; j++)
-                nxt[j] = (j ? 2.0 * Tk[(k - 1) & 1][j - 1] : 0.0) - (j <= k - 2 ? Tk[k & 1][j] : 0.0);
-            for (int j = 0; j <= k; j++) cur[j] = nxt[j];
-        }
-        for (int j = 0; j <= k; j++) b[j] += x[k] * cur[j];
-    }
-    return E;
-}
-
-// Stage degrees per largest kappa: the fewest products whose composed error
-// stays below 5e-15.
-const struct { double kappa; int deg[3]; } ISQ_PLANS[ISQ_CLASSES] = {
-    {4.0, {4, 6, 0}},   {12.0, {4, 9, 0}},  {28.0, {6, 9, 0}},  {56.0, {9, 9, 0}},    {120.0, {4, 4, 4}},
-    {240.0, {4, 4, 6}}, {600.0, {4, 4, 9}}, {1200.0, {4, 6, 9}}, {4000.0, {6, 9, 9}},
-};
-
-IsqTable g_table;
-std::once_flag g_table_once;
-
-void build_table() {
-    for (int c = 0; c < ISQ_CLASSES; c++) {
-        IsqClass& k = g_table.cls[c];
-        k.kappa = ISQ_PLANS[c].kappa;
-        double l = 1.0 / std::sqrt(k.kappa), u = 1.0;
-        for (int s = 0; s < 3; s++) {
-            const int d = k.deg[s] = ISQ_PLANS[c].deg[s];
-            if (!d) break;
-            const double e = remez_isqrt(l, u, d, k.b[s], &k.mid[s], &k.hw[s]);
-            // the next stage's interval, a little wider than the error left
-            l = 1.0 - 1.05 * e - 1e-12;
-            u = 1.0 + 1.05 * e + 1e-12;
-        }
-    }
-}
-
-}  // namespace
 
 // products of a class's program
 static int isq_products(const IsqClass& c) {
@@ -168,9 +51,9 @@ static int isq_products(const IsqClass& c) {
     return p;
 }
 
-const IsqTable& isq_table() {
-    std::call_once(g_table_once, build_table);
-    return g_table;
+const IsqTable& isq_table(bool wide) {
+    static const IsqTable tab[2] = {isq_build_table(false), isq_build_table(true)};
+    return tab[wide ? 1 : 0];
 }
 
 // ---------------------------------------------------------------------------
@@ -537,7 +420,7 @@ struct IsqEmit {
         o.d[0] = d0; o.d[1] = d1; o.d[2] = d2; o.d[3] = d3;
         op[k++] = o;
     }
-    // W(X) of degree d into buffer w, scaled by f, for the symmetric matrix in
+    // The polynomial of degree d in X into buffer w, scaled by f, for the symmetric matrix in
     // buffer p with X = s p + g I (s = 1, g = 0: the buffer holds X itself).
     // Buffers x2, x3, t, u hold the powers and inner sums.
     __device__ void poly(int p, double s, double g, int d, const double* b, double f, int x2, int x3, int t, int u,
@@ -617,17 +500,17 @@ __global__ __launch_bounds__(64) void isq_plan_kernel(const int* ns, IsqLanczos 
                     // buffers free here: 1 2 3 4 and, after X, none of z, y
                     e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 1, 2, 3, 4, k.deg[s] == 9 ? 3 : 4);
                     const int w = k.deg[s] == 9 ? 3 : 4;
-                    e.put(y, w, -1, -1, 2, -1, 1.0, 0, 0, 0);
-                    e.put(z, w, -1, -1, 1, -1, 1.0, 0, 0, 0);
+                    e.put(y, w, y, -1, 2, -1, 1.0, 1.0, 0, 0);
+                    e.put(z, w, z, -1, 1, -1, 1.0, 1.0, 0, 0);
                     z = 1;
                     y = 2;
                 } else if (z == 5) {
                     // y is free once X is formed
                     e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 1, 2, 3, 4, 6);
-                    e.put(z, 6, -1, -1, ISQ_RESULT, -1, 1.0, 0, 0, 0);
+                    e.put(z, 6, z, -1, ISQ_RESULT, -1, 1.0, 1.0, 0, 0);
                 } else {
                     e.poly(7, 1.0, 0.0, k.deg[s], k.b[s], 1.0, 2, 3, 4, 5, 6);
-                    e.put(z, 6, -1, -1, ISQ_RESULT, -1, 1.0, 0, 0, 0);
+                    e.put(z, 6, z, -1, ISQ_RESULT, -1, 1.0, 1.0, 0, 0);
                 }
             }
         }
@@ -1138,7 +1021,7 @@ __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBa
         });
         return o;
     };
-    // W(X) for X in bX and in registers; uses bX and bT, leaves W in registers
+    // the polynomial for X in bX and in registers; uses bX and bT, leaves it in registers
     auto poly = [&](const Reg& X, int d, const double* p) {
         const Reg X2 = mul(bX, bX);
         if (d == 4) {
@@ -1195,9 +1078,12 @@ __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBa
         __syncthreads();
         put(bT, W);
         __syncthreads();
-        const Reg Z = mul(bZ, bT);
-        Reg Y;
-        if (!last) Y = mul(bY, bT);
+        Reg Z = mul(bZ, bT), Y;  // Z + Z (W - I)
+        each([&](int r, int c, int i, int j, int q) { Z.v[i][j][q] += bZ[ix(r, c)]; });
+        if (!last) {
+            Y = mul(bY, bT);
+            each([&](int r, int c, int i, int j, int q) { Y.v[i][j][q] += bY[ix(r, c)]; });
+        }
         __syncthreads();
         put(bZ, Z);
         if (!last) put(bY, Y);
@@ -1284,10 +1170,11 @@ static int isq_squares(const int* ns, int nmat, bool embed) {
 
 void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int* ns_host, LaunchProfiler* prof) {
     const MatBatch<double> Q = {w.bufs.p[0], w.bufs.ld, w.bufs.stride};
+    const bool wide = w.mod.mods == ISQ_MODS_SHORT;
     if (nmax <= 64) {
         const MatBatch<double> Z = {w.bufs.p[ISQ_RESULT], w.bufs.ld, w.bufs.stride};
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(nmat), dim3(256), 0, st, Q, Z, w.ns, isq_table(), w.cls, w.check,
+            hipLaunchKernelGGL(kernel, dim3(nmat), dim3(256), 0, st, Q, Z, w.ns, isq_table(wide), w.cls, w.check,
                                isq_lanczos_wgs(nmax), w.zmax);
         };
         if (nmax <= 32) go(isq_tiny_kernel<32>);
@@ -1310,7 +1197,7 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     if (nmax > L.one)
         for (int j = 0; j < steps; j++) hipLaunchKernelGGL(lanczos, mv, dim3(256), 0, st, Q, w.ns, L, j);
     const int squares = w.zmax ? isq_squares(ns_host, nmat, w.embed) : 0;
-    hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(), w.ops, w.cls, w.order,
+    hipLaunchKernelGGL(isq_plan_kernel, dim3(nmat), dim3(64), 0, st, w.ns, L, steps, isq_table(wide), w.ops, w.cls, w.order,
                        w.mod.mods > 0, squares);
     const int shape = isq_shape(ns_host, nmat, w.embed);
     const bool timed = prof && prof->enabled && prof->launches;
@@ -1349,7 +1236,7 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
         for (int k = 0; k < ISQ_OPMAX; k++) {
             double flops = 0.0;
             for (int b = 0; b < nmat; b++)
-                if (cls[b] >= 0 && k < isq_products(isq_table().cls[cls[b]])) flops += (w.embed ? 0.5 : w.mod.mods ? w.mod.mods : 1.0) * ns_host[b] * ns_host[b] * ns_host[b];
+                if (cls[b] >= 0 && k < isq_products(isq_table(wide).cls[cls[b]])) flops += (w.embed ? 0.5 : w.mod.mods ? w.mod.mods : 1.0) * ns_host[b] * ns_host[b] * ns_host[b];
             if (flops > 0.0) prof->work[rec0 + k] = flops;
             else prof->kind[rec0 + k] = -1;
         }

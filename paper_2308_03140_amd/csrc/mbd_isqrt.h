@@ -1,10 +1,9 @@
 // Workspaces and launches of the direct inverse square root (k_isqrt.hip).
 #pragma once
+#include "isq_table.h"
 #include "mbd_internal.h"
 #include "mbd_sys.h"
 
-#define ISQ_CLASSES 9      // spectral classes (largest kappa) with a plan each
-#define ISQ_OPMAX 17       // products of the longest program
 #define ISQ_SQUARES 6      // most squarings of Q^{-1/2} before the Lanczos run for lambda_min
 #define ISQ_OPS (ISQ_OPMAX + ISQ_SQUARES)
 #define ISQ_NBUF 8         // matrix buffers, buffer 0 = Q
@@ -23,15 +22,7 @@
 #define ISQ_CHECK 1e-12    // largest accepted |I - Z Q Z|_F / sqrt(n)
 #define ISQ_CHECK_SHORT 1e-10  // with the shorter residue products
 
-struct IsqClass {
-    double kappa;
-    int deg[3];
-    double b[3][10], mid[3], hw[3];
-};
-struct IsqTable {
-    IsqClass cls[ISQ_CLASSES];
-};
-const IsqTable& isq_table();
+const IsqTable& isq_table(bool wide);
 
 struct IsqOp {
     signed char a, b, e1, e2, out, out2;

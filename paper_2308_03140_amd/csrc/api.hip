@@ -835,8 +835,10 @@ mbd_status run_core(mbd_ctx* c, std::vector<SysDesc>& sds, unsigned want, std::v
     PhaseTimer ph_eg(&c->prof, st, 7, direct);
     iw.embed = per != nullptr;
     if (direct) {
+        iw.sd = sd_dev;
+        iw.om = om;
         isq_launch(st, iw, nmax, nmat, nsh.data(), &c->prof);
-        isq_energy_launch(st, iw, sd_dev, nsys, nmax, om, per ? qmult : nullptr, status);
+        isq_energy_launch(st, iw, sd_dev, nsys, nmax, per ? qmult : nullptr, status);
         HIPCHK(hipGetLastError(), "direct root");
     } else if (!fp32) {
         // periodic matrices are real embeddings: without vectors each

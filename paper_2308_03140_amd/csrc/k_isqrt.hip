@@ -724,13 +724,15 @@ static bool isq_own(int nmat) { return 8 * ((nmat + GEMM_NXCD - 1) / GEMM_NXCD *
 // ---------------------------------------------------------------------------
 // trace and check
 // ---------------------------------------------------------------------------
-// pass 0: y1 = Z x (x random) and the row block's share of sum Q o Z;
+// pass 0: y1 = Z x (x random) and the row block's share of sum Q o Z, less its
+// omega: the energy is half that difference, three digits smaller than either,
+// and rounds with its own size;
 // pass 1: y2 = Q y1; pass 2: x - Z y2 and the row block's sum of its squares.
 // A matrix without a program is skipped (its result is never read).
 template <bool EMB>
 __global__ __launch_bounds__(256) void isq_check_kernel(MatBatch<double> Q, MatBatch<double> Z, const int* ns,
-                                                          const int* cls, double* yv, long long sV, double* part,
-                                                          int nwg_max, int pass) {
+                                                          const int* cls, const SysDesc* sd, const double* om, double* yv,
+                                                          long long sV, double* part, int nwg_max, int pass) {
     __shared__ double red[4][ISQ_MVR], red4[4];
     const int b = blockIdx.z, n = ns[b], nr = EMB ? n / 2 : n;
     const int r0 = blockIdx.x * ISQ_MVR;
@@ -781,19 +783,22 @@ __global__ __launch_bounds__(256) void isq_check_kernel(MatBatch<double> Q, MatB
                     }
                 }
         double* pb = part + ((long long)b * nwg_max + blockIdx.x) * 2;
-        if (pass == 0) pb[0] = EMB ? 2.0 * e : e;
+        if (pass == 0) {
+            const double* omp = om + sd[EMB ? 0 : b].atom_off;
+            for (int r = r0; r < min(r0 + ISQ_MVR, nr); r++) e -= omp[r / 3];
+            pb[0] = EMB ? 2.0 * e : e;
+        }
         if (pass == 2) pb[1] = s;
     }
 }
 
-// Energy from the traces (E = w sum_q Tr(Q Z) - (3/2) sum omega) and the
+// Energy from the traces (E = w sum_q (Tr(Q Z) - Tr omega), omega per row) and the
 // verdict of the check; lambda_min from the Lanczos run on Z when wanted.
 // Systems whose evaluation failed keep their gradient outputs untouched: no
 // gradient kernel sees an atom of them.
 __global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int* ns, const int* cls,
-                                                           const double* part, int nwg_max, const double* om,
-                                                           const double* mmult, const double* zmax, double check,
-                                                           unsigned* status) {
+                                                           const double* part, int nwg_max, const double* mmult,
+                                                           const double* zmax, double check, unsigned* status) {
     __shared__ double red[4];
     const int s = blockIdx.x;
     SysDesc& S = sd[s];
@@ -823,12 +828,9 @@ __global__ __launch_bounds__(256) void isq_energy_kernel(SysDesc* sd, const int*
     ok = __syncthreads_and(ok);
     esum = block_sum256(esum, red);
     lmin = -block_max256(-lmin, red);
-    double wsum = 0.0;
-    for (int i = threadIdx.x; i < S.N; i += 256) wsum += om[S.atom_off + i];
-    wsum = block_sum256(wsum, red);
     if (threadIdx.x == 0) {
         if (!ok) status[s] |= MBD_ST_NO_ROOT;
-        if (S.energy) *S.energy = esum - 1.5 * wsum;
+        if (S.energy) *S.energy = esum;
         if (S.errors) {
             S.errors[0] = lmin;
             S.errors[1] = S.errors[2] = S.errors[3] = 0.0;
@@ -936,7 +938,8 @@ __device__ double isq_tiny_lanczos(const double* M, double* vb, int n, int steps
 // squarings).
 template <int NP>
 __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBatch<double> Zo, const int* ns, IsqTable tab,
-                                                         int* cls, double* part, int nwg_max, double* zmax) {
+                                                         const SysDesc* sd, const double* om, int embed, int* cls,
+                                                         double* part, int nwg_max, double* zmax) {
     constexpr int T = NP / 32;  // 16 x 16 tiles per wavefront and direction
     __shared__ __align__(16) double lds[4][NP * (NP + 1)];
     __shared__ double al[ISQ_LMAX], be[ISQ_LMAX], red[4], sh[2], vb[NP];
@@ -1089,21 +1092,27 @@ __global__ __launch_bounds__(256) void isq_tiny_kernel(MatBatch<double> Q, MatBa
         if (!last) put(bY, Y);
         __syncthreads();
     }
-    // result, trace and |I - Z Q Z|_F^2 from the product itself
+    // result, trace (less omega, row by row) and |I - Z Q Z|_F^2 from the product itself
     double e = 0.0, rr = 0.0;
     double* Zb = Zo.at(b);
-    for (int x = tid; x < n * n; x += 256) {
-        const int r = x % n, c = x / n;
-        const double z = bZ[ix(c, r)];
-        Zb[r + (long long)c * Zo.ld] = z;
-        e += z * Qb[r + (long long)c * Q.ld];
+    {
+        const int r = tid % NP;
+        for (int c = tid / NP; c < NP; c += 256 / NP) {
+            const bool in = r < n && c < n;
+            const double q = in ? Qb[r + (long long)c * Q.ld] : 0.0, z = bZ[ix(c, r)];
+            if (in) Zb[r + (long long)c * Zo.ld] = z;
+            e += in ? z * q : 0.0;
+            bT[ix(c, r)] = q;
+        }
+    }
+    bX[tid] = e;
+    __syncthreads();
+    e = 0.0;
+    if (tid < n) {
+        for (int k = 0; k < 256 / NP; k++) e += bX[tid + k * NP];
+        e -= om[sd[embed ? 0 : b].atom_off + (embed ? tid % (n / 2) : tid) / 3];
     }
     e = block_sum256(e, red);
-    for (int x = tid; x < NP * NP; x += 256) {
-        const int r = x % NP, c = x / NP;
-        bT[ix(c, r)] = r < n && c < n ? Qb[r + (long long)c * Q.ld] : 0.0;
-    }
-    __syncthreads();
     put(bX, mul(bT, bZ));
     __syncthreads();
     {
@@ -1174,8 +1183,8 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     if (nmax <= 64) {
         const MatBatch<double> Z = {w.bufs.p[ISQ_RESULT], w.bufs.ld, w.bufs.stride};
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(nmat), dim3(256), 0, st, Q, Z, w.ns, isq_table(wide), w.cls, w.check,
-                               isq_lanczos_wgs(nmax), w.zmax);
+            hipLaunchKernelGGL(kernel, dim3(nmat), dim3(256), 0, st, Q, Z, w.ns, isq_table(wide), w.sd, w.om,
+                               w.embed ? 1 : 0, w.cls, w.check, isq_lanczos_wgs(nmax), w.zmax);
         };
         if (nmax <= 32) go(isq_tiny_kernel<32>);
         else go(isq_tiny_kernel<64>);
@@ -1245,7 +1254,7 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     const int nwg = isq_lanczos_wgs(nmax);
     const auto check = w.embed ? isq_check_kernel<true> : isq_check_kernel<false>;
     for (int p = 0; p < 3; p++)
-        hipLaunchKernelGGL(check, mv, dim3(256), 0, st, Q, Z, w.ns, w.cls, w.yv, w.lan.sV, w.check, nwg, p);
+        hipLaunchKernelGGL(check, mv, dim3(256), 0, st, Q, Z, w.ns, w.cls, w.sd, w.om, w.yv, w.lan.sV, w.check, nwg, p);
     if (!w.zmax) return;
     for (int i = 0; i < squares; i++) product(ISQ_OPMAX + i, nullptr, nullptr);
     const int last = isq_lsteps(squares), every = isq_lcheck(squares);
@@ -1266,9 +1275,9 @@ void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int*
     }
 }
 
-void isq_energy_launch(hipStream_t st, const IsqWork& w, SysDesc* sd, int nsys, int nmax, const double* om,
-                       const double* mmult, unsigned* status) {
+void isq_energy_launch(hipStream_t st, const IsqWork& w, SysDesc* sd, int nsys, int nmax, const double* mmult,
+                       unsigned* status) {
     hipLaunchKernelGGL(isq_energy_kernel, dim3(nsys), dim3(256), 0, st, sd, w.ns, w.cls, w.check, isq_lanczos_wgs(nmax),
-                       om, mmult, w.zmax,
+                       mmult, w.zmax,
                        w.mod.mods == ISQ_MODS_SHORT ? ISQ_CHECK_SHORT : ISQ_CHECK, status);
 }

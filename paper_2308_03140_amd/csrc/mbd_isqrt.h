@@ -62,6 +62,8 @@ struct IsqMod {
 };
 struct IsqWork {
     const int* ns;
+    const SysDesc* sd;  // of the systems (matrix b's, or the one cell's)
+    const double* om;
     IsqMod mod;
     bool embed;     // real embeddings of Hermitian matrices (order even)
     IsqBufs bufs;
@@ -94,5 +96,5 @@ struct LaunchProfiler;
 void isq_launch(hipStream_t st, const IsqWork& w, int nmax, int nmat, const int* ns_host, LaunchProfiler* prof);
 // energies, errors[0..3] and MBD_ST_NO_ROOT of the systems; a failed system's
 // descriptor loses its atoms and gradient outputs
-void isq_energy_launch(hipStream_t st, const IsqWork& w, SysDesc* sd, int nsys, int nmax, const double* om,
-                       const double* mmult, unsigned* status);
+void isq_energy_launch(hipStream_t st, const IsqWork& w, SysDesc* sd, int nsys, int nmax, const double* mmult,
+                       unsigned* status);

@@ -105,27 +105,6 @@ def cpu_baseline(sizes=(500, 700), n_full=2000):
                       "extrapolated with it to one N=%d evaluation" % (a, b, t[a], t[b], p, b, n_full)}
 
 
-def column_traffic(kind):
-    """HBM bytes per launch of one per-column kernel from the committed
-    rocprofv3 counter runs (FETCH_SIZE + WRITE_SIZE, scaled by the copy-kernel
-    calibration), or None when the kernel source has changed since the
-    counters were taken."""
-    path = COLUMN_KERNELS[kind][1]
-    if not os.path.exists(path):
-        return None
-    kv = {}
-    with open(path) as f:
-        for line in f:
-            if "=" in line and not line.startswith("#"):
-                k, v = line.split("=", 1)
-                kv[k.strip()] = v.strip()
-    with open(SYMV_SOURCE, "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()[:16]
-    if kv.get("kernel_source_sha256_16") != sha or "hbm_bytes_per_launch" not in kv:
-        return None
-    return float(kv["hbm_bytes_per_launch"])
-
-
 def timed(fn, steps, warmup, torch):
     out = None
     for _ in range(warmup):
@@ -435,8 +414,8 @@ def leg_rsscs(args, torch, T, A):
 
 
 def pmc_pass(torch, T):
-    """Runs under rocprofv3 --pmc: one FP32+refine N=2000 evaluation with every
-    kernel dispatched individually (no launch graph, default launch shapes, so
+    """Runs under rocprofv3 --pmc: one FP32+refine N=2000 evaluation through the
+    diagonalisation (eigenvalues wanted) with every kernel dispatched individually (no launch graph, default launch shapes, so
     the counter collection sees each dispatch), then one device-to-device copy
     of 2^28 floats (1 GiB read + 1 GiB written) whose counters calibrate
     FETCH_SIZE and WRITE_SIZE.  (A second evaluation, about 25k counted
@@ -448,7 +427,7 @@ def pmc_pass(torch, T):
     args = [torch.tensor(c[k], device=dev) for k in ("coords", "alpha0", "omega", "rvdw")]
     ctx = T.Context(0, "fp32_refined")
     log("[bench] pmc pass: evaluation")
-    T.evaluate(ctx, *args, beta=c["beta"], a=c["a"])
+    T.evaluate(ctx, *args, beta=c["beta"], a=c["a"], eigvals=True)
     torch.cuda.synchronize()
     x = torch.ones(1 << 28, dtype=torch.float32, device=dev)
     y = torch.empty_like(x)
@@ -624,8 +603,9 @@ def mfma_summary(pmc_dir, trace_dir):
 
 def trace_summary(trace_dir, steps, warmup):
     """Average duration of each FP32 per-column kernel over the evaluations of
-    a `--legs c2` run traced by rocprofv3 --kernel-trace (its kernel_trace.csv
-    under trace_dir).  Every FP32 reduction ends with one LDS tail launch, so
+    a run traced by rocprofv3 --kernel-trace (its kernel_trace.csv under
+    trace_dir) whose evaluations are diagonalised (eigenvalues wanted; those
+    of the c2 leg are not).  Every FP32 reduction ends with one LDS tail launch, so
     the trace is cut there: the per-column launches of the last warmup +
     steps + 1 reductions (warm-up, timed, profiled) are kept and the
     autotuner's candidate reductions before them left out."""
@@ -681,12 +661,12 @@ def main():
                     help="write the SYMV HBM-traffic file under profiles/ from two --pmc-pass counter runs")
     ap.add_argument("--trace-summary", metavar="TRACE_DIR", default=None,
                     help="average SYMV kernel duration per evaluation from a rocprofv3 --kernel-trace run of "
-                         "--legs c2 with the same --steps/--warmup")
+                         "diagonalised FP32+refine evaluations, --steps + --warmup + 1 of them at its end")
     ap.add_argument("--mfma-summary", nargs=2, metavar=("PMC_DIR", "TRACE_DIR"), default=None,
                     help="write the matrix-core utilisation table of the GEMM kernels under profiles/ from a "
                          "--pmc-pass counter run (MfmaUtil, MfmaFlops*) and a kernel-trace run of the same pass")
     ap.add_argument("--pmc-pass", action="store_true",
-                    help="counter-collection pass: one FP32+refine N=2000 evaluation, then a plain device copy "
+                    help="counter-collection pass: one diagonalised FP32+refine N=2000 evaluation, then a plain device copy "
                          "of 1 GiB (the calibration kernel of known traffic); prints no JSON line")
     args = ap.parse_args()
     if args.gpus != 1:
@@ -757,7 +737,7 @@ def main():
         "config": {"workload": "finite cluster N=2000 atoms (Q 6000x6000 real symmetric), energy + forces; "
                                "seed 2, 0.1 atoms/A^3, alpha0 x %.4f (collapse rule)" % r["alpha_scale"],
                    "path": "Q^{-1/2} by coupled minimax polynomial iterations (no eigenvectors), checked; symmetric "
-                           "products from exact INT8 products modulo 12 (fp32_refined) or 14 (fp64) coprime numbers; "
+                           "products from exact INT8 products modulo 12 (fp32_refined) or 15 (fp64) coprime numbers; "
                            "lambda_min by Lanczos"},
         "fp64_s": r["fp64"]["s"],
         "autotune_s": {p: r[p]["tune_s"] for p in ("fp64", "fp32_refined")},

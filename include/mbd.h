@@ -64,7 +64,7 @@ typedef enum {
  * Q^{-1/2} and Tr Q^{1/2} directly, in products on the matrix cores and
  * without an eigen-decomposition, and checks the result (|I - Q^{-1/2} Q
  * Q^{-1/2}| at rounding level).  A system that fails the check (collapsed, or
- * lambda_max/lambda_min above about 4000), one whose eigenvalues are wanted
+ * lambda_max/lambda_min above about 3700), one whose eigenvalues are wanted
  * (MBD_WANT_EIGVALS), one whose workspaces do not fit MBD_WORKSPACE_LIMIT, and
  * every other MBD_FP32_REFINED system (all of a batch with a smaller member,
  * all cells, and all of a context with MBD_REFINE_TOL set), goes through the
